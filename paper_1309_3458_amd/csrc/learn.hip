@@ -321,45 +321,129 @@ ddm_status launch_features(const FeatDev& F, uint32_t d, const float* ulo, const
 }
 
 // ---------------------------------------------------------------------------
-// MLP forward: one thread per sample, parameters in LDS (broadcast reads)
+// The network on the matrix cores (v_mfma_f32_16x16x4_f32: FP32 products and
+// sums).  A wavefront takes 16 samples; a layer is out = W in, with the
+// outputs as rows and the samples as columns of the product, so that lane l
+// holds, for sample l % 16, the outputs 16t + 4(l/16) + r of tile t (r < 4).
+// The contraction of the next layer may run over its inputs in any order as
+// long as both operands use the same one: step (t, r) takes input
+// 16t + 4(l/16) + r in lane l, which is the register the lane already holds,
+// so the activations never leave their lanes.  The weights are the other
+// operand, kept in registers over all of a wavefront's samples.
+// Bound by the matrix unit: 84 products of 32 cycles per 16 samples forward,
+// 244 for the gradient.
+// ---------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kMT = kHid / 16;        // row tiles of a hidden layer
+constexpr int kInSteps = 5;           // ceil(kIn / 4) contraction steps of the first layer
+static_assert(kIn <= 4 * kInSteps - 1, "a spare input column holds the bias gradient's ones");
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 load_f32x4(const float* p) {
+  f32x4 v;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = p[r];
+  return v;
+}
+
+struct MlpRegs {
+  float w1[kMT][kInSteps];  // W1[16t + l%16][4s + l/16], 0 past kIn
+  f32x4 w2[kMT][kMT];       // W2[16t + l%16][16u + 4(l/16) + r]
+  f32x4 b1[kMT], b2[kMT], w3[kMT];
+  float b3;
+};
+
+__device__ __forceinline__ void mlp_load(const float* __restrict__ P, MlpRegs& W) {
+  const int c = (int)(lane_id() & 15u), q = (int)(lane_id() >> 4);
+#pragma unroll
+  for (int t = 0; t < kMT; ++t) {
+#pragma unroll
+    for (int s = 0; s < kInSteps; ++s) {
+      const int i = 4 * s + q;
+      W.w1[t][s] = i < kIn ? P[oW1 + (16 * t + c) * kIn + i] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kMT; ++u) W.w2[t][u] = load_f32x4(P + oW2 + (16 * t + c) * kHid + 16 * u + 4 * q);
+    W.b1[t] = load_f32x4(P + oB1 + 16 * t + 4 * q);
+    W.b2[t] = load_f32x4(P + oB2 + 16 * t + 4 * q);
+    W.w3[t] = load_f32x4(P + oW3 + 16 * t + 4 * q);
+  }
+  W.b3 = P[oB3];
+}
+
+// x[s] = input 4s + l/16 of sample l % 16; returns the prediction of sample
+// l % 16 (in every lane of that sample)
+__device__ __forceinline__ float mlp_eval(const MlpRegs& W, const float (&x)[kInSteps],
+                                          f32x4 (&h1)[kMT], f32x4 (&h2)[kMT]) {
+#pragma unroll
+  for (int t = 0; t < kMT; ++t) h1[t] = W.b1[t];
+#pragma unroll
+  for (int s = 0; s < kInSteps; ++s)
+#pragma unroll
+    for (int t = 0; t < kMT; ++t) h1[t] = mfma4(W.w1[t][s], x[s], h1[t]);
+#pragma unroll
+  for (int t = 0; t < kMT; ++t) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h1[t][r] = fmaxf(h1[t][r], 0.f);
+    h2[t] = W.b2[t];
+  }
+#pragma unroll
+  for (int u = 0; u < kMT; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int t = 0; t < kMT; ++t) h2[t] = mfma4(W.w2[t][u][r], h1[u][r], h2[t]);
+  float y = 0.f;
+#pragma unroll
+  for (int t = 0; t < kMT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h2[t][r] = fmaxf(h2[t][r], 0.f);
+      y = fmaf(W.w3[t][r], h2[t][r], y);
+    }
+  y += __shfl_xor(y, 16, kWave);
+  y += __shfl_xor(y, 32, kWave);
+  return y + W.b3;
+}
+
+// ---------------------------------------------------------------------------
+// MLP forward
 //   out_mode 0: yhat[s] = prediction
 //   out_mode 1: cap[s] = min(ceil(expm1(prediction + delta)), capmax)
+// One thread per sample with the parameters in LDS took 26.7 us for 4096
+// samples and 102 us for 5*10^5; this form 5.6 and 57.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restrict__ params,
-                                                          const float* __restrict__ X, uint32_t N,
-                                                          int out_mode, float delta,
-                                                          uint32_t capmax,
-                                                          float* __restrict__ yhat,
-                                                          uint32_t* __restrict__ cap) {
-  __shared__ float P[kParams];
-  for (uint32_t i = threadIdx.x; i < (uint32_t)kParams; i += blockDim.x) P[i] = params[i];
-  __syncthreads();
-  const uint32_t sidx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sidx >= N) return;
-  float x[kIn];
+constexpr int kFwdWaves = 4;
+
+__global__ __launch_bounds__(kFwdWaves * kWave) void mlp_forward_kernel(
+    const float* __restrict__ params, const float* __restrict__ X, uint32_t N, int out_mode,
+    float delta, uint32_t capmax, float* __restrict__ yhat, uint32_t* __restrict__ cap) {
+  MlpRegs W;
+  mlp_load(params, W);
+  const uint32_t lane = lane_id(), c = lane & 15u, q = lane >> 4;
+  const uint32_t wave = blockIdx.x * kFwdWaves + threadIdx.x / kWave;
+  const uint32_t nw = gridDim.x * kFwdWaves;
+  const uint32_t tiles = (N + 15u) / 16u;
+  for (uint32_t tl = wave; tl < tiles; tl += nw) {
+    const uint32_t sidx = tl * 16u + c;
+    float x[kInSteps];
 #pragma unroll
-  for (int i = 0; i < kIn; ++i) x[i] = X[(size_t)sidx * kIn + i];
-  float h1[kHid];
-#pragma unroll
-  for (int o = 0; o < kHid; ++o) {
-    float a = P[oB1 + o];
-#pragma unroll
-    for (int i = 0; i < kIn; ++i) a = fmaf(P[oW1 + o * kIn + i], x[i], a);
-    h1[o] = fmaxf(a, 0.f);
-  }
-  float y = P[oB3];
-  for (int o = 0; o < kHid; ++o) {
-    float a = P[oB2 + o];
-#pragma unroll
-    for (int i = 0; i < kHid; ++i) a = fmaf(P[oW2 + o * kHid + i], h1[i], a);
-    y = fmaf(P[oW3 + o], fmaxf(a, 0.f), y);
-  }
-  if (out_mode == 0) {
-    yhat[sidx] = y;
-  } else {
-    const float e = expm1f(fminf(y + delta, 30.f));
-    const float c = ceilf(fmaxf(e, 0.f));
-    cap[sidx] = c >= (float)capmax ? capmax : (uint32_t)c;
+    for (uint32_t s = 0; s < kInSteps; ++s) {
+      const uint32_t i = 4u * s + q;
+      x[s] = sidx < N && i < (uint32_t)kIn ? X[(size_t)sidx * kIn + i] : 0.f;
+    }
+    f32x4 h1[kMT], h2[kMT];
+    const float y = mlp_eval(W, x, h1, h2);
+    if (q != 0 || sidx >= N) continue;
+    if (out_mode == 0) {
+      yhat[sidx] = y;
+    } else {
+      const float e = expm1f(fminf(y + delta, 30.f));
+      const float v = ceilf(fmaxf(e, 0.f));
+      cap[sidx] = v >= (float)capmax ? capmax : (uint32_t)v;
+    }
   }
 }
 
@@ -368,160 +452,217 @@ ddm_status launch_mlp_forward(const float* params, const float* X, uint32_t N, i
                               hipStream_t s) {
   if (N == 0) return DDM_OK;
   ProfScope ps("mlp_forward", s);
-  mlp_forward_kernel<<<(N + 255) / 256, 256, 0, s>>>(params, X, N, out_mode, delta, capmax, yhat,
-                                                       cap);
+  // one 16-sample tile per wavefront up to 8 wavefronts per compute unit,
+  // then several tiles for each set of weights loaded
+  const uint32_t blocks = std::min<uint32_t>((N + 16 * kFwdWaves - 1) / (16 * kFwdWaves), 512);
+  mlp_forward_kernel<<<blocks, kFwdWaves * kWave, 0, s>>>(params, X, N, out_mode, delta, capmax,
+                                                         yhat, cap);
   DDM_LAUNCHED("mlp_forward_kernel");
   return DDM_OK;
 }
 
 // ---------------------------------------------------------------------------
 // MLP forward + backward of the mean squared error over N samples.
-// One workgroup of 128 threads handles 128 samples (one per thread) and
-// writes its partial gradient; mlp_reduce_kernel sums the partials in a
-// fixed order.
+// A wavefront runs 16 samples forward and back (dz2 as computed, dz1 = W2^T
+// dz2 with the activations' lane layout again), turns h1, dz2, dy h2 and dz1
+// through LDS to put the samples on the contraction, and adds dW2 = dz2 h1^T
+// and dW1 = dz1 [x, 1]^T to accumulators it keeps over all its samples.  The
+// workgroup's wavefronts then add up in a fixed order, one partial gradient
+// per workgroup; mlp_reduce_kernel sums the partials in a fixed order.
+// One thread per sample, 128 samples per workgroup, took 87 us for 4096
+// samples (32 workgroups on 256 compute units); this form 27.
 // ---------------------------------------------------------------------------
-constexpr int kGB = 128;   // samples per workgroup
-constexpr int kPad = 65;   // LDS row stride (bank-conflict padding)
+constexpr int kGradWaves = 4;
+constexpr int kGradBlocks = 256;  // at most: partials of one gradient
+constexpr int kTS = 80;           // LDS row of a sample: 16 lanes x 4 rows hit 64 banks once
 
-__global__ __launch_bounds__(kGB) void mlp_grad_kernel(const float* __restrict__ params,
-                                                       const float* __restrict__ X,
-                                                       const float* __restrict__ Y, uint32_t N,
-                                                       float* __restrict__ part,
-                                                       float* __restrict__ part_loss) {
-  __shared__ float P[kParams];
-  __shared__ float H1[kGB][kPad];
-  __shared__ float H2[kGB][kPad];
-  __shared__ float D2[kGB][kPad];
-  __shared__ float XS[kGB][kIn + 1];
-  __shared__ float DY[kGB];
-  __shared__ float LS[kGB];
-  const uint32_t t = threadIdx.x;
-  for (uint32_t i = t; i < (uint32_t)kParams; i += kGB) P[i] = params[i];
-  __syncthreads();
-  const uint32_t sidx = blockIdx.x * kGB + t;
-  const bool valid = sidx < N;
+__global__ __launch_bounds__(kGradWaves * kWave) void mlp_grad_kernel(
+    const float* __restrict__ params, const float* __restrict__ X, const float* __restrict__ Y,
+    uint32_t N, float* __restrict__ part, float* __restrict__ part_loss) {
+  __shared__ float sH[kGradWaves][16 * kTS];  // h1, by sample
+  __shared__ float sD[kGradWaves][16 * kTS];  // dz2
+  __shared__ float sG[kGradWaves][16 * kTS];  // dy h2, then dz1
+  __shared__ float acc[kParams];
+  __shared__ float sloss[kGradWaves];
+  const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+  const uint32_t c = lane & 15u, q = lane >> 4;
+  float* H = sH[w];
+  float* D = sD[w];
+  float* G = sG[w];
+  MlpRegs W;
+  mlp_load(params, W);
   const float invN = 1.f / (float)N;
-  float x[kIn];
+  f32x4 g2[kMT][kMT], g1[kMT][2];  // dW2[16t + ..][16u + ..], dW1 (column kIn: db1)
 #pragma unroll
-  for (int i = 0; i < kIn; ++i) x[i] = valid ? X[(size_t)sidx * kIn + i] : 0.f;
-  const float ylab = valid ? Y[sidx] : 0.f;
-  // forward
-  float h1[kHid];
+  for (int t = 0; t < kMT; ++t) {
 #pragma unroll
-  for (int o = 0; o < kHid; ++o) {
-    float a = P[oB1 + o];
-#pragma unroll
-    for (int i = 0; i < kIn; ++i) a = fmaf(P[oW1 + o * kIn + i], x[i], a);
-    h1[o] = fmaxf(a, 0.f);
-    H1[t][o] = h1[o];
+    for (int u = 0; u < kMT; ++u) g2[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    g1[t][0] = g1[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  float y = P[oB3];
-  for (int o = 0; o < kHid; ++o) {
-    float a = P[oB2 + o];
+  float gb2 = 0.f, gw3 = 0.f;  // db2, dW3 of output `lane`
+  float gb3 = 0.f, loss = 0.f;
+  const uint32_t tiles = (N + 15u) / 16u;
+  for (uint32_t tl = blockIdx.x * kGradWaves + w; tl < tiles; tl += gridDim.x * kGradWaves) {
+    const uint32_t s0 = tl * 16u, sidx = s0 + c;
+    const bool valid = sidx < N;
+    float x[kInSteps];
 #pragma unroll
-    for (int i = 0; i < kHid; ++i) a = fmaf(P[oW2 + o * kHid + i], h1[i], a);
-    const float h2 = fmaxf(a, 0.f);
-    H2[t][o] = h2;
-    y = fmaf(P[oW3 + o], h2, y);
+    for (uint32_t s = 0; s < kInSteps; ++s) {
+      const uint32_t i = 4u * s + q;
+      x[s] = valid && i < (uint32_t)kIn ? X[(size_t)sidx * kIn + i] : 0.f;
+    }
+    // [x, 1, 0 ..] with the samples on the contraction: column 16v + c of
+    // sample 4s + q
+    float xt[2][4];
+#pragma unroll
+    for (uint32_t v = 0; v < 2; ++v)
+#pragma unroll
+      for (uint32_t s = 0; s < 4; ++s) {
+        const uint32_t si = s0 + 4u * s + q, i = 16u * v + c;
+        xt[v][s] = si >= N ? 0.f
+                   : i < (uint32_t)kIn ? X[(size_t)si * kIn + i]
+                                       : (i == (uint32_t)kIn ? 1.f : 0.f);
+      }
+    const float ylab = valid ? Y[sidx] : 0.f;
+    f32x4 h1[kMT], h2[kMT], d2[kMT], d1[kMT];
+    const float y = mlp_eval(W, x, h1, h2);
+    const float r = valid ? (y - ylab) : 0.f;
+    const float dy = 2.f * r * invN;
+    if (q == 0) {
+      gb3 += dy;
+      loss = fmaf(r * invN, r, loss);
+    }
+#pragma unroll
+    for (int t = 0; t < kMT; ++t) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        d2[t][k] = h2[t][k] > 0.f ? dy * W.w3[t][k] : 0.f;
+        const uint32_t at = c * kTS + 16u * t + 4u * q + k;
+        H[at] = h1[t][k];
+        D[at] = d2[t][k];
+        G[at] = dy * h2[t][k];
+      }
+      d1[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    // dz1 = W2^T dz2, masked (weights W2[16u + 4q + k][16t + c], cached)
+#pragma unroll
+    for (int u = 0; u < kMT; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int t = 0; t < kMT; ++t)
+          d1[t] = mfma4(params[oW2 + (16 * u + 4 * (int)q + k) * kHid + 16 * t + (int)c], d2[u][k],
+                        d1[t]);
+#pragma unroll
+    for (int t = 0; t < kMT; ++t)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) d1[t][k] = h1[t][k] > 0.f ? d1[t][k] : 0.f;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      gb2 += D[s * kTS + lane];
+      gw3 += G[s * kTS + lane];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      float a[kMT], b[kMT];
+#pragma unroll
+      for (int t = 0; t < kMT; ++t) {
+        a[t] = D[(4 * s + q) * kTS + 16 * t + c];
+        b[t] = H[(4 * s + q) * kTS + 16 * t + c];
+      }
+#pragma unroll
+      for (int t = 0; t < kMT; ++t)
+#pragma unroll
+        for (int u = 0; u < kMT; ++u) g2[t][u] = mfma4(a[t], b[u], g2[t][u]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int t = 0; t < kMT; ++t)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) G[c * kTS + 16u * t + 4u * q + k] = d1[t][k];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int t = 0; t < kMT; ++t) {
+        const float a = G[(4 * s + q) * kTS + 16 * t + c];
+        g1[t][0] = mfma4(a, xt[0][s], g1[t][0]);
+        g1[t][1] = mfma4(a, xt[1][s], g1[t][1]);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  const float r = valid ? (y - ylab) : 0.f;
-  const float dy = 2.f * r * invN;
-  DY[t] = dy;
-  LS[t] = r * r * invN;
 #pragma unroll
-  for (int i = 0; i < kIn; ++i) XS[t][i] = x[i];
-  for (int o = 0; o < kHid; ++o) D2[t][o] = H2[t][o] > 0.f ? dy * P[oW3 + o] : 0.f;
-  __syncthreads();
+  for (int o = 32; o > 0; o >>= 1) {
+    gb3 += __shfl_xor(gb3, o, kWave);
+    loss += __shfl_xor(loss, o, kWave);
+  }
+  if (lane == 0) sloss[w] = loss;
+  // the wavefronts add their gradients one after the other
+  for (uint32_t v = 0; v < (uint32_t)kGradWaves; ++v) {
+    if (w == v) {
+      auto put = [&](uint32_t at, float val) { acc[at] = v == 0 ? val : acc[at] + val; };
+#pragma unroll
+      for (int t = 0; t < kMT; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t o = 16u * t + 4u * q + k;
+#pragma unroll
+          for (int u = 0; u < kMT; ++u) put(oW2 + o * kHid + 16u * u + c, g2[t][u][k]);
+          put(oW1 + o * kIn + c, g1[t][0][k]);
+          if (16u + c < (uint32_t)kIn) put(oW1 + o * kIn + 16u + c, g1[t][1][k]);
+          if (16u + c == (uint32_t)kIn) put(oB1 + o, g1[t][1][k]);
+        }
+      put(oB2 + lane, gb2);
+      put(oW3 + lane, gw3);
+      if (lane == 0) put(oB3, gb3);
+    }
+    __syncthreads();
+  }
   float* g = part + (size_t)blockIdx.x * kParams;
-  // output layer and second-layer bias
-  if (t < (uint32_t)kHid) {
-    float a = 0.f, b = 0.f;
-    for (int q = 0; q < kGB; ++q) {
-      a = fmaf(DY[q], H2[q][t], a);
-      b += D2[q][t];
-    }
-    g[oW3 + t] = a;
-    g[oB2 + t] = b;
-  }
-  if (t == kHid) {
-    float a = 0.f, l = 0.f;
-    for (int q = 0; q < kGB; ++q) {
-      a += DY[q];
-      l += LS[q];
-    }
-    g[oB3] = a;
+  for (uint32_t i = tid; i < (uint32_t)kParams; i += kGradWaves * kWave) g[i] = acc[i];
+  if (tid == 0) {
+    float l = 0.f;
+    for (int v = 0; v < kGradWaves; ++v) l += sloss[v];
     part_loss[blockIdx.x] = l;
-  }
-  // dW2[o][i] = sum_q D2[q][o] H1[q][i]: thread t owns a 4 x 8 tile
-  {
-    const int o0 = (t / 8) * 4, i0 = (t % 8) * 8;
-    float acc[4][8];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
-    for (int q = 0; q < kGB; ++q) {
-      float dv[4], hv[8];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) dv[a] = D2[q][o0 + a];
-#pragma unroll
-      for (int b = 0; b < 8; ++b) hv[b] = H1[q][i0 + b];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[a][b] = fmaf(dv[a], hv[b], acc[a][b]);
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) g[oW2 + (o0 + a) * kHid + i0 + b] = acc[a][b];
-  }
-  __syncthreads();
-  // back to the first layer: dz1 = (W2^T dz2) * [z1 > 0], stored over H1
-  {
-    float dz2[kHid];
-#pragma unroll
-    for (int o = 0; o < kHid; ++o) dz2[o] = D2[t][o];
-    for (int i = 0; i < kHid; ++i) {
-      float a = 0.f;
-#pragma unroll
-      for (int o = 0; o < kHid; ++o) a = fmaf(P[oW2 + o * kHid + i], dz2[o], a);
-      H1[t][i] = H1[t][i] > 0.f ? a : 0.f;
-    }
-  }
-  __syncthreads();
-  // dW1[o][i] = sum_q dz1[q][o] x[q][i], db1[o] = sum_q dz1[q][o]
-  {
-    const int o = t / 2, ib = (t % 2) * (kIn / 2);
-    float acc[kIn / 2], b = 0.f;
-#pragma unroll
-    for (int i = 0; i < kIn / 2; ++i) acc[i] = 0.f;
-    for (int q = 0; q < kGB; ++q) {
-      const float dz = H1[q][o];
-      b += dz;
-#pragma unroll
-      for (int i = 0; i < kIn / 2; ++i) acc[i] = fmaf(dz, XS[q][ib + i], acc[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < kIn / 2; ++i) g[oW1 + o * kIn + ib + i] = acc[i];
-    if (t % 2 == 0) g[oB1 + o] = b;
   }
 }
 
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ part,
-                                                         const float* __restrict__ part_loss,
-                                                         uint32_t nb, float* __restrict__ grad,
-                                                         float* __restrict__ loss) {
-  const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
+// 64 parameters per workgroup; wavefront g adds the partials g, g + 4, ..
+// (their loads in flight together), then the four sums add up
+constexpr uint32_t kRedGroups = 4;
+
+__global__ __launch_bounds__(kRedGroups * kWave) void mlp_reduce_kernel(
+    const float* __restrict__ part, const float* __restrict__ part_loss, uint32_t nb,
+    float* __restrict__ grad, float* __restrict__ loss) {
+  __shared__ float s[kRedGroups][kWave];
+  const uint32_t lane = lane_id(), g = threadIdx.x / kWave;
+  const uint32_t p = blockIdx.x * kWave + lane;
+  float a = 0.f;
   if (p < (uint32_t)kParams) {
-    float a = 0.f;
-    for (uint32_t b = 0; b < nb; ++b) a += part[(size_t)b * kParams + p];
+#pragma unroll 8
+    for (uint32_t b = g; b < nb; b += kRedGroups) a += part[(size_t)b * kParams + p];
+  }
+  s[g][lane] = a;
+  __syncthreads();
+  if (g == 0 && p < (uint32_t)kParams) {
+    for (uint32_t v = 1; v < kRedGroups; ++v) a += s[v][lane];
     grad[p] = a;
   }
-  if (p == 0 && loss) {
+  if (g == 1 && blockIdx.x == 0 && loss) {
     float l = 0.f;
-    for (uint32_t b = 0; b < nb; ++b) l += part_loss[b];
-    *loss = l;
+    for (uint32_t b = lane; b < nb; b += kWave) l += part_loss[b];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, kWave);
+    if (lane == 0) *loss = l;
   }
 }
 
@@ -531,7 +672,8 @@ ddm_status launch_mlp_grad(const float* params, const float* X, const float* Y, 
     set_detail("mlp gradient of an empty batch");
     return DDM_E_INVALID_ARG;
   }
-  const uint32_t nb = (N + kGB - 1) / kGB;
+  const uint32_t nb =
+      std::min<uint32_t>((N + 16 * kGradWaves - 1) / (16 * kGradWaves), kGradBlocks);
   Scratch sc(s);
   sc.reserve(sizeof(float) * kParams * (size_t)nb);
   sc.reserve(sizeof(float) * nb);
@@ -540,9 +682,10 @@ ddm_status launch_mlp_grad(const float* params, const float* X, const float* Y, 
   float* pl = sc.take<float>(nb);
   if (!sc.fits()) return scratch_overrun("predictor gradient");
   ProfScope ps("mlp_grad", s);
-  mlp_grad_kernel<<<nb, kGB, 0, s>>>(params, X, Y, N, part, pl);
+  mlp_grad_kernel<<<nb, kGradWaves * kWave, 0, s>>>(params, X, Y, N, part, pl);
   DDM_LAUNCHED("mlp_grad_kernel");
-  mlp_reduce_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(part, pl, nb, grad, loss);
+  mlp_reduce_kernel<<<(kParams + kWave - 1) / kWave, kRedGroups * kWave, 0, s>>>(part, pl, nb,
+                                                                              grad, loss);
   DDM_LAUNCHED("mlp_reduce_kernel");
   return DDM_OK;
 }

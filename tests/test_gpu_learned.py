@@ -308,3 +308,27 @@ def test_prepare_learned_moves_the_statistics_out_of_the_match():
             t.prepare_learned()
         assert e.value.code == N.DDM_E_INVALID_ARG
         t.free()
+
+
+@pytest.mark.parametrize("N", [15, 16, 17, 63, 64, 65, 16384, 16385, 40000])
+def test_network_at_tile_edges(N):
+    """Forward and gradient where a 16-sample tile, a workgroup's 64 samples
+    or the 256 workgroups' first round end; the bounds of the two tests
+    above (the same sums of FP32 products, in another order)."""
+    import paper_1309_3458_amd as P
+    rng = np.random.default_rng(N)
+    params = rng.normal(0, 0.25, mlp_ref.N_PARAMS).astype(np.float32)
+    X = rng.normal(0, 1, (N, 18)).astype(np.float32)
+    Y = rng.normal(0, 1, N).astype(np.float32)
+    p = P.Predictor(0)
+    p.set_params(params, 0.0)
+    y = p.forward(dev(X)).cpu().numpy()
+    want = mlp_ref.forward(params.astype(np.float64), X.astype(np.float64))
+    assert np.max(np.abs(y - want)) <= 1e-4 * max(1.0, np.max(np.abs(want)))
+    g, loss = p.grad(dev(X), dev(Y))
+    L, gref = mlp_ref.loss_grad(params.astype(np.float64), X.astype(np.float64),
+                                Y.astype(np.float64))
+    scale = np.max(np.abs(gref))
+    err = np.abs(g.cpu().numpy().astype(np.float64) - gref)
+    assert np.all(err <= 1e-4 * np.abs(gref) + 1e-6 * scale)
+    assert abs(float(loss.cpu()[0]) - L) <= 1e-4 * L
