@@ -365,7 +365,7 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
   // still stashing
   uint32_t sch = tile_id * kStashStatic, sfill = 0;
   uint32_t slast = sch + kStashStatic - 1;  // last chunk the tile holds
-  bool sok = STASH;
+  bool sok = STASH && uniform_u32(O.snext[kStashSlices]) == 0;
   uint64_t myhm = 0;  // this lane's update: hits among the flushed candidates
 
   // stash: room for `tot` more entries from this wave, in the current chunk
@@ -490,8 +490,9 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
       // each lane stashes its own update's hits among these candidates: a
       // wave prefix of the hit counts places them, one chunk request (if
       // any) covers the whole flush (most flushes have no hit at all)
-      if (ballot(myhm != 0) != 0) {
-        const uint32_t pcl = (uint32_t)__popcll(myhm);
+      const bool some = ballot(myhm != 0) != 0;
+      const uint32_t pcl = (uint32_t)__popcll(myhm);
+      if (some && sok) {
         uint32_t incl = pcl;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -563,6 +564,8 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
             }
           }
         }
+      }
+      if (some) {
         if constexpr (XP) {
           if (lane < nq) xl.cnt[lane] += pcl;
         } else {
