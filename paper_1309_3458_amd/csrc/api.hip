@@ -222,9 +222,13 @@ ddm_status scratch_overrun(const char* where) {
   return DDM_E_DEVICE;
 }
 
-Scratch::~Scratch() {
+void Scratch::drop() {
   if (base_ && !ext_ && !dry_) dev_free(base_, s_);
+  base_ = nullptr;
+  want_ = used_ = 0;
 }
+
+Scratch::~Scratch() { drop(); }
 
 bool Scratch::commit() {
   if (want_ == 0) want_ = 256;

@@ -16,6 +16,7 @@
 // single exclusive scan of the per-update counts gives every instance's
 // output range: instance i owns out[off[qbase_i] .. off[qbase_i + m_i]).
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -34,7 +35,8 @@ struct BInst {
   uint32_t n, m, d;
   uint32_t qbase;  // first global update index
   uint32_t bbase;  // first bucket
-  uint32_t nb;     // buckets per dimension
+  uint32_t nb;     // cells per class (probe dimension)
+  uint32_t cb[DDM_MAX_D];  // d > 1: cells along each dimension, the class's own first
   uint32_t qpt;    // updates per traversal work item
   uint64_t ebase;  // first element of the key kernel (d * n elements)
   int32_t* flag;   // nonzero: invalid coordinates
@@ -141,35 +143,41 @@ __global__ __launch_bounds__(kProbeThreads) void b_probe_kernel(const BInst* __r
       cnt[gj] = bad ? 0u : res[0] - res[1];
       sub = (uint32_t)(((uint64_t)(bad ? 0u : res[0]) * b.nb) / ((uint64_t)b.n + 1));
     } else {
-      uint32_t best = 0xffffffffu, bqa = 0, bx = 0;
-      for (uint32_t k = 0; k < d; ++k) {
+      // class and cell as in the single-instance matcher: dimension 0 unless
+      // another one's range is less than half as long, cells of quantile
+      // ranges along a serpentine
+      uint32_t best = 0, mid[DDM_MAX_D];
+#pragma unroll
+      for (uint32_t k = 0; k < DDM_MAX_D; ++k) {
+        mid[k] = 0;
+        if (k >= d) continue;
         const float a = b.u_lo[(size_t)k * b.m + j], c = b.u_hi[(size_t)k * b.m + j];
         bad = bad || !valid_extent(a, c);
-        const uint32_t xh = f2key(c);
-        const uint32_t qa = quant_count(sq[k], xh, true);
+        const uint32_t qa = quant_count(sq[k], f2key(c), true);
         const uint32_t qb =
             quant_count(sq[k], f2key(nextafterf(a - b.T.maxlen[k], -INFINITY)), false);
+        mid[k] = quant_count(sq[k], f2key(0.5f * a + 0.5f * c), true);
         const uint32_t est = qa - min(qa, qb);
-        if (est < best) {
+        if (k == 0 || 2u * est + 16u < best) {
           best = est;
           bk = k;
-          bqa = qa;
-          bx = xh;
         }
       }
-      float fine = 0.f;
-      if (bqa >= kQuant) {
-        fine = (float)kQuant - 0.5f;
-      } else if (bqa > 0) {
-        const uint32_t kl = sq[bk][qslot(bqa - 1)], ku = sq[bk][qslot(bqa)];
-        const float fr = ku > kl ? (float)(bx - kl) / (float)(ku - kl) : 0.f;
-        fine = (float)(bqa - 1) + fminf(fr, 0.999f);
+      if (bad) bk = 0;
+#pragma unroll
+      for (uint32_t s = 0; s < DDM_MAX_D; ++s) {
+        if (s >= d) continue;
+        const uint32_t kk = s == 0 ? bk : s - 1 + (s - 1 >= bk ? 1u : 0u);
+        uint32_t qp = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < DDM_MAX_D; ++k)
+          if (k == kk) qp = mid[k];
+        const uint32_t n = b.cb[s];
+        uint32_t i = min(qp * n / (kQuant + 1u), n - 1u);
+        if (sub & 1u) i = n - 1u - i;
+        sub = sub * n + i;
       }
-      if (bad) {
-        bk = 0;
-        fine = 0.f;
-      }
-      sub = (uint32_t)(fine * (float)b.nb / (float)kQuant);
+      if (bad) sub = 0;
     }
     sub = min(sub, b.nb - 1u);
     kstar[gj] = (uint8_t)bk;
@@ -283,16 +291,16 @@ __global__ __launch_bounds__(256) void b_tilemap_kernel(uint32_t G, const uint32
 // per tile (the grid covers the largest possible number of tiles, waves
 // beyond the actual number return); otherwise a fixed grid whose
 // wavefronts take tiles from the ticket until they are exhausted.
-template <bool FILL, bool STASH = false>
+template <TileMode MODE>
 __global__ __launch_bounds__(kTileWaves * kWave) void b_traverse_kernel(
     const BInst* __restrict__ I, uint32_t G, const uint32_t* __restrict__ tp,
     const uint32_t* __restrict__ tmap, const uint32_t* __restrict__ gstart,
     const uint32_t* __restrict__ gcount, const uint32_t* __restrict__ perm,
     uint32_t* __restrict__ ticket, uint32_t persistent, const uint32_t* __restrict__ status,
     SegOut O, const uint32_t* __restrict__ stash_done) {
-  __shared__ float s_cand[kTileWaves][2 * DDM_MAX_D * kRing];
+  __shared__ __align__(16) float s_cand[kTileWaves][2 * DDM_MAX_D * kRing];
   __shared__ uint32_t s_cid[kTileWaves][kRing];
-  __shared__ float4 s_q[kTileWaves][kWave * 2];
+  constexpr bool FILL = MODE == kTileFill;
   const uint32_t wave = threadIdx.x / kWave;
   const uint32_t lane = lane_id();
   if (FILL && uniform_u32(*status) != 0) return;
@@ -320,27 +328,27 @@ __global__ __launch_bounds__(kTileWaves * kWave) void b_traverse_kernel(
     if (skip_multi && dd > 1) continue;
     switch (dd) {
       case 1:
-        tile_body<1, FILL, STASH>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
-                                  s_cand[wave], s_cid[wave], s_q[wave], lane, item);
+        tile_body<1, MODE>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
+                                  s_cand[wave], s_cid[wave], lane, item);
         break;
       case 2:
-        tile_body<2, FILL, STASH>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
-                                  s_cand[wave], s_cid[wave], s_q[wave], lane, item);
+        tile_body<2, MODE>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
+                                  s_cand[wave], s_cid[wave], lane, item);
         break;
       case 3:
-        tile_body<3, FILL, STASH>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
-                                  s_cand[wave], s_cid[wave], s_q[wave], lane, item);
+        tile_body<3, MODE>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
+                                  s_cand[wave], s_cid[wave], lane, item);
         break;
       default:
-        tile_body<4, FILL, STASH>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
-                                  s_cand[wave], s_cid[wave], s_q[wave], lane, item);
+        tile_body<4, MODE>(b.T, b.u_lo, b.u_hi, b.m, perm, b.qbase, k, qbeg, nq, O,
+                                  s_cand[wave], s_cid[wave], lane, item);
         break;
     }
     wave_sync();
   }
 }
 
-// capacity and input check (one thread): status and total for the host
+// capacity and input check (one wavefront): status and total for the host
 // With a stash (snext non-null), *stash_done = 1 if the check passed and
 // the stash holds every hit of the count traversal (then the stash scatter
 // places the pairs of the instances with d > 1 and the fill skips them).
@@ -349,11 +357,14 @@ __global__ void b_status_kernel(const BInst* __restrict__ I, uint32_t count,
                                 uint32_t* __restrict__ status, uint64_t* __restrict__ words,
                                 const uint32_t* __restrict__ snext,
                                 uint32_t* __restrict__ stash_done) {
+  // one wavefront; the lanes share the instances' flags
+  bool bad = false;
+  for (uint32_t i = threadIdx.x; i < count; i += kWave) bad = bad || *I[i].flag != 0;
+  const bool any = ballot(bad) != 0;
   if (threadIdx.x != 0) return;
   const uint64_t total = off[M];
-  uint32_t st = total > capacity ? kBatchStatusCapacity : 0u;
-  for (uint32_t i = 0; i < count; ++i)
-    if (*I[i].flag) st |= kBatchStatusInput;
+  const uint32_t st =
+      (total > capacity ? kBatchStatusCapacity : 0u) | (any ? kBatchStatusInput : 0u);
   *status = st;
   if (snext) *stash_done = (st == 0 && snext[kStashSlices] == 0) ? 1u : 0u;
   words[0] = total;
@@ -446,6 +457,7 @@ struct ddm_batch {
   uint32_t ntrees = 0, index_items = 0;
   uint2* lowmap = nullptr;
   uint32_t nlow = 0;
+  size_t lowlds = 0;  // dynamic LDS of the low pass (the strips of the largest d)
   std::vector<std::pair<uint2*, uint32_t>> highmaps;  // per pass S = 11, 22, ...
   uint2* probemap = nullptr;
   uint32_t nprobe = 0;
@@ -483,6 +495,19 @@ struct ddm_batch {
 namespace ddm {
 ddm_status ensure_segsort_attr();
 
+// the strips' dynamic LDS exceeds the default limit at d = 4
+static ddm_status ensure_low_attr() {
+  static std::once_flag once;
+  static hipError_t err = hipSuccess;
+  std::call_once(once, [] {
+    err = hipFuncSetAttribute((const void*)b_tree_low_kernel,
+                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)strip_lds_bytes(DDM_MAX_D));
+  });
+  if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute", __FILE__, __LINE__);
+  return DDM_OK;
+}
+
 // count half: trees, probe, order, count traversal, offsets, ranges
 static ddm_status batch_count_half(ddm_batch* b, hipStream_t s) {
   // clear counters, histograms, flags and length bounds
@@ -494,7 +519,7 @@ static ddm_status batch_count_half(ddm_batch* b, hipStream_t s) {
   if (r != DDM_OK) return r;
   b_index_kernel<<<dim3((b->index_items + 255) / 256, b->ntrees), 256, 0, s>>>(b->jobs);
   DDM_LAUNCHED("b_index_kernel");
-  b_tree_low_kernel<<<b->nlow, kTreeThreads, 0, s>>>(b->jobs, b->lowmap);
+  b_tree_low_kernel<<<b->nlow, kTreeThreads, b->lowlds, s>>>(b->jobs, b->lowmap);
   DDM_LAUNCHED("b_tree_low_kernel");
   uint32_t S = kChunkLog;
   for (auto& hm : b->highmaps) {
@@ -531,11 +556,11 @@ static ddm_status batch_count_half(ddm_batch* b, hipStream_t s) {
       O.snext = b->snext;
       O.sfirst = b->sfirst;
       O.sslice = b->sslice;
-      b_traverse_kernel<false, true><<<b->grid, kTileWaves * kWave, 0, s>>>(
+      b_traverse_kernel<kTileStash><<<b->grid, kTileWaves * kWave, 0, s>>>(
           b->inst, b->G, b->tpc, b->tmapc, b->gstart, b->gcount, b->perm, b->tickets,
           b->opts.waves_per_cu, b->status, O, nullptr);
     } else {
-      b_traverse_kernel<false><<<b->grid, kTileWaves * kWave, 0, s>>>(
+      b_traverse_kernel<kTileCount><<<b->grid, kTileWaves * kWave, 0, s>>>(
           b->inst, b->G, b->tpc, b->tmapc, b->gstart, b->gcount, b->perm, b->tickets,
           b->opts.waves_per_cu, b->status, O, nullptr);
     }
@@ -570,7 +595,7 @@ static ddm_status batch_fill_half(ddm_batch* b, hipStream_t s) {
     SegOut O{};
     O.base = b->off;
     O.out = b->out;
-    b_traverse_kernel<true><<<b->grid, kTileWaves * kWave, 0, s>>>(
+    b_traverse_kernel<kTileFill><<<b->grid, kTileWaves * kWave, 0, s>>>(
         b->inst, b->G, b->tpf, b->tmapf, b->gstart, b->gcount, b->perm, b->tickets + 1,
         b->opts.waves_per_cu, b->status, O, b->stash ? b->stash_done : nullptr);
     DDM_LAUNCHED("b_traverse_kernel");
@@ -623,7 +648,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
   }
   uint64_t M = 0, elems = 0, Btot = 0;
   uint32_t nmax = 0, ntrees = 0, narr = 0, ntiles = 0, nlow = 0, nprobe = 0, items = kQuant;
-  uint32_t maxH = 0;
+  uint32_t maxH = 0, dmax = 0;
   uint64_t tiles_max = 0;
   for (uint32_t i = 0; i < count; ++i) {
     const ddm_batch_instance& q = inst[i];
@@ -637,6 +662,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
     uint32_t H = 0;
     while (((1ull << H) - 1) < q.n) ++H;
     maxH = std::max(maxH, H);
+    dmax = std::max(dmax, q.d);
     M += q.m;
     elems += (uint64_t)q.d * q.n;
     nmax = std::max(nmax, q.n);
@@ -672,6 +698,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
   b->ntiles = ntiles;
   b->nlow = nlow;
   b->nprobe = nprobe;
+  b->lowlds = dmax > 1 ? strip_lds_bytes(dmax) : 0;
   b->index_items = items;
   hipError_t e = hipGetDevice(&b->device);
   if (e != hipSuccess) {
@@ -701,6 +728,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
   // offsets of per-instance storage (relative to mem), patched to pointers
   struct InstOff {
     size_t rec[DDM_MAX_D], mx[DDM_MAX_D], bm[DDM_MAX_D], sidx_lo[DDM_MAX_D], quant[DDM_MAX_D];
+    size_t srec[DDM_MAX_D], sid[DDM_MAX_D], sbox[DDM_MAX_D];
     size_t id, klo, khi, sidx_hi, maxlen, flag, klo_tmp, khi_tmp, val_tmp;
     uint32_t H, P, C, ns;
   };
@@ -722,6 +750,12 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
       f.bm[k] = take(sizeof(float) * f.C);
       f.sidx_lo[k] = take(sizeof(uint32_t) * f.ns);
       f.quant[k] = take(sizeof(uint32_t) * kQuant);
+      if (q.d > 1) {
+        const size_t slots = (size_t)strip_count(q.n) << kStripLog;
+        f.srec[k] = take(sizeof(float) * slots * 2 * q.d);
+        f.sid[k] = take(sizeof(uint32_t) * slots);
+        f.sbox[k] = take(sizeof(float) * (slots / 64) * 2 * q.d);
+      }
     }
     f.id = take(sizeof(uint32_t) * (size_t)(q.n + 1) * q.d);
     f.klo = take(sizeof(uint32_t) * (size_t)q.n * q.d);
@@ -741,6 +775,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
     bi.qbase = (uint32_t)qbase;
     bi.bbase = (uint32_t)bbase;
     bi.nb = std::max<uint32_t>(1, (q.m + 7) / 8);
+    cell_shape(q.m, q.d, bi.nb, bi.cb);
     bi.qpt = q.qpt ? q.qpt : o.qpt;
     bi.ebase = ebase;
     qbase += q.m;
@@ -855,7 +890,13 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
       T.sidx_lo[k] = P32(f.sidx_lo[k]);
       T.sidx_hi[k] = q.d == 1 ? P32(f.sidx_hi) : nullptr;
       T.quant[k] = P32(f.quant[k]);
+      if (q.d > 1) {
+        T.srec[k] = PF(f.srec[k]);
+        T.sid[k] = P32(f.sid[k]);
+        T.sbox[k] = PF(f.sbox[k]);
+      }
     }
+    T.nblk = q.d > 1 ? strip_count(q.n) * kStripBlocks : 0u;
     T.maxlen = (const float*)(zmaxlen + (size_t)i * DDM_MAX_D);
     T.n = q.n;
     T.d = q.d;
@@ -875,6 +916,11 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
       j.sidx_lo = P32(f.sidx_lo[k]);
       j.sidx_hi = q.d == 1 ? P32(f.sidx_hi) : nullptr;
       j.quant = P32(f.quant[k]);
+      if (q.d > 1) {
+        j.srec = PF(f.srec[k]);
+        j.sid = P32(f.sid[k]);
+        j.sbox = PF(f.sbox[k]);
+      }
       j.maxlen_bits = zmaxlen + (size_t)i * DDM_MAX_D + k;
       j.n = q.n;
       j.d = q.d;
@@ -972,6 +1018,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
     return r;
   }
   ddm_status r = ensure_segsort_attr();
+  if (r == DDM_OK) r = ensure_low_attr();
   if (r != DDM_OK) {
     ddm_batch_free(b);
     return r;

@@ -75,6 +75,8 @@ struct Scratch {
     return reinterpret_cast<T*>(p);
   }
   bool fits() const { return used_ <= want_; }
+  // gives the block back now (stream-ordered, as at destruction)
+  void drop();
   hipStream_t s_;
   char* base_ = nullptr;
   size_t want_ = 0, used_ = 0;
@@ -133,7 +135,13 @@ struct TreeDev {
   // kQuant quantiles of the sorted lower-bound keys: quant[k][i] =
   // skey_lo[k][floor(i n / kQuant)]
   const uint32_t* quant[DDM_MAX_D];
-  uint32_t n, d, H, ns;
+  // d > 1: the records in strips, their ids and block boxes (tree_dev.h), or
+  // null; nblk blocks
+  const float* srec[DDM_MAX_D];
+  const uint32_t* sid[DDM_MAX_D];
+  const float* sbox[DDM_MAX_D];
+  const float* rid;  // the set as n records by id: lo_0, hi_0, lo_1, .. (or null)
+  uint32_t n, d, H, ns, nblk;
 };
 
 constexpr uint32_t kQuant = 4096;
@@ -187,6 +195,47 @@ __device__ __forceinline__ float uniform_f32(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
+// inclusive sum of v over lanes 0..lane of the wavefront: row shifts by 1,
+// 2, 4 and 8 (lanes before the row's start add 0) give each 16-lane row
+// its own prefix; broadcasting lane 15 into row 1 and lane 47 into row 3,
+// then lane 31 into rows 2 and 3, carries the row totals forward
+__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// v of the lane that the DPP control names, this lane's own where there is none
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_own(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false);
+}
+// folds v over the wavefront with row shifts and row broadcasts (as
+// wave_scan_dpp); the whole lies in the last lane
+template <class F>
+__device__ __forceinline__ uint32_t wave_fold_dpp(uint32_t v, F op) {
+  v = op(v, dpp_or_own<0x111, 0xf>(v));
+  v = op(v, dpp_or_own<0x112, 0xf>(v));
+  v = op(v, dpp_or_own<0x114, 0xf>(v));
+  v = op(v, dpp_or_own<0x118, 0xf>(v));
+  v = op(v, dpp_or_own<0x142, 0xa>(v));
+  v = op(v, dpp_or_own<0x143, 0xc>(v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+__device__ __forceinline__ float wave_min(float v) {
+  return __uint_as_float(wave_fold_dpp(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fminf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return __uint_as_float(wave_fold_dpp(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
 // first index in sorted keys[0..n) with keys[i] >= x
 __device__ __forceinline__ uint32_t lower_bound_u32(const uint32_t* __restrict__ keys, uint32_t n,
                                                     uint32_t x) {
@@ -382,6 +431,12 @@ ddm_status match_learned_begin_granted(const ddm_tree* t, const float* upd_lo,
                                        const ddm_predictor* pred, uint64_t* out_count,
                                        hipStream_t s, const ddm_match_opts* opts,
                                        ddm_pending** out_pending, const ArenaGrant& grant);
+
+// ddm_match_begin for a caller that accounts device memory: without the dense
+// form, whose scratch is not bounded by the pairs
+ddm_status match_begin_bounded(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
+                               uint32_t m, uint64_t* out_count, hipStream_t s,
+                               const ddm_match_opts* opts, ddm_pending** out_pending);
 
 // the same for K pairs and any n (ids above 2^20 are sorted from a copy)
 ddm_status sort_segments_keys(const uint64_t* off, uint32_t m, uint64_t* out, uint64_t K,

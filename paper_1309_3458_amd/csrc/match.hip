@@ -6,27 +6,31 @@
 //   1. probe: d = 1 (bits1_kernel): the exact count of every update from
 //      two binary searches on sorted lower and upper bounds (the BITS
 //      identity recalled in Sec. II), already the final count.  d > 1
-//      (probe_kernel): the probe dimension k* with the fewest candidate
-//      positions, estimated from quantiles of the sorted lower bounds held
-//      in LDS, bounds of those positions, and the update's bucket (k* and
-//      its place in tree k*, or a cell of tree positions and the other
-//      dimensions) with its rank inside the bucket.
-//   2. updates placed in bucket order (a counting sort), cut into tiles of
-//      up to 64 updates of one bucket.
-//   3. count traversal (d > 1): one wavefront per tile scans the tile's
-//      candidate positions of tree k* and tests every candidate in all d
-//      dimensions (membership in every per-dimension overlap set is decided
-//      by that dimension's own predicate, so the intersection of Sec. III-A
-//      is formed without listing the per-dimension sets); the hits are kept
-//      when they fit.  The lane form walks Algorithm 4 per update instead.
+//      (probe_kernel): the probe dimension k* (of the few candidate
+//      positions), estimated from quantiles of the sorted lower bounds held
+//      in LDS, bounds of those positions, and the update's cell (k* and its
+//      place in every dimension) with its rank inside the cell.
+//   2. updates placed in cell order (a counting sort); a tile is up to 64
+//      consecutive ones.
+//   3. count traversal (d > 1): one wavefront per tile reads the blocks of
+//      subscriptions whose boxes meet the tile's and tests every candidate in
+//      all d dimensions (membership in every per-dimension overlap set is
+//      decided by that dimension's own predicate, so the intersection of Sec.
+//      III-A is formed without listing the per-dimension sets); the hits are
+//      kept when they fit.  The lane form walks Algorithm 4 per update
+//      instead.
 //   4. exclusive scan of the counts -> segment offsets, total K.
 //   5. the kept hits placed, or a fill traversal (the same scan) writing
 //      each hit into the update's own segment (each query owns its column
 //      of M, so lanes never conflict).
 //   6. per-segment sort by subscription id.
+// Dense sets (by a sample before the count, by their counts, or by
+// prediction) go another way (dense.h): the tiles' candidates are listed and
+// sorted by id, and the pairs come out of the tests in order, without 5 and 6.
 // The learned single pass replaces 3-5 by one traversal that writes into
 // slots sized by a predictor while counting exactly.
 #include "ddm_internal.h"
+#include "dense.h"
 #include "traverse.h"
 
 #include <algorithm>
@@ -60,48 +64,42 @@ int tree_device(const ddm_tree* t);
 // from kQuant quantiles of the sorted lower bounds held in LDS; any choice of
 // k* gives the same pairs, only the work differs.
 //
-// Both kernels bucket the update by (k*, position of q.hi in tree k*) and
-// take its rank inside the bucket from the histogram atomic, so the order is
-// a counting sort without a second pass of atomics.
+// Both kernels put the update into a cell and take its rank inside the cell
+// from the histogram atomic, so the order is a counting sort without a second
+// pass of atomics.  d = 1: cells are ranges of the position of q.hi.  d > 1: a
+// class per probe dimension, each with a grid of cells over the quantiles of
+// every dimension, numbered along a serpentine (each line runs back where the
+// last one ended), so that any 64 consecutive updates are neighbours in every
+// dimension.  A tile is 64 (or 32 or 16) consecutive updates of a class, full
+// wherever it starts: its enclosing box, which decides how many blocks it
+// reads and how many candidates it tests, is that of about 64 neighbours.
+// Cells that tiles could not cross left them a third full where updates were
+// few (76,543 updates in 4096 cells: 19 per tile) and as wide as the cell where
+// they were many.
 // --------------------------------------------------------------------------
-constexpr uint32_t kBucketsPerDim = 8192;
-constexpr uint32_t kBuckets = kBucketsPerDim * DDM_MAX_D;
-// The rank of an update in its bucket comes from a device-scope atomic on
-// the bucket's counter; counters 128 bytes apart (one per cache line), so
-// that the atomics of different buckets do not queue on one line (at
-// 10^6 boxes all updates fall into the 4096 cells of their probe dimension,
-// and with packed counters about a thousand atomics would share each line).
-constexpr uint32_t kCntPad = 32;
+constexpr uint32_t kCells = 16384;  // cells per class
+constexpr uint32_t kBuckets = kCells * DDM_MAX_D;
+// The rank of an update in its cell comes from a device-scope atomic on the
+// cell's counter; counters 32 bytes apart, so that the atomics of different
+// cells do not queue on one line.
+constexpr uint32_t kCntPad = 8;
+// cells of one workgroup of the scan of the counters
+constexpr uint32_t kCellBlock = 2048;
+constexpr uint32_t kCellBlocks = kCells / kCellBlock;  // per class
 
-// d > 1: the first half of a dimension's buckets are ranges of the position
-// in tree k*; an update whose candidate range is longer than kCellRange
-// positions goes instead to the second half: cells of B0 position ranges
-// times B1 ranges (equal numbers of lower bounds, from the quantiles) of
-// each other dimension, B0 * B1^(d-1) = kLineBins, so that the updates of a
-// tile are close in every dimension and the tile's enclosing box filters
-// most candidates before they are tested one by one.  Only very short
-// ranges, where scanning dominates, keep the 1-D order.  The shape follows
-// the update's estimated range: a tile scans its cell's width plus one
-// update's range, so B0 is the power of two nearest to the number of
-// ranges of that length in the tree (B1 = 2^e, B0 = kLineBins / 2^(e(d-1))).
-// Measured (match, one MI355X): 10^6 boxes d = 2 alpha = 1 0.40 -> 0.30 ms,
-// d = 3 0.50 -> 0.25 ms, alpha = 10 1.22 -> 1.00 ms, against a threshold of
-// 4096 and fixed shapes.
-constexpr uint32_t kLineBins = kBucketsPerDim / 2;
-constexpr uint32_t kCellRange = 256;
-constexpr float kCellBias = 0.0f;  // log2 of (B0 * range / positions) aimed at
+struct CellShape {
+  uint32_t b[DDM_MAX_D];  // cells along each dimension, as cell_shape gives them
+};
 
-// log2 B1 for an update whose candidate range holds about `best` of the
-// kQuant quantile steps (B0 then about kQuant / best), at least 2 cells per
-// dimension and at least 16 position ranges
-template <int D>
-__device__ __forceinline__ uint32_t cell_log2(uint32_t best) {
-  const float x = (log2f((float)best) - kCellBias) / (float)(D - 1);
-  const int e = (int)floorf(x + 0.5f);
-  return (uint32_t)max(1, min(e, 8 / (D - 1)));
+// updates per tile: 64, or fewer (down to 4) while that leaves at most
+// kFewTiles tiles, so that the chip has wavefronts to run (17,389 updates of
+// 21 hits each, count: 73 us with 16 to a tile, 21 with 4)
+constexpr uint32_t kFewTiles = 8192;
+static uint32_t tile_updates(uint32_t m) {
+  uint32_t q = 4;
+  while (q < 64u && m > q * kFewTiles) q *= 2;
+  return q;
 }
-// the shape of a probe dimension no sampled update takes with cells
-__host__ __device__ constexpr uint32_t kCellLog2Default(int D) { return D == 2 ? 3 : D == 3 ? 2 : 1; }
 
 __global__ __launch_bounds__(256) void bits1_kernel(TreeDev T, const float* __restrict__ ulo,
                                                     const float* __restrict__ uhi, uint32_t m,
@@ -127,21 +125,21 @@ __global__ __launch_bounds__(256) void bits1_kernel(TreeDev T, const float* __re
     const uint32_t ph = bad ? 0u : res[0];
     cmin[j] = c;
     kstar[j] = 0;
-    const uint32_t bu = min((uint32_t)(((uint64_t)ph * kBucketsPerDim) / ((uint64_t)T.n + 1)),
-                            kBucketsPerDim - 1u);
+    const uint32_t bu =
+        min((uint32_t)(((uint64_t)ph * kCells) / ((uint64_t)T.n + 1)), kCells - 1u);
     bucket[j] = bu;
     rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
   }
   if (ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
 }
 
-// the probe estimate of update j: the dimension k* with the fewest
-// candidate positions (best, in quantile steps), #quantiles <= q.hi there
-// (bqa) and its key (bx), the box centre, and whether the extent is invalid
+// the probe estimate of an update: the probe dimension bk, #quantiles <=
+// q.hi and < q.lo - maxlen there (bqa, bqb), #quantiles <= the box centre in
+// every dimension, and whether the extent is invalid
 template <int D>
 struct ProbeEst {
-  uint32_t best, bk, bqa, bqb, bx;
-  float mid[D];
+  uint32_t bk, bqa, bqb;
+  uint32_t mid[D];
   float hits;  // subscriptions met, were the dimensions independent
   bool bad;
 };
@@ -188,67 +186,57 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
                                                       const uint32_t (*sq)[kQuantPad],
                                                       const UpdExt<D>& e) {
   ProbeEst<D> P;
-  P.best = 0xffffffffu;
-  P.bk = 0;
-  P.bqa = 0;
-  P.bqb = 0;
-  P.bx = 0;
   P.bad = false;
-  uint32_t xh[D], xl[D], qa[D], qb[D];
+  uint32_t xh[D], xl[D], xm[D], qa[D], qb[D], qm[D];
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const float a = e.a[k], b = e.b[k];
     P.bad = P.bad || !valid_extent(a, b);
-    P.mid[k] = 0.5f * a + 0.5f * b;
     xh[k] = f2key(b);
     xl[k] = f2key(nextafterf(a - T.maxlen[k], -INFINITY));
-    qa[k] = 0;
-    qb[k] = 0;
+    xm[k] = f2key(0.5f * a + 0.5f * b);
+    qa[k] = qb[k] = qm[k] = 0;
   }
-  // the 2D quantile searches (#quantiles <= xh, #quantiles < xl per
-  // dimension) advance in lockstep, so their LDS reads overlap
+  // the 3D quantile searches (#quantiles <= xh, < xl, <= xm per dimension)
+  // advance in lockstep, so their LDS reads overlap
 #pragma unroll
   for (uint32_t step = kQuant; step > 0; step >>= 1) {
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-      const uint32_t ca = qa[k] + step, cb = qb[k] + step;
+      const uint32_t ca = qa[k] + step, cb = qb[k] + step, cm = qm[k] + step;
       const uint32_t va = ca <= kQuant ? sq[k][qslot(ca - 1)] : 0xffffffffu;
       const uint32_t vb = cb <= kQuant ? sq[k][qslot(cb - 1)] : 0xffffffffu;
+      const uint32_t vm = cm <= kQuant ? sq[k][qslot(cm - 1)] : 0xffffffffu;
       if (ca <= kQuant && va <= xh[k]) qa[k] = ca;
       if (cb <= kQuant && vb < xl[k]) qb[k] = cb;
+      if (cm <= kQuant && vm <= xm[k]) qm[k] = cm;
     }
   }
+  // dimension 0, unless another one's range is less than half as long: one
+  // class where the dimensions are alike (a tile's neighbours are then not
+  // spread over several classes), separate ones for updates that are narrow
+  // in different dimensions
+  uint32_t best = 0;
   P.hits = (float)T.n;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const uint32_t est = qa[k] - min(qa[k], qb[k]);
     P.hits *= fmaxf((float)est, 0.5f) * (1.f / (float)kQuant);
-    if (est < P.best) {
-      P.best = est;
+    P.mid[k] = qm[k];
+    if (k == 0 || 2u * est + 16u < best) {
+      best = est;
       P.bk = (uint32_t)k;
       P.bqa = qa[k];
       P.bqb = qb[k];
-      P.bx = xh[k];
     }
   }
   return P;
 }
 
-template <int D>
-__device__ __forceinline__ bool cell_mode(uint32_t best, uint32_t n) {
-  return (uint64_t)best * n > (uint64_t)kCellRange * kQuant;
-}
-
-// The cell shape of each probe dimension (run by one workgroup of at least
-// kShapeSamples threads): the most common cell_log2 over up to
-// kShapeSamples updates spread evenly over the set, among those that would
-// take that dimension with cells.
-// One shape per dimension keeps the cells of different updates from sharing
-// buckets while meaning different boxes (a tile that mixed them would scan
-// the union of far-apart ranges).
 constexpr uint32_t kShapeSamples = 256;
 
-// The samples also decide whether the count traversal keeps its hits: when
+// Up to kShapeSamples updates spread evenly over the set decide whether the
+// count traversal keeps its hits: when
 // the estimated hits (the candidate fractions of the dimensions multiplied,
 // as if they were independent) exceed kStashDenseHits per update or the
 // stash's counted chunks, the stash is marked full before it is used, and the
@@ -260,59 +248,35 @@ constexpr uint32_t kShapeSamples = 256;
 // dimensions are correlated may still overflow the stash.
 constexpr float kStashDenseHits = 32.f;
 
+// (run by one workgroup of at least kShapeSamples threads)
 template <int D, uint32_t THREADS>
-__device__ __forceinline__ void sample_cell_shape(const TreeDev& T, const float* __restrict__ ulo,
-                                                  const float* __restrict__ uhi, uint32_t m,
-                                                  uint32_t* __restrict__ shape,
-                                                  uint32_t* __restrict__ full, uint32_t room) {
+__device__ __forceinline__ void sample_density(const TreeDev& T, const float* __restrict__ ulo,
+                                               const float* __restrict__ uhi, uint32_t m,
+                                               uint32_t* __restrict__ full, uint32_t room) {
   static_assert(THREADS >= kShapeSamples, "one sample per thread");
   __shared__ uint32_t sq[D][kQuantPad];
-  __shared__ uint32_t hist[D][16];
   __shared__ float whits[kShapeSamples / kWave];
   const uint32_t S = min(m, kShapeSamples);
   UpdExt<D> e{};
   if (threadIdx.x < S) e = load_ext<D>(ulo, uhi, m, (uint32_t)(((uint64_t)threadIdx.x * m) / S));
-  for (uint32_t i = threadIdx.x; i < D * 16; i += THREADS) hist[i / 16][i % 16] = 0;
   load_quant_lds<D, THREADS>(T, sq);
   __syncthreads();
   if (threadIdx.x < kShapeSamples) {
-    // (k*, shape) of this lane's sample, or none; counted per wavefront
-    // (one LDS add per distinct value, as the samples mostly agree)
-    uint32_t key = ~0u;
     float hits = 0.f;
     if (threadIdx.x < S) {
       const ProbeEst<D> P = probe_estimate<D>(T, sq, e);
       if (!P.bad) hits = P.hits;
-      if (!P.bad && cell_mode<D>(P.best, T.n)) key = P.bk * 16u + cell_log2<D>(P.best);
-    }
-    uint64_t left = ballot(key != ~0u);
-    while (left) {
-      const uint32_t lead = (uint32_t)__builtin_ctzll(left);
-      const uint32_t lk = (uint32_t)__shfl((int)key, (int)lead, kWave);
-      const uint64_t same = ballot(key == lk) & left;
-      if (lane_id() == lead) atomicAdd(&hist[lk / 16u][lk % 16u], (uint32_t)__popcll(same));
-      left &= ~same;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, kWave);
     if (lane_id() == 0) whits[threadIdx.x / kWave] = hits;
   }
   __syncthreads();
-  if (threadIdx.x == 0 && full) {
+  if (threadIdx.x == 0) {
     float t = 0.f;
     for (uint32_t w = 0; w < kShapeSamples / kWave; ++w) t += whits[w];
     t /= (float)S;
-    *full = t > kStashDenseHits || t * (float)m > (float)room ? 1u : 0u;
-  }
-  if (threadIdx.x < D) {
-    const uint32_t k = threadIdx.x;
-    uint32_t e = kCellLog2Default(D), c = 0;
-    for (uint32_t x = 1; x < 16; ++x)
-      if (hist[k][x] > c) {
-        c = hist[k][x];
-        e = x;
-      }
-    shape[k] = e;
+    *full = t > kStashDenseHits || t * (float)m > (float)room ? kStashDense : 0u;
   }
 }
 
@@ -320,7 +284,7 @@ constexpr uint32_t kProbeThreads = 1024;
 template <int D>
 __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const float* __restrict__ ulo,
                                                      const float* __restrict__ uhi, uint32_t m,
-                                                     const uint32_t* __restrict__ shape,
+                                                     CellShape shape,
                                                      uint8_t* __restrict__ kstar,
                                                      uint32_t* __restrict__ bucket,
                                                      uint32_t* __restrict__ rank,
@@ -338,29 +302,7 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
   if (act) {
     const ProbeEst<D> P = probe_estimate<D>(T, sq, e);
     bad = P.bad;
-    uint32_t bk = P.bk;
-    const uint32_t best = P.best, bqa = P.bqa, bx = P.bx;
-    // position of q.hi in tree k*, interpolated between its two quantiles
-    float fine;
-    if (bqa == 0) {
-      fine = 0.f;
-    } else if (bqa >= kQuant) {
-      fine = (float)kQuant - 0.5f;
-    } else {
-      uint32_t kl = 0, ku = 0;
-#pragma unroll
-      for (int k = 0; k < D; ++k)
-        if ((uint32_t)k == bk) {
-          kl = sq[k][qslot(bqa - 1)];
-          ku = sq[k][qslot(bqa)];
-        }
-      const float fr = ku > kl ? (float)(bx - kl) / (float)(ku - kl) : 0.f;
-      fine = (float)(bqa - 1) + fminf(fr, 0.999f);
-    }
-    if (bad) {
-      bk = 0;
-      fine = 0.f;
-    }
+    const uint32_t bk = bad ? 0u : P.bk;
     kstar[j] = (uint8_t)bk;
     // bounds of the candidate positions in tree k* from the quantiles
     // quant[i] = skey_lo[floor(i n / kQuant)]: bqb quantiles lie below
@@ -368,153 +310,107 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
     // bqa quantiles are <= q.hi and quantile bqa is not, so at most
     // floor(bqa n / kQuant) keys are (positions are 1-based)
     {
-      const uint32_t qb = P.bqb, qa = bqa;
+      const uint32_t qb = P.bqb, qa = P.bqa;
       const uint32_t lo = qb ? (uint32_t)(((uint64_t)(qb - 1) * T.n) / kQuant) + 1u : 0u;
       const uint32_t hi = qa < kQuant ? (uint32_t)(((uint64_t)qa * T.n) / kQuant) : T.n;
       pb[j] = bad ? make_uint2(1u, 0u) : make_uint2(lo + 1u, hi);
     }
-    uint32_t sub;
-    if (!bad && cell_mode<D>(best, T.n)) {
-      const uint32_t e = shape[bk];
-      const uint32_t B1 = 1u << e, B0 = kLineBins >> ((D - 1) * e);
-      sub = min((uint32_t)(fine * (float)B0 / (float)kQuant), B0 - 1u);
+    uint32_t sub = 0;
 #pragma unroll
-      for (int k = 0; k < D; ++k) {
-        if ((uint32_t)k == bk) continue;
-        const uint32_t qp = quant_count(sq[k], f2key(P.mid[k]), true);
-        sub = sub * B1 + min(qp * B1 / (kQuant + 1u), B1 - 1u);
-      }
-      sub += kLineBins;
-    } else {
-      sub = min((uint32_t)(fine * (float)kLineBins / (float)kQuant), kLineBins - 1u);
+    for (int s = 0; s < D; ++s) {
+      const uint32_t kk = s == 0 ? bk : (uint32_t)(s - 1) + (((uint32_t)(s - 1) >= bk) ? 1u : 0u);
+      uint32_t qp = 0;
+#pragma unroll
+      for (int k = 0; k < D; ++k)
+        if ((uint32_t)k == kk) qp = P.mid[k];
+      const uint32_t n = shape.b[s];
+      uint32_t i = min(qp * n / (kQuant + 1u), n - 1u);
+      if (sub & 1u) i = n - 1u - i;  // the serpentine's way back
+      sub = sub * n + i;
     }
-    const uint32_t bu = bk * kBucketsPerDim + sub;
+    const uint32_t bu = bk * kCells + (bad ? 0u : sub);
     bucket[j] = bu;
     rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
   }
   if (ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
 }
 
-// exclusive scan of the bucket counts (one workgroup, through LDS); the
-// number of updates of each probe dimension falls out of group boundaries.
-// With tprefix non-null, also the exclusive prefix of the buckets' tiles of
-// at most 64 updates (tprefix[kBuckets] = all tiles).  Only the d *
-// kBucketsPerDim buckets of the probe dimensions in use are scanned (PER =
-// d * 8 per thread); bhist and tprefix are written up to that bound
-// inclusive, so that the last bucket has an end.
-// the padded bucket counters gathered into consecutive words (many
-// workgroups, so that the single-workgroup scan below reads dense memory)
-__global__ __launch_bounds__(256) void bucket_gather_kernel(const uint32_t* __restrict__ bcnt,
-                                                            uint32_t nb,
-                                                            uint32_t* __restrict__ dense) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nb) dense[i] = bcnt[(size_t)i * kCntPad];
-}
-
-template <uint32_t PER>
-__global__ __launch_bounds__(1024) void bucket_scan_kernel(uint32_t* __restrict__ bhist,
-                                                           uint32_t m,
-                                                           uint32_t* __restrict__ gstart_out,
-                                                           uint32_t* __restrict__ gcount,
-                                                           uint32_t* __restrict__ tprefix) {
-  // thread tid owns buckets tid*PER .. tid*PER+PER-1, kept in registers; the
-  // LDS copy is padded (one word per PER, PER + 1 odd) so that these reads
-  // do not conflict, and global reads and writes go through it in
-  // coalesced order
-  constexpr uint32_t NB = PER * 1024;
-  static_assert(NB <= kBuckets && NB % kBucketsPerDim == 0, "whole probe dimensions");
-  __shared__ uint32_t sb[NB + 1024];
-  __shared__ uint32_t wsum[1024 / kWave];
-  __shared__ uint32_t tws[1024 / kWave];
-  __shared__ uint32_t gstart[DDM_MAX_D + 1];
+// exclusive scan of each workgroup's kCellBlock cell counts, and its total
+__global__ __launch_bounds__(256) void cell_scan_kernel(const uint32_t* __restrict__ bcnt,
+                                                        uint32_t* __restrict__ boff,
+                                                        uint32_t* __restrict__ bsum) {
+  constexpr uint32_t PER = kCellBlock / 256;
+  __shared__ uint32_t sb[kCellBlock + 256];
+  __shared__ uint32_t wsum[256 / kWave];
   const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  if (tid <= DDM_MAX_D) gstart[tid] = m;  // dimensions beyond d hold no update
-  for (uint32_t i = tid; i < NB; i += 1024) sb[i + i / PER] = bhist[i];
+  const uint32_t base = blockIdx.x * kCellBlock;
+  uint32_t v[PER];
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) v[r] = bcnt[(size_t)(base + r * 256 + tid) * kCntPad];
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const uint32_t i = r * 256 + tid;
+    sb[i + i / PER] = v[r];
+  }
   __syncthreads();
-  uint32_t c[PER];
-  uint32_t sum = 0, tsum = 0;
+  uint32_t c[PER], sum = 0;
 #pragma unroll
   for (uint32_t i = 0; i < PER; ++i) {
     c[i] = sb[tid * (PER + 1) + i];
     sum += c[i];
-    tsum += (c[i] + 63u) / 64u;
   }
-  uint32_t inc = sum, tinc = tsum;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t t2 = __shfl_up(inc, o, kWave);
-    const uint32_t t3 = __shfl_up(tinc, o, kWave);
-    if (lane >= (uint32_t)o) {
-      inc += t2;
-      tinc += t3;
-    }
-  }
-  if (lane == kWave - 1) {
-    wsum[wave] = inc;
-    tws[wave] = tinc;
-  }
+  const uint32_t inc = wave_scan_dpp(sum);
+  if (lane == kWave - 1) wsum[wave] = inc;
   __syncthreads();
-  uint32_t before = 0, tbefore = 0, ttotal = 0;
-  for (uint32_t w = 0; w < 1024 / kWave; ++w) {
-    if (w < wave) {
-      before += wsum[w];
-      tbefore += tws[w];
-    }
-    ttotal += tws[w];
+  uint32_t run = inc - sum, total = 0;
+  for (uint32_t w = 0; w < 256 / kWave; ++w) {
+    if (w < wave) run += wsum[w];
+    total += wsum[w];
   }
-  if (tprefix) {
-    uint32_t trun = tbefore + tinc - tsum;
-#pragma unroll
-    for (uint32_t i = 0; i < PER; ++i) {
-      sb[tid * (PER + 1) + i] = trun;
-      trun += (c[i] + 63u) / 64u;
-    }
-    __syncthreads();
-    for (uint32_t i = tid; i < NB; i += 1024) tprefix[i] = sb[i + i / PER];
-    if (tid == 0) {
-      tprefix[NB] = ttotal;
-      tprefix[kBuckets] = ttotal;
-    }
-    __syncthreads();
-  }
-  uint32_t run = before + inc - sum;
 #pragma unroll
   for (uint32_t i = 0; i < PER; ++i) {
-    const uint32_t x = tid * PER + i;  // a probe dimension starts at x % kBucketsPerDim == 0
-    if (x % kBucketsPerDim == 0) gstart[x / kBucketsPerDim] = run;
     sb[tid * (PER + 1) + i] = run;
     run += c[i];
   }
   __syncthreads();
-  for (uint32_t i = tid; i < NB; i += 1024) bhist[i] = sb[i + i / PER];
-  if (tid == 0 && NB < kBuckets) bhist[NB] = m;
-  if (tid < DDM_MAX_D) {
-    gcount[tid] = gstart[tid + 1] - gstart[tid];
-    gstart_out[tid] = gstart[tid];
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) {
+    const uint32_t i = r * 256 + tid;
+    boff[base + i] = sb[i + i / PER];
   }
+  if (tid == 0) bsum[blockIdx.x] = total;
 }
 
-// updates in bucket order; with tmap non-null also tile -> bucket for the
-// nb buckets (thread j does update j and bucket j)
-__global__ __launch_bounds__(256) void bucket_scatter_kernel(const uint32_t* __restrict__ bucket,
-                                                             const uint32_t* __restrict__ rank,
-                                                             uint32_t m,
-                                                             const uint32_t* __restrict__ bhist,
-                                                             uint32_t* __restrict__ perm,
-                                                             const uint32_t* __restrict__ tprefix,
-                                                             uint32_t* __restrict__ tmap,
-                                                             uint32_t nb) {
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < m) perm[bhist[bucket[j]] + rank[j]] = j;
-  if (tmap && j < nb)
-    for (uint32_t t = tprefix[j]; t < tprefix[j + 1]; ++t) tmap[t] = j;
+// updates in cell order: every workgroup scans the nb totals of the cell
+// blocks (at most 64); the first one also writes the classes' starts and sizes
+__global__ __launch_bounds__(256) void cell_scatter_kernel(
+    const uint32_t* __restrict__ bucket, const uint32_t* __restrict__ rank, uint32_t m,
+    const uint32_t* __restrict__ boff, const uint32_t* __restrict__ bsum, uint32_t nb,
+    uint32_t* __restrict__ perm, uint32_t* __restrict__ gstart, uint32_t* __restrict__ gcount) {
+  static_assert(kCellBlocks * DDM_MAX_D <= kWave, "one lane per cell block");
+  __shared__ uint32_t first[kWave + 1];
+  const uint32_t j = blockIdx.x * 256 + threadIdx.x;
+  const uint32_t bu = j < m ? bucket[j] : 0u, r = j < m ? rank[j] : 0u;
+  if (threadIdx.x < kWave) {
+    const uint32_t v = threadIdx.x < nb ? bsum[threadIdx.x] : 0u;
+    const uint32_t inc = wave_scan_dpp(v);
+    first[threadIdx.x + 1] = inc;
+    if (threadIdx.x == 0) first[0] = 0;
+  }
+  __syncthreads();
+  if (j < m) perm[first[bu / kCellBlock] + boff[bu] + r] = j;
+  if (blockIdx.x == 0 && threadIdx.x < DDM_MAX_D) {
+    const uint32_t a = first[threadIdx.x * kCellBlocks], e = first[(threadIdx.x + 1) * kCellBlocks];
+    gstart[threadIdx.x] = a;
+    gcount[threadIdx.x] = e - a;
+  }
 }
 
 // --------------------------------------------------------------------------
 // Tiles balanced by work (the learned single pass: predicted hits; the
-// plain fill: the exact counts).  Within each bucket the updates are cut
-// into tiles at every 64th update (as for the count) and also wherever the
-// hits accumulated since the bucket's start cross a multiple of H (below),
+// plain fill: the exact counts).  Within each class the updates are cut
+// into tiles as for the count and also wherever the
+// hits accumulated since the class's start cross a multiple of H (below),
 // so that a wavefront never takes a tile of much more output than H: dense
 // regions get several small tiles, which run on separate wavefronts,
 // instead of one long one.
@@ -544,31 +440,32 @@ __global__ __launch_bounds__(256) void work_in_order_kernel(const uint32_t* __re
 
 // flag[p] = 1 where a tile starts; cw: exclusive scan of w (cw[m] = total)
 __global__ __launch_bounds__(256) void tile_cut_kernel(const uint32_t* __restrict__ perm,
-                                                       const uint32_t* __restrict__ bucket,
-                                                       const uint32_t* __restrict__ boff,
+                                                       const uint8_t* __restrict__ kstar,
+                                                       const uint32_t* __restrict__ gstart,
                                                        const uint64_t* __restrict__ cw,
-                                                       uint32_t m, uint32_t* __restrict__ flag) {
+                                                       uint32_t m, uint32_t qpt,
+                                                       uint32_t* __restrict__ flag) {
   const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= m) return;
   const uint64_t H = max((2ull * 64ull * cw[m]) / ((uint64_t)m * kCutDiv), kCutMinHits);
-  const uint32_t s = boff[bucket[perm[p]]];
-  bool cut = p == s || ((p - s) & 63u) == 0;
+  const uint32_t s = gstart[kstar[perm[p]]];
+  bool cut = p == s || (p - s) % qpt == 0;
   if (!cut) cut = (cw[p] - cw[s]) / H != (cw[p - 1] - cw[s]) / H;
   flag[p] = cut ? 1u : 0u;
 }
 
 // tile t starts at the t-th flagged position; tstart[ntiles] = m
 __global__ __launch_bounds__(256) void tile_list_kernel(const uint32_t* __restrict__ perm,
-                                                        const uint32_t* __restrict__ bucket,
+                                                        const uint8_t* __restrict__ kstar,
                                                         const uint32_t* __restrict__ flag,
                                                         const uint64_t* __restrict__ tidx,
                                                         uint32_t m, uint32_t* __restrict__ tstart,
-                                                        uint32_t* __restrict__ tbuck) {
+                                                        uint32_t* __restrict__ tclass) {
   const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p < m && flag[p]) {
     const uint32_t t = (uint32_t)tidx[p];
     tstart[t] = p;
-    tbuck[t] = bucket[perm[p]];
+    tclass[t] = kstar[perm[p]];
   }
   if (p == 0) tstart[(uint32_t)tidx[m]] = m;
 }
@@ -659,46 +556,45 @@ __global__ __launch_bounds__(1024) void lane_kernel(TreeDev T, const float* __re
 // --------------------------------------------------------------------------
 // 3/5b. tile traversal for one instance (body in traverse.h)
 // --------------------------------------------------------------------------
-template <int D, bool FILL>
-__global__ __launch_bounds__(kTileWaves * kWave) void tile_kernel(
-    TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
-    UpdSet US, SegOut O) {
+constexpr uint32_t kXcds = 8;     // accelerator dies (each with its own L2) of the device
+constexpr uint32_t kXcdRun = 32;  // consecutive workgroups of tiles given to one die
+
+// tiles of US.qpt consecutive updates of a class (or the tiles of a list), one
+// wavefront each; the grid covers the largest possible number of tiles
+template <int D, TileMode MODE>
+__global__ __launch_bounds__(kTileWaves * kWave)
+__attribute__((amdgpu_waves_per_eu(D <= 2 ? 8 : 6)))
+void tile_kernel(TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi,
+                 uint32_t m, UpdSet US, SegOut O) {
   constexpr int R = 2 * D;
-  constexpr int RV = (R + 3) / 4;
-  __shared__ float s_cand[kTileWaves][R][kRing];
+  __shared__ __align__(16) float s_cand[kTileWaves][R * kRing];
   __shared__ uint32_t s_cid[kTileWaves][kRing];
-  __shared__ float4 s_q[kTileWaves][kWave][RV];
   const uint32_t wave = threadIdx.x / kWave;
   const uint32_t lane = lane_id();
-  const uint32_t tile = blockIdx.x * kTileWaves + wave;
-
-  // locate the tile inside its probe-dimension group
-  uint32_t qbeg = 0, tacc = 0, nq = 0, k = 0;
-  bool found = false;
-  const uint32_t qpt = US.qpt;
+  uint32_t total = 0;
+  if (US.tstart) {
+    total = uniform_u32((uint32_t)*US.ntiles);
+  } else {
 #pragma unroll
-  for (int g = 0; g < D; ++g) {
-    const uint32_t gs = uniform_u32(US.gcount[g]);
-    const uint32_t nt = (gs + qpt - 1) / qpt;
-    if (!found) {
-      if (tile < tacc + nt) {
-        found = true;
-        k = (uint32_t)g;
-        const uint32_t lt = tile - tacc;
-        qbeg = uniform_u32(US.gstart[g]) + lt * qpt;
-        nq = min(qpt, gs - lt * qpt);
-      } else {
-        tacc += nt;
-      }
-    }
+    for (int g = 0; g < D; ++g) total += (uniform_u32(US.gcount[g]) + US.qpt - 1) / US.qpt;
   }
-  if (!found) return;
-  k = uniform_u32(k);
-  nq = uniform_u32(nq);
-  qbeg = uniform_u32(qbeg);
-
-  tile_body<D, FILL>(T, ulo, uhi, m, US.perm, 0, k, qbeg, nq, O, &s_cand[wave][0][0],
-                     &s_cid[wave][0], &s_q[wave][0][0], lane, 0u, US.pb);
+  // Workgroups go to the XCDs in turn (workgroup i to XCD i mod kXcds).
+  // Neighbouring tiles scan the same part of the tree, so within each window
+  // of kXcds * kXcdRun workgroups the ones on XCD x take kXcdRun consecutive
+  // groups of tiles, whose scans then share that XCD's L2; the workgroups
+  // past the last whole window keep their order.  Any one-to-one map is
+  // correct; this one only changes which L2 serves a tile.
+  const uint32_t nblk = (total + kTileWaves - 1) / kTileWaves;
+  uint32_t blk = blockIdx.x;
+  if (blk >= nblk) return;
+  constexpr uint32_t W = kXcds * kXcdRun;
+  if (blk < nblk / W * W) blk = blk / W * W + blk % kXcds * kXcdRun + blk % W / kXcds;
+  const uint32_t item = blk * kTileWaves + wave;
+  if (item >= total) return;
+  uint32_t k, qbeg, nq;
+  tile_span<D>(US, item, &k, &qbeg, &nq);
+  tile_body<D, MODE>(T, ulo, uhi, m, US.perm, 0u, k, qbeg, nq, O, s_cand[wave], s_cid[wave], lane,
+                     item, US.pb);
 }
 
 // --------------------------------------------------------------------------
@@ -722,88 +618,6 @@ __device__ __forceinline__ void bitonic_regs(uint64_t (&v)[N]) {
         }
       }
     }
-  }
-}
-
-// Where segment j's unsorted keys are.  In the single-pass form the updates
-// that fitted their slots still sit in the slot arena; every other segment
-// is in place in the output.  The sorts below read a segment from its source
-// and write it sorted to its final position, so moving slots into place
-// costs no extra pass.
-// bucket-aligned tiles, one wavefront each (the grid covers the largest
-// possible number of tiles; the waves beyond the actual number return).
-// The traversal is latency-bound, so the register budget of the fill and of
-// the d = 1 forms is set for eight wavefronts per SIMD; the count kernels
-// for d >= 2 (with the transposed flush beside the direct one) for seven,
-// where they spill nothing (at eight they kept 12 registers per lane in
-// scratch and ran 4% slower).
-#ifndef DDM_TILE_COUNT_WAVES
-#define DDM_TILE_COUNT_WAVES 7
-#endif
-constexpr uint32_t kXcds = 8;     // accelerator dies (each with its own L2) of the device
-constexpr uint32_t kXcdRun = 32;  // consecutive workgroups of tiles given to one die
-
-// The count pass (d >= 2) runs the transposed flush beside the untransposed
-// one; with both, seven wavefronts per SIMD leave it room without spilling.
-template <int D, bool FILL>
-constexpr int tile_waves_per_eu() {
-  return (!FILL && D >= 2) ? DDM_TILE_COUNT_WAVES : 8;
-}
-
-template <int D, bool FILL, bool STASH = false>
-__global__ __launch_bounds__(kTileWaves * kWave)
-__attribute__((amdgpu_waves_per_eu(tile_waves_per_eu<D, FILL>())))
-void tile_bucket_kernel(
-    TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
-    UpdSet US, SegOut O) {
-  constexpr int R = 2 * D;
-  constexpr int RV = (R + 3) / 4;
-  // the count pass (d >= 2) takes the transposed flush
-  constexpr bool XP = !FILL && D >= 2;
-  constexpr int XW = XP ? kWave : 1;
-  __shared__ float s_cand[kTileWaves][R * kRing];
-  __shared__ uint32_t s_cid[kTileWaves][kRing];
-  __shared__ float4 s_q[kTileWaves][kWave * RV];
-  __shared__ float s_lo1[kTileWaves][XW];
-  __shared__ uint32_t s_xcnt[kTileWaves][XW];
-  __shared__ uint32_t s_xj[kTileWaves][XW];
-  const uint32_t wave = threadIdx.x / kWave;
-  const uint32_t lane = lane_id();
-  const bool list = US.tstart != nullptr;
-  const uint32_t total = list ? uniform_u32((uint32_t)*US.ntiles)
-                              : uniform_u32(US.tprefix[kBuckets]);
-  {
-    // Workgroups go to the XCDs in turn (workgroup i to XCD i mod kXcds).
-    // Neighbouring tiles (the cells of one probe range) scan the same part
-    // of the tree, so within each window of kXcds * kXcdRun workgroups the
-    // ones on XCD x take kXcdRun consecutive groups of tiles, whose scans
-    // then share that XCD's L2; the workgroups past the last whole window
-    // keep their order.  Any one-to-one map is correct; this one only
-    // changes which L2 serves a tile (measured at 10^6 boxes: d = 2, alpha
-    // = 1 -1%, d = 3 -8%, d = 4 -25%, d = 2, alpha = 10 +7%).
-    const uint32_t nblk = (total + kTileWaves - 1) / kTileWaves;
-    uint32_t blk = blockIdx.x;
-    if (blk >= nblk) return;
-    constexpr uint32_t W = kXcds * kXcdRun;
-    if (blk < nblk / W * W) blk = blk / W * W + blk % kXcds * kXcdRun + blk % W / kXcds;
-    const uint32_t item = blk * kTileWaves + wave;
-    if (item >= total) return;
-    uint32_t b, qbeg, nq;
-    if (list) {
-      b = uniform_u32(US.tbuck[item]);
-      qbeg = uniform_u32(US.tstart[item]);
-      nq = uniform_u32(US.tstart[item + 1]) - qbeg;
-    } else {
-      b = uniform_u32(US.tmap[item]);
-      const uint32_t lt = item - uniform_u32(US.tprefix[b]);
-      const uint32_t start = uniform_u32(US.boff[b]);
-      const uint32_t end = b + 1 < kBuckets ? uniform_u32(US.boff[b + 1]) : US.total;
-      qbeg = start + lt * 64u;
-      nq = min(64u, end - qbeg);
-    }
-    tile_body<D, FILL, STASH, XP>(T, ulo, uhi, m, US.perm, 0u, b / kBucketsPerDim, qbeg, nq, O,
-                                  s_cand[wave], s_cid[wave], s_q[wave], lane, item, US.pb,
-                                  XpLds{s_lo1[wave], s_xcnt[wave], s_xj[wave]});
   }
 }
 
@@ -834,6 +648,12 @@ __device__ __forceinline__ SegAt seg_at(const SegSrc& S, uint32_t j, const uint6
   return SegAt{nullptr, out + b};
 }
 
+// the same for a list of ids sorted into ids (every list lies in its slots, or
+// at its own place)
+__device__ __forceinline__ SegAt list_at(const SegSrc& S, uint32_t j, uint64_t b) {
+  return SegAt{S.slots ? S.slots + S.so.base[j] : S.ids + b, nullptr};
+}
+
 template <int N>
 __device__ __forceinline__ void sort_small_segment(const uint64_t* __restrict__ src,
                                                    uint64_t* __restrict__ dst, uint32_t len) {
@@ -849,22 +669,23 @@ __device__ __forceinline__ void sort_small_segment(const uint64_t* __restrict__ 
 constexpr uint32_t kSegMid = 2048;  // longest segment sorted in LDS by bitonic
 
 // the same, from 4-byte ids, keys formed with the update's high word
-template <int N>
+template <int N, typename OUT>
 __device__ __forceinline__ void sort_small_ids(const uint32_t* __restrict__ src, uint64_t jhi,
-                                               uint64_t* __restrict__ dst, uint32_t len) {
+                                               OUT* __restrict__ dst, uint32_t len) {
   uint64_t v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = ((uint32_t)i < len) ? (jhi | src[i]) : ~0ull;
   bitonic_regs<N>(v);
 #pragma unroll
   for (int i = 0; i < N; ++i)
-    if ((uint32_t)i < len) dst[i] = v[i];
+    if ((uint32_t)i < len) dst[i] = (OUT)v[i];
 }
 
-// IDS: segments may be 4-byte ids (S.ids or S.slots); else all are keys
-template <bool IDS>
+// IDS: segments may be 4-byte ids (S.ids or S.slots); else all are keys.
+// OUT: 64-bit keys, or 32-bit ids alone (then every segment is ids)
+template <bool IDS, typename OUT>
 __global__ __launch_bounds__(256) void segsort_small_kernel(const uint64_t* __restrict__ off,
-                                                            uint32_t m, uint64_t* __restrict__ out,
+                                                            uint32_t m, OUT* __restrict__ out,
                                                             SegSrc S,
                                                             uint32_t* __restrict__ lists,
                                                             uint32_t* __restrict__ list_count) {
@@ -874,27 +695,26 @@ __global__ __launch_bounds__(256) void segsort_small_kernel(const uint64_t* __re
   const uint64_t len64 = off[j + 1] - b;
   if (len64 == 0) return;
   const uint32_t len = len64 > 0xffffffffull ? 0xffffffffu : (uint32_t)len64;
-  const SegAt a = IDS ? seg_at(S, j, out, b) : SegAt{nullptr, out + b};
-  if (IDS && a.ids && len <= 32) {
-    const uint32_t* ip = a.ids;
-    const uint64_t jhi = (uint64_t)j << 32;
-    if (len == 1) out[b] = jhi | ip[0];
-    else if (len <= 4) sort_small_ids<4>(ip, jhi, out + b, len);
-    else if (len <= 8) sort_small_ids<8>(ip, jhi, out + b, len);
-    else if (len <= 16) sort_small_ids<16>(ip, jhi, out + b, len);
-    else sort_small_ids<32>(ip, jhi, out + b, len);
-    return;
-  }
-  const uint64_t* src = a.keys;  // in place
-  if (len == 1) return;
-  if (len <= 4) {
-    sort_small_segment<4>(src, out + b, len);
-  } else if (len <= 8) {
-    sort_small_segment<8>(src, out + b, len);
-  } else if (len <= 16) {
-    sort_small_segment<16>(src, out + b, len);
-  } else if (len <= 32) {
-    sort_small_segment<32>(src, out + b, len);
+  if (len <= 32) {
+    SegAt a{};
+    if constexpr (sizeof(OUT) == 4) a = list_at(S, j, b);
+    else a = IDS ? seg_at(S, j, out, b) : SegAt{nullptr, out + b};
+    if (IDS && a.ids) {
+      const uint32_t* ip = a.ids;
+      const uint64_t jhi = (uint64_t)j << 32;
+      if (len == 1) out[b] = (OUT)(jhi | ip[0]);
+      else if (len <= 4) sort_small_ids<4>(ip, jhi, out + b, len);
+      else if (len <= 8) sort_small_ids<8>(ip, jhi, out + b, len);
+      else if (len <= 16) sort_small_ids<16>(ip, jhi, out + b, len);
+      else sort_small_ids<32>(ip, jhi, out + b, len);
+    } else if constexpr (sizeof(OUT) == 8) {
+      const uint64_t* src = a.keys;  // in place
+      if (len == 1) return;
+      if (len <= 4) sort_small_segment<4>(src, out + b, len);
+      else if (len <= 8) sort_small_segment<8>(src, out + b, len);
+      else if (len <= 16) sort_small_segment<16>(src, out + b, len);
+      else sort_small_segment<32>(src, out + b, len);
+    }
   } else if (len <= kSegMid) {
     lists[atomicAdd(&list_count[0], 1u)] = j;
   } else {
@@ -917,9 +737,9 @@ __global__ __launch_bounds__(256) void segsort_small_kernel(const uint64_t* __re
 // directions, partner i ^ j for j = k/2 .. 1) is faster there: measured on
 // the 256-instance batch, segment sort 0.83 ms classic, 0.88 all-ascending,
 // 0.79 with the split; 16-hotspot workload 9.7 -> 9.1 ms.
-template <int V, typename SRC>
+template <int V, typename SRC, typename OUT>
 __device__ __forceinline__ void wave_bitonic_segment(const SRC* __restrict__ src,
-                                                     uint64_t* __restrict__ dst, uint32_t len,
+                                                     OUT* __restrict__ dst, uint32_t len,
                                                      uint64_t jhi, uint32_t* __restrict__ sh,
                                                      uint32_t lane) {
   constexpr uint32_t P2 = 64u * V;
@@ -1015,16 +835,16 @@ __device__ __forceinline__ void wave_bitonic_segment(const SRC* __restrict__ src
 #pragma unroll
   for (int r = 0; r < V; ++r) sh[lane * V + r] = v[r];
   wave_sync();
-  for (uint32_t i = lane; i < len; i += kWave) dst[i] = jhi | sh[i];
+  for (uint32_t i = lane; i < len; i += kWave) dst[i] = (OUT)(jhi | sh[i]);
   wave_sync();
 }
 
 constexpr int kSegWaves = 4;  // wavefronts per workgroup of the mid sort
 
 // the register width for a segment of len (33..2048) keys
-template <typename SRC>
+template <typename SRC, typename OUT>
 __device__ __forceinline__ void sort_wave_segment(const SRC* __restrict__ src,
-                                                  uint64_t* __restrict__ dst, uint32_t len,
+                                                  OUT* __restrict__ dst, uint32_t len,
                                                   uint64_t jhi, uint32_t* __restrict__ sh,
                                                   uint32_t lane) {
   if (len <= 64) wave_bitonic_segment<1>(src, dst, len, jhi, sh, lane);
@@ -1035,9 +855,9 @@ __device__ __forceinline__ void sort_wave_segment(const SRC* __restrict__ src,
   else wave_bitonic_segment<32>(src, dst, len, jhi, sh, lane);
 }
 
-template <bool IDS>
+template <bool IDS, typename OUT>
 __global__ __launch_bounds__(kSegWaves * kWave) void segsort_mid_kernel(
-    const uint64_t* __restrict__ off, uint64_t* __restrict__ out, SegSrc S,
+    const uint64_t* __restrict__ off, OUT* __restrict__ out, SegSrc S,
     const uint32_t* __restrict__ lists, const uint32_t* __restrict__ list_count) {
   __shared__ uint32_t shw[kSegWaves][kSegMid];
   const uint32_t wave = threadIdx.x / kWave;
@@ -1049,11 +869,13 @@ __global__ __launch_bounds__(kSegWaves * kWave) void segsort_mid_kernel(
     const uint32_t j = uniform_u32(lists[li]);
     const uint64_t b = off[j];
     const uint32_t len = uniform_u32((uint32_t)(off[j + 1] - b));
-    uint64_t* dst = out + b;
-    const SegAt a = IDS ? seg_at(S, j, out, b) : SegAt{nullptr, out + b};
+    OUT* dst = out + b;
+    SegAt a{};
+    if constexpr (sizeof(OUT) == 4) a = list_at(S, j, b);
+    else a = IDS ? seg_at(S, j, out, b) : SegAt{nullptr, out + b};
     if (IDS && a.ids) {
       sort_wave_segment(a.ids, dst, len, (uint64_t)j << 32, sh, lane);
-    } else {
+    } else if constexpr (sizeof(OUT) == 8) {
       // every key of the segment carries the same update id in its high word
       const uint64_t jhi = readlane_u64(a.keys[0], 0) & 0xffffffff00000000ull;
       sort_wave_segment(a.keys, dst, len, jhi, sh, lane);
@@ -1270,20 +1092,6 @@ __device__ __forceinline__ uint32_t popc4(uint4 q) {
   return __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w);
 }
 
-// inclusive sum of v over lanes 0..lane of the wavefront: row shifts by 1,
-// 2, 4 and 8 (lanes before the row's start add 0) give each 16-lane row
-// its own prefix; broadcasting lane 15 into row 1 and lane 47 into row 3,
-// then lane 31 into rows 2 and 3, carries the row totals forward
-__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
-  return v;
-}
-
 // largest v over the wavefront (the same row shifts and broadcasts, with
 // max; lanes before a row's start contribute 0), read from the last lane
 __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
@@ -1366,10 +1174,10 @@ static_assert(bitmap_lds_bytes(kMaxBitWords) +
 
 // MAXR: most uint4 entries per thread (kBmRNarrow or kBmRWide); SLOTS:
 // segments may be read from the slots of the single-pass form
-template <uint32_t MAXR, bool SLOTS>
+template <uint32_t MAXR, bool SLOTS, typename OUT>
 __global__ __launch_bounds__(kBmThreads) __attribute__((amdgpu_waves_per_eu(DDM_BM_WAVES)))
 void segsort_bitmap_kernel(const uint64_t* __restrict__ off, uint32_t m,
-                           uint64_t* __restrict__ out, SegSrc S,
+                           OUT* __restrict__ out, SegSrc S,
                            const uint32_t* __restrict__ lists,
                            const uint32_t* __restrict__ list_count, uint32_t words) {
   extern __shared__ uint4 bm4[];
@@ -1406,12 +1214,13 @@ void segsort_bitmap_kernel(const uint64_t* __restrict__ off, uint32_t m,
   };
   // a segment's keys are in its slot when every hit fits there, else in place
   auto seg_of = [&](uint32_t li, const BmMeta& q) {
-    BmSeg g{0, 0, out, nullptr, 0};
+    BmSeg g{0, 0, nullptr, nullptr, 0};
+    if constexpr (sizeof(OUT) == 8) g.src = out;
     if (li >= cntl) return g;
     g.j = uniform_v(q.j);
     g.b = uniform_v64(q.b);
     g.len = uniform_v(q.elo) - (uint32_t)g.b;
-    g.src = out + g.b;
+    if constexpr (sizeof(OUT) == 8) g.src = out + g.b;
     if (S.ids) g.isrc = S.ids + g.b;
     if (SLOTS) {
       // slot room: min(base + cap, limit) - base (cap form), else next base - base
@@ -1536,7 +1345,7 @@ void segsort_bitmap_kernel(const uint64_t* __restrict__ off, uint32_t m,
       }
     };
     const uint64_t jhi = (uint64_t)s_hi << 32;
-    uint64_t* dst = out + cg.b;
+    OUT* dst = out + cg.b;
     if (cg.len > PRE) {
       // a segment longer than the register window: its ids are read back
       // from the bitmap in order (the keys in memory may already be
@@ -1586,7 +1395,7 @@ void segsort_bitmap_kernel(const uint64_t* __restrict__ off, uint32_t m,
           }
         }
         __syncthreads();
-        for (uint32_t i = tid; i < cend - cbase; i += kBmThreads) dst[cbase + i] = jhi | lst[i];
+        for (uint32_t i = tid; i < cend - cbase; i += kBmThreads) dst[cbase + i] = (OUT)(jhi | lst[i]);
         __syncthreads();  // staging free; at the end the bitmap is no longer read
       }
 #pragma unroll 1
@@ -1624,7 +1433,7 @@ void segsort_bitmap_kernel(const uint64_t* __restrict__ off, uint32_t m,
         __syncthreads();
         for (uint32_t i = tid; i < cn; i += kBmThreads) {
           const uint32_t v = bits[i];
-          if (v) dst[cbase + i] = jhi | (v - 1u);
+          if (v) dst[cbase + i] = (OUT)(jhi | (v - 1u));
           bits[i] = 0u;
         }
         // the words of the last staged entry past the staged positions
@@ -1732,30 +1541,22 @@ static ddm_status launch_traverse(const MatchPlan& P, const TreeDev& T, const fl
     ProfScope ps(FILL ? (US.qpt == 1 ? "traverse_tile1_fill"
                                      : US.tstart ? "traverse_tile_fill_balanced"
                                                  : "traverse_tile_fill")
-                      : (O.skey && US.tmap ? "traverse_tile_count_stash" : "traverse_tile_count"),
+                      : (O.skey ? "traverse_tile_count_stash" : "traverse_tile_count"),
                  s);
-    if (US.tmap || US.tstart) {
-      // at most one partial tile per bucket; a tile list cut by predicted
-      // work as well has at most one more tile per crossing of a multiple
-      // of H (at most total / H = m * kCutDiv / 128), and never more tiles
-      // than updates
-      uint32_t tiles = (US.total + 63u) / 64u + std::min<uint32_t>(US.total, kBuckets);
-      if (US.tstart)
-        tiles = (uint32_t)std::min<uint64_t>(
-            (uint64_t)tiles + ((uint64_t)US.total * kCutDiv + 127u) / 128u + 1u, US.total);
-      const uint32_t grid = (tiles + kTileWaves - 1) / kTileWaves;
-      if (!FILL && O.skey)
-        tile_bucket_kernel<D, false, true><<<grid, kTileWaves * kWave, 0, s>>>(T, ulo, uhi, m,
-                                                                              US, O);
-      else
-        tile_bucket_kernel<D, FILL><<<grid, kTileWaves * kWave, 0, s>>>(T, ulo, uhi, m, US, O);
-      DDM_LAUNCHED("tile_bucket_kernel");
-    } else {
-      const uint32_t tiles = (US.total + US.qpt - 1) / US.qpt + D;
-      tile_kernel<D, FILL><<<(tiles + kTileWaves - 1) / kTileWaves, kTileWaves * kWave, 0, s>>>(
-          T, ulo, uhi, m, US, O);
-      DDM_LAUNCHED("tile_kernel");
-    }
+    // at most one partial tile per class; a tile list cut by work as well has
+    // at most one more tile per crossing of a multiple of H (at most total /
+    // H = m * kCutDiv / 128), and never more tiles than updates
+    uint32_t tiles = (US.total + US.qpt - 1) / US.qpt + D;
+    if (US.tstart)
+      tiles = (uint32_t)std::min<uint64_t>(
+          (uint64_t)tiles + ((uint64_t)US.total * kCutDiv + 127u) / 128u + 1u, US.total);
+    const uint32_t grid = (tiles + kTileWaves - 1) / kTileWaves;
+    if (!FILL && O.skey)
+      tile_kernel<D, kTileStash><<<grid, kTileWaves * kWave, 0, s>>>(T, ulo, uhi, m, US, O);
+    else
+      tile_kernel<D, FILL ? kTileFill : kTileCount>
+          <<<grid, kTileWaves * kWave, 0, s>>>(T, ulo, uhi, m, US, O);
+    DDM_LAUNCHED("tile_kernel");
   }
   return DDM_OK;
 }
@@ -1800,12 +1601,12 @@ struct MatchState {
   uint8_t* kstar = nullptr;
   uint32_t* rank = nullptr;
   uint32_t* bucket = nullptr;
-  uint32_t* bhist = nullptr;
-  uint32_t* bcnt = nullptr;  // bucket counters, kCntPad words apart
+  uint32_t* boff = nullptr;  // first update of each cell, within its cell block
+  uint32_t* bsum = nullptr;  // updates of each cell block
+  uint32_t* bcnt = nullptr;  // cell counters, kCntPad words apart
   uint32_t* perm = nullptr;
   uint32_t* gstart = nullptr;
   uint32_t* gcount = nullptr;
-  uint32_t* shape = nullptr;  // cell shape (log2 B1) of each probe dimension
   uint32_t* pb = nullptr;     // per update: candidate position bounds (d > 1)
   bool pb_ok = false;
   bool balanced = false;  // the learned single pass runs the work-cut tile list
@@ -1829,11 +1630,8 @@ struct MatchState {
   uint32_t* wtile = nullptr;   // work in perm order, then cut flags
   uint64_t* cwork = nullptr;   // exclusive scan of the work, then of the flags
   uint32_t* tstart = nullptr;
-  uint32_t* tbuck = nullptr;
+  uint32_t* tclass = nullptr;
   uint32_t novf = 0;
-  // bucket-aligned tiles
-  uint32_t* tprefix = nullptr;
-  uint32_t* tmap = nullptr;
   uint32_t* maxcnt = nullptr;  // device: the largest count (longest segment)
   uint64_t maxseg = ~0ull;     // host copy after the count
   // stash of the count traversal (plain path, d > 1): usable when complete
@@ -1849,19 +1647,27 @@ struct MatchState {
   uint32_t stiles = 0;     // tiles that ran
   uint32_t sused_max = 0;  // most counted chunks used in one slice
   bool stash_ok = false;
+  // candidates of the tiles (counted when the set is dense)
+  uint32_t* tcand = nullptr;   // per tile
+  uint64_t* tsum = nullptr;    // [kListSlices] sums
+  uint32_t* tmaxs = nullptr;   // [kListSlices] maxima
+  bool may_dense = false;      // the caller allows the scratch of the dense form
+  bool dense = false;          // the units hold the hits
+  bool plain_fill = false;     // learned, but neither slots nor units: a fill by the counts
+  Scratch dense_sc;
+  DenseUnits units;
+  uint32_t units_max = 0;
   // no allocation of any kind (the scratch is external, the read-back goes
   // to pageable host memory): the no-allocation entry point
   bool noalloc = false;
-  explicit MatchState(hipStream_t s) : sc(s), slots_sc(s), stash_sc(s) {}
+  explicit MatchState(hipStream_t s)
+      : sc(s), slots_sc(s), stash_sc(s), dense_sc(s) {}
   UpdSet all() const {
-    UpdSet U{perm, gstart, gcount, m, 64};
-    U.boff = bhist;
-    U.tprefix = tprefix;
-    U.tmap = tmap;
+    UpdSet U{perm, gstart, gcount, m, tile_updates(m)};
     U.pb = pb_ok ? pb : nullptr;
     if (balanced) {
       U.tstart = tstart;
-      U.tbuck = tbuck;
+      U.tclass = tclass;
       U.ntiles = cwork + m;
     }
     return U;
@@ -1869,42 +1675,49 @@ struct MatchState {
 };
 
 // zeroes the match's counters; with a stash (snext non-null) also sets the
-// slices' next free chunks; for d > 1 (D > 1) the last workgroup also picks
-// the cell shape of every probe dimension and sets the stash's overflow mark
-// (a stash exists only for d > 1)
+// slices' next free chunks, and one more workgroup its overflow mark from a
+// sample of the updates (a stash exists only for d > 1)
 template <int D>
 __global__ __launch_bounds__(1024) void match_init_kernel(
-    uint32_t* __restrict__ gcount, int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count,
-    uint32_t* __restrict__ bcnt, uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice,
-    uint32_t* __restrict__ maxcnt, TreeDev T, const float* __restrict__ ulo,
-    const float* __restrict__ uhi, uint32_t m, uint32_t* __restrict__ shape) {
+    int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
+    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint32_t* __restrict__ maxcnt,
+    uint64_t* __restrict__ tsum, uint32_t* __restrict__ tmaxs, TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m) {
+  static_assert(kCells % 1024 == 0, "whole workgroups");
+  if constexpr (D > 1) {
+    if (blockIdx.x == D * kCells / 1024) {
+      sample_density<D, 1024>(T, ulo, uhi, m, snext + kStashSlices,
+                              sslice * (kStashSlices * kStashChunk));
+      return;
+    }
+  }
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kBuckets) bcnt[(size_t)i * kCntPad] = 0;
-  if (i < DDM_MAX_D) gcount[i] = 0;
+  bcnt[(size_t)i * kCntPad] = 0;
   if (i == 0) {
     *flag = 0;
     *maxcnt = 0;
   }
   if (i < 2) lists_count[i] = 0;
-  if (snext && i < kStashSlices) snext[i] = sfirst + i * sslice;
-  if constexpr (D > 1) {
-    if (blockIdx.x == gridDim.x - 1)
-      sample_cell_shape<D, 1024>(T, ulo, uhi, m, shape, snext ? snext + kStashSlices : nullptr,
-                                 sslice * (kStashSlices * kStashChunk));
+  if (i < kListSlices) {
+    tsum[i] = 0;
+    tmaxs[i] = 0;
   }
+  if (snext && i < kStashSlices) snext[i] = sfirst + i * sslice;
 }
 
 // the words the host reads after the count: dst[0] = K, dst[1] = the tree's
-// and the updates' flags; with a stash, dst[2] = (tiles << 32) | most
-// counted chunks used in one slice, dst[3] = overflow; dst[4] = the largest
-// count
+// and the updates' flags; dst[2] = (tiles << 32) | most counted chunks of the
+// stash used in one slice, dst[3] = the stash's mark; dst[4] = the largest
+// count; dst[5], dst[6] = candidates of all tiles and of the fullest
 __global__ void gather_flags_kernel(const int32_t* __restrict__ tflag,
                                     const int32_t* __restrict__ uflag,
                                     const uint64_t* __restrict__ off, uint32_t m,
                                     uint64_t* __restrict__ dst,
                                     const uint32_t* __restrict__ snext,
-                                    const uint32_t* __restrict__ tprefix, uint32_t sfirst,
-                                    uint32_t sslice, const uint32_t* __restrict__ maxcnt) {
+                                    const uint32_t* __restrict__ gcount, uint32_t d, uint32_t qpt,
+                                    uint32_t sfirst, uint32_t sslice,
+                                    const uint32_t* __restrict__ maxcnt,
+                                    const uint64_t* __restrict__ tsum,
+                                    const uint32_t* __restrict__ tmaxs) {
   // one wavefront; the lanes share the slices
   const uint32_t lane = threadIdx.x;
   if (lane == 0) {
@@ -1912,16 +1725,23 @@ __global__ void gather_flags_kernel(const int32_t* __restrict__ tflag,
     dst[0] = off[m];
     dst[1] = (uint64_t)(uint32_t)(*tflag) | ((uint64_t)(uint32_t)(*uflag) << 32);
   }
-  if (snext) {
-    uint32_t mx = 0;
+  uint32_t mx = 0;
+  if (snext)
     for (uint32_t s = lane; s < kStashSlices; s += kWave)
       mx = max(mx, min(snext[s] - (sfirst + s * sslice), sslice));
+  mx = wave_max_u32(mx);
+  uint32_t tiles = 0;
+  for (uint32_t g = 0; g < d; ++g) tiles += (gcount[g] + qpt - 1) / qpt;
+  static_assert(kListSlices == kWave, "one lane per slice");
+  uint64_t ts = tsum[lane];
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
-    if (lane == 0) {
-      dst[2] = ((uint64_t)tprefix[kBuckets] << 32) | mx;
-      dst[3] = snext[kStashSlices];
-    }
+  for (int o = kWave / 2; o > 0; o >>= 1) ts += __shfl_xor(ts, o, kWave);
+  const uint32_t tm = wave_max_u32(tmaxs[lane]);
+  if (lane == 0) {
+    dst[2] = ((uint64_t)tiles << 32) | mx;
+    dst[3] = snext ? snext[kStashSlices] : 0u;
+    dst[5] = ts;
+    dst[6] = tm;
   }
 }
 
@@ -1935,8 +1755,10 @@ static ddm_status launch_probe(const TreeDev& T, const float* ulo, const float* 
     DDM_LAUNCHED("bits1_kernel");
   } else {
     ProfScope ps("probe", s);
+    CellShape shape;
+    cell_shape(m, D, kCells, shape.b);
     probe_kernel<D><<<(m + kProbeThreads - 1) / kProbeThreads, kProbeThreads, 0, s>>>(
-        T, ulo, uhi, m, st.shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag,
+        T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag,
         reinterpret_cast<uint2*>(st.pb));
     DDM_LAUNCHED("probe_kernel");
   }
@@ -1957,8 +1779,9 @@ __global__ __launch_bounds__(256) void overflow_kernel(UpdSet US, uint32_t d, Se
   if ((uint64_t)cnt[j] > e - b) perm_ovf[US.gstart[g] + atomicAdd(&govf[g], 1u)] = j;
 }
 
-__global__ void learned_init_kernel(uint32_t* __restrict__ govf) {
+__global__ void learned_init_kernel(uint32_t* __restrict__ govf, uint64_t* __restrict__ over) {
   if (threadIdx.x < DDM_MAX_D) govf[threadIdx.x] = 0;
+  if (threadIdx.x == 0) *over = 0;
 }
 
 __global__ void learned_words_kernel(const uint32_t* __restrict__ govf,
@@ -2007,11 +1830,12 @@ __global__ void stash_scatter_kernel(const uint64_t* __restrict__ skey,
 }
 
 // stash entries: the hint (a caller's capacity) or 4 per update, plus one
-// chunk per possible tile (a tile's last chunk is partly used; the bound is
-// the launch's own: one tile per 64 updates plus one partial tile per
-// bucket), plus 64Ki
+// chunk per possible tile (a tile's last chunk is partly used), plus 64Ki
+// (a bound of the tiles that grows with m)
 static uint64_t stash_tiles(uint32_t m) {
-  return (m + 63u) / 64u + std::min<uint64_t>(m, kBuckets);
+  return std::max<uint64_t>(((uint64_t)m + 63) / 64,
+                            std::min<uint64_t>(((uint64_t)m + 3) / 4, kFewTiles)) +
+         DDM_MAX_D;
 }
 // counted chunks per slice: room for the hint (or 4 hits per update) plus
 // one partly used chunk per tile and 1024 more, over the slices
@@ -2038,8 +1862,6 @@ struct FrontPieces {
   uint64_t* dwords = nullptr;
 };
 
-static size_t front_max_tiles(uint32_t m) { return ((size_t)m + 63) / 64 + kBuckets; }
-
 static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
   if (learned) {
     sc.reserve(sizeof(float) * (size_t)m * kFeatures);  // X
@@ -2050,18 +1872,18 @@ static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
     sc.reserve(sizeof(uint32_t) * m);                   // work / cut flags
     sc.reserve(sizeof(uint64_t) * (m + 1));             // their scan
     sc.reserve(sizeof(uint32_t) * ((size_t)m + 1));     // tile starts
-    sc.reserve(sizeof(uint32_t) * m);                   // tile buckets
+    sc.reserve(sizeof(uint32_t) * m);                   // tile classes
   }
   sc.reserve(sizeof(uint32_t) * m);          // cmin
   sc.reserve(m);                             // kstar
   sc.reserve(sizeof(uint32_t) * m);          // rank
   sc.reserve(sizeof(uint32_t) * m);          // bucket
   sc.reserve(sizeof(uint32_t) * m);          // perm
-  sc.reserve(sizeof(uint32_t) * kBuckets);   // bucket offsets
-  sc.reserve(sizeof(uint32_t) * kBuckets * kCntPad);  // bucket counters
+  sc.reserve(sizeof(uint32_t) * kBuckets);   // cell offsets
+  sc.reserve(sizeof(uint32_t) * kWave);      // cell block totals
+  sc.reserve(sizeof(uint32_t) * kBuckets * kCntPad);  // cell counters
   sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // gstart
   sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // gcount
-  sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // shape
   sc.reserve(sizeof(int32_t));               // flag
   sc.reserve(sizeof(uint32_t) * m);          // cnt
   sc.reserve(sizeof(uint64_t) * (m + 1));    // off
@@ -2070,9 +1892,10 @@ static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
   sc.reserve(sizeof(uint32_t) * 2);              // segment list counts
   sc.reserve(sizeof(uint64_t) * 8);              // device words for readback
   sc.reserve(sizeof(uint32_t));                  // largest count
-  sc.reserve(sizeof(uint32_t) * (kBuckets + 1));     // tile prefix
-  sc.reserve(sizeof(uint32_t) * front_max_tiles(m));  // tile -> bucket
   sc.reserve(sizeof(uint32_t) * 2 * (size_t)m);       // candidate position bounds
+  sc.reserve(sizeof(uint32_t) * stash_tiles(m));      // candidates per tile
+  sc.reserve(sizeof(uint64_t) * kListSlices);         // their sums
+  sc.reserve(sizeof(uint32_t) * kListSlices);         // and maxima
 }
 
 static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, FrontPieces* fp) {
@@ -2081,11 +1904,11 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
   st.rank = sc.take<uint32_t>(m);
   st.bucket = sc.take<uint32_t>(m);
   st.perm = sc.take<uint32_t>(m);
-  st.bhist = sc.take<uint32_t>(kBuckets);
+  st.boff = sc.take<uint32_t>(kBuckets);
+  st.bsum = sc.take<uint32_t>(kWave);
   st.bcnt = sc.take<uint32_t>((size_t)kBuckets * kCntPad);
   st.gstart = sc.take<uint32_t>(DDM_MAX_D);
   st.gcount = sc.take<uint32_t>(DDM_MAX_D);
-  st.shape = sc.take<uint32_t>(DDM_MAX_D);
   st.m = m;
   st.flag = sc.take<int32_t>(1);
   st.cnt = sc.take<uint32_t>(m);
@@ -2095,9 +1918,10 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
   fp->lists_count = sc.take<uint32_t>(2);
   fp->dwords = sc.take<uint64_t>(8);
   st.maxcnt = sc.take<uint32_t>(1);
-  st.tprefix = sc.take<uint32_t>(kBuckets + 1);
-  st.tmap = sc.take<uint32_t>(front_max_tiles(m));
   st.pb = sc.take<uint32_t>(2 * (size_t)m);
+  st.tcand = sc.take<uint32_t>(stash_tiles(m));
+  st.tsum = sc.take<uint64_t>(kListSlices);
+  st.tmaxs = sc.take<uint32_t>(kListSlices);
   if (learned) {
     st.X = sc.take<float>((size_t)m * kFeatures);
     st.cap = sc.take<uint32_t>(m);
@@ -2107,7 +1931,7 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
     st.wtile = sc.take<uint32_t>(m);
     st.cwork = sc.take<uint64_t>(m + 1);
     st.tstart = sc.take<uint32_t>((size_t)m + 1);
-    st.tbuck = sc.take<uint32_t>(m);
+    st.tclass = sc.take<uint32_t>(m);
   }
 }
 
@@ -2131,17 +1955,195 @@ static void stash_take(Scratch& sc, MatchState& st) {
   st.snext = sc.take<uint32_t>(kStashSlices + 1);
 }
 
+// candidates of every tile: counted (O.ids null) or listed
+static ddm_status list_any(uint32_t d, const TreeDev& T, const float* ulo, const float* uhi,
+                           uint32_t m, const UpdSet& US, const SegOut& O, hipStream_t s) {
+  ProfScope ps("candidate_lists", s);
+  const uint32_t tiles = (US.total + US.qpt - 1) / US.qpt + d;
+  const uint32_t grid = (tiles + kTileWaves - 1) / kTileWaves, th = kTileWaves * kWave;
+  switch (d) {
+    case 1: tile_kernel<1, kTileList><<<grid, th, 0, s>>>(T, ulo, uhi, m, US, O); break;
+    case 2: tile_kernel<2, kTileList><<<grid, th, 0, s>>>(T, ulo, uhi, m, US, O); break;
+    case 3: tile_kernel<3, kTileList><<<grid, th, 0, s>>>(T, ulo, uhi, m, US, O); break;
+    default: tile_kernel<4, kTileList><<<grid, th, 0, s>>>(T, ulo, uhi, m, US, O); break;
+  }
+  DDM_LAUNCHED("tile_kernel");
+  return DDM_OK;
+}
+
+// d = 1: hits per update from which the dense form is taken (the counts are
+// exact before any traversal)
+constexpr uint64_t kDenseHits1 = 16;
+// learned: predicted hits per update from which it is taken
+constexpr double kLearnedDenseHits = 32.0;
+// most candidates whose lists and masks (16 bytes each) the match allocates
+constexpr uint64_t kDenseMaxCandidates = 1ull << 30;
+
+template <typename OUT>
+static ddm_status sort_segments_window(const uint64_t* off, uint32_t m, OUT* out, uint32_t n,
+                                       uint32_t* lists, uint32_t* lists_count, hipStream_t s,
+                                       const SegSrc& S, uint64_t max_len);
+
+// Lists and sorts the candidates, tests them and sums the counts into cnt.
+// room null: tcand counts them, `total` in all, at most `longest` in a tile.
+// Otherwise tile t's list has room for room[t] of them, `total` in all; tcand
+// is counted on the way and *over counts the tiles whose candidates did not
+// fit (their counts are then short and nothing of it may be used).
+// *made stays false when the lists are too large or their memory is not to be
+// had (nothing is enqueued then).
+static ddm_status dense_units(const ddm_tree* t, const TreeDev& T, const float* ulo,
+                              const float* uhi, uint32_t m, MatchState& st, uint64_t total,
+                              uint64_t longest, const uint32_t* room, uint64_t* over,
+                              uint32_t* cnt, hipStream_t s, bool* made) {
+  const uint32_t d = tree_d(t), tiles = st.stiles;
+  *made = false;
+  if (total > kDenseMaxCandidates || tiles == 0) return DDM_OK;
+  const uint64_t umax = total / kUnit + tiles;
+  Scratch& sc = st.dense_sc;  // until the pairs are written
+  sc.drop();
+  sc.reserve(sizeof(uint64_t) * ((size_t)tiles + 1));
+  sc.reserve(sizeof(uint32_t) * std::max<uint64_t>(total, 1));
+  sc.reserve(sizeof(uint32_t) * tiles);
+  sc.reserve(sizeof(uint2) * umax);
+  sc.reserve(sizeof(uint32_t) * 4);
+  sc.reserve(sizeof(uint2) * kUnit * umax);
+  sc.reserve(sizeof(uint32_t) * kWave * umax);
+  Scratch tc(s);              // until the lists are sorted
+  tc.reserve(sizeof(uint32_t) * std::max<uint64_t>(total, 1));
+  tc.reserve(sizeof(uint32_t) * 2 * (size_t)tiles);
+  tc.reserve(sizeof(uint64_t) * scan_tmp_words(tiles));
+  tc.reserve(sizeof(uint64_t) * ((size_t)tiles + 1));
+  tc.reserve(sizeof(uint32_t) * tiles);
+  if (!sc.commit() || !tc.commit()) {
+    sc.drop();
+    set_detail("");
+    return DDM_OK;
+  }
+  DenseUnits& U = st.units;
+  uint64_t* toff = sc.take<uint64_t>((size_t)tiles + 1);
+  uint32_t* sorted = sc.take<uint32_t>(std::max<uint64_t>(total, 1));
+  U.ubase = sc.take<uint32_t>(tiles);
+  U.umap = sc.take<uint2>(umax);
+  U.ucount = sc.take<uint32_t>(4);  // and the two counters of the sort's lists
+  U.bits = sc.take<uint2>((size_t)kUnit * umax);
+  U.ucnt = sc.take<uint32_t>((size_t)kWave * umax);
+  uint32_t* raw = tc.take<uint32_t>(std::max<uint64_t>(total, 1));
+  uint32_t* lists = tc.take<uint32_t>(2 * (size_t)tiles);
+  uint64_t* tmp = tc.take<uint64_t>(scan_tmp_words(tiles));
+  uint64_t* roff = tc.take<uint64_t>((size_t)tiles + 1);
+  uint32_t* len = tc.take<uint32_t>(tiles);
+  if (!sc.fits() || !tc.fits()) return scratch_overrun("dense match");
+  U.toff = toff;
+  U.list = sorted;
+  st.units_max = (uint32_t)umax;
+  zero_u32_kernel<<<1, 64, 0, s>>>(U.ucount, 4);
+  DDM_LAUNCHED("zero_u32_kernel");
+  SegOut O{};
+  O.ids = raw;
+  SegSrc S{};
+  const UpdSet US = st.all();
+  ddm_status r;
+  if (!room) {
+    r = scan_u32_u64(st.tcand, toff, tiles, tmp, s);
+    if (r != DDM_OK) return r;
+    O.base = toff;
+    r = list_any(d, T, ulo, uhi, m, US, O, s);
+    if (r != DDM_OK) return r;
+    S.ids = raw;
+  } else {
+    r = scan_u32_u64(room, roff, tiles, tmp, s);
+    if (r != DDM_OK) return r;
+    O.base = roff;
+    O.tcand = st.tcand;
+    O.tsum = st.tsum;
+    O.tmax = st.tmaxs;
+    r = list_any(d, T, ulo, uhi, m, US, O, s);
+    if (r != DDM_OK) return r;
+    tile_clip_kernel<<<(tiles + 255) / 256, 256, 0, s>>>(st.tcand, room, tiles, len, over);
+    DDM_LAUNCHED("tile_clip_kernel");
+    r = scan_u32_u64(len, toff, tiles, tmp, s);
+    if (r != DDM_OK) return r;
+    S.slots = raw;
+    S.so.base = roff;
+    S.cnt = len;
+  }
+  {
+    ProfScope ps("listsort", s);
+    r = sort_segments_window(toff, tiles, sorted, tree_n(t), lists, U.ucount + 1, s, S, longest);
+    if (r != DDM_OK) return r;
+  }
+  ProfScope ps("dense_test", s);
+  dense_units_kernel<<<(tiles + 255) / 256, 256, 0, s>>>(U, tiles);
+  DDM_LAUNCHED("dense_units_kernel");
+  const uint32_t g = (uint32_t)((umax + kUnitWaves - 1) / kUnitWaves), th = kUnitWaves * kWave;
+  const uint32_t gt = (tiles + kUnitWaves - 1) / kUnitWaves;
+#define DDM_DENSE(DD)                                                        \
+  dense_test_kernel<DD><<<g, th, 0, s>>>(U, US, T.rid, ulo, uhi, m);         \
+  dense_sum_kernel<DD><<<gt, th, 0, s>>>(U, US, tiles, cnt)
+  switch (d) {
+    case 1: DDM_DENSE(1); break;
+    case 2: DDM_DENSE(2); break;
+    case 3: DDM_DENSE(3); break;
+    default: DDM_DENSE(4); break;
+  }
+#undef DDM_DENSE
+  DDM_LAUNCHED("dense_test_kernel");
+  *made = true;
+  return DDM_OK;
+}
+
+// room for the tiles' lists from the predictor: its estimate for a tile's
+// enclosing box, taken as an update's extent, and a margin (d <= 3); boxes and
+// room from sc, whose pieces the caller has reserved
+static ddm_status predict_room(const ddm_tree* t, const float* ulo, const float* uhi, uint32_t m,
+                               const MatchState& st, const ddm_predictor* pred, float* boxes,
+                               uint32_t* room, hipStream_t s) {
+  const uint32_t d = tree_d(t), tiles = st.stiles;
+  float* blo = boxes;
+  float* bhi = boxes + (size_t)d * tiles;
+  const uint32_t g = (tiles + kUnitWaves - 1) / kUnitWaves, th = kUnitWaves * kWave;
+  if (d == 2)
+    tile_boxes_kernel<2><<<g, th, 0, s>>>(st.all(), ulo, uhi, m, tiles, blo, bhi);
+  else
+    tile_boxes_kernel<3><<<g, th, 0, s>>>(st.all(), ulo, uhi, m, tiles, blo, bhi);
+  DDM_LAUNCHED("tile_boxes_kernel");
+  ddm_status r = launch_features(tree_feat(t), d, blo, bhi, tiles, st.X, s);
+  if (r != DDM_OK) return r;
+  r = launch_mlp_forward(predictor_params(pred), st.X, tiles, 1, predictor_delta(pred), 1u << 29,
+                         nullptr, room, s);
+  if (r != DDM_OK) return r;
+  tile_room_kernel<<<(tiles + 255) / 256, 256, 0, s>>>(room, tiles, tree_n(t));
+  DDM_LAUNCHED("tile_room_kernel");
+  return DDM_OK;
+}
+
+// the pairs of the units, at their final places
+static ddm_status dense_expand(uint32_t d, const MatchState& st, uint64_t* out, hipStream_t s) {
+  ProfScope ps(st.learned ? "traverse_tile_fill_balanced" : "traverse_tile_fill_units", s);
+  const uint32_t g = (st.units_max + kUnitWaves - 1) / kUnitWaves, th = kUnitWaves * kWave;
+  const UpdSet US = st.all();
+  switch (d) {
+    case 1: dense_expand_kernel<1><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
+    case 2: dense_expand_kernel<2><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
+    case 3: dense_expand_kernel<3><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
+    default: dense_expand_kernel<4><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
+  }
+  DDM_LAUNCHED("dense_expand_kernel");
+  return DDM_OK;
+}
+
 static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* uhi, uint32_t m,
                              const MatchPlan& P, MatchState& st, uint32_t* counts_out,
                              uint32_t** lists, uint32_t** lists_count, hipStream_t s,
                              const ddm_predictor* pred = nullptr, uint64_t budget = 0,
                              bool want_stash = false, uint64_t stash_hint = 0,
-                             const ArenaGrant* grant = nullptr) {
+                             const ArenaGrant* grant = nullptr, bool may_dense = false) {
   const uint32_t d = tree_d(t);
   const TreeDev T = tree_dev(t);
   Scratch& sc = st.sc;
   // the single pass replaces the count traversal, which only exists for d > 1
   st.learned = pred != nullptr && d > 1;
+  st.may_dense = may_dense;
   front_reserve(sc, m, st.learned);
   if (!sc.commit()) return DDM_E_NOMEM;
   FrontPieces fp;
@@ -2152,8 +2154,9 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   uint64_t* dwords = fp.dwords;
   if (!sc.fits()) return scratch_overrun("front_half");
   st.pb_ok = d > 1;  // written by the probe kernel (d = 1 takes exact counts instead)
+  Scratch learned_tiles(s);  // boxes and room of the tiles (learned, dense)
   if (st.learned) {
-    learned_init_kernel<<<1, 64, 0, s>>>(st.govf);
+    learned_init_kernel<<<1, 64, 0, s>>>(st.govf, dwords + 7);
     DDM_LAUNCHED("learned_init_kernel");
   }
 
@@ -2174,11 +2177,11 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   }
   {
     uint32_t* sn = st.stash ? st.snext : nullptr;
-    const unsigned g = kBuckets / 1024;
-#define DDM_INIT(DD)                                                                          \
-  match_init_kernel<DD><<<g, 1024, 0, s>>>(st.gcount, st.flag, *lists_count, st.bcnt, sn,    \
-                                          st.sfirst, st.sslice, st.maxcnt, T, ulo, uhi, m, \
-                                          st.shape)
+    const unsigned g = d * kCells / 1024 + (sn ? 1u : 0u);
+#define DDM_INIT(DD)                                                                         \
+  match_init_kernel<DD><<<g, 1024, 0, s>>>(st.flag, *lists_count, st.bcnt, sn, st.sfirst,    \
+                                           st.sslice, st.maxcnt, st.tsum, st.tmaxs, T, ulo,   \
+                                           uhi, m)
     switch (d) {
       case 1: DDM_INIT(1); break;
       case 2: DDM_INIT(2); break;
@@ -2198,24 +2201,12 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   if (r != DDM_OK) return r;
   {
     ProfScope ps("order", s);
-    uint32_t* tp = P.traversal == DDM_TRAVERSE_TILE ? st.tprefix : nullptr;
-    // the counts of the d probe dimensions' buckets, dense, into bhist (the
-    // scan turns them into offsets in place)
-    const uint32_t nbd = d * kBucketsPerDim;
-    bucket_gather_kernel<<<(nbd + 255) / 256, 256, 0, s>>>(st.bcnt, nbd, st.bhist);
-    DDM_LAUNCHED("bucket_gather_kernel");
-    switch (d) {
-      case 1: bucket_scan_kernel<8><<<1, 1024, 0, s>>>(st.bhist, m, st.gstart, st.gcount, tp); break;
-      case 2: bucket_scan_kernel<16><<<1, 1024, 0, s>>>(st.bhist, m, st.gstart, st.gcount, tp); break;
-      case 3: bucket_scan_kernel<24><<<1, 1024, 0, s>>>(st.bhist, m, st.gstart, st.gcount, tp); break;
-      default: bucket_scan_kernel<32><<<1, 1024, 0, s>>>(st.bhist, m, st.gstart, st.gcount, tp); break;
-    }
-    DDM_LAUNCHED("bucket_scan_kernel");
-    const bool tiles = P.traversal == DDM_TRAVERSE_TILE;
-    const uint32_t nb = tiles ? d * kBucketsPerDim : 0u;
-    bucket_scatter_kernel<<<(std::max(m, nb) + 255) / 256, 256, 0, s>>>(
-        st.bucket, st.rank, m, st.bhist, st.perm, st.tprefix, tiles ? st.tmap : nullptr, nb);
-    DDM_LAUNCHED("bucket_scatter_kernel");
+    const uint32_t nb = d * kCellBlocks;
+    cell_scan_kernel<<<nb, 256, 0, s>>>(st.bcnt, st.boff, st.bsum);
+    DDM_LAUNCHED("cell_scan_kernel");
+    cell_scatter_kernel<<<(m + 255) / 256, 256, 0, s>>>(st.bucket, st.rank, m, st.boff, st.bsum, nb,
+                                                       st.perm, st.gstart, st.gcount);
+    DDM_LAUNCHED("cell_scatter_kernel");
   }
   // per-update counts
   const uint32_t* counts = st.cmin;
@@ -2232,57 +2223,91 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     if (r != DDM_OK) return r;
     r = scan_u32_u64(st.cap, st.soff, m, stmp, s);
     if (r != DDM_OK) return r;
-    if (P.traversal == DDM_TRAVERSE_TILE) {
-      ProfScope ps("balance", s);
-      const unsigned g = (m + 255) / 256;
-      work_in_order_kernel<<<g, 256, 0, s>>>(st.perm, st.cap, m, st.wtile);
-      DDM_LAUNCHED("work_in_order_kernel");
-      r = scan_u32_u64(st.wtile, st.cwork, m, stmp, s);
-      if (r != DDM_OK) return r;
-      tile_cut_kernel<<<g, 256, 0, s>>>(st.perm, st.bucket, st.bhist, st.cwork, m, st.wtile);
-      DDM_LAUNCHED("tile_cut_kernel");
-      r = scan_u32_u64(st.wtile, st.cwork, m, stmp, s);
-      if (r != DDM_OK) return r;
-      tile_list_kernel<<<g, 256, 0, s>>>(st.perm, st.bucket, st.wtile, st.cwork, m, st.tstart,
-                                         st.tbuck);
-      DDM_LAUNCHED("tile_list_kernel");
-      st.balanced = true;
-    }
-    {
-      // arena sized to the predicted total, or to the caller's budget if
-      // that is smaller (one extra stream synchronization); updates whose
-      // slots fall beyond the arena overflow and are filled exactly later
-      uint64_t* hw0 = nullptr;
-      r = host_words(&hw0);
-      if (r != DDM_OK) return r;
-      DDM_HIP(hipMemcpyAsync(hw0 + 4, st.soff + m, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-      DDM_HIP(hipStreamSynchronize(s));
-      budget = budget == 0 ? hw0[4] : std::min<uint64_t>(budget, hw0[4]);
-      // a caller that accounts device memory grants the arena before it is
-      // allocated (it may wait there, or grant less)
-      if (grant) {
-        const uint64_t g = (*grant)(budget);
-        if (g == kArenaRefused) {
-          set_detail("slot arena not granted");
-          return DDM_E_NOMEM;
-        }
-        budget = std::min<uint64_t>(budget, g);
+    // predicted total (one extra stream synchronization)
+    uint64_t* hw0 = nullptr;
+    r = host_words(&hw0);
+    if (r != DDM_OK) return r;
+    DDM_HIP(hipMemcpyAsync(hw0 + 4, st.soff + m, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    DDM_HIP(hipMemcpyAsync(hw0 + 5, st.gcount, sizeof(uint32_t) * DDM_MAX_D, hipMemcpyDeviceToHost,
+                           s));
+    DDM_HIP(hipStreamSynchronize(s));
+    const uint64_t predicted = hw0[4];
+    if (may_dense && budget == 0 && !grant && P.traversal == DDM_TRAVERSE_TILE &&
+        tree_n(t) <= kMaxBitWords * 32 && (double)predicted > kLearnedDenseHits * (double)m) {
+      // dense by prediction, and no limit on the memory: the tiles' candidate
+      // lists are sized by the predictor and filled in one pass, and the pairs
+      // come from them (the predicted slots are then only reported)
+      st.stiles = 0;
+      for (uint32_t g = 0; g < d; ++g) {
+        const uint32_t c = reinterpret_cast<const uint32_t*>(hw0 + 5)[g];
+        st.stiles += (c + tile_updates(m) - 1) / tile_updates(m);
       }
+      learned_tiles.reserve(sizeof(float) * 2 * d * (size_t)st.stiles);
+      learned_tiles.reserve(sizeof(uint32_t) * st.stiles);
+      learned_tiles.reserve(sizeof(uint64_t) * ((size_t)st.stiles + 1));
+      learned_tiles.reserve(sizeof(uint64_t) * scan_tmp_words(st.stiles));
+      if (!learned_tiles.commit()) return DDM_E_NOMEM;
+      float* boxes = learned_tiles.take<float>(2 * d * (size_t)st.stiles);
+      uint32_t* room = learned_tiles.take<uint32_t>(st.stiles);
+      uint64_t* rsum = learned_tiles.take<uint64_t>((size_t)st.stiles + 1);
+      uint64_t* rtmp = learned_tiles.take<uint64_t>(scan_tmp_words(st.stiles));
+      if (!learned_tiles.fits()) return scratch_overrun("predicted lists");
+      r = predict_room(t, ulo, uhi, m, st, pred, boxes, room, s);
+      if (r != DDM_OK) return r;
+      r = scan_u32_u64(room, rsum, st.stiles, rtmp, s);
+      if (r != DDM_OK) return r;
+      DDM_HIP(hipMemcpyAsync(hw0 + 4, rsum + st.stiles, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+      DDM_HIP(hipStreamSynchronize(s));
+      r = dense_units(t, T, ulo, uhi, m, st, hw0[4], ~0ull, room, dwords + 7, st.cnt, s, &st.dense);
+      if (r != DDM_OK) return r;
+    }
+    // the slot arena: the predicted total, or the caller's budget if that is
+    // smaller; updates whose slots fall beyond it overflow and are filled
+    // exactly later
+    budget = budget == 0 ? predicted : std::min<uint64_t>(budget, predicted);
+    // a caller that accounts device memory grants the arena before it is
+    // allocated (it may wait there, or grant less)
+    if (grant) {
+      const uint64_t g = (*grant)(budget);
+      if (g == kArenaRefused) {
+        set_detail("slot arena not granted");
+        return DDM_E_NOMEM;
+      }
+      budget = std::min<uint64_t>(budget, g);
     }
     st.budget = budget;
-    st.slots_sc.reserve(sizeof(uint32_t) * (budget ? budget : 1));
-    if (!st.slots_sc.commit()) return DDM_E_NOMEM;
-    st.slots = st.slots_sc.take<uint32_t>(budget ? budget : 1);
-    if (!st.slots_sc.fits()) return scratch_overrun("slot arena");
     SO.base = st.soff;
     SO.cap = st.cap;
     SO.limit = budget;
-    SO.cnt = st.cnt;
-    SO.out = nullptr;
-    SO.ids = st.slots;  // the hits' subscription ids, 4 bytes each
-    r = traverse_any<true>(d, P, T, ulo, uhi, m, st.all(), st.kstar, SO, s);
-    if (r != DDM_OK) return r;
     counts = st.cnt;
+    if (!st.dense) {
+      if (P.traversal == DDM_TRAVERSE_TILE) {
+        ProfScope ps("balance", s);
+        const unsigned g = (m + 255) / 256;
+        work_in_order_kernel<<<g, 256, 0, s>>>(st.perm, st.cap, m, st.wtile);
+        DDM_LAUNCHED("work_in_order_kernel");
+        r = scan_u32_u64(st.wtile, st.cwork, m, stmp, s);
+        if (r != DDM_OK) return r;
+        tile_cut_kernel<<<g, 256, 0, s>>>(st.perm, st.kstar, st.gstart, st.cwork, m, tile_updates(m),
+                                          st.wtile);
+        DDM_LAUNCHED("tile_cut_kernel");
+        r = scan_u32_u64(st.wtile, st.cwork, m, stmp, s);
+        if (r != DDM_OK) return r;
+        tile_list_kernel<<<g, 256, 0, s>>>(st.perm, st.kstar, st.wtile, st.cwork, m, st.tstart,
+                                           st.tclass);
+        DDM_LAUNCHED("tile_list_kernel");
+        st.balanced = true;
+      }
+      st.slots_sc.reserve(sizeof(uint32_t) * (budget ? budget : 1));
+      if (!st.slots_sc.commit()) return DDM_E_NOMEM;
+      st.slots = st.slots_sc.take<uint32_t>(budget ? budget : 1);
+      if (!st.slots_sc.fits()) return scratch_overrun("slot arena");
+      SO.cnt = st.cnt;
+      SO.out = nullptr;
+      SO.ids = st.slots;  // the hits' subscription ids, 4 bytes each
+      r = traverse_any<true>(d, P, T, ulo, uhi, m, st.all(), st.kstar, SO, s);
+      if (r != DDM_OK) return r;
+    }
   } else if (d > 1) {
     SegOut O{};
     O.cnt = st.cnt;
@@ -2293,6 +2318,9 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
       O.snext = st.snext;
       O.sfirst = st.sfirst;
       O.sslice = st.sslice;
+      O.tcand = st.tcand;
+      O.tsum = st.tsum;
+      O.tmax = st.tmaxs;
     }
     r = traverse_any<false>(d, P, T, ulo, uhi, m, st.all(), st.kstar, O, s);
     if (r != DDM_OK) return r;
@@ -2302,30 +2330,67 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     copy_counts_kernel<<<(m + 255) / 256, 256, 0, s>>>(counts, counts_out, m);
     DDM_LAUNCHED("copy_counts_kernel");
   }
-  r = scan_u32_u64(counts, st.off, m, stmp, s, st.maxcnt);
-  if (r != DDM_OK) return r;
-  gather_flags_kernel<<<1, 64, 0, s>>>(tree_flag(t), st.flag, st.off, m, dwords,
-                                       st.stash ? st.snext : nullptr, st.tprefix, st.sfirst,
-                                       st.sslice, st.maxcnt);
-  DDM_LAUNCHED("gather_flags_kernel");
-  if (st.learned) {
+  auto offsets = [&]() -> ddm_status {
+    const ddm_status q = scan_u32_u64(counts, st.off, m, stmp, s, st.maxcnt);
+    if (q != DDM_OK) return q;
+    gather_flags_kernel<<<1, 64, 0, s>>>(tree_flag(t), st.flag, st.off, m, dwords,
+                                         st.stash ? st.snext : nullptr, st.gcount, d,
+                                         tile_updates(m), st.sfirst, st.sslice, st.maxcnt,
+                                         st.tsum, st.tmaxs);
+    DDM_LAUNCHED("gather_flags_kernel");
+    return DDM_OK;
+  };
+  // the updates whose hits exceed their predicted slots, and the words of both
+  auto learned_words = [&]() -> ddm_status {
+    if (!st.learned) return DDM_OK;
     overflow_kernel<<<(m + 255) / 256, 256, 0, s>>>(st.all(), d, SO, st.cnt, st.perm_ovf,
                                                     st.govf);
     DDM_LAUNCHED("overflow_kernel");
     learned_words_kernel<<<1, 64, 0, s>>>(st.govf, st.soff, m, dwords);
     DDM_LAUNCHED("learned_words_kernel");
-  }
+    return DDM_OK;
+  };
+  r = offsets();
+  if (r == DDM_OK) r = learned_words();
+  if (r != DDM_OK) return r;
   uint64_t hw_local[8] = {};
   uint64_t* hw = hw_local;
   if (!st.noalloc) {
     r = host_words(&hw);
     if (r != DDM_OK) return r;
   }
-  DDM_HIP(hipMemcpyAsync(hw, dwords, 5 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-  DDM_HIP(hipStreamSynchronize(s));
+  auto read_words = [&]() -> ddm_status {
+    DDM_HIP(hipMemcpyAsync(hw, dwords, 8 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    DDM_HIP(hipStreamSynchronize(s));
+    st.K = hw[0];
+    st.maxseg = hw[4];
+    return DDM_OK;
+  };
+  r = read_words();
+  if (r != DDM_OK) return r;
   const uint64_t flags = hw[1];
-  st.K = hw[0];
-  st.maxseg = hw[4];
+  if (st.learned && st.dense && hw[7] != 0 && flags == 0) {
+    // some tile had more candidates than its predicted room: the lists again,
+    // sized by the counts (or, without their memory, count and fill)
+    st.stash = false;
+    r = dense_units(t, T, ulo, uhi, m, st, hw[5], hw[6], nullptr, nullptr, st.cnt, s, &st.dense);
+    if (r != DDM_OK) return r;
+    if (!st.dense) {
+      st.plain_fill = true;
+      SegOut O{};
+      O.cnt = st.cnt;
+      r = traverse_any<false>(d, P, T, ulo, uhi, m, st.all(), st.kstar, O, s);
+      if (r != DDM_OK) return r;
+    }
+    learned_init_kernel<<<1, 64, 0, s>>>(st.govf, dwords + 7);
+    DDM_LAUNCHED("learned_init_kernel");
+    zero_u32_kernel<<<1, 64, 0, s>>>(st.maxcnt, 1);
+    DDM_LAUNCHED("zero_u32_kernel");
+    r = offsets();
+    if (r == DDM_OK) r = learned_words();
+    if (r == DDM_OK) r = read_words();
+    if (r != DDM_OK) return r;
+  }
   if (st.learned) {
     st.novf = (uint32_t)hw[2];
     st.slots_total = hw[3];
@@ -2346,6 +2411,48 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   if (flags >> 32) {
     set_detail("update coordinates: NaN/inf or lo > hi");
     return DDM_E_INVALID_INPUT;
+  }
+  // Dense sets: a set marked before the count has only its candidates counted
+  // so far; one that overflowed the stash, or (d = 1) has its exact counts,
+  // takes the dense form too, once its candidates are counted.
+  const bool marked = st.stash && (hw[3] & kStashDense);
+  const bool fits = st.may_dense && tree_n(t) <= kMaxBitWords * 32;
+  bool dense = marked;
+  if (!marked && fits && P.traversal == DDM_TRAVERSE_TILE && !counts_out && !st.learned &&
+      (d == 1 ? st.K > kDenseHits1 * m : st.stash && !st.stash_ok)) {
+    SegOut O{};
+    O.tcand = st.tcand;
+    O.tsum = st.tsum;
+    O.tmax = st.tmaxs;
+    r = list_any(d, T, ulo, uhi, m, st.all(), O, s);
+    if (r == DDM_OK) r = offsets();
+    if (r == DDM_OK) r = read_words();
+    if (r != DDM_OK) return r;
+    dense = true;
+  }
+  if (dense) {
+    st.stiles = (uint32_t)(hw[2] >> 32);
+    st.stash = false;  // its memory goes back
+    st.stash_sc.drop();
+    bool made = false;
+    if (fits) {
+      r = dense_units(t, T, ulo, uhi, m, st, hw[5], hw[6], nullptr, nullptr, st.cnt, s, &made);
+      if (r != DDM_OK) return r;
+    }
+    st.dense = made;
+    if (marked) {
+      if (!made) {  // no memory for the units: count by a traversal after all
+        SegOut O{};
+        O.cnt = st.cnt;
+        r = traverse_any<false>(d, P, T, ulo, uhi, m, st.all(), st.kstar, O, s);
+        if (r != DDM_OK) return r;
+      }
+      zero_u32_kernel<<<1, 64, 0, s>>>(st.maxcnt, 1);
+      DDM_LAUNCHED("zero_u32_kernel");
+      r = offsets();
+      if (r == DDM_OK) r = read_words();
+      if (r != DDM_OK) return r;
+    }
   }
   return DDM_OK;
 }
@@ -2385,13 +2492,17 @@ ddm_status ensure_segsort_attr() {
     err = hipFuncSetAttribute((const void*)segsort_big_kernel,
                               hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)(kMaxBitWords * sizeof(uint32_t)));
-    const void* fns[4] = {(const void*)segsort_bitmap_kernel<kBmRNarrow, false>,
-                          (const void*)segsort_bitmap_kernel<kBmRNarrow, true>,
-                          (const void*)segsort_bitmap_kernel<kBmRWide, false>,
-                          (const void*)segsort_bitmap_kernel<kBmRWide, true>};
-    for (int i = 0; i < 4 && err == hipSuccess; ++i)
+    const void* fns[8] = {(const void*)segsort_bitmap_kernel<kBmRNarrow, false, uint64_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRNarrow, true, uint64_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRNarrow, false, uint32_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRNarrow, true, uint32_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRWide, false, uint64_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRWide, true, uint64_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRWide, false, uint32_t>,
+                          (const void*)segsort_bitmap_kernel<kBmRWide, true, uint32_t>};
+    for (int i = 0; i < 8 && err == hipSuccess; ++i)
       err = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)bitmap_lds_bytes(i < 2 ? kMaxBitWords / 2 : kMaxBitWords));
+                                (int)bitmap_lds_bytes(i < 4 ? kMaxBitWords / 2 : kMaxBitWords));
   });
   if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute", __FILE__, __LINE__);
   return DDM_OK;
@@ -2412,58 +2523,63 @@ ddm_status sort_segments_keys(const uint64_t* off, uint32_t m, uint64_t* out, ui
   return sort_segments(off, m, out, K, n, lists, lists_count, s, SegSrc{});
 }
 
+// The segments of up to kSegMid keys, and the longer ones too when every id is
+// below 2^20 (OUT: 64-bit keys, or 32-bit ids from lists of ids).
 // max_len: the longest segment if known; size classes that cannot occur
-// are not launched.  tmp_sc: where the id copy of the bitmap sort comes from
+// are not launched.
+template <typename OUT>
+static ddm_status sort_segments_window(const uint64_t* off, uint32_t m, OUT* out, uint32_t n,
+                                       uint32_t* lists, uint32_t* lists_count, hipStream_t s,
+                                       const SegSrc& S, uint64_t max_len) {
+  constexpr bool IDS = sizeof(OUT) == 4;
+  const bool ids = IDS || S.ids || S.slots;
+  if (ids)
+    segsort_small_kernel<true, OUT><<<(m + 255) / 256, 256, 0, s>>>(off, m, out, S, lists,
+                                                                    lists_count);
+  else
+    segsort_small_kernel<IDS, OUT><<<(m + 255) / 256, 256, 0, s>>>(off, m, out, S, lists,
+                                                                   lists_count);
+  DDM_LAUNCHED("segsort_small_kernel");
+  if (max_len <= 32) return DDM_OK;  // every segment sorted in registers
+  if (ids)
+    segsort_mid_kernel<true, OUT><<<4096, kSegWaves * kWave, 0, s>>>(off, out, S, lists,
+                                                                     lists_count);
+  else
+    segsort_mid_kernel<IDS, OUT><<<4096, kSegWaves * kWave, 0, s>>>(off, out, S, lists,
+                                                                    lists_count);
+  DDM_LAUNCHED("segsort_mid_kernel");
+  if (max_len <= kSegMid || n > kMaxBitWords * 32) return DDM_OK;
+  // one bitmap window: every listed segment by the bitmap kernel, one
+  // resident workgroup per slot of the chip (each takes every G-th segment)
+  ddm_status r = ensure_segsort_attr();
+  if (r != DDM_OK) return r;
+  const uint32_t words = std::max<uint32_t>(1u, (n + 31) / 32);
+  const size_t lds = bitmap_lds_bytes(words);
+  int dev = 0, cus = 0, per = 0;
+  DDM_HIP(hipGetDevice(&dev));
+  DDM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  auto* fn = segsort_bitmap_kernel<kBmRNarrow, false, OUT>;
+  if (n > kMaxBitWords * 16) fn = segsort_bitmap_kernel<kBmRWide, false, OUT>;
+  if (S.slots)
+    fn = n > kMaxBitWords * 16 ? segsort_bitmap_kernel<kBmRWide, true, OUT>
+                               : segsort_bitmap_kernel<kBmRNarrow, true, OUT>;
+  DDM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)fn, kBmThreads, lds));
+  const uint32_t grid = (uint32_t)std::max(1, cus * std::max(1, per));
+  fn<<<grid, kBmThreads, lds, s>>>(off, m, out, S, lists, lists_count, words);
+  DDM_LAUNCHED("segsort_bitmap_kernel");
+  return DDM_OK;
+}
+
+// Every segment of K keys.  tmp_sc: where the id copy of the bitmap sort comes from
 // (an external scratch in the no-allocation match), else allocated here.
 ddm_status sort_segments(const uint64_t* off, uint32_t m, uint64_t* out, uint64_t K, uint32_t n,
                          uint32_t* lists, uint32_t* lists_count, hipStream_t s,
                          const SegSrc& S, uint64_t max_len, Scratch* tmp_sc) {
   ProfScope ps("segsort", s);
-  if (S.ids || S.slots)
-    segsort_small_kernel<true><<<(m + 255) / 256, 256, 0, s>>>(off, m, out, S, lists, lists_count);
-  else
-    segsort_small_kernel<false><<<(m + 255) / 256, 256, 0, s>>>(off, m, out, S, lists,
-                                                                lists_count);
-  DDM_LAUNCHED("segsort_small_kernel");
-  if (max_len <= 32) return DDM_OK;  // every segment sorted in registers
-  if (S.ids || S.slots)
-    segsort_mid_kernel<true><<<4096, kSegWaves * kWave, 0, s>>>(off, out, S, lists, lists_count);
-  else
-    segsort_mid_kernel<false><<<4096, kSegWaves * kWave, 0, s>>>(off, out, S, lists, lists_count);
-  DDM_LAUNCHED("segsort_mid_kernel");
-  if (max_len <= kSegMid) return DDM_OK;
-  ddm_status r = ensure_segsort_attr();
+  ddm_status r = sort_segments_window(off, m, out, n, lists, lists_count, s, S, max_len);
+  if (r != DDM_OK || max_len <= kSegMid || n <= kMaxBitWords * 32) return r;
+  r = ensure_segsort_attr();
   if (r != DDM_OK) return r;
-  if (n <= kMaxBitWords * 32) {
-    // one bitmap window: every listed segment by the bitmap kernel, one
-    // resident workgroup per slot of the chip (each takes every G-th segment)
-    const uint32_t words = std::max<uint32_t>(1u, (n + 31) / 32);
-    const size_t lds = bitmap_lds_bytes(words);
-    int dev = 0, cus = 0, per = 0;
-    DDM_HIP(hipGetDevice(&dev));
-    DDM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    const bool narrow = n <= kMaxBitWords * 16, slots = S.slots != nullptr;
-    const void* fn = narrow ? (slots ? (const void*)segsort_bitmap_kernel<kBmRNarrow, true>
-                                     : (const void*)segsort_bitmap_kernel<kBmRNarrow, false>)
-                            : (slots ? (const void*)segsort_bitmap_kernel<kBmRWide, true>
-                                     : (const void*)segsort_bitmap_kernel<kBmRWide, false>);
-    DDM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, kBmThreads, lds));
-    const uint32_t grid = (uint32_t)std::max(1, cus * std::max(1, per));
-    if (narrow && slots)
-      segsort_bitmap_kernel<kBmRNarrow, true><<<grid, kBmThreads, lds, s>>>(off, m, out, S, lists,
-                                                                   lists_count, words);
-    else if (narrow)
-      segsort_bitmap_kernel<kBmRNarrow, false><<<grid, kBmThreads, lds, s>>>(off, m, out, S, lists,
-                                                                    lists_count, words);
-    else if (slots)
-      segsort_bitmap_kernel<kBmRWide, true><<<grid, kBmThreads, lds, s>>>(off, m, out, S, lists,
-                                                                   lists_count, words);
-    else
-      segsort_bitmap_kernel<kBmRWide, false><<<grid, kBmThreads, lds, s>>>(off, m, out, S, lists,
-                                                                    lists_count, words);
-    DDM_LAUNCHED("segsort_bitmap_kernel");
-    return DDM_OK;
-  }
   const uint32_t words = std::min<uint32_t>(kMaxBitWords, (n + 31) / 32);
   uint32_t* tmp = nullptr;
   Scratch local(s);
@@ -2524,19 +2640,27 @@ struct ddm_pending {
 static ddm_status match_begin(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
                               uint32_t m, uint64_t* out_count, void* stream,
                               const ddm_match_opts* opts, ddm_pending** out_pending,
-                              bool want_stash, uint64_t stash_hint);
+                              bool want_stash, uint64_t stash_hint, bool may_dense);
 
 extern "C" ddm_status ddm_match_begin(const ddm_tree* t, const float* upd_lo,
                                       const float* upd_hi, uint32_t m, uint64_t* out_count,
                                       void* stream, const ddm_match_opts* opts,
                                       ddm_pending** out_pending) {
-  return match_begin(t, upd_lo, upd_hi, m, out_count, stream, opts, out_pending, true, 0);
+  return match_begin(t, upd_lo, upd_hi, m, out_count, stream, opts, out_pending, true, 0, true);
 }
+
+namespace ddm {
+ddm_status match_begin_bounded(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
+                               uint32_t m, uint64_t* out_count, hipStream_t s,
+                               const ddm_match_opts* opts, ddm_pending** out_pending) {
+  return match_begin(t, upd_lo, upd_hi, m, out_count, s, opts, out_pending, true, 0, false);
+}
+}  // namespace ddm
 
 static ddm_status match_begin(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
                               uint32_t m, uint64_t* out_count, void* stream,
                               const ddm_match_opts* opts, ddm_pending** out_pending,
-                              bool want_stash, uint64_t stash_hint) {
+                              bool want_stash, uint64_t stash_hint, bool may_dense) {
   set_detail("");
   if (!out_count || !out_pending) {
     set_detail("out_count / out_pending is NULL");
@@ -2562,7 +2686,7 @@ static ddm_status match_begin(const ddm_tree* t, const float* upd_lo, const floa
   pd->uhi = upd_hi;
   pd->m = m;
   r = front_half(t, upd_lo, upd_hi, m, P, pd->st, nullptr, &pd->lists, &pd->lists_count, s,
-                 nullptr, 0, want_stash, stash_hint);
+                 nullptr, 0, want_stash, stash_hint, nullptr, may_dense);
   if (r != DDM_OK) {
     delete pd;
     return r;
@@ -2609,7 +2733,7 @@ static ddm_status learned_begin(const ddm_tree* t, const float* upd_lo, const fl
   pd->uhi = upd_hi;
   pd->m = m;
   r = front_half(t, upd_lo, upd_hi, m, P, pd->st, nullptr, &pd->lists, &pd->lists_count, s, pred,
-                 slot_budget, false, 0, grant);
+                 slot_budget, false, 0, grant, true);
   if (r != DDM_OK) {
     delete pd;
     return r;
@@ -2693,14 +2817,14 @@ static ddm_status balance_fill_tiles(const MatchState& st, uint32_t m, Scratch& 
   DDM_LAUNCHED("work_in_order_kernel");
   ddm_status r = scan_u32_u64(w, cw, m, tmp, s);
   if (r != DDM_OK) return r;
-  tile_cut_kernel<<<g, 256, 0, s>>>(st.perm, st.bucket, st.bhist, cw, m, w);
+  tile_cut_kernel<<<g, 256, 0, s>>>(st.perm, st.kstar, st.gstart, cw, m, tile_updates(m), w);
   DDM_LAUNCHED("tile_cut_kernel");
   r = scan_u32_u64(w, cw, m, tmp, s);
   if (r != DDM_OK) return r;
-  tile_list_kernel<<<g, 256, 0, s>>>(st.perm, st.bucket, w, cw, m, ts, tb);
+  tile_list_kernel<<<g, 256, 0, s>>>(st.perm, st.kstar, w, cw, m, ts, tb);
   DDM_LAUNCHED("tile_list_kernel");
   U->tstart = ts;
-  U->tbuck = tb;
+  U->tclass = tb;
   U->ntiles = cw + m;
   return DDM_OK;
 }
@@ -2723,7 +2847,9 @@ extern "C" ddm_status ddm_match_finish(ddm_pending* pd, uint64_t* out_pairs, uin
     O.out = out_pairs;
     Scratch fsc(pd->s);        // the fill's ids and tile lists (until the sort has run)
     uint32_t* fids = nullptr;  // the fill's 4-byte ids, if it writes them
-    if (st.learned) {
+    if (st.dense) {
+      r = dense_expand(tree_d(pd->t), st, out_pairs, pd->s);
+    } else if (st.learned && !st.plain_fill) {
       // segments that fitted their slots are moved into place by the
       // segment sort; overflowed ones are filled in place here
       if (st.novf > 0) {
@@ -2757,7 +2883,7 @@ extern "C" ddm_status ddm_match_finish(ddm_pending* pd, uint64_t* out_pairs, uin
       const uint64_t H = std::max<uint64_t>(
           (2ull * 64ull * st.K) / ((uint64_t)pd->m * kCutDiv), kCutMinHits);
       const bool use_ids = !st.noalloc && tree_n(pd->t) <= kMaxBitWords * 32;
-      const bool bal = !st.noalloc && pd->plan.traversal == DDM_TRAVERSE_TILE && U.tmap &&
+      const bool bal = !st.noalloc && pd->plan.traversal == DDM_TRAVERSE_TILE &&
                        (st.maxseg == ~0ull || 64ull * st.maxseg > H);
       if (use_ids) fsc.reserve(sizeof(uint32_t) * st.K);
       if (bal) balance_reserve(pd->m, fsc);
@@ -2772,10 +2898,10 @@ extern "C" ddm_status ddm_match_finish(ddm_pending* pd, uint64_t* out_pairs, uin
         r = traverse_any<true>(tree_d(pd->t), pd->plan, T, pd->ulo, pd->uhi, pd->m, U, st.kstar,
                                O, pd->s);
     }
-    if (r == DDM_OK) {
+    if (r == DDM_OK && !st.dense) {
       SegSrc S{};
       S.ids = fids;
-      if (st.learned) {
+      if (st.learned && !st.plain_fill) {
         S.slots = st.slots;
         S.so.base = st.soff;
         S.so.cap = st.cap;
@@ -2797,12 +2923,10 @@ extern "C" ddm_status ddm_match_ex(const ddm_tree* t, const float* upd_lo, const
                                    uint64_t* out_count, void* stream,
                                    const ddm_match_opts* opts) {
   ddm_pending* pd = nullptr;
-  // the capacity sizes the count traversal's stash (none for a size query,
-  // for capacities beyond what a stash may hold, or for dense results)
-  ddm_status r = match_begin(t, upd_lo, upd_hi, m, out_count, stream, opts, &pd,
-                             capacity > 0 && capacity <= kStashMaxEntries &&
-                                 capacity <= kStashMaxPerUpdate * m,
-                             capacity);
+  // the capacity sizes the count traversal's stash (none for a size query),
+  // up to kStashMaxPerUpdate hits per update
+  ddm_status r = match_begin(t, upd_lo, upd_hi, m, out_count, stream, opts, &pd, capacity > 0,
+                             std::min<uint64_t>(capacity, kStashMaxPerUpdate * m), capacity > 0);
   if (r != DDM_OK) return r;
   if (*out_count > capacity) {
     ddm_match_abort(pd);

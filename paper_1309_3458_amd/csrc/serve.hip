@@ -410,7 +410,7 @@ ddm_status process(ddm_server* S, ddm_server_req* q, hipStream_t s, std::string*
       return DDM_OK;
     }
   } else {
-    st = ddm_match_begin(t, r.upd_lo, r.upd_hi, r.m, &K, s, &mo, &pend);
+    st = match_begin_bounded(t, r.upd_lo, r.upd_hi, r.m, &K, s, &mo, &pend);
   }
   if (st != DDM_OK) {
     if (held) {

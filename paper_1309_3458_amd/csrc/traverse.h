@@ -5,6 +5,9 @@
 
 #include "ddm_internal.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace ddm {
 
 // --------------------------------------------------------------------------
@@ -28,6 +31,20 @@ __device__ __forceinline__ void load_rec(const float* __restrict__ p, float (&v)
     const float4 b = reinterpret_cast<const float4*>(p)[1];
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  }
+}
+
+template <int D>
+__device__ __forceinline__ void store_rec(float* __restrict__ p, const float (&v)[2 * D]) {
+  if constexpr (D == 2 || D == 4) {
+#pragma unroll
+    for (int q = 0; q < D / 2; ++q)
+      reinterpret_cast<float4*>(p)[q] =
+          make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < D; ++q)
+      reinterpret_cast<float2*>(p)[q] = make_float2(v[2 * q], v[2 * q + 1]);
   }
 }
 
@@ -64,16 +81,34 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
-  return uniform_f32(v);
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  return wave_fold_dpp(v, [](uint32_t a, uint32_t b) { return min(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  return wave_fold_dpp(v, [](uint32_t a, uint32_t b) { return max(a, b); });
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return uniform_f32(v);
+__device__ __forceinline__ uint32_t readlane_u32(uint32_t v, uint32_t lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane);
+}
+__device__ __forceinline__ float readlane_f32(float v, uint32_t lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), (int)lane));
+}
+// v with lane `lane` replaced by x (both uniform); the compiler has the
+// intrinsic but no builtin for it
+extern "C" __device__ int ddm_writelane(int x, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t writelane_u32(uint32_t v, uint32_t x, uint32_t lane) {
+  return (uint32_t)ddm_writelane((int)x, (int)lane, (int)v);
+}
+// 2 acc + (this lane's bit of m): one add with the mask as the carries
+__device__ __forceinline__ uint32_t shift_in(uint32_t acc, uint64_t m) {
+  uint32_t r;
+  asm("v_addc_co_u32_e64 %0, vcc, %1, %1, %2" : "=v"(r) : "v"(acc), "s"(m) : "vcc");
+  return r;
+}
+// whether this lane's bit of the (uniform) mask is set
+__device__ __forceinline__ bool lane_of(uint64_t m) {
+  return __builtin_amdgcn_inverse_ballot_w64(m);
 }
 
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t lane) {
@@ -89,23 +124,16 @@ struct UpdSet {
   const uint32_t* gstart;
   const uint32_t* gcount;
   uint32_t total;     // upper bound of sum(gcount), for the launch size
-  uint32_t qpt = 64;  // updates per wavefront in the tile traversal (64 or 1)
-  // bucket-aligned tiles (optional): bucket b holds perm[boff[b] ..
-  // boff[b+1]) (the last ends at `total`), tiles of 64 updates never cross a
-  // bucket, tile t belongs to bucket tmap[t], the buckets' first tiles are
-  // tprefix[b] and there are tprefix[nbuckets] tiles
-  const uint32_t* boff = nullptr;
-  const uint32_t* tprefix = nullptr;
-  const uint32_t* tmap = nullptr;
+  uint32_t qpt = 64;  // updates per wavefront in the tile traversal
   // optional: per update j, pb[2j] <= the first and pb[2j+1] >= the last
   // position of its candidate range in its probe tree (bounds from the
   // probe's quantile searches); tiles then skip their own searches
   const uint32_t* pb = nullptr;
-  // optional tile list (replaces the 64-update tiles of tprefix / tmap):
-  // tile t holds perm[tstart[t] .. tstart[t+1]) (at most 64 updates, one
-  // bucket), belongs to bucket tbuck[t], and there are *ntiles tiles
+  // optional tile list (replaces the tiles of qpt updates): tile t holds
+  // perm[tstart[t] .. tstart[t+1]) (at most 64 updates of one class), belongs
+  // to class tclass[t], and there are *ntiles tiles
   const uint32_t* tstart = nullptr;
-  const uint32_t* tbuck = nullptr;
+  const uint32_t* tclass = nullptr;
   const uint64_t* ntiles = nullptr;
 };
 
@@ -128,6 +156,9 @@ struct UpdSet {
 constexpr uint32_t kStashChunk = 64;
 constexpr uint32_t kStashStatic = 2;
 constexpr uint32_t kStashSlices = 256;
+// snext[kStashSlices]: 1 overflow, 2 (set before the count) a dense set
+constexpr uint32_t kStashDense = 2;
+constexpr uint32_t kListSlices = 64;
 constexpr uint32_t kStashGrab = 4;  // at least this many counted chunks per request
 // at most 2^28 stashed hits (4 GiB of stash); larger results overflow it and
 // take the fill traversal
@@ -154,6 +185,13 @@ struct SegOut {
   uint32_t* sowner = nullptr;  // optional: tile of every counted chunk a tile takes
   uint32_t sfirst = 0;
   uint32_t sslice = 0;
+  // LIST, and the stash form of a dense set (tcand optional in LIST): the number
+  // of candidates of each tile, their sums and maxima over the tiles t with t %
+  // kListSlices alike; LIST with ids: the ids of tile t's candidates, as far as
+  // they fit, to ids[base[t] .. base[t + 1])
+  uint32_t* tcand = nullptr;
+  uint64_t* tsum = nullptr;
+  uint32_t* tmax = nullptr;
 };
 
 __device__ __forceinline__ bool upd_index(const UpdSet& U, uint32_t t, uint32_t d,
@@ -200,56 +238,112 @@ __device__ __forceinline__ void seg_bounds(const SegOut& O, uint32_t j, uint64_t
 // is the update's hits among them, and a prefix popcount places the hits
 // contiguously in the update's own segment.
 // --------------------------------------------------------------------------
+// d > 1: a tile whose range spans at least kStripRange positions takes the
+// blocks of the strips it touches instead (tree_dev.h), testing 64 block
+// boxes at once.  Shorter ranges hold fewer blocks than the 32 of a strip.
+constexpr uint32_t kChunkPosLog = 11;  // positions of a strip
+constexpr uint32_t kStripRange = 1024;
 constexpr int kTileWaves = 4;
 constexpr int kRing = 128;
 
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, kWave));
-  return uniform_u32(v);
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, kWave));
-  return uniform_u32(v);
-}
-
 // One tile of the traversal: updates perm[qbeg .. qbeg + nq) (global indices;
 // qoff is subtracted to index the instance's coordinates), probe dimension k
-// of tree set T.  LDS per wavefront: s_cand [2D][kRing] floats, s_cid
-// [kRing], s_q [64][RV] float4.
-// XP (count pass only, d >= 2, one instance): the flush is transposed.  The
-// tile's updates are sorted once by their lower bound in record slot 1 (the
-// first dimension after the probe dimension) into LDS (s_lo1, s_q, s_xj);
-// each candidate lane binary-searches the window of updates whose slot-1
-// extent can meet its own (lower bound in [c.lo1 - longest update, c.hi1],
-// bounds rounded outwards, so the window is a superset) and tests only those
-// exactly, in every dimension.  A cell of the tile spans a far wider range
-// in the other dimensions than one update, so a window holds a few updates
-// where the untransposed flush tests all 64.  Hits are counted per update
-// in LDS (s_xcnt); the atomic's result is the hit's rank for the stash.
-constexpr uint32_t kXpWindow = 8;  // widest window the transposed flush takes
+// of tree set T.  LDS per wavefront: s_cand [kRing][2D] floats (records), s_cid
+// [kRing].
+//
+// Candidates are tested 64 at a time (a flush), in one of two forms, whichever
+// takes fewer vector instructions; both leave in lane u the mask of the
+// candidates that update u meets:
+//   by candidate: the update's bounds sit in its lane, every candidate is
+//     compared with all updates at once (its first dimension from the lane
+//     that holds it, the others broadcast from LDS), and the result is shifted
+//     into each lane's mask with one add-with-carry: 2 + 2D + 1 instructions
+//     for a candidate, whatever the number of updates;
+//   by update: every lane holds a candidate, the update's bounds come from its
+//     lane, and its mask is written to that lane: 4D + 2 instructions for an
+//     update, whatever the number of candidates.
+// Reading each update's bounds from LDS, with a ballot, a lane extract and a
+// count per update, took about 31 instructions for an update; a window search
+// per candidate over the updates sorted in a second dimension took fewer only
+// where cells were wide (10^6 boxes, d = 3, count with strips and cells alike:
+// 217 us with it, 177 us this way).
+// Tests 64 candidates (lane l holds record v of candidate l; past c they are
+// empty) against the updates of the lanes (bounds ql, qh; lanes from nq on hold
+// none): *mlo and *mhi receive the mask of the candidates that the lane's update
+// meets.  cd: 64 records of LDS; lanes with `put` write theirs there first if
+// they are read.
+template <int D>
+__device__ __forceinline__ void test_masks(const float (&ql)[D], const float (&qh)[D], uint32_t nq,
+                                           const float (&v)[2 * D], float* __restrict__ cd,
+                                           uint32_t lane, uint32_t c, bool put, uint32_t* mlo_out,
+                                           uint32_t* mhi_out) {
+  constexpr int R = 2 * D;
+  uint32_t mlo = 0, mhi = 0;
+  const uint32_t groups = (c + 15u) / 16u;
+  if (groups * 16u * (2u * D + 3u) < nq * (4u * D + 2u)) {
+    if (D > 1) {
+      if (put) store_rec<D>(cd + lane * R, v);
+      wave_sync();
+    }
+    for (uint32_t g = 0; g < groups; ++g) {
+      const float* __restrict__ cg = cd + 16u * g * R;
+      uint32_t acc = 0;
+#pragma unroll
+      for (int i = 15; i >= 0; --i) {
+        const uint32_t ln = 16u * g + (uint32_t)i;
+        uint64_t m = ballot(readlane_f32(v[0], ln) <= qh[0]);
+        m &= ballot(ql[0] <= readlane_f32(v[1], ln));
+#pragma unroll
+        for (int s = 1; s < D; ++s) {
+          const float2 b = *reinterpret_cast<const float2*>(cg + i * R + 2 * s);
+          m &= ballot(b.x <= qh[s]);
+          m &= ballot(ql[s] <= b.y);
+        }
+        acc = shift_in(acc, m);
+      }
+      if (g < 2) mlo |= acc << (16u * g);
+      else mhi |= acc << (16u * (g - 2u));
+    }
+  } else {
+    for (uint32_t u0 = 0; u0 < nq; u0 += 4) {
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t u = u0 + q;  // below 64; lanes from nq on meet nothing
+        uint64_t m = ~0ull;
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+          m &= ballot(v[2 * s] <= readlane_f32(qh[s], u));
+          m &= ballot(readlane_f32(ql[s], u) <= v[2 * s + 1]);
+        }
+        mlo = writelane_u32(mlo, (uint32_t)m, u);
+        mhi = writelane_u32(mhi, (uint32_t)(m >> 32), u);
+      }
+    }
+  }
+  *mlo_out = mlo;
+  *mhi_out = mhi;
+}
 
-struct XpLds {
-  float* lo1;     // [64] sorted slot-1 lower bounds (+inf past nq)
-  uint32_t* cnt;  // [64] hits per sorted update
-  uint32_t* j;    // [64] update index of each sorted update
+enum TileMode {
+  kTileCount,  // counts
+  kTileFill,   // hits into the updates' segments or slots, counts if asked
+  kTileStash,  // counts and kept hits; a set marked dense: as kTileList
+  kTileList    // the tile's candidates: their number, or their ids
 };
 
-template <int D, bool FILL, bool STASH = false, bool XP = false>
+template <int D, TileMode MODE>
 __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restrict__ ulo,
                                           const float* __restrict__ uhi, uint32_t m,
                                           const uint32_t* __restrict__ perm, uint32_t qoff,
                                           uint32_t k, uint32_t qbeg, uint32_t nq, const SegOut& O,
                                           float* __restrict__ s_cand, uint32_t* __restrict__ s_cid,
-                                          float4* __restrict__ s_q, uint32_t lane,
-                                          uint32_t tile_id = 0,
-                                          const uint32_t* __restrict__ pb = nullptr,
-                                          XpLds xl = XpLds{}) {
+                                          uint32_t lane, uint32_t tile_id = 0,
+                                          const uint32_t* __restrict__ pb = nullptr) {
   constexpr int R = 2 * D;
-  constexpr int RV = (R + 3) / 4;
-  static_assert(!XP || (!FILL && D >= 2), "the transposed flush counts, for d >= 2");
+  constexpr bool FILL = MODE == kTileFill, STASH = MODE == kTileStash;
+  nq = uniform_u32(nq);
+  const uint32_t sflag = STASH ? uniform_u32(O.snext[kStashSlices]) : 0u;
+  const bool listing = MODE == kTileList || (STASH && (sflag & kStashDense));
   const bool qv = lane < nq;
   const uint32_t gj = qv ? perm[qbeg + lane] : 0u;  // global update index
   const uint32_t j = gj - qoff;                      // index within the instance
@@ -262,59 +356,6 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
       ql[s] = INFINITY;
       qh[s] = -INFINITY;
     }
-  }
-  float tmax1 = 0.f;  // XP: longest slot-1 extent of the tile, rounded up
-  uint32_t jx = j;    // the update this lane stands for (XP: in sorted order)
-  if constexpr (XP) {
-    // bitonic sort of the lanes' (slot-1 lower bound, lane) pairs; lanes
-    // past nq sort last
-    float key = qv ? ql[1] : INFINITY;
-    uint32_t src = lane;
-#pragma unroll
-    for (uint32_t kk = 2; kk <= (uint32_t)kWave; kk <<= 1) {
-#pragma unroll
-      for (uint32_t jj = kk >> 1; jj > 0; jj >>= 1) {
-        const float ok = __shfl_xor(key, (int)jj, kWave);
-        const uint32_t os = (uint32_t)__shfl_xor((int)src, (int)jj, kWave);
-        const bool up = (lane & kk) == 0, lower = (lane & jj) == 0;
-        const bool other_less = ok < key || (ok == key && os < src);
-        if (lower == up ? other_less : !other_less) {
-          key = ok;
-          src = os;
-        }
-      }
-    }
-    // this lane now holds the rank-`lane` update: take its bounds
-    float sl[D], sh[D];
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      sl[s] = __shfl(ql[s], (int)src, kWave);
-      sh[s] = __shfl(qh[s], (int)src, kWave);
-    }
-    const uint32_t sj = (uint32_t)__shfl((int)j, (int)src, kWave);
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      ql[s] = sl[s];
-      qh[s] = sh[s];
-    }
-    xl.lo1[lane] = qv ? sl[1] : INFINITY;
-    xl.cnt[lane] = 0;
-    xl.j[lane] = sj;
-    jx = sj;
-    tmax1 = nextafterf(wave_max(qv ? sh[1] - sl[1] : 0.f), INFINITY);
-  }
-  {
-    float qr[4 * RV];
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      qr[2 * s] = ql[s];
-      qr[2 * s + 1] = qh[s];
-    }
-#pragma unroll
-    for (int r = R; r < 4 * RV; ++r) qr[r] = 0.f;
-#pragma unroll
-    for (int vv = 0; vv < RV; ++vv)
-      s_q[lane * RV + vv] = make_float4(qr[4 * vv], qr[4 * vv + 1], qr[4 * vv + 2], qr[4 * vv + 3]);
   }
   float elo[D], ehi[D];
 #pragma unroll
@@ -353,21 +394,18 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
   const uint64_t mystart = mybase;
   uint64_t* __restrict__ out = O.out;
   uint32_t* __restrict__ oids = O.ids;
-  const uint64_t jhi = (uint64_t)jx << 32;
-  const uint32_t nq4 = (nq + 3u) & ~3u;
-  wave_sync();
 
-  const float* __restrict__ rec = T.rec[k];
+  const float* rec = T.rec[k];
   const float* __restrict__ bmx = T.bmax[k];
-  const uint32_t* __restrict__ ids = T.id[k];
+  const uint32_t* ids = T.id[k];
   uint32_t head = 0, tail = 0;
+  const uint64_t lbase = MODE == kTileList && O.ids ? O.base[tile_id] : 0ull;
+  const uint64_t lend = MODE == kTileList && O.ids ? O.base[tile_id + 1] : 0ull;
   // stash chunk of the wave (uniform): id, entries used, last static chunk,
   // still stashing
   uint32_t sch = tile_id * kStashStatic, sfill = 0;
   uint32_t slast = sch + kStashStatic - 1;  // last chunk the tile holds
-  bool sok = STASH && uniform_u32(O.snext[kStashSlices]) == 0;
-  uint64_t myhm = 0;  // this lane's update: hits among the flushed candidates
-
+  bool sok = STASH && sflag == 0;
   // stash: room for `tot` more entries from this wave, in the current chunk
   // and (if needed) nnew more chunks starting at `first` (static ones of the
   // tile, else counted ones from the slices); false once the stash is full
@@ -427,303 +465,214 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
     }
   };
 
-  auto flush_classic = [&](uint32_t c) {
+  // tests candidates head .. head + c against the tile's updates
+  auto flush = [&](uint32_t cnt) {
     wave_sync();
-    const uint64_t cvm = (c >= (uint32_t)kWave) ? ~0ull : ((1ull << c) - 1ull);
-    const uint32_t slot = (head + lane) & (kRing - 1);
+    const uint32_t c = uniform_u32(cnt);
+    const uint32_t h0 = uniform_u32(head & (kRing - 1));  // a multiple of 64: no wrap inside
     float v[R];
+    load_rec<D>(s_cand + (h0 + lane) * R, v);
+    const uint32_t sid = s_cid[h0 + lane];
+    if (lane >= c) {  // the last flush: nothing meets an empty slot
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = s_cand[r * kRing + slot];
-    const uint32_t sid = s_cid[slot];
-    for (uint32_t qi = 0; qi < nq4; qi += 4) {
-      uint64_t hm[4];
-      bool hit[4];  // this lane's bit of hm (the fill stores under it)
-#pragma unroll
-      for (uint32_t u = 0; u < 4; ++u) {
-        float q[4 * RV];
-#pragma unroll
-        for (int vv = 0; vv < RV; ++vv) {
-          const float4 t4 = s_q[(qi + u) * RV + vv];
-          q[4 * vv] = t4.x;
-          q[4 * vv + 1] = t4.y;
-          q[4 * vv + 2] = t4.z;
-          q[4 * vv + 3] = t4.w;
-        }
-        // one compare per lane mask, combined with scalar ANDs
-        uint64_t h = cvm;
-        bool hl = lane < c;
-#pragma unroll
-        for (int s = 0; s < D; ++s) {
-          const bool c1 = v[2 * s] <= q[2 * s + 1], c2 = q[2 * s] <= v[2 * s + 1];
-          h &= ballot(c1);
-          h &= ballot(c2);
-          hl = hl && c1 && c2;
-        }
-        hm[u] = h;
-        hit[u] = hl;
-      }
-      if ((hm[0] | hm[1] | hm[2] | hm[3]) != 0) {
-#pragma unroll
-        for (uint32_t u = 0; u < 4; ++u) {
-          if (hm[u] == 0) continue;
-          const uint32_t qq = qi + u;
-          const uint32_t pc = (uint32_t)__popcll(hm[u]);
-          if (FILL) {
-            const uint64_t b = readlane_u64(mybase, qq);
-            const uint64_t e = readlane_u64(myend, qq);
-            const uint64_t jq = readlane_u64(jhi, qq);
-            const uint64_t dst = b + mask_rank(hm[u]);
-            if (hit[u] && dst < e) {
-              if (oids) oids[dst] = sid;
-              else out[dst] = jq | sid;
-            }
-            if (lane == qq) mybase += pc;
-          } else if constexpr (STASH || XP) {
-            if (lane == qq) myhm = hm[u];
-          } else {
-            if (lane == qq) mycnt += pc;
-          }
-        }
+      for (int s = 0; s < D; ++s) {
+        v[2 * s] = INFINITY;
+        v[2 * s + 1] = -INFINITY;
       }
     }
-    if constexpr (STASH) {
-      // each lane stashes its own update's hits among these candidates: a
-      // wave prefix of the hit counts places them, one chunk request (if
-      // any) covers the whole flush (most flushes have no hit at all)
-      const bool some = ballot(myhm != 0) != 0;
-      const uint32_t pcl = (uint32_t)__popcll(myhm);
-      if (some && sok) {
-        uint32_t incl = pcl;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-          const uint32_t t = (uint32_t)__shfl_up((int)incl, o, kWave);
-          if (lane >= (uint32_t)o) incl += t;
+    uint32_t mlo, mhi;  // this lane's update: its hits among the candidates
+    test_masks<D>(ql, qh, nq, v, s_cand + h0 * R, lane, c, lane >= c, &mlo, &mhi);
+    const uint32_t pcl = (uint32_t)__popc(mlo) + (uint32_t)__popc(mhi);
+    uint64_t some = ballot(pcl != 0);
+    if constexpr (FILL) {
+      // the hits of each update go to consecutive slots of its segment; a
+      // segment without room for all of them is written under a guard
+      const bool tight = ballot(mybase + pcl > myend) != 0;
+      while (some) {
+        const uint32_t u = (uint32_t)__builtin_ctzll(some);
+        some &= some - 1;
+        const uint64_t m = readlane_u64((uint64_t)mhi << 32 | mlo, u);
+        const uint64_t b = readlane_u64(mybase, u);
+        const uint32_t r = mask_rank(m);
+        bool w = lane_of(m);
+        if (tight) w = w && b + r < readlane_u64(myend, u);
+        if (oids) {
+          if (w) (oids + b)[r] = sid;
+        } else {
+          const uint64_t jq = (uint64_t)readlane_u32(j, u) << 32;
+          if (w) (out + b)[r] = jq | sid;
         }
-        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-        if (tot > 0 && sok) {
-          const uint32_t room = kStashChunk - sfill;
-          uint32_t first = 0, nnew = 0;
-          if (room < tot) {
-            // hits beyond the current chunk go to consecutive new ones: the
-            // tile's next static chunks, else counted ones (the static
-            // chunks left over are then marked empty)
-            nnew = (tot - room + kStashChunk - 1) / kStashChunk;
-            if (sch + nnew <= slast) {
-              first = sch + 1;
-            } else {
-              // the tile's slice first, then the following ones; the part
-              // of a slice too short for the request is marked empty
-              const uint32_t take = max(nnew, kStashGrab);
-              if (sch < slast && lane < slast - sch) O.sused[sch + 1 + lane] = 0;
-              bool got = false;
-              for (uint32_t a = 0, sl = tile_id % kStashSlices; a < kStashSlices && !got;
-                   ++a, sl = (sl + 1) % kStashSlices) {
-                const uint32_t send = O.sfirst + (sl + 1) * O.sslice;
-                uint32_t f = 0;
-                if (lane == 0) {
-                  // a slice already used up is passed over without an atomic
-                  f = __hip_atomic_load(O.snext + sl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                  if (f < send) f = atomicAdd(O.snext + sl, take);
-                }
-                first = uniform_u32(f);
-                if (first < send && take <= send - first) {
-                  got = true;
-                } else if (first < send && lane < send - first) {
-                  O.sused[first + lane] = 0;
-                }
-              }
-              if (!got) {
-                sok = false;
-                if (lane == 0) atomicOr(O.snext + kStashSlices, 1u);
-              } else {
-                if (O.sowner && lane < take) O.sowner[first + lane] = tile_id;
-                slast = first + take - 1;
-              }
-            }
-          }
-          if (sok) {
-            uint64_t hv = myhm;
-            uint32_t v = incl - pcl, r = XP ? (lane < nq ? xl.cnt[lane] : 0u) : mycnt;
+      }
+      mybase += pcl;
+    } else {
+      if constexpr (STASH) {
+        // each lane stashes its own update's hits: a wave prefix of the hit
+        // counts places them, one chunk request (if any) covers the flush
+        // (most flushes of a sparse set have no hit at all)
+        if (sok && some) {
+          const uint32_t incl = wave_scan_dpp(pcl);
+          const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+          uint32_t room, first, nnew;
+          if (stash_room(tot, &room, &first, &nnew)) {
+            uint64_t hv = (uint64_t)mhi << 32 | mlo;
+            uint32_t at = incl - pcl, r = mycnt;
             while (hv) {
               const uint32_t ci = (uint32_t)__builtin_ctzll(hv);
               hv &= hv - 1;
-              const uint64_t e = v < room ? (uint64_t)sch * kStashChunk + sfill + v
-                                          : (uint64_t)first * kStashChunk + (v - room);
-              O.skey[e] = jhi | s_cid[(head + ci) & (kRing - 1)];
+              const uint64_t e = at < room ? (uint64_t)sch * kStashChunk + sfill + at
+                                           : (uint64_t)first * kStashChunk + (at - room);
+              O.skey[e] = (uint64_t)j << 32 | s_cid[h0 + ci];
               O.srank[e] = r;
-              ++v;
+              ++at;
               ++r;
             }
-            if (nnew) {
-              if (lane == 0) O.sused[sch] = kStashChunk;
-              if (lane + 1 < nnew) O.sused[first + lane] = kStashChunk;
-              sch = first + nnew - 1;
-              sfill = tot - room - (nnew - 1) * kStashChunk;
-            } else {
-              sfill += tot;
-            }
+            stash_advance(tot, room, first, nnew);
           }
         }
       }
-      if (some) {
-        if constexpr (XP) {
-          if (lane < nq) xl.cnt[lane] += pcl;
-        } else {
-          mycnt += pcl;
-        }
-        myhm = 0;
-      }
-    } else if constexpr (XP) {
-      if (lane < nq) xl.cnt[lane] += (uint32_t)__popcll(myhm);
-      myhm = 0;
+      mycnt += pcl;
     }
     head += c;
     wave_sync();
-  };
-  auto flush_xp = [&](uint32_t c) {
-    wave_sync();
-    const bool in = lane < c;
-    const uint32_t slot = (head + lane) & (kRing - 1);
-    float v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = s_cand[r * kRing + slot];
-    const uint32_t sid = s_cid[slot];
-    // window [a, b) of the sorted updates that may meet the candidate in
-    // slot 1: lower bound >= c.lo1 - tmax1 (rounded down) and <= c.hi1
-    const float klo = nextafterf(v[2] - tmax1, -INFINITY), khi = v[3];
-    uint32_t a = 0, b = 0;
-#pragma unroll
-    for (uint32_t step = kWave; step > 0; step >>= 1) {
-      if (a + step <= (uint32_t)kWave && xl.lo1[a + step - 1] < klo) a += step;
-      if (b + step <= (uint32_t)kWave && xl.lo1[b + step - 1] <= khi) b += step;
-    }
-    if (!in) b = a;
-    // dense cells (wide windows): the untransposed loop over all updates is
-    // cheaper; it keeps its counts and ranks in the same LDS counters
-    if (wave_max_u32(b - a) > kXpWindow) {
-      flush_classic(c);
-      return;
-    }
-    auto meets = [&](uint32_t u) {
-      float q[4 * RV];
-#pragma unroll
-      for (int vv = 0; vv < RV; ++vv) {
-        const float4 t4 = s_q[u * RV + vv];
-        q[4 * vv] = t4.x;
-        q[4 * vv + 1] = t4.y;
-        q[4 * vv + 2] = t4.z;
-        q[4 * vv + 3] = t4.w;
-      }
-      bool ok = true;
-#pragma unroll
-      for (int s2 = 0; s2 < D; ++s2)
-        ok = ok && (v[2 * s2] <= q[2 * s2 + 1]) && (q[2 * s2] <= v[2 * s2 + 1]);
-      return ok;
-    };
-    if constexpr (!STASH) {
-      for (uint32_t u = a; u < b; ++u)
-        if (meets(u)) atomicAdd(&xl.cnt[u], 1u);
-    } else {
-      uint32_t nh = 0;
-      for (uint32_t u = a; u < b; ++u) nh += meets(u) ? 1u : 0u;
-      if (ballot(nh != 0) != 0) {
-        uint32_t incl = nh;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-          const uint32_t t = (uint32_t)__shfl_up((int)incl, o, kWave);
-          if (lane >= (uint32_t)o) incl += t;
-        }
-        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-        uint32_t room = 0, first = 0, nnew = 0;
-        const bool keep = sok && stash_room(tot, &room, &first, &nnew);
-        uint32_t vpos = incl - nh;
-        for (uint32_t u = a; u < b; ++u) {
-          if (!meets(u)) continue;
-          const uint32_t r = atomicAdd(&xl.cnt[u], 1u);
-          if (keep) {
-            const uint64_t e = vpos < room ? (uint64_t)sch * kStashChunk + sfill + vpos
-                                           : (uint64_t)first * kStashChunk + (vpos - room);
-            O.skey[e] = ((uint64_t)xl.j[u] << 32) | sid;
-            O.srank[e] = r;
-          }
-          ++vpos;
-        }
-        if (keep) stash_advance(tot, room, first, nnew);
-      }
-    }
-    head += c;
-    wave_sync();
-  };
-
-  auto flush = [&](uint32_t c) {
-    if constexpr (XP) flush_xp(c);
-    else flush_classic(c);
-  };
-
-  // one block of 64 candidate positions: test against the tile's box in
-  // every dimension, compact the survivors into the ring
-  auto stage = [&](const float (&v)[R], uint32_t id, bool inb) {
-    bool cnd = inb;
-#pragma unroll
-    for (int s = 0; s < D; ++s) cnd = cnd & (v[2 * s] <= ehi[s]) & (elo[s] <= v[2 * s + 1]);
-    const uint64_t cm = ballot(cnd);
-    if (cnd) {
-      const uint32_t slot = (tail + mask_rank(cm)) & (kRing - 1);
-#pragma unroll
-      for (int r = 0; r < R; ++r) s_cand[r * kRing + slot] = v[r];
-      s_cid[slot] = id;
-    }
-    tail += (uint32_t)__popcll(cm);
-    if (tail - head >= (uint32_t)kWave) flush(kWave);
   };
 
   if (Pbeg <= Pend) {
-    const uint32_t c0 = Pbeg >> kBlockLog, c1 = Pend >> kBlockLog;
-    for (uint32_t cb = c0; cb <= c1; cb += kWave) {
-      const uint32_t c = cb + lane;
-      const bool keep = (c <= c1) && (bmx[c] >= elo[0]);
-      uint64_t bm = ballot(keep);
-      while (bm != 0) {
-        // two kept blocks at a time: both loads are in flight together
-        const uint32_t b0 = (uint32_t)__builtin_ctzll(bm);
-        bm &= bm - 1;
-        const bool two = bm != 0;
-        const uint32_t b1 = two ? (uint32_t)__builtin_ctzll(bm) : b0;
-        if (two) bm &= bm - 1;
-        const uint32_t blkA = cb + b0, blkB = cb + b1;
-        const uint32_t pA = max(blkA << kBlockLog, Pbeg) + lane;
-        const uint32_t pB = max(blkB << kBlockLog, Pbeg) + lane;
-        const bool inA = pA <= min((blkA << kBlockLog) + (1u << kBlockLog) - 1u, Pend);
-        const bool inB = two && pB <= min((blkB << kBlockLog) + (1u << kBlockLog) - 1u, Pend);
-        float vA[R], vB[R];
-        uint32_t idA = 0, idB = 0;
+    // blocks of 64 candidates: of the strips the range touches, kept when
+    // their box meets the tile's (d > 1), or of the positions themselves,
+    // kept when their maxupper reaches the tile's least lower bound
+    const bool strips = D > 1 && T.sbox[k] != nullptr && Pend - Pbeg >= kStripRange;
+    uint32_t c0, c1, first = Pbeg, last = Pend;
+    if (strips) {
+      c0 = Pbeg >> kChunkPosLog << (kChunkPosLog - kBlockLog);
+      c1 = min((Pend >> kChunkPosLog << (kChunkPosLog - kBlockLog)) +
+                   (1u << (kChunkPosLog - kBlockLog)),
+               T.nblk) - 1u;
+      first = 0u;
+      last = ~0u;
+      rec = T.srec[k];
+      ids = T.sid[k];
+    } else {
+      c0 = Pbeg >> kBlockLog;
+      c1 = Pend >> kBlockLog;
+    }
+    const float* __restrict__ box = T.sbox[k];
+    // 64 blocks are looked at together; of those kept, two at a time are
+    // loaded (both in flight) and staged one after the other: tested against
+    // the tile's box in every dimension, the survivors appended to the ring,
+    // which is flushed whenever it holds 64 and at the end
+    uint32_t cb = c0, done = 0;
+    uint64_t bm = 0;
+    bool second = false;
+    float vA[R], vB[R];
+    uint32_t idA = 0, idB = 0;
+    bool inA = false, inB = false;
+    while (!done) {
+      if (second) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) vA[r] = vB[r] = 0.f;
-        if (inA) {
-          load_rec<D>(rec + (size_t)pA * R, vA);
-          idA = ids[pA];
+        for (int r = 0; r < R; ++r) vA[r] = vB[r];
+        idA = idB;
+        inA = inB;
+        second = false;
+      } else {
+        while (bm == 0 && cb <= c1) {
+          const uint32_t c = cb + lane;
+          bool keep = c <= c1;
+          if (strips) {
+            if (keep) {
+              float b[R];
+#pragma unroll
+              for (int r = 0; r < R; ++r) b[r] = box[(size_t)r * T.nblk + c];
+#pragma unroll
+              for (int s = 0; s < D; ++s)
+                keep = keep & (b[2 * s] <= ehi[s]) & (elo[s] <= b[2 * s + 1]);
+            }
+          } else {
+            keep = keep && bmx[c] >= elo[0];
+          }
+          bm = ballot(keep);
+          cb += kWave;
         }
-        if (inB) {
-          load_rec<D>(rec + (size_t)pB * R, vB);
-          idB = ids[pB];
+        inA = false;
+        if (bm != 0) {
+          const uint32_t b0 = (uint32_t)__builtin_ctzll(bm);
+          bm &= bm - 1;
+          second = bm != 0;
+          const uint32_t b1 = second ? (uint32_t)__builtin_ctzll(bm) : b0;
+          if (second) bm &= bm - 1;
+          const uint32_t blkA = cb - kWave + b0, blkB = cb - kWave + b1;
+          const uint32_t pA = max(blkA << kBlockLog, first) + lane;
+          const uint32_t pB = max(blkB << kBlockLog, first) + lane;
+          inA = pA <= min((blkA << kBlockLog) + (1u << kBlockLog) - 1u, last);
+          inB = second && pB <= min((blkB << kBlockLog) + (1u << kBlockLog) - 1u, last);
+#pragma unroll
+          for (int r = 0; r < R; ++r) vA[r] = vB[r] = 0.f;
+          if (inA) {
+            load_rec<D>(rec + (size_t)pA * R, vA);
+            idA = ids[pA];
+          }
+          if (inB) {
+            load_rec<D>(rec + (size_t)pB * R, vB);
+            idB = ids[pB];
+          }
+        } else {
+          done = 1;
         }
-        stage(vA, idA, inA);
-        stage(vB, idB, inB);
+      }
+      bool cnd = inA;
+#pragma unroll
+      for (int s = 0; s < D; ++s) cnd = cnd & (vA[2 * s] <= ehi[s]) & (elo[s] <= vA[2 * s + 1]);
+      const uint64_t cm = ballot(cnd);
+      if (listing) {
+        if (MODE == kTileList && O.ids) {
+          const uint64_t at = lbase + tail + mask_rank(cm);
+          if (cnd && at < lend) O.ids[at] = idA;
+        }
+        tail += (uint32_t)__popcll(cm);
+        continue;
+      }
+      if constexpr (MODE != kTileList) {
+        if (cnd) {
+          const uint32_t slot = (tail + mask_rank(cm)) & (kRing - 1);
+          store_rec<D>(s_cand + slot * R, vA);
+          s_cid[slot] = idA;
+        }
+        tail += (uint32_t)__popcll(cm);
+        const uint32_t c = tail - head;
+        if (c >= (uint32_t)kWave || (done && c != 0)) flush(min(c, (uint32_t)kWave));
       }
     }
-    if (tail != head) flush(tail - head);
   }
   if (STASH && sok) {
     if (lane == 0) O.sused[sch] = sfill;
     if (sch < slast && lane < slast - sch) O.sused[sch + 1 + lane] = 0;
   }
-  if constexpr (XP) {
-    wave_sync();
-    if (qv) O.cnt[xl.j[lane] + qoff] = xl.cnt[lane];
-  } else if (qv) {
+  if (listing) {
+    if (O.tcand && lane == 0) {
+      O.tcand[tile_id] = tail;
+      atomicAdd((unsigned long long*)(O.tsum + tile_id % kListSlices), (unsigned long long)tail);
+      atomicMax(O.tmax + tile_id % kListSlices, tail);
+    }
+    if (MODE == kTileList) return;
+  }
+  if (qv) {
     if (!FILL) O.cnt[gj] = mycnt;
     else if (O.cnt) O.cnt[gj] = (uint32_t)(mybase - mystart);
   }
+}
+
+// Cells of m updates in d dimensions (d > 1): along each dimension, the class's
+// own first and the others ascending.  All but the last are cut into as many
+// ranges as there are tiles of 64 along a dimension, the last into as many as
+// the rest of the `cells` allow, so that a tile takes a few cells of one line.
+inline void cell_shape(uint32_t m, uint32_t d, uint32_t cells, uint32_t (&b)[DDM_MAX_D]) {
+  uint32_t rest = cells;
+  for (uint32_t s = 0; s < DDM_MAX_D; ++s) b[s] = 1;
+  const double g = std::pow((double)m / 64.0, 1.0 / (double)d);
+  for (uint32_t s = 0; s + 1 < d; ++s) {
+    b[s] = std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(g + 0.5), rest / 2));
+    rest /= b[s];
+  }
+  b[d - 1] = std::max<uint32_t>(1u, rest);
 }
 
 // Quantiles held in LDS are padded by one word after every 64: the lanes of

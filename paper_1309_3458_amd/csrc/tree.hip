@@ -32,6 +32,10 @@ struct ddm_tree {
   uint32_t* sidx_lo[DDM_MAX_D] = {};
   uint32_t* sidx_hi[DDM_MAX_D] = {};
   uint32_t* quant[DDM_MAX_D] = {};
+  float* srec[DDM_MAX_D] = {};  // d > 1: strips (tree_dev.h)
+  uint32_t* sid[DDM_MAX_D] = {};
+  float* sbox[DDM_MAX_D] = {};
+  float* rid = nullptr;  // the set as records by id
   uint32_t ns = 0;              // ceil(n / 64) search samples
   uint32_t C = 0;               // blocks of 64 positions
   float* maxlen = nullptr;      // d floats (device)
@@ -61,7 +65,12 @@ TreeDev tree_dev(const ddm_tree* t) {
     T.sidx_lo[k] = t->sidx_lo[k];
     T.sidx_hi[k] = t->sidx_hi[k];
     T.quant[k] = t->quant[k];
+    T.srec[k] = t->srec[k];
+    T.sid[k] = t->sid[k];
+    T.sbox[k] = t->sbox[k];
   }
+  T.nblk = t->d > 1 ? strip_count(t->n) * kStripBlocks : 0u;
+  T.rid = t->rid;
   T.ns = t->ns;
   T.maxlen = t->maxlen;
   T.n = t->n;
@@ -146,7 +155,13 @@ size_t tree_bytes_estimate(uint32_t n, uint32_t d) {
   const size_t bm_b = al(sizeof(float) * std::max<uint64_t>(1, (P + 1) >> kBlockLog));
   const size_t si_b = al(sizeof(uint32_t) * (size_t)((n + 63) / 64) * d);
   const size_t qu_b = al(sizeof(uint32_t) * kQuant * d);
-  return rec_b * d + mx_b * d + id_b + 2 * key_b + bm_b * d + 2 * si_b + qu_b + 256 + 256 +
+  size_t strip_b = 0;
+  if (d > 1) {
+    const size_t slots = (size_t)strip_count(n) << kStripLog;
+    strip_b = d * (al(sizeof(float) * slots * 2 * d) + al(sizeof(uint32_t) * slots) +
+                   al(sizeof(float) * (slots / 64) * 2 * d));
+  }
+  return strip_b + al(sizeof(float) * (size_t)n * 2 * d) + rec_b * d + mx_b * d + id_b + 2 * key_b + bm_b * d + 2 * si_b + qu_b + 256 + 256 +
          al(sizeof(float) * 4 * DDM_MAX_D) + al(sizeof(uint32_t) * DDM_MAX_D * 2 * (kFeatBins + 1)) +
          al(sizeof(uint32_t) * kSatWords);
 }
@@ -167,6 +182,9 @@ static TreeJobs make_jobs(const ddm_tree* t, const float* lo, const float* hi) {
     j.sidx_lo = t->sidx_lo[k];
     j.sidx_hi = sort_hi ? t->sidx_hi[k] : nullptr;
     j.quant = t->quant[k];
+    j.srec = t->srec[k];
+    j.sid = t->sid[k];
+    j.sbox = t->sbox[k];
     j.maxlen_bits = (uint32_t*)t->maxlen + k;
     j.n = t->n;
     j.d = t->d;
@@ -177,6 +195,20 @@ static TreeJobs make_jobs(const ddm_tree* t, const float* lo, const float* hi) {
     j.ns = t->ns;
   }
   return J;
+}
+
+// the strips' dynamic LDS exceeds the default limit at d = 4
+static ddm_status ensure_tree_attr() {
+  static std::once_flag once;
+  static hipError_t err = hipSuccess;
+  std::call_once(once, [] {
+    for (const void* f : {(const void*)tree_low_kernel, (const void*)tree_refit_kernel})
+      if (err == hipSuccess)
+        err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)strip_lds_bytes(DDM_MAX_D));
+  });
+  if (err != hipSuccess) return hip_fail(err, "hipFuncSetAttribute", __FILE__, __LINE__);
+  return DDM_OK;
 }
 
 // samples/quantiles of the sorted keys, then maxupper and block maxima; the
@@ -191,10 +223,15 @@ static ddm_status enqueue_tree_passes(const ddm_tree* t, const TreeJobs& J, bool
   }
   ProfScope ps("tree_build", s);
   dim3 g((t->P + 1 + kChunk - 1) / kChunk, d);
+  const size_t lds = d > 1 ? strip_lds_bytes(d) : 0;
+  if (lds) {
+    const ddm_status st = ensure_tree_attr();
+    if (st != DDM_OK) return st;
+  }
   if (gather)
-    tree_low_kernel<<<g, kTreeThreads, 0, s>>>(J);
+    tree_low_kernel<<<g, kTreeThreads, lds, s>>>(J);
   else
-    tree_refit_kernel<<<g, kTreeThreads, 0, s>>>(J);
+    tree_refit_kernel<<<g, kTreeThreads, lds, s>>>(J);
   DDM_LAUNCHED("tree_low_kernel");
   for (uint32_t S = kChunkLog; S < t->H; S += kChunkLog) {
     const uint32_t q_end = (t->P >> S) + 1;
@@ -221,13 +258,11 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
   sc.reserve(sizeof(uint32_t) * (size_t)n * d);  // hi keys tmp
   sc.reserve(sizeof(uint32_t) * (size_t)n * d);  // payload tmp
   sc.reserve(sort_bytes);
-  sc.reserve(sizeof(float) * 2 * (size_t)n * d);  // the set as records
   if (!sc.commit()) return DDM_E_NOMEM;
   uint32_t* klo_tmp = sc.take<uint32_t>((size_t)n * d);
   uint32_t* khi_tmp = sc.take<uint32_t>((size_t)n * d);
   uint32_t* val_tmp = sc.take<uint32_t>((size_t)n * d);
   char* sort_scratch = sc.take<char>(sort_bytes);
-  float* recin = sc.take<float>(2 * (size_t)n * d);
   if (!sc.fits()) return scratch_overrun("tree build");
 
   {
@@ -235,7 +270,7 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
     const uint64_t total = (uint64_t)n * d;
     build_keys_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(
         lo, hi, n, d, t->skey_lo[0], sort_hi ? t->skey_hi[0] : nullptr, t->id[0], t->flag,
-        recin);
+        t->rid);
     DDM_LAUNCHED("build_keys_kernel");
   }
   uint32_t na = 0;
@@ -253,7 +288,7 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
   ddm_status st = radix_sort_onesweep(host, narr, 4, sort_scratch, t->flag, s);
   if (st != DDM_OK) return st;
   TreeJobs J = make_jobs(t, lo, hi);
-  for (uint32_t k = 0; k < d; ++k) J.j[k].recin = recin;
+  for (uint32_t k = 0; k < d; ++k) J.j[k].recin = t->rid;
   return enqueue_tree_passes(t, J, true, s);
 }
 
@@ -267,6 +302,7 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
 // ---------------------------------------------------------------------------
 struct TreePtrs {
   float* rec[DDM_MAX_D];
+  float* rid;  // records by id
   const uint32_t* id[DDM_MAX_D];
   uint32_t* pos[DDM_MAX_D];  // position of every subscription in tree k
   uint32_t* key[DDM_MAX_D];  // sorted lower keys with the moves applied
@@ -321,6 +357,8 @@ __global__ void upd_apply_kernel(TreePtrs A, const uint32_t* __restrict__ ids,
   float* r = A.rec[k] + (size_t)A.pos[k][ids[c]] * 2 * D;
   r[0] = lo[(size_t)k * count + c];
   r[1] = hi[(size_t)k * count + c];
+  A.rid[((size_t)ids[c] * D + k) * 2] = r[0];
+  A.rid[((size_t)ids[c] * D + k) * 2 + 1] = r[1];
   uint32_t slot = 1;
   for (uint32_t kk = 0; kk < D; ++kk) {
     if (kk == k) continue;
@@ -389,6 +427,7 @@ static ddm_status tree_update(ddm_tree* t, const uint32_t* ids, const float* nlo
     DDM_HIP(hipMemcpyAsync(A.key[k], t->skey_lo[k], sizeof(uint32_t) * n,
                            hipMemcpyDeviceToDevice, s));
   }
+  A.rid = t->rid;
   A.n = n;
   A.d = d;
   tree_init_kernel<<<1, 64, 0, s>>>(flag, nullptr, 0);
@@ -581,6 +620,19 @@ extern "C" ddm_status ddm_build(const float* sub_lo, const float* sub_hi, uint32
     p += qu_b;
     for (uint32_t k = 0; k < d; ++k) t->quant[k] = qu + (size_t)k * kQuant;
   }
+  if (d > 1) {
+    const size_t slots = (size_t)strip_count(n) << kStripLog;
+    for (uint32_t k = 0; k < d; ++k) {
+      t->srec[k] = (float*)p;
+      p += al(sizeof(float) * slots * 2 * d);
+      t->sid[k] = (uint32_t*)p;
+      p += al(sizeof(uint32_t) * slots);
+      t->sbox[k] = (float*)p;
+      p += al(sizeof(float) * (slots / 64) * 2 * d);
+    }
+  }
+  t->rid = (float*)p;
+  p += al(sizeof(float) * (size_t)n * 2 * d);
   t->maxlen = (float*)p;
   p += 256;
   t->fstat = (float*)p;
