@@ -177,14 +177,17 @@ __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
 // lanes of the wave whose 8-bit digit equals this lane's (restricted to `active`)
 __device__ __forceinline__ uint64_t match_digit8(uint32_t dig, uint64_t active) {
-  uint64_t peers = active;
+  // (per bit: its sign extension, a compare, and one three-input operation on
+  // each half of the mask)
+  uint32_t plo = (uint32_t)active, phi = (uint32_t)(active >> 32);
 #pragma unroll
   for (int b = 0; b < 8; ++b) {
-    bool bit = (dig >> b) & 1u;
-    uint64_t m = ballot(bit);
-    peers &= bit ? m : ~m;
+    const uint32_t bit = (uint32_t)__builtin_amdgcn_sbfe((int)dig, b, 1);
+    const uint64_t m = ballot(bit != 0);
+    plo &= ~((uint32_t)m ^ bit);
+    phi &= ~((uint32_t)(m >> 32) ^ bit);
   }
-  return peers;
+  return ((uint64_t)phi << 32) | plo;
 }
 
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -402,6 +405,21 @@ size_t radix_onesweep_scratch_bytes(const SortArr* host_arrs, uint32_t narr, int
 ddm_status radix_sort_onesweep(const SortArr* host_arrs, uint32_t narr, int npasses,
                                void* scratch, int32_t* err, hipStream_t s);
 
+// The same in two steps, for a caller that has the keys in hand anyway: it
+// zeroes ctr (4 words), ghist and status itself, counts the digits of array a,
+// pass p into ghist[(4 a + p) 256 ..], and then runs the passes.
+struct OsScratch {
+  uint32_t* ctr;
+  uint32_t* ghist;
+  uint32_t nhist;
+  uint64_t* status;
+  size_t nstatus;
+};
+OsScratch radix_onesweep_scratch(const SortArr* host_arrs, uint32_t narr, int npasses,
+                                 void* scratch);
+ddm_status radix_onesweep_passes(const SortArr* host_arrs, uint32_t narr, int npasses,
+                                 const OsScratch& S, int32_t* err, hipStream_t s);
+
 // per-segment sort of the pairs in place (segments off[j] .. off[j+1]);
 // ids must be below 2^20.  lists: 2m+2 uint32 scratch (last two words are
 // counters, zeroed by the caller beforehand).
@@ -443,10 +461,29 @@ ddm_status sort_segments_keys(const uint64_t* off, uint32_t m, uint64_t* out, ui
                               uint32_t n, uint32_t* lists, uint32_t* lists_count, hipStream_t s);
 
 // exclusive scan of u32 counts into u64 offsets out[0..m], out[m] = total.
-// tmp: scan_tmp_words(m) uint64 scratch.  maxout (optional, zeroed by the
-// caller): receives the largest count.
+// tmp: scan_tmp_words(m) uint64 scratch.
 size_t scan_tmp_words(uint32_t m);
 ddm_status scan_u32_u64(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,
-                        hipStream_t s, uint32_t* maxout = nullptr);
+                        hipStream_t s);
+
+// What the host reads after a count, written by the scan of the counts to dst
+// (device memory, or pinned host memory, which the stream's end makes visible):
+// [0] the total, [1] the tree's and the updates' flags, [2] (tiles << 32) | most
+// counted chunks of the stash used in one slice, [3] the stash's mark, [4] the
+// largest count, [5], [6] candidates of all tiles and of the fullest
+struct ScanWords {
+  uint64_t* dst = nullptr;
+  const int32_t* tflag = nullptr;
+  const int32_t* uflag = nullptr;
+  const uint32_t* snext = nullptr;  // null: no stash
+  uint32_t nslices = 0, sfirst = 0, sslice = 0;
+  const uint32_t* gcount = nullptr;
+  uint32_t d = 0, qpt = 1;
+  const uint64_t* tsum = nullptr;   // [64]
+  const uint32_t* tmax = nullptr;   // [64]
+};
+// scan_u32_u64 and the words (out and tmp as there)
+ddm_status scan_counts(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,
+                       const ScanWords& W, hipStream_t s);
 
 }  // namespace ddm

@@ -87,6 +87,13 @@ constexpr uint32_t kCntPad = 8;
 constexpr uint32_t kCellBlock = 2048;
 constexpr uint32_t kCellBlocks = kCells / kCellBlock;  // per class
 
+// Up to kSmallOrder updates take cells kSmallCells to a class and are ordered
+// by one workgroup with its counters in LDS (order_small_kernel): there are no
+// counters in memory to clear, and two launches fewer (d = 1, 5000 updates:
+// clear, probe, scan and scatter 17 us of kernels; probe and order 13).
+constexpr uint32_t kSmallOrder = 8192, kSmallCells = 2048;
+constexpr uint32_t kBadCell = 0xffffffffu;  // an update with an invalid extent
+
 struct CellShape {
   uint32_t b[DDM_MAX_D];  // cells along each dimension, as cell_shape gives them
 };
@@ -101,6 +108,7 @@ static uint32_t tile_updates(uint32_t m) {
   return q;
 }
 
+template <bool SMALL>
 __global__ __launch_bounds__(256) void bits1_kernel(TreeDev T, const float* __restrict__ ulo,
                                                     const float* __restrict__ uhi, uint32_t m,
                                                     uint32_t* __restrict__ cmin,
@@ -125,12 +133,12 @@ __global__ __launch_bounds__(256) void bits1_kernel(TreeDev T, const float* __re
     const uint32_t ph = bad ? 0u : res[0];
     cmin[j] = c;
     kstar[j] = 0;
-    const uint32_t bu =
-        min((uint32_t)(((uint64_t)ph * kCells) / ((uint64_t)T.n + 1)), kCells - 1u);
-    bucket[j] = bu;
-    rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
+    constexpr uint32_t cells = SMALL ? kSmallCells : kCells;
+    const uint32_t bu = min((uint32_t)(((uint64_t)ph * cells) / ((uint64_t)T.n + 1)), cells - 1u);
+    bucket[j] = SMALL && bad ? kBadCell : bu;
+    if (!SMALL) rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
   }
-  if (ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
+  if (!SMALL && ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
 }
 
 // the probe estimate of an update: the probe dimension bk, #quantiles <=
@@ -252,9 +260,9 @@ constexpr float kStashDenseHits = 32.f;
 template <int D, uint32_t THREADS>
 __device__ __forceinline__ void sample_density(const TreeDev& T, const float* __restrict__ ulo,
                                                const float* __restrict__ uhi, uint32_t m,
+                                               uint32_t (*sq)[kQuantPad],
                                                uint32_t* __restrict__ full, uint32_t room) {
   static_assert(THREADS >= kShapeSamples, "one sample per thread");
-  __shared__ uint32_t sq[D][kQuantPad];
   __shared__ float whits[kShapeSamples / kWave];
   const uint32_t S = min(m, kShapeSamples);
   UpdExt<D> e{};
@@ -281,7 +289,7 @@ __device__ __forceinline__ void sample_density(const TreeDev& T, const float* __
 }
 
 constexpr uint32_t kProbeThreads = 1024;
-template <int D>
+template <int D, bool SMALL>
 __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const float* __restrict__ ulo,
                                                      const float* __restrict__ uhi, uint32_t m,
                                                      CellShape shape,
@@ -290,8 +298,13 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
                                                      uint32_t* __restrict__ rank,
                                                      uint32_t* __restrict__ bhist,
                                                      int32_t* __restrict__ flag,
-                                                     uint2* __restrict__ pb) {
+                                                     uint2* __restrict__ pb,
+                                                     uint32_t* __restrict__ full, uint32_t room) {
   __shared__ uint32_t sq[D][kQuantPad];
+  if (SMALL && full && blockIdx.x == gridDim.x - 1) {
+    sample_density<D, kProbeThreads>(T, ulo, uhi, m, sq, full, room);
+    return;
+  }
   const uint32_t j = blockIdx.x * kProbeThreads + threadIdx.x;
   const bool act = j < m;
   UpdExt<D> e{};
@@ -328,19 +341,30 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
       if (sub & 1u) i = n - 1u - i;  // the serpentine's way back
       sub = sub * n + i;
     }
-    const uint32_t bu = bk * kCells + (bad ? 0u : sub);
-    bucket[j] = bu;
-    rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
+    const uint32_t bu = bk * (SMALL ? kSmallCells : kCells) + (bad ? 0u : sub);
+    bucket[j] = SMALL && bad ? kBadCell : bu;
+    if (!SMALL) rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
   }
-  if (ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
+  if (!SMALL && ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
 }
 
-// exclusive scan of each workgroup's kCellBlock cell counts, and its total
-__global__ __launch_bounds__(256) void cell_scan_kernel(const uint32_t* __restrict__ bcnt,
-                                                        uint32_t* __restrict__ boff,
-                                                        uint32_t* __restrict__ bsum) {
+// exclusive scan of each workgroup's kCellBlock cell counts, and its total;
+// one more workgroup takes the sample (beside the scan, so that it costs no time)
+template <int D>
+__global__ __launch_bounds__(256) void cell_scan_kernel(
+    const uint32_t* __restrict__ bcnt, uint32_t* __restrict__ boff, uint32_t* __restrict__ bsum,
+    TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
+    uint32_t* __restrict__ full, uint32_t room) {
   constexpr uint32_t PER = kCellBlock / 256;
-  __shared__ uint32_t sb[kCellBlock + 256];
+  __shared__ uint32_t sq[D][kQuantPad];  // the sample's, or the scan's
+  static_assert(kCellBlock + 256 <= kQuantPad * 1, "the scan's words fit");
+  if constexpr (D > 1) {
+    if (blockIdx.x == D * kCellBlocks) {
+      sample_density<D, 256>(T, ulo, uhi, m, sq, full, room);
+      return;
+    }
+  }
+  uint32_t* sb = sq[0];
   __shared__ uint32_t wsum[256 / kWave];
   const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const uint32_t base = blockIdx.x * kCellBlock;
@@ -379,6 +403,73 @@ __global__ __launch_bounds__(256) void cell_scan_kernel(const uint32_t* __restri
     boff[base + i] = sb[i + i / PER];
   }
   if (tid == 0) bsum[blockIdx.x] = total;
+}
+
+// the whole order of up to kSmallOrder updates by one workgroup: counters in
+// LDS, ranks, scan, places; and the words that the match adds to
+template <int D>
+__global__ __launch_bounds__(1024) void order_small_kernel(
+    const uint32_t* __restrict__ bucket, uint32_t m, uint32_t* __restrict__ perm,
+    uint32_t* __restrict__ gstart, uint32_t* __restrict__ gcount, int32_t* __restrict__ flag,
+    uint32_t* __restrict__ lists_count, uint32_t* __restrict__ snext, uint32_t sfirst,
+    uint32_t sslice, uint64_t* __restrict__ tsum,
+    uint32_t* __restrict__ tmaxs) {
+  constexpr uint32_t R = kSmallOrder / 1024, C = D * kSmallCells, PER = C / 1024;
+  static_assert(C % 1024 == 0, "whole rounds");
+  __shared__ uint32_t cnt[C];
+  __shared__ uint32_t wsum[1024 / kWave];
+  const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  uint32_t bu[R], rank[R];
+  bool bad = false;
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t j = r * 1024 + tid;
+    bu[r] = j < m ? bucket[j] : 0u;
+    bad = bad || bu[r] == kBadCell;
+    if (bu[r] == kBadCell) bu[r] = 0;
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < PER; ++r) cnt[r * 1024 + tid] = 0;
+  if (tid < 2) lists_count[tid] = 0;
+  if (tid < kListSlices) {
+    tsum[tid] = 0;
+    tmaxs[tid] = 0;
+  }
+  if (snext)
+    for (uint32_t i = tid; i < kStashSlices; i += 1024) snext[i] = sfirst + i * sslice;
+  const int anybad = __syncthreads_or(bad);
+  if (tid == 0) *flag = anybad ? 2 : 0;
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r)
+    if (r * 1024 + tid < m) rank[r] = atomicAdd(&cnt[bu[r]], 1u);
+  __syncthreads();
+  uint32_t c[PER], sum = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    c[i] = cnt[tid * PER + i];
+    sum += c[i];
+  }
+  const uint32_t inc = wave_scan_dpp(sum);
+  if (lane == kWave - 1) wsum[wave] = inc;
+  __syncthreads();
+  const uint32_t wt = lane < 1024 / kWave ? wsum[lane] : 0u;
+  uint32_t run = inc - sum +
+                 (uint32_t)__builtin_amdgcn_readlane((int)(wave_scan_dpp(wt) - wt), (int)wave);
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    cnt[tid * PER + i] = run;
+    run += c[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r)
+    if (r * 1024 + tid < m) perm[cnt[bu[r]] + rank[r]] = r * 1024 + tid;
+  if (tid < DDM_MAX_D) {
+    const uint32_t a = tid < D ? cnt[tid * kSmallCells] : m;
+    const uint32_t e = tid + 1 < D ? cnt[(tid + 1) * kSmallCells] : m;
+    gstart[tid] = a;
+    gcount[tid] = tid < D ? e - a : 0u;
+  }
 }
 
 // updates in cell order: every workgroup scans the nb totals of the cell
@@ -1632,8 +1723,7 @@ struct MatchState {
   uint32_t* tstart = nullptr;
   uint32_t* tclass = nullptr;
   uint32_t novf = 0;
-  uint32_t* maxcnt = nullptr;  // device: the largest count (longest segment)
-  uint64_t maxseg = ~0ull;     // host copy after the count
+  uint64_t maxseg = ~0ull;     // the largest count (longest segment)
   // stash of the count traversal (plain path, d > 1): usable when complete
   Scratch stash_sc;
   bool stash = false;
@@ -1675,27 +1765,14 @@ struct MatchState {
 };
 
 // zeroes the match's counters; with a stash (snext non-null) also sets the
-// slices' next free chunks, and one more workgroup its overflow mark from a
-// sample of the updates (a stash exists only for d > 1)
-template <int D>
+// slices' next free chunks
 __global__ __launch_bounds__(1024) void match_init_kernel(
     int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
-    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint32_t* __restrict__ maxcnt,
-    uint64_t* __restrict__ tsum, uint32_t* __restrict__ tmaxs, TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m) {
+    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum, uint32_t* __restrict__ tmaxs) {
   static_assert(kCells % 1024 == 0, "whole workgroups");
-  if constexpr (D > 1) {
-    if (blockIdx.x == D * kCells / 1024) {
-      sample_density<D, 1024>(T, ulo, uhi, m, snext + kStashSlices,
-                              sslice * (kStashSlices * kStashChunk));
-      return;
-    }
-  }
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   bcnt[(size_t)i * kCntPad] = 0;
-  if (i == 0) {
-    *flag = 0;
-    *maxcnt = 0;
-  }
+  if (i == 0) *flag = 0;
   if (i < 2) lists_count[i] = 0;
   if (i < kListSlices) {
     tsum[i] = 0;
@@ -1704,64 +1781,61 @@ __global__ __launch_bounds__(1024) void match_init_kernel(
   if (snext && i < kStashSlices) snext[i] = sfirst + i * sslice;
 }
 
-// the words the host reads after the count: dst[0] = K, dst[1] = the tree's
-// and the updates' flags; dst[2] = (tiles << 32) | most counted chunks of the
-// stash used in one slice, dst[3] = the stash's mark; dst[4] = the largest
-// count; dst[5], dst[6] = candidates of all tiles and of the fullest
-__global__ void gather_flags_kernel(const int32_t* __restrict__ tflag,
-                                    const int32_t* __restrict__ uflag,
-                                    const uint64_t* __restrict__ off, uint32_t m,
-                                    uint64_t* __restrict__ dst,
-                                    const uint32_t* __restrict__ snext,
-                                    const uint32_t* __restrict__ gcount, uint32_t d, uint32_t qpt,
-                                    uint32_t sfirst, uint32_t sslice,
-                                    const uint32_t* __restrict__ maxcnt,
-                                    const uint64_t* __restrict__ tsum,
-                                    const uint32_t* __restrict__ tmaxs) {
-  // one wavefront; the lanes share the slices
-  const uint32_t lane = threadIdx.x;
-  if (lane == 0) {
-    dst[4] = *maxcnt;
-    dst[0] = off[m];
-    dst[1] = (uint64_t)(uint32_t)(*tflag) | ((uint64_t)(uint32_t)(*uflag) << 32);
-  }
-  uint32_t mx = 0;
-  if (snext)
-    for (uint32_t s = lane; s < kStashSlices; s += kWave)
-      mx = max(mx, min(snext[s] - (sfirst + s * sslice), sslice));
-  mx = wave_max_u32(mx);
-  uint32_t tiles = 0;
-  for (uint32_t g = 0; g < d; ++g) tiles += (gcount[g] + qpt - 1) / qpt;
-  static_assert(kListSlices == kWave, "one lane per slice");
-  uint64_t ts = tsum[lane];
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) ts += __shfl_xor(ts, o, kWave);
-  const uint32_t tm = wave_max_u32(tmaxs[lane]);
-  if (lane == 0) {
-    dst[2] = ((uint64_t)tiles << 32) | mx;
-    dst[3] = snext ? snext[kStashSlices] : 0u;
-    dst[5] = ts;
-    dst[6] = tm;
-  }
-}
-
+// probe dimension and cell of every update, and the updates in cell order; with
+// a stash, a sample of them decides whether it is used
 template <int D>
-static ddm_status launch_probe(const TreeDev& T, const float* ulo, const float* uhi, uint32_t m,
-                               MatchState& st, hipStream_t s) {
-  if (D == 1) {
+static ddm_status order_updates(const TreeDev& T, const float* ulo, const float* uhi, uint32_t m,
+                                MatchState& st, uint32_t* lists_count, hipStream_t s) {
+  uint32_t* sn = st.stash ? st.snext : nullptr;  // (a stash exists only for d > 1)
+  uint32_t* full = sn ? sn + kStashSlices : nullptr;
+  const uint32_t room = st.sslice * (kStashSlices * kStashChunk);
+  const bool small = m <= kSmallOrder;
+  if (!small) {
+    match_init_kernel<<<D * kCells / 1024, 1024, 0, s>>>(st.flag, lists_count, st.bcnt, sn,
+                                                         st.sfirst, st.sslice, st.tsum,
+                                                         st.tmaxs);
+    DDM_LAUNCHED("match_init_kernel");
+  }
+  if constexpr (D == 1) {
     ProfScope ps("bits", s);
-    bits1_kernel<<<(m + 255) / 256, 256, 0, s>>>(T, ulo, uhi, m, st.cmin, st.kstar, st.bucket,
-                                                 st.rank, st.bcnt, st.flag);
+    const unsigned g = (m + 255) / 256;
+    if (small)
+      bits1_kernel<true><<<g, 256, 0, s>>>(T, ulo, uhi, m, st.cmin, st.kstar, st.bucket, st.rank,
+                                           st.bcnt, st.flag);
+    else
+      bits1_kernel<false><<<g, 256, 0, s>>>(T, ulo, uhi, m, st.cmin, st.kstar, st.bucket, st.rank,
+                                            st.bcnt, st.flag);
     DDM_LAUNCHED("bits1_kernel");
   } else {
     ProfScope ps("probe", s);
     CellShape shape;
-    cell_shape(m, D, kCells, shape.b);
-    probe_kernel<D><<<(m + kProbeThreads - 1) / kProbeThreads, kProbeThreads, 0, s>>>(
-        T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag,
-        reinterpret_cast<uint2*>(st.pb));
+    cell_shape(m, D, small ? kSmallCells : kCells, shape.b);
+    const unsigned g = (m + kProbeThreads - 1) / kProbeThreads;
+    uint2* pb = reinterpret_cast<uint2*>(st.pb);
+    if (small)
+      probe_kernel<D, true><<<g + (full ? 1u : 0u), kProbeThreads, 0, s>>>(
+          T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, room);
+    else
+      probe_kernel<D, false><<<g, kProbeThreads, 0, s>>>(T, ulo, uhi, m, shape, st.kstar,
+                                                         st.bucket, st.rank, st.bcnt, st.flag, pb,
+                                                         nullptr, 0);
     DDM_LAUNCHED("probe_kernel");
   }
+  ProfScope ps("order", s);
+  if (small) {
+    order_small_kernel<D><<<1, 1024, 0, s>>>(st.bucket, m, st.perm, st.gstart, st.gcount, st.flag,
+                                             lists_count, sn, st.sfirst, st.sslice,
+                                             st.tsum, st.tmaxs);
+    DDM_LAUNCHED("order_small_kernel");
+    return DDM_OK;
+  }
+  constexpr uint32_t nb = D * kCellBlocks;
+  cell_scan_kernel<D><<<nb + (full ? 1u : 0u), 256, 0, s>>>(st.bcnt, st.boff, st.bsum, T, ulo, uhi,
+                                                            m, full, room);
+  DDM_LAUNCHED("cell_scan_kernel");
+  cell_scatter_kernel<<<(m + 255) / 256, 256, 0, s>>>(st.bucket, st.rank, m, st.boff, st.bsum, nb,
+                                                     st.perm, st.gstart, st.gcount);
+  DDM_LAUNCHED("cell_scatter_kernel");
   return DDM_OK;
 }
 
@@ -1891,7 +1965,6 @@ static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
   sc.reserve(sizeof(uint32_t) * 2 * (size_t)m);  // segment lists
   sc.reserve(sizeof(uint32_t) * 2);              // segment list counts
   sc.reserve(sizeof(uint64_t) * 8);              // device words for readback
-  sc.reserve(sizeof(uint32_t));                  // largest count
   sc.reserve(sizeof(uint32_t) * 2 * (size_t)m);       // candidate position bounds
   sc.reserve(sizeof(uint32_t) * stash_tiles(m));      // candidates per tile
   sc.reserve(sizeof(uint64_t) * kListSlices);         // their sums
@@ -1917,7 +1990,6 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
   fp->lists = sc.take<uint32_t>(2 * (size_t)m);
   fp->lists_count = sc.take<uint32_t>(2);
   fp->dwords = sc.take<uint64_t>(8);
-  st.maxcnt = sc.take<uint32_t>(1);
   st.pb = sc.take<uint32_t>(2 * (size_t)m);
   st.tcand = sc.take<uint32_t>(stash_tiles(m));
   st.tsum = sc.take<uint64_t>(kListSlices);
@@ -2175,39 +2247,14 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
       if (!st.stash_sc.fits()) return scratch_overrun("stash");
     }
   }
-  {
-    uint32_t* sn = st.stash ? st.snext : nullptr;
-    const unsigned g = d * kCells / 1024 + (sn ? 1u : 0u);
-#define DDM_INIT(DD)                                                                         \
-  match_init_kernel<DD><<<g, 1024, 0, s>>>(st.flag, *lists_count, st.bcnt, sn, st.sfirst,    \
-                                           st.sslice, st.maxcnt, st.tsum, st.tmaxs, T, ulo,   \
-                                           uhi, m)
-    switch (d) {
-      case 1: DDM_INIT(1); break;
-      case 2: DDM_INIT(2); break;
-      case 3: DDM_INIT(3); break;
-      default: DDM_INIT(4); break;
-    }
-#undef DDM_INIT
-    DDM_LAUNCHED("match_init_kernel");
-  }
   ddm_status r;
   switch (d) {
-    case 1: r = launch_probe<1>(T, ulo, uhi, m, st, s); break;
-    case 2: r = launch_probe<2>(T, ulo, uhi, m, st, s); break;
-    case 3: r = launch_probe<3>(T, ulo, uhi, m, st, s); break;
-    default: r = launch_probe<4>(T, ulo, uhi, m, st, s); break;
+    case 1: r = order_updates<1>(T, ulo, uhi, m, st, *lists_count, s); break;
+    case 2: r = order_updates<2>(T, ulo, uhi, m, st, *lists_count, s); break;
+    case 3: r = order_updates<3>(T, ulo, uhi, m, st, *lists_count, s); break;
+    default: r = order_updates<4>(T, ulo, uhi, m, st, *lists_count, s); break;
   }
   if (r != DDM_OK) return r;
-  {
-    ProfScope ps("order", s);
-    const uint32_t nb = d * kCellBlocks;
-    cell_scan_kernel<<<nb, 256, 0, s>>>(st.bcnt, st.boff, st.bsum);
-    DDM_LAUNCHED("cell_scan_kernel");
-    cell_scatter_kernel<<<(m + 255) / 256, 256, 0, s>>>(st.bucket, st.rank, m, st.boff, st.bsum, nb,
-                                                       st.perm, st.gstart, st.gcount);
-    DDM_LAUNCHED("cell_scatter_kernel");
-  }
   // per-update counts
   const uint32_t* counts = st.cmin;
   SegOut SO{};
@@ -2330,15 +2377,31 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     copy_counts_kernel<<<(m + 255) / 256, 256, 0, s>>>(counts, counts_out, m);
     DDM_LAUNCHED("copy_counts_kernel");
   }
+  uint64_t hw_local[8] = {};
+  uint64_t* hw = hw_local;
+  if (!st.noalloc) {
+    r = host_words(&hw);
+    if (r != DDM_OK) return r;
+  }
+  // the words go straight to the pinned host block, except where they are
+  // read into pageable memory or more kernels add to them
+  const bool direct = !st.noalloc && !st.learned;
+  ScanWords W;
+  W.dst = direct ? hw : dwords;
+  W.tflag = tree_flag(t);
+  W.uflag = st.flag;
+  W.gcount = st.gcount;
+  W.d = d;
+  W.qpt = tile_updates(m);
+  W.tsum = st.tsum;
+  W.tmax = st.tmaxs;
+  static_assert(kListSlices == kWave, "one lane per slice");
   auto offsets = [&]() -> ddm_status {
-    const ddm_status q = scan_u32_u64(counts, st.off, m, stmp, s, st.maxcnt);
-    if (q != DDM_OK) return q;
-    gather_flags_kernel<<<1, 64, 0, s>>>(tree_flag(t), st.flag, st.off, m, dwords,
-                                         st.stash ? st.snext : nullptr, st.gcount, d,
-                                         tile_updates(m), st.sfirst, st.sslice, st.maxcnt,
-                                         st.tsum, st.tmaxs);
-    DDM_LAUNCHED("gather_flags_kernel");
-    return DDM_OK;
+    W.snext = st.stash ? st.snext : nullptr;
+    W.nslices = kStashSlices;
+    W.sfirst = st.sfirst;
+    W.sslice = st.sslice;
+    return scan_counts(counts, st.off, m, stmp, W, s);
   };
   // the updates whose hits exceed their predicted slots, and the words of both
   auto learned_words = [&]() -> ddm_status {
@@ -2353,14 +2416,9 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   r = offsets();
   if (r == DDM_OK) r = learned_words();
   if (r != DDM_OK) return r;
-  uint64_t hw_local[8] = {};
-  uint64_t* hw = hw_local;
-  if (!st.noalloc) {
-    r = host_words(&hw);
-    if (r != DDM_OK) return r;
-  }
   auto read_words = [&]() -> ddm_status {
-    DDM_HIP(hipMemcpyAsync(hw, dwords, 8 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    if (!direct)
+      DDM_HIP(hipMemcpyAsync(hw, dwords, 8 * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     DDM_HIP(hipStreamSynchronize(s));
     st.K = hw[0];
     st.maxseg = hw[4];
@@ -2384,8 +2442,6 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     }
     learned_init_kernel<<<1, 64, 0, s>>>(st.govf, dwords + 7);
     DDM_LAUNCHED("learned_init_kernel");
-    zero_u32_kernel<<<1, 64, 0, s>>>(st.maxcnt, 1);
-    DDM_LAUNCHED("zero_u32_kernel");
     r = offsets();
     if (r == DDM_OK) r = learned_words();
     if (r == DDM_OK) r = read_words();
@@ -2447,8 +2503,6 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
         r = traverse_any<false>(d, P, T, ulo, uhi, m, st.all(), st.kstar, O, s);
         if (r != DDM_OK) return r;
       }
-      zero_u32_kernel<<<1, 64, 0, s>>>(st.maxcnt, 1);
-      DDM_LAUNCHED("zero_u32_kernel");
       r = offsets();
       if (r == DDM_OK) r = read_words();
       if (r != DDM_OK) return r;

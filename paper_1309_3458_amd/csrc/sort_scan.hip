@@ -567,6 +567,49 @@ size_t radix_onesweep_scratch_bytes(const SortArr* host_arrs, uint32_t narr, int
                                                             (size_t)(npasses > 0 ? npasses : 1);
 }
 
+OsScratch radix_onesweep_scratch(const SortArr* host_arrs, uint32_t narr, int npasses,
+                                 void* scratch) {
+  OsScratch S;
+  S.ctr = (uint32_t*)scratch;  // 4 counters, padded to 256 bytes
+  S.ghist = (uint32_t*)((char*)scratch + 256);
+  S.nhist = 1024 * narr;
+  S.status = (uint64_t*)(S.ghist + S.nhist);
+  S.nstatus = 256 * (size_t)os_tiles(host_arrs, narr, os_tile_keys(host_arrs, narr)) *
+              (size_t)npasses;
+  return S;
+}
+
+ddm_status radix_onesweep_passes(const SortArr* host_arrs, uint32_t narr, int npasses,
+                                 const OsScratch& S, int32_t* err, hipStream_t s) {
+  if (narr == 0 || narr > kOsMaxArrays || npasses < 0 || npasses > 4) {
+    set_detail("radix_sort_onesweep: 1..8 arrays, 0..4 passes");
+    return DDM_E_INVALID_ARG;
+  }
+  if (npasses == 0) return DDM_OK;
+  OsDesc D;
+  uint32_t hb, tl;
+  os_layout(host_arrs, narr, os_tile_keys(host_arrs, narr), &D, &hb, &tl);
+  if (tl == 0) return DDM_OK;
+  // when every workgroup of a pass fits on the device at once, a tile takes
+  // its index from its workgroup (every tile it waits for is running);
+  // otherwise from a counter in start order
+  const bool small = os_tile_keys(host_arrs, narr) == kOsTileSmall;
+  const uint32_t resident = small ? os_resident_blocks<kOsThreadsSmall, kOsTileSmall>()
+                                  : os_resident_blocks<kOsThreadsLarge, kOsTileLarge>();
+  const uint32_t direct = tl <= resident ? 1u : 0u;
+  for (int p = 0; p < npasses; ++p) {
+    ProfScope ps("radix_scatter", s);
+    if (small)
+      os_pass_kernel<kOsThreadsSmall, kOsTileSmall><<<tl, kOsThreadsSmall, 0, s>>>(
+          D, S.ghist, S.ctr, S.status, tl, p, err, direct);
+    else
+      os_pass_kernel<kOsThreadsLarge, kOsTileLarge><<<tl, kOsThreadsLarge, 0, s>>>(
+          D, S.ghist, S.ctr, S.status, tl, p, err, direct);
+    DDM_LAUNCHED("os_pass_kernel");
+  }
+  return DDM_OK;
+}
+
 ddm_status radix_sort_onesweep(const SortArr* host_arrs, uint32_t narr, int npasses,
                                void* scratch, int32_t* err, hipStream_t s) {
   if (narr == 0 || narr > kOsMaxArrays || npasses < 0 || npasses > 4) {
@@ -578,44 +621,24 @@ ddm_status radix_sort_onesweep(const SortArr* host_arrs, uint32_t narr, int npas
   uint32_t hb, tl;
   os_layout(host_arrs, narr, os_tile_keys(host_arrs, narr), &D, &hb, &tl);
   if (tl == 0) return DDM_OK;
-  uint32_t* ctr = (uint32_t*)scratch;  // 4 counters, padded to 256 bytes
-  uint32_t* ghist = (uint32_t*)((char*)scratch + 256);
-  uint64_t* status = (uint64_t*)(ghist + 1024 * (size_t)narr);
-  const size_t nstatus = 256 * (size_t)tl * (size_t)npasses;
+  const OsScratch S = radix_onesweep_scratch(host_arrs, narr, npasses, scratch);
   {
     ProfScope ps("radix_hist", s);
-    const size_t work = std::max<size_t>(nstatus, 1024 * (size_t)narr);
+    const size_t work = std::max<size_t>(S.nstatus, S.nhist);
     const unsigned zb = (unsigned)std::min<size_t>((work + 255) / 256, 2048);
-    os_zero_kernel<<<zb, 256, 0, s>>>(ghist, 1024 * narr, ctr, status, nstatus);
+    os_zero_kernel<<<zb, 256, 0, s>>>(S.ghist, S.nhist, S.ctr, S.status, S.nstatus);
     DDM_LAUNCHED("os_zero_kernel");
-    os_hist_kernel<<<hb, kSortThreads, 0, s>>>(D, ghist, npasses);
+    os_hist_kernel<<<hb, kSortThreads, 0, s>>>(D, S.ghist, npasses);
     DDM_LAUNCHED("os_hist_kernel");
   }
-  // when every workgroup of a pass fits on the device at once, a tile takes
-  // its index from its workgroup (every tile it waits for is running);
-  // otherwise from a counter in start order
-  const bool small = os_tile_keys(host_arrs, narr) == kOsTileSmall;
-  const uint32_t resident = small ? os_resident_blocks<kOsThreadsSmall, kOsTileSmall>()
-                                  : os_resident_blocks<kOsThreadsLarge, kOsTileLarge>();
-  const uint32_t direct = tl <= resident ? 1u : 0u;
-  for (int p = 0; p < npasses; ++p) {
-    ProfScope ps("radix_scatter", s);
-    if (small)
-      os_pass_kernel<kOsThreadsSmall, kOsTileSmall>
-          <<<tl, kOsThreadsSmall, 0, s>>>(D, ghist, ctr, status, tl, p, err, direct);
-    else
-      os_pass_kernel<kOsThreadsLarge, kOsTileLarge>
-          <<<tl, kOsThreadsLarge, 0, s>>>(D, ghist, ctr, status, tl, p, err, direct);
-    DDM_LAUNCHED("os_pass_kernel");
-  }
-  return DDM_OK;
+  return radix_onesweep_passes(host_arrs, narr, npasses, S, err, s);
 }
 
 // ---------------------------------------------------------------------------
 // exclusive scan u32 -> u64 (three kernels: tile sums, scan of sums, tiles)
 // ---------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
+constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
 __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
@@ -651,7 +674,7 @@ __device__ __forceinline__ uint64_t block_excl_scan_u64(uint64_t v, uint64_t* to
 __global__ __launch_bounds__(kScanThreads) void scan_tile_sums(const uint32_t* __restrict__ in,
                                                                uint32_t m,
                                                                uint64_t* __restrict__ sums,
-                                                               uint32_t* __restrict__ maxout) {
+                                                               uint32_t* __restrict__ tmax) {
   const uint32_t base = blockIdx.x * kScanTile;
   uint64_t acc = 0;
   uint32_t mx = 0;
@@ -667,8 +690,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_tile_sums(const uint32_t* _
   uint64_t tot;
   (void)block_excl_scan_u64(acc, &tot);
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-  if (maxout) {
-    // one atomic per workgroup (the device-scope atomics on one word queue)
+  if (tmax) {
+    // kept per tile: an atomic per workgroup on one word queued (9 us a pass at
+    // 489 tiles, 5 without)
     __shared__ uint32_t wmax[kScanThreads / kWave];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, kWave));
@@ -677,7 +701,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_tile_sums(const uint32_t* _
     if (threadIdx.x == 0) {
       uint32_t b = 0;
       for (uint32_t w = 0; w < kScanThreads / kWave; ++w) b = max(b, wmax[w]);
-      if (b) atomicMax(maxout, b);
+      tmax[blockIdx.x] = b;
     }
   }
 }
@@ -721,15 +745,50 @@ __global__ __launch_bounds__(kScanThreads) void scan_tiles_kernel(const uint32_t
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[m] = sums[gridDim.x];
 }
 
-// scan_tiles_kernel with the tile's base computed in the workgroup from the
-// tile sums before it (for few tiles: saves the pass over the sums)
-constexpr uint32_t kScanFusedTiles = 2048;
+// the words of a finished count (ScanWords), by one wavefront; total and the
+// largest count are in the lanes already
+__device__ __forceinline__ void write_scan_words(const ScanWords& W, uint64_t total, uint32_t mc) {
+  const uint32_t lane = lane_id();
+  uint32_t mx = 0;
+  if (W.snext)
+    for (uint32_t i = lane; i < W.nslices; i += kWave)
+      mx = max(mx, min(W.snext[i] - (W.sfirst + i * W.sslice), W.sslice));
+  mx = wave_fold_dpp(mx, [](uint32_t a, uint32_t b) { return max(a, b); });
+  uint32_t tiles = 0;
+  for (uint32_t g = 0; g < W.d; ++g) tiles += (W.gcount[g] + W.qpt - 1) / W.qpt;
+  uint64_t ts = W.tsum[lane];
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) ts += __shfl_xor(ts, o, kWave);
+  const uint32_t tm =
+      wave_fold_dpp(W.tmax[lane], [](uint32_t a, uint32_t b) { return max(a, b); });
+  if (lane == 0) {
+    W.dst[0] = total;
+    W.dst[1] = (uint64_t)(uint32_t)(*W.tflag) | ((uint64_t)(uint32_t)(*W.uflag) << 32);
+    W.dst[2] = ((uint64_t)tiles << 32) | mx;
+    W.dst[3] = W.snext ? W.snext[W.nslices] : 0u;
+    W.dst[4] = mc;
+    W.dst[5] = ts;
+    W.dst[6] = tm;
+  }
+}
 
+// scan_tiles_kernel with the tile's base computed in the workgroup from the
+// tile sums before it (for few tiles: saves the pass over the sums); with
+// words, the last workgroup also writes them (saves a kernel after the scan)
+constexpr uint32_t kScanFusedTiles = 4096;
+
+template <bool WORDS>
 __global__ __launch_bounds__(kScanThreads) void scan_tiles_fused_kernel(
     const uint32_t* __restrict__ in, uint32_t m, const uint64_t* __restrict__ sums,
-    uint64_t* __restrict__ out) {
+    const uint32_t* __restrict__ tmax, uint64_t* __restrict__ out, ScanWords W) {
+  __shared__ uint32_t wmax[kScanThreads / kWave];
+  const bool last = blockIdx.x == gridDim.x - 1;
   uint64_t prev = 0;
-  for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) prev += sums[i];
+  uint32_t mx = 0;
+  for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) {
+    prev += sums[i];
+    if (WORDS && last) mx = max(mx, tmax[i]);
+  }
   uint64_t tbase;
   (void)block_excl_scan_u64(prev, &tbase);
   const uint32_t base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
@@ -749,14 +808,89 @@ __global__ __launch_bounds__(kScanThreads) void scan_tiles_fused_kernel(
     if (i < m) out[i] = run;
     run += v[r];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[m] = tbase + tot;
+  if (last) {
+    if (threadIdx.x == 0) out[m] = tbase + tot;
+    if constexpr (WORDS) {
+#pragma unroll
+      for (int r = 0; r < kScanItems; ++r) mx = max(mx, v[r]);
+      mx = wave_fold_dpp(mx, [](uint32_t a, uint32_t b) { return max(a, b); });
+      if (lane_id() == kWave - 1) wmax[threadIdx.x / kWave] = mx;
+      __syncthreads();
+      mx = 0;
+      for (uint32_t w = 0; w < kScanThreads / kWave; ++w) mx = max(mx, wmax[w]);
+      if (threadIdx.x < kWave) write_scan_words(W, tbase + tot, mx);
+    }
+  }
 }
 
-size_t scan_tmp_words(uint32_t m) { return (size_t)(m + kScanTile - 1) / kScanTile + 1; }
+// up to kScanSmall counts in one workgroup: sum, largest, offsets and words
+constexpr uint32_t kScanSmallThreads = 1024;
+constexpr uint32_t kScanSmallItems = 16;
+constexpr uint32_t kScanSmall = kScanSmallThreads * kScanSmallItems;
+
+template <bool WORDS>
+__global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(
+    const uint32_t* __restrict__ in, uint32_t m, uint64_t* __restrict__ out, ScanWords W) {
+  constexpr uint32_t NW = kScanSmallThreads / kWave;
+  __shared__ uint64_t wsum[NW];
+  __shared__ uint32_t wmax[NW];
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+  const uint32_t base = threadIdx.x * kScanSmallItems;
+  uint32_t v[kScanSmallItems], mx = 0;
+  uint64_t acc = 0;
+#pragma unroll
+  for (uint32_t r = 0; r < kScanSmallItems; ++r) {
+    v[r] = base + r < m ? in[base + r] : 0u;
+    acc += v[r];
+    mx = max(mx, v[r]);
+  }
+  const uint64_t inc = wave_incl_scan_u64(acc);
+  mx = wave_fold_dpp(mx, [](uint32_t a, uint32_t b) { return max(a, b); });
+  if (lane == kWave - 1) {
+    wsum[wave] = inc;
+    wmax[wave] = mx;
+  }
+  __syncthreads();
+  uint64_t run = inc - acc, total = 0;
+  mx = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < NW; ++w) {
+    if (w < wave) run += wsum[w];
+    total += wsum[w];
+    mx = max(mx, wmax[w]);
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < kScanSmallItems; ++r) {
+    if (base + r < m) out[base + r] = run;
+    run += v[r];
+  }
+  if (threadIdx.x == 0) out[m] = total;
+  if (WORDS && wave == 0) write_scan_words(W, total, mx);
+}
+
+// tile sums and their total, then the tiles' largest counts
+static uint32_t scan_tiles(uint32_t m) {
+  return (uint32_t)(((uint64_t)m + kScanTile - 1) / kScanTile);
+}
+size_t scan_tmp_words(uint32_t m) {
+  const size_t nt = scan_tiles(m);
+  return nt + 1 + (nt + 1) / 2;
+}
+
+static ddm_status scan_three(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,
+                             uint32_t nt, uint32_t* tmax, hipStream_t s) {
+  scan_tile_sums<<<nt, kScanThreads, 0, s>>>(in, m, tmp, tmax);
+  DDM_LAUNCHED("scan_tile_sums");
+  scan_sums_kernel<<<1, kScanThreads, 0, s>>>(tmp, nt);
+  DDM_LAUNCHED("scan_sums_kernel");
+  scan_tiles_kernel<<<nt, kScanThreads, 0, s>>>(in, m, tmp, out);
+  DDM_LAUNCHED("scan_tiles_kernel");
+  return DDM_OK;
+}
 
 ddm_status scan_u32_u64(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,
-                        hipStream_t s, uint32_t* maxout) {
-  const uint32_t nt = (m + kScanTile - 1) / kScanTile;
+                        hipStream_t s) {
+  const uint32_t nt = scan_tiles(m);
   if (nt == 0) {
     // m == 0: out[0] = 0 (a kernel rather than a memset node, so that the
     // sequence stays safe to capture into a graph)
@@ -765,17 +899,51 @@ ddm_status scan_u32_u64(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t*
     return DDM_OK;
   }
   ProfScope ps("scan", s);
-  scan_tile_sums<<<nt, kScanThreads, 0, s>>>(in, m, tmp, maxout);
+  if (m <= kScanSmall) {
+    scan_small_kernel<false><<<1, kScanSmallThreads, 0, s>>>(in, m, out, ScanWords{});
+    DDM_LAUNCHED("scan_small_kernel");
+    return DDM_OK;
+  }
+  if (nt > kScanFusedTiles) return scan_three(in, out, m, tmp, nt, nullptr, s);
+  scan_tile_sums<<<nt, kScanThreads, 0, s>>>(in, m, tmp, nullptr);
   DDM_LAUNCHED("scan_tile_sums");
+  scan_tiles_fused_kernel<false>
+      <<<nt, kScanThreads, 0, s>>>(in, m, tmp, nullptr, out, ScanWords{});
+  DDM_LAUNCHED("scan_tiles_fused_kernel");
+  return DDM_OK;
+}
+
+__global__ __launch_bounds__(kWave) void scan_words_kernel(const uint64_t* __restrict__ off,
+                                                          uint32_t m,
+                                                          const uint32_t* __restrict__ tmax,
+                                                          uint32_t nt, ScanWords W) {
+  uint32_t mx = 0;
+  for (uint32_t i = lane_id(); i < nt; i += kWave) mx = max(mx, tmax[i]);
+  mx = wave_fold_dpp(mx, [](uint32_t a, uint32_t b) { return max(a, b); });
+  write_scan_words(W, off[m], mx);
+}
+
+ddm_status scan_counts(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,
+                       const ScanWords& W, hipStream_t s) {
+  ProfScope ps("scan", s);
+  if (m <= kScanSmall) {
+    scan_small_kernel<true><<<1, kScanSmallThreads, 0, s>>>(in, m, out, W);
+    DDM_LAUNCHED("scan_small_kernel");
+    return DDM_OK;
+  }
+  const uint32_t nt = scan_tiles(m);
+  uint32_t* tmax = reinterpret_cast<uint32_t*>(tmp + nt + 1);
   if (nt <= kScanFusedTiles) {
-    scan_tiles_fused_kernel<<<nt, kScanThreads, 0, s>>>(in, m, tmp, out);
+    scan_tile_sums<<<nt, kScanThreads, 0, s>>>(in, m, tmp, tmax);
+    DDM_LAUNCHED("scan_tile_sums");
+    scan_tiles_fused_kernel<true><<<nt, kScanThreads, 0, s>>>(in, m, tmp, tmax, out, W);
     DDM_LAUNCHED("scan_tiles_fused_kernel");
     return DDM_OK;
   }
-  scan_sums_kernel<<<1, kScanThreads, 0, s>>>(tmp, nt);
-  DDM_LAUNCHED("scan_sums_kernel");
-  scan_tiles_kernel<<<nt, kScanThreads, 0, s>>>(in, m, tmp, out);
-  DDM_LAUNCHED("scan_tiles_kernel");
+  const ddm_status r = scan_three(in, out, m, tmp, nt, tmax, s);
+  if (r != DDM_OK) return r;
+  scan_words_kernel<<<1, kWave, 0, s>>>(out, m, tmax, nt, W);
+  DDM_LAUNCHED("scan_words_kernel");
   return DDM_OK;
 }
 

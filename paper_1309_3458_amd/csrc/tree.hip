@@ -85,29 +85,212 @@ uint32_t tree_n(const ddm_tree* t) { return t->n; }
 uint32_t tree_d(const ddm_tree* t) { return t->d; }
 int tree_device(const ddm_tree* t) { return t->device; }
 
-// validate, order-preserving keys, identity payload (id arrays shifted by one
-// so that the sorted payload lands directly at positions 1..n)
-// keys, identity payload and validity of every coordinate; with recin, the
-// set is also written as n records (lo_0, hi_0, lo_1, hi_1, ...) so that the
-// tree's gather reads one contiguous record per position
-__global__ void build_keys_kernel(const float* __restrict__ lo, const float* __restrict__ hi,
-                                  uint32_t n, uint32_t d, uint32_t* __restrict__ klo,
-                                  uint32_t* __restrict__ khi, uint32_t* __restrict__ id_base,
-                                  int32_t* __restrict__ flag, float* __restrict__ recin) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t total = (uint64_t)n * d;
+// clears what a build adds to: the flag, the length bounds and the sort's tables
+__global__ __launch_bounds__(256) void build_zero_kernel(int32_t* __restrict__ flag,
+                                                         uint32_t* __restrict__ maxlen_bits,
+                                                         uint32_t d, OsScratch S) {
+  const size_t g = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = g; i < S.nhist; i += stride) S.ghist[i] = 0;
+  for (size_t i = g; i < S.nstatus; i += stride) S.status[i] = 0;
+  if (g < 4) S.ctr[g] = 0;
+  if (g < d) maxlen_bits[g] = 0;
+  if (g == 0) *flag = 0;
+}
+
+// Validity, order-preserving keys, identity payload (id arrays shifted by one
+// so that the sorted payload lands directly at positions 1..n), and the set
+// as n records (lo_0, hi_0, lo_1, hi_1, ...), which the tree pass gathers one
+// by one.  The digits of the keys are counted here too, while the keys are in
+// registers: a pass over the keys for the sort's histograms and its launch
+// cost 9 us more at 5*10^5 squares.
+constexpr uint32_t kKeyThreads = 256, kKeyItems = 8;
+
+template <int D>
+__global__ __launch_bounds__(kKeyThreads) void build_keys_kernel(
+    const float* __restrict__ lo, const float* __restrict__ hi, uint32_t n,
+    uint32_t* __restrict__ klo, uint32_t* __restrict__ khi, uint32_t* __restrict__ id_base,
+    int32_t* __restrict__ flag, float* __restrict__ recin, uint32_t* __restrict__ ghist) {
+  constexpr int A = D == 1 ? 2 : D;  // arrays sorted: lower bounds, for d = 1 the upper ones too
+  __shared__ uint32_t h[A * 4][256];
+  const uint32_t tid = threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < A * 4; ++q) h[q][tid] = 0;
+  const uint32_t base = blockIdx.x * (kKeyThreads * kKeyItems) + tid;
+  float a[kKeyItems][D], b[kKeyItems][D];
+#pragma unroll
+  for (uint32_t r = 0; r < kKeyItems; ++r) {
+    const uint32_t i = base + r * kKeyThreads;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      a[r][k] = i < n ? lo[(size_t)k * n + i] : 0.f;
+      b[r][k] = i < n ? hi[(size_t)k * n + i] : 0.f;
+    }
+  }
+  __syncthreads();
   bool bad = false;
-  if (idx < total) {
-    const uint32_t k = (uint32_t)(idx / n);
-    const uint32_t i = (uint32_t)(idx - (uint64_t)k * n);
-    const float a = lo[idx], b = hi[idx];
-    bad = !valid_extent(a, b);
-    klo[idx] = f2key(a);
-    if (khi) khi[idx] = f2key(b);
-    id_base[(size_t)k * (n + 1) + 1 + i] = i;
-    if (recin) *reinterpret_cast<float2*>(recin + ((size_t)i * d + k) * 2) = make_float2(a, b);
+#pragma unroll
+  for (uint32_t r = 0; r < kKeyItems; ++r) {
+    const uint32_t i = base + r * kKeyThreads;
+    if (i < n) {
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        bad = bad || !valid_extent(a[r][k], b[r][k]);
+        const uint32_t kl = f2key(a[r][k]);
+        klo[(size_t)k * n + i] = kl;
+        id_base[(size_t)k * (n + 1) + 1 + i] = i;
+        *reinterpret_cast<float2*>(recin + ((size_t)i * D + k) * 2) = make_float2(a[r][k], b[r][k]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) atomicAdd(&h[k * 4 + p][(kl >> (8 * p)) & 255u], 1u);
+        if (D == 1) {
+          const uint32_t kh = f2key(b[r][k]);
+          khi[i] = kh;
+#pragma unroll
+          for (int p = 0; p < 4; ++p) atomicAdd(&h[(A - 1) * 4 + p][(kh >> (8 * p)) & 255u], 1u);
+        }
+      }
+    }
   }
   if (ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 1);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < A * 4; ++q) {
+    const uint32_t c = h[q][tid];
+    if (c) atomicAdd(&ghist[q * 256 + tid], c);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Small sets: keys and sort in one kernel, one workgroup per sorted array, all
+// passes in LDS.  The general path's eight launches are bound by latency there:
+// a pass over 5000 keys takes 8 us for what is 60 KB.  Wavefront w ranks keys
+// w * 64 R .. in order (a ballot match per round, counters of its own), so that
+// the sort is stable, as the general one is.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kSmallThreads = 1024, kSmallMax = 8192;
+
+template <int R>
+__global__ __launch_bounds__(kSmallThreads) void build_small_kernel(
+    const float* __restrict__ lo, const float* __restrict__ hi, uint32_t n, uint32_t d,
+    uint32_t* __restrict__ klo, uint32_t* __restrict__ khi, uint32_t* __restrict__ id_base,
+    int32_t* __restrict__ flag, uint32_t* __restrict__ maxlen_bits, float* __restrict__ recin) {
+  constexpr uint32_t W = kSmallThreads / kWave, N = kSmallThreads * R;
+  __shared__ uint32_t lkey[N];
+  __shared__ uint16_t lval[N];
+  __shared__ uint32_t wcnt[W][256];
+  __shared__ uint32_t wsum[4];
+  __shared__ uint32_t sbad;
+  const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+  const uint32_t k = blockIdx.x < d ? blockIdx.x : 0u;  // dimension; array d (d = 1): its upper bounds
+  const bool upper = blockIdx.x >= d;
+  const uint32_t base = wave * (R * kWave) + lane;
+  if (tid == 0) sbad = 0;
+  uint32_t key[R], val[R];
+  bool bad = false;
+  {
+    float a[R], b[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      const uint32_t i = base + r * kWave;
+      a[r] = i < n ? lo[(size_t)k * n + i] : 0.f;
+      b[r] = i < n ? hi[(size_t)k * n + i] : 0.f;
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      const uint32_t i = base + r * kWave;
+      key[r] = f2key(upper ? b[r] : a[r]);
+      val[r] = i;
+      bad = bad || !valid_extent(a[r], b[r]);
+      if (!upper && i < n)
+        *reinterpret_cast<float2*>(recin + ((size_t)i * d + k) * 2) = make_float2(a[r], b[r]);
+    }
+  }
+  // the first workgroup looks at every dimension, so that the flag has one writer
+  if (blockIdx.x == 0)
+    for (uint32_t kk = 1; kk < d; ++kk) {
+      float a[R], b[R];
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = base + r * kWave;
+        a[r] = i < n ? lo[(size_t)kk * n + i] : 0.f;
+        b[r] = i < n ? hi[(size_t)kk * n + i] : 0.f;
+      }
+#pragma unroll
+      for (uint32_t r = 0; r < R; ++r) bad = bad || !valid_extent(a[r], b[r]);
+    }
+  __syncthreads();
+  if (bad) sbad = 1;
+  for (uint32_t pass = 0; pass < 4; ++pass) {
+    const uint32_t shift = 8u * pass;
+    for (uint32_t i = lane; i < 256; i += kWave) wcnt[wave][i] = 0;
+    uint32_t loc[R];
+    // (a wavefront's own counters: LDS operations of one wavefront are in order)
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      const bool valid = base + r * kWave < n;
+      const uint32_t dig = (key[r] >> shift) & 255u;
+      const uint64_t peers = match_digit8(dig, ballot(valid));
+      const uint32_t rk = mask_rank(peers);
+      const uint32_t c = valid ? wcnt[wave][dig] : 0u;
+      loc[r] = c + rk;
+      if (valid && rk == 0) wcnt[wave][dig] = c + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    // digit tid: the wavefronts' counts become offsets within the digit, then
+    // the digits are placed
+    uint32_t tot = 0, inc = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (uint32_t w = 0; w < W; ++w) tot += wcnt[w][tid];
+      inc = wave_scan_dpp(tot);
+      if (lane == kWave - 1) wsum[wave] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t run = inc - tot;
+      for (uint32_t w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+      for (uint32_t w = 0; w < W; ++w) {
+        const uint32_t c = wcnt[w][tid];
+        wcnt[w][tid] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      if (base + r * kWave < n) {
+        const uint32_t at = wcnt[wave][(key[r] >> shift) & 255u] + loc[r];
+        lkey[at] = key[r];
+        lval[at] = (uint16_t)val[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+      const uint32_t i = base + r * kWave;
+      if (i < n) {
+        key[r] = lkey[i];
+        val[r] = lval[i];
+      }
+    }
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = base + r * kWave;
+    if (i < n) {
+      if (upper) {
+        khi[i] = key[r];
+      } else {
+        klo[(size_t)k * n + i] = key[r];
+        id_base[(size_t)k * (n + 1) + 1 + i] = val[r];
+      }
+    }
+  }
+  if (tid == 0) {
+    if (!upper) maxlen_bits[k] = 0;
+    if (blockIdx.x == 0) *flag = sbad ? 1 : 0;
+  }
 }
 
 // up to DDM_MAX_D tree jobs passed by value (one build)
@@ -115,25 +298,30 @@ struct TreeJobs {
   TreeJob j[DDM_MAX_D];
 };
 
-// samples and quantiles: job blockIdx.y, items blockIdx.x * 256 + tid
-__global__ void build_index_kernel(TreeJobs J) {
-  tree_index_item(J.j[blockIdx.y], blockIdx.x * blockDim.x + threadIdx.x);
-}
-
-__global__ void tree_init_kernel(int32_t* __restrict__ flag, uint32_t* __restrict__ maxlen_bits,
-                                 uint32_t d) {
+__global__ void flag_zero_kernel(int32_t* __restrict__ flag) {
   if (threadIdx.x == 0) *flag = 0;
-  if (threadIdx.x < d) maxlen_bits[threadIdx.x] = 0;
 }
 
 // job blockIdx.y, chunk blockIdx.x
+// job blockIdx.y, chunk blockIdx.x - 1; the first workgroup takes the samples
+// and quantiles instead (they need the sorted keys only, so their loads run
+// beside the other workgroups': 5 us less than a kernel of their own at 5*10^5)
+__device__ __forceinline__ bool tree_index_group(const TreeJob& J) {
+  if (blockIdx.x != 0) return false;
+  const uint32_t items = max(J.ns, (uint32_t)kQuant);
+  for (uint32_t c = threadIdx.x; c < items; c += kTreeThreads) tree_index_item(J, c);
+  return true;
+}
+
 __global__ __launch_bounds__(kTreeThreads) void tree_low_kernel(TreeJobs J) {
-  tree_low_chunk(J.j[blockIdx.y], blockIdx.x);
+  if (tree_index_group(J.j[blockIdx.y])) return;
+  tree_low_chunk(J.j[blockIdx.y], blockIdx.x - 1);
 }
 
 // the same pass over records already in place (extents moved)
 __global__ __launch_bounds__(kTreeThreads) void tree_refit_kernel(TreeJobs J) {
-  tree_low_chunk<false>(J.j[blockIdx.y], blockIdx.x);
+  if (tree_index_group(J.j[blockIdx.y])) return;
+  tree_low_chunk<false>(J.j[blockIdx.y], blockIdx.x - 1);
 }
 
 __global__ __launch_bounds__(kTreeThreads) void tree_high_kernel(TreeJobs J, uint32_t S) {
@@ -211,18 +399,13 @@ static ddm_status ensure_tree_attr() {
   return DDM_OK;
 }
 
-// samples/quantiles of the sorted keys, then maxupper and block maxima; the
+// samples/quantiles of the sorted keys, maxupper and block maxima; the
 // records are gathered from the inputs (gather) or already in place
 static ddm_status enqueue_tree_passes(const ddm_tree* t, const TreeJobs& J, bool gather,
                                       hipStream_t s) {
   const uint32_t d = t->d;
-  {
-    dim3 g((std::max(t->ns, kQuant) + 255) / 256, d);
-    build_index_kernel<<<g, 256, 0, s>>>(J);
-    DDM_LAUNCHED("build_index_kernel");
-  }
   ProfScope ps("tree_build", s);
-  dim3 g((t->P + 1 + kChunk - 1) / kChunk, d);
+  dim3 g((t->P + 1 + kChunk - 1) / kChunk + 1, d);
   const size_t lds = d > 1 ? strip_lds_bytes(d) : 0;
   if (lds) {
     const ddm_status st = ensure_tree_attr();
@@ -249,6 +432,29 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
   // final counts; for d > 1 the probe dimension comes from lower bounds only
   const bool sort_hi = d == 1;
   const uint32_t narr = sort_hi ? 2 * d : d;
+  if (n <= kSmallMax) {
+    {
+      ProfScope ps("build_keys", s);
+#define DDM_SMALL(R)                                                                     \
+  build_small_kernel<R><<<narr, kSmallThreads, 0, s>>>(lo, hi, n, d, t->skey_lo[0],     \
+                                                       t->skey_hi[0], t->id[0], t->flag, \
+                                                       (uint32_t*)t->maxlen, t->rid)
+      switch ((n + kSmallThreads - 1) / kSmallThreads) {
+        case 1: DDM_SMALL(1); break;
+        case 2: DDM_SMALL(2); break;
+        case 3: DDM_SMALL(3); break;
+        case 4: DDM_SMALL(4); break;
+        case 5: DDM_SMALL(5); break;
+        case 6: DDM_SMALL(6); break;
+        default: DDM_SMALL(8); break;
+      }
+#undef DDM_SMALL
+      DDM_LAUNCHED("build_small_kernel");
+    }
+    TreeJobs J = make_jobs(t, lo, hi);
+    for (uint32_t k = 0; k < d; ++k) J.j[k].recin = t->rid;
+    return enqueue_tree_passes(t, J, true, s);
+  }
   // the sort's arrays (buffer 1 of each is filled in once scratch exists)
   SortArr host[2 * DDM_MAX_D];
   for (uint32_t i = 0; i < narr; ++i) host[i] = SortArr{{nullptr, nullptr}, {nullptr, nullptr}, n, 0};
@@ -265,14 +471,6 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
   char* sort_scratch = sc.take<char>(sort_bytes);
   if (!sc.fits()) return scratch_overrun("tree build");
 
-  {
-    ProfScope ps("build_keys", s);
-    const uint64_t total = (uint64_t)n * d;
-    build_keys_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(
-        lo, hi, n, d, t->skey_lo[0], sort_hi ? t->skey_hi[0] : nullptr, t->id[0], t->flag,
-        t->rid);
-    DDM_LAUNCHED("build_keys_kernel");
-  }
   uint32_t na = 0;
   for (uint32_t k = 0; k < d; ++k) {
     SortArr& a = host[na++];
@@ -285,7 +483,27 @@ ddm_status enqueue_tree_build(ddm_tree* t, const float* lo, const float* hi, hip
     b.k[0] = t->skey_hi[k];
     b.k[1] = khi_tmp + (size_t)k * n;
   }
-  ddm_status st = radix_sort_onesweep(host, narr, 4, sort_scratch, t->flag, s);
+  const OsScratch S = radix_onesweep_scratch(host, narr, 4, sort_scratch);
+  {
+    ProfScope ps("build_keys", s);
+    const unsigned zb = (unsigned)std::min<size_t>((std::max<size_t>(S.nstatus, S.nhist) + 255) / 256, 2048);
+    build_zero_kernel<<<zb, 256, 0, s>>>(t->flag, (uint32_t*)t->maxlen, d, S);
+    DDM_LAUNCHED("build_zero_kernel");
+    const unsigned g = (n + kKeyThreads * kKeyItems - 1) / (kKeyThreads * kKeyItems);
+#define DDM_KEYS(DD)                                                                            \
+  build_keys_kernel<DD><<<g, kKeyThreads, 0, s>>>(lo, hi, n, t->skey_lo[0],                     \
+                                                  sort_hi ? t->skey_hi[0] : nullptr, t->id[0], \
+                                                  t->flag, t->rid, S.ghist)
+    switch (d) {
+      case 1: DDM_KEYS(1); break;
+      case 2: DDM_KEYS(2); break;
+      case 3: DDM_KEYS(3); break;
+      default: DDM_KEYS(4); break;
+    }
+#undef DDM_KEYS
+    DDM_LAUNCHED("build_keys_kernel");
+  }
+  ddm_status st = radix_onesweep_passes(host, narr, 4, S, t->flag, s);
   if (st != DDM_OK) return st;
   TreeJobs J = make_jobs(t, lo, hi);
   for (uint32_t k = 0; k < d; ++k) J.j[k].recin = t->rid;
@@ -430,8 +648,8 @@ static ddm_status tree_update(ddm_tree* t, const uint32_t* ids, const float* nlo
   A.rid = t->rid;
   A.n = n;
   A.d = d;
-  tree_init_kernel<<<1, 64, 0, s>>>(flag, nullptr, 0);
-  DDM_LAUNCHED("tree_init_kernel");
+  flag_zero_kernel<<<1, 64, 0, s>>>(flag);
+  DDM_LAUNCHED("flag_zero_kernel");
   upd_pos_kernel<<<dim3((n + 255) / 256, d), 256, 0, s>>>(A);
   DDM_LAUNCHED("upd_pos_kernel");
   upd_check_kernel<<<(count + 255) / 256, 256, 0, s>>>(ids, nlo, nhi, count, n, d, flag);
@@ -494,8 +712,6 @@ static ddm_status tree_update(ddm_tree* t, const uint32_t* ids, const float* nlo
   DDM_LAUNCHED("upd_gather_kernel");
   upd_scatter_kernel<<<(count + 255) / 256, 256, 0, s>>>(ids, nlo, nhi, count, n, d, lo, hi);
   DDM_LAUNCHED("upd_scatter_kernel");
-  tree_init_kernel<<<1, 64, 0, s>>>(t->flag, (uint32_t*)t->maxlen, d);
-  DDM_LAUNCHED("tree_init_kernel");
   return enqueue_tree_build(t, lo, hi, s);
 }
 
@@ -585,7 +801,6 @@ extern "C" ddm_status ddm_build(const float* sub_lo, const float* sub_hi, uint32
   const size_t qu_b = al(sizeof(uint32_t) * kQuant * d);
   const size_t total = tree_bytes_estimate(n, d);
   void* blk = dev_alloc(total, s);
-  hipError_t e = hipSuccess;
   if (!blk) {
     delete t;
     set_detail("ddm_build: device allocation failed");
@@ -642,13 +857,6 @@ extern "C" ddm_status ddm_build(const float* sub_lo, const float* sub_hi, uint32
   t->sat = (uint32_t*)p;
   p += al(sizeof(uint32_t) * kSatWords);
   t->flag = (int32_t*)p;
-  tree_init_kernel<<<1, 64, 0, s>>>(t->flag, (uint32_t*)t->maxlen, d);
-  e = hipGetLastError();
-  if (e != hipSuccess) {
-    dev_free(t->block, s);
-    delete t;
-    return hip_fail(e, "tree_init_kernel", __FILE__, __LINE__);
-  }
   ddm_status st = enqueue_tree_build(t, sub_lo, sub_hi, s);
   if (st != DDM_OK) {
     dev_free(t->block, s);
