@@ -416,11 +416,13 @@ ddm_status ddm_tree_update(ddm_tree* t, const uint32_t* ids, const float* new_lo
  *   DDM_DYNAMIC_SUBSCRIPTIONS or DDM_DYNAMIC_UPDATES) to new extents:
  *   ids device uint32 (distinct, below the set's size), new_lo/new_hi
  *   device [d][count] float32 (column c is the new extent of ids[c]).  The
- *   moved set's tree is refitted or rebuilt (as ddm_tree_update); a moved
+ *   moved set's tree is merged (up to 8192 moves, d > 1), or refitted or
+ *   rebuilt (as ddm_tree_update); a moved
  *   update's column of M is recomputed with one query of T_S, a moved
  *   subscription's row with one query of T_U; the resident result drops the
  *   moved ids' old pairs and merges the new ones.  out_count (host, may be
- *   NULL) receives the new K.  Synchronizes the stream a few times.  On
+ *   NULL) receives the new K.  Synchronizes the stream (once where the
+ *   tree is merged).  On
  *   DDM_E_INVALID_INPUT (id out of range or repeated, invalid extent)
  *   nothing changes.  K must stay below 2^32.
  * ddm_dynamic_result -- the current pairs (device pointer, sorted

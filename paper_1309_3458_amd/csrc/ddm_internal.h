@@ -486,4 +486,27 @@ struct ScanWords {
 ddm_status scan_counts(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,
                        const ScanWords& W, hipStream_t s);
 
+// Moves of a resident tree by merging (tree.hip): up to kTreeMoveMax moved
+// extents, ids ascending and distinct; words: tree_move_words() of scratch.
+// tree_move_sort only reads the tree (and bears ids that turn out bad);
+// tree_move_apply moves the extents.
+constexpr uint32_t kTreeMoveMax = 8192;
+struct TreeMove {
+  const uint32_t* sid;
+  const float* lo;  // [d][count], in the order of sid
+  const float* hi;
+  const uint32_t* bits;  // the moved ids as a bitmap
+  uint32_t count;
+  uint32_t* words;
+};
+bool tree_move_ok(const ddm_tree* t, uint32_t count);
+size_t tree_move_words(const ddm_tree* t, uint32_t count);
+ddm_status tree_move_sort(const ddm_tree* t, const TreeMove& M, hipStream_t s);
+ddm_status tree_move_apply(ddm_tree* t, const TreeMove& M, hipStream_t s);
+
+// kHostWords pinned words of the calling thread, for device-to-host reads: a
+// match uses the first 8, ddm_dynamic_move those from kHostWordsMove
+constexpr uint32_t kHostWords = 16, kHostWordsMove = 8;
+ddm_status host_words(uint64_t** out);
+
 }  // namespace ddm

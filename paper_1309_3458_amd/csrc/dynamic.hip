@@ -5,19 +5,23 @@
 // update needs one query of T_S, a moved subscription one query of T_U).
 //
 // A move of c extents of one set:
-//   1. the moved ids are sorted (their new extents follow), marked in a
-//      bitmap (a repeated id is refused) and their tree is refitted or
-//      rebuilt (ddm_tree_update, which also validates the new extents);
-//   2. their new extents overwrite the resident copy of the set;
-//   3. the moved extents query the other set's tree: moved updates give
-//      their columns of M directly (keys in update order); moved
-//      subscriptions give their rows, which a stable radix sort of the
-//      update ids turns into (update, subscription) key order;
-//   4. the resident result drops every pair of a moved id (one pass with the
-//      bitmap and a compaction) and merges the recomputed pairs in (both
-//      lists are sorted and disjoint: each element's place is its index plus
-//      the number of smaller elements of the other list).
+//   1. the moved ids are marked in a bitmap (a repeated id is refused) and
+//      checked with their new extents; the bitmap's prefix counts rank them,
+//      so they are put in ascending order without a sort;
+//   2. the resident pairs of moved ids are counted out tile by tile;
+//   3. the moved extents query the other set's tree.  Its synchronization is
+//      the only one: it also brings the check and the count, and nothing has
+//      been changed before it;
+//   4. moved updates give their columns of M directly (keys in update order);
+//      moved subscriptions give their rows, which a stable sort by update id
+//      turns into (update, subscription) key order;
+//   5. the moved set's tree is merged (a few moves, d > 1), refitted or rebuilt
+//      (ddm_tree_update), and the new extents go to the resident copy;
+//   6. one pass drops the moved ids' pairs and merges the recomputed ones into
+//      a new result (both lists are sorted: an element's place is its index
+//      less the dropped ones before it plus the new ones before it).
 // The result is always exactly the pairs of the current sets, sorted.
+#include "block_sort.h"
 #include "ddm_internal.h"
 
 #include <algorithm>
@@ -39,23 +43,25 @@ struct ddm_dynamic {
 
 namespace ddm {
 
-__global__ void dyn_iota_kernel(uint32_t* __restrict__ v, uint32_t count) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) v[i] = i;
-}
-
-__global__ void dyn_zero_kernel(uint32_t* __restrict__ p, uint64_t count) {
+__global__ void dyn_zero_kernel(uint32_t* __restrict__ p, uint64_t count,
+                                int32_t* __restrict__ flag) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) p[i] = 0;
+  if (i == 0) *flag = 0;
 }
 
-// marks the moved ids; flag[0] |= 1 for an id out of range, |= 2 for a
-// repeated id
-__global__ void dyn_mark_kernel(const uint32_t* __restrict__ ids, uint32_t count,
+// marks the moved ids; flag |= 1 for an id out of range, |= 2 for a repeated
+// id, |= 4 for an extent that is not valid
+__global__ void dyn_mark_kernel(const uint32_t* __restrict__ ids, const float* __restrict__ lo,
+                                const float* __restrict__ hi, uint32_t count, uint32_t d,
                                 uint32_t limit, uint32_t* __restrict__ bits,
                                 int32_t* __restrict__ flag) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= count) return;
+  bool bad = false;
+  for (uint32_t k = 0; k < d; ++k)
+    bad = bad || !valid_extent(lo[(size_t)k * count + c], hi[(size_t)k * count + c]);
+  if (bad) atomicOr(flag, 4);
   const uint32_t id = ids[c];
   if (id >= limit) {
     atomicOr(flag, 1);
@@ -65,24 +71,101 @@ __global__ void dyn_mark_kernel(const uint32_t* __restrict__ ids, uint32_t count
   if (old & (1u << (id & 31))) atomicOr(flag, 2);
 }
 
-// sorted moved ids (with their positions in the caller's arrays) -> the new
-// extents in that order, and written into the resident copy of the set
-__global__ void dyn_gather_scatter_kernel(const uint32_t* __restrict__ sid,
-                                          const uint32_t* __restrict__ spos, uint32_t count,
-                                          uint32_t d, const float* __restrict__ new_lo,
-                                          const float* __restrict__ new_hi,
-                                          float* __restrict__ glo, float* __restrict__ ghi,
-                                          float* __restrict__ set_lo, float* __restrict__ set_hi,
-                                          uint32_t set_count) {
+// marked ids before each word of the bitmap, by one workgroup (16 words to a
+// thread and round); and the words for the host: the flag, and the resident
+// pairs that stay (*kept)
+constexpr uint32_t kRankThreads = 1024, kRankWords = 16;
+__global__ __launch_bounds__(kRankThreads) void dyn_rank_kernel(
+    const uint32_t* __restrict__ bits, uint32_t words, uint32_t* __restrict__ before,
+    const int32_t* __restrict__ flag, const uint64_t* __restrict__ kept,
+    uint64_t* __restrict__ host) {
+  __shared__ uint32_t wsum[2][kRankThreads / kWave];
+  const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  if (tid == 0) {
+    host[0] = (uint64_t)(uint32_t)*flag;
+    host[1] = kept ? *kept : 0;
+  }
+  uint32_t base = 0, turn = 0;
+  for (uint32_t w0 = 0; w0 < words; w0 += kRankThreads * kRankWords, turn ^= 1u) {
+    const uint32_t at = w0 + tid * kRankWords;
+    const bool whole = at + kRankWords <= words;  // (both arrays start at 256 bytes)
+    uint32_t c[kRankWords], sum = 0;
+    if (whole) {
+      uint4 v[kRankWords / 4];
+#pragma unroll
+      for (uint32_t q = 0; q < kRankWords / 4; ++q)
+        v[q] = reinterpret_cast<const uint4*>(bits + at)[q];
+#pragma unroll
+      for (uint32_t q = 0; q < kRankWords / 4; ++q) {
+        c[4 * q] = (uint32_t)__popc(v[q].x);
+        c[4 * q + 1] = (uint32_t)__popc(v[q].y);
+        c[4 * q + 2] = (uint32_t)__popc(v[q].z);
+        c[4 * q + 3] = (uint32_t)__popc(v[q].w);
+      }
+    } else {
+#pragma unroll
+      for (uint32_t q = 0; q < kRankWords; ++q)
+        c[q] = at + q < words ? (uint32_t)__popc(bits[at + q]) : 0u;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kRankWords; ++q) sum += c[q];
+    const uint32_t inc = wave_scan_dpp(sum);
+    if (lane == kWave - 1) wsum[turn][wave] = inc;
+    __syncthreads();
+    const uint32_t wt = lane < kRankThreads / kWave ? wsum[turn][lane] : 0u;
+    const uint32_t wi = wave_scan_dpp(wt);
+    uint32_t run = base + inc - sum + (uint32_t)__builtin_amdgcn_readlane((int)(wi - wt), (int)wave);
+    base += (uint32_t)__builtin_amdgcn_readlane((int)wi, kWave - 1);
+#pragma unroll
+    for (uint32_t q = 0; q < kRankWords; ++q) {
+      const uint32_t here = c[q];
+      c[q] = run;
+      run += here;
+    }
+    if (whole) {
+#pragma unroll
+      for (uint32_t q = 0; q < kRankWords / 4; ++q)
+        reinterpret_cast<uint4*>(before + at)[q] =
+            make_uint4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+    } else {
+#pragma unroll
+      for (uint32_t q = 0; q < kRankWords; ++q)
+        if (at + q < words) before[at + q] = c[q];
+    }
+  }
+}
+
+// the moved ids ascending, and their new extents in that order
+__global__ void dyn_gather_kernel(const uint32_t* __restrict__ ids, uint32_t count, uint32_t d,
+                                  uint32_t limit, const float* __restrict__ new_lo,
+                                  const float* __restrict__ new_hi,
+                                  const uint32_t* __restrict__ bits,
+                                  const uint32_t* __restrict__ before, uint32_t* __restrict__ sid,
+                                  float* __restrict__ glo, float* __restrict__ ghi) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= count) return;
-  const uint32_t id = sid[c], p = spos[c];
+  const uint32_t id = ids[c];
+  if (id >= limit) return;  // (refused by the host later)
+  const uint32_t at =
+      before[id >> 5] + (uint32_t)__popc(bits[id >> 5] & ((1u << (id & 31u)) - 1u));
+  sid[at] = id;
   for (uint32_t k = 0; k < d; ++k) {
-    const float lo = new_lo[(size_t)k * count + p], hi = new_hi[(size_t)k * count + p];
-    glo[(size_t)k * count + c] = lo;
-    ghi[(size_t)k * count + c] = hi;
-    set_lo[(size_t)k * set_count + id] = lo;
-    set_hi[(size_t)k * set_count + id] = hi;
+    glo[(size_t)k * count + at] = new_lo[(size_t)k * count + c];
+    ghi[(size_t)k * count + at] = new_hi[(size_t)k * count + c];
+  }
+}
+
+// the new extents into the resident copy of the set
+__global__ void dyn_scatter_kernel(const uint32_t* __restrict__ sid, uint32_t count, uint32_t d,
+                                   const float* __restrict__ glo, const float* __restrict__ ghi,
+                                   float* __restrict__ set_lo, float* __restrict__ set_hi,
+                                   uint32_t set_count) {
+  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= count) return;
+  const uint32_t id = sid[c];
+  for (uint32_t k = 0; k < d; ++k) {
+    set_lo[(size_t)k * set_count + id] = glo[(size_t)k * count + c];
+    set_hi[(size_t)k * set_count + id] = ghi[(size_t)k * count + c];
   }
 }
 
@@ -113,28 +196,76 @@ __global__ void dyn_join_kernel(const uint32_t* __restrict__ upd, const uint32_t
   if (i < K) keys[i] = ((uint64_t)upd[i] << 32) | sub[i];
 }
 
-// keep[i] = 1 if pair i involves no moved id (of the moved set)
-__global__ void dyn_keep_kernel(const uint64_t* __restrict__ keys, uint64_t K,
-                                const uint32_t* __restrict__ bits, int rows,
-                                uint32_t* __restrict__ keep) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= K) return;
-  const uint64_t k = keys[i];
-  const uint32_t id = rows ? (uint32_t)k : (uint32_t)(k >> 32);
-  keep[i] = (bits[id >> 5] >> (id & 31)) & 1u ? 0u : 1u;
+// The rows of moved subscriptions in key order at once, for up to kRowsSmall
+// pairs: split, sorted by update id (stable) and joined in one workgroup, in
+// place of twelve launches (10^4 pairs: 24 us in place of 53 us and their gaps).
+constexpr uint32_t kRowsSmall = 16 * kBlockSortThreads;
+template <int R>
+__global__ __launch_bounds__(kBlockSortThreads) void dyn_rows_kernel(
+    uint64_t* __restrict__ keys, uint32_t K, const uint32_t* __restrict__ sid, uint32_t passes) {
+  __shared__ BlockSortLds<R, uint32_t> L;
+  uint32_t key[R], val[R];
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = block_sort_index<R>(r);
+    const uint64_t k = i < K ? keys[i] : 0u;
+    key[r] = (uint32_t)k;
+    val[r] = (uint32_t)(k >> 32);
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r)
+    if (block_sort_index<R>(r) < K) val[r] = sid[val[r]];
+  block_sort<R>(L, key, val, K, passes);
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = block_sort_index<R>(r);
+    if (i < K) keys[i] = ((uint64_t)key[r] << 32) | val[r];
+  }
 }
 
-__global__ void dyn_compact_kernel(const uint64_t* __restrict__ keys, uint64_t K,
-                                   const uint32_t* __restrict__ keep,
-                                   const uint64_t* __restrict__ pos, uint64_t* __restrict__ out) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < K && keep[i]) out[pos[i]] = keys[i];
+// The resident pairs without the moved ids' ones, tile by tile: a mask of the
+// pairs that stay for every 64, how many stay before it in the tile, and how
+// many of the tile.
+constexpr uint32_t kPairTile = 2048, kPairThreads = 256;
+constexpr uint32_t kPairRounds = kPairTile / kPairThreads, kPairWaves = kPairThreads / kWave;
+
+__global__ __launch_bounds__(kPairThreads) void dyn_keep_kernel(
+    const uint64_t* __restrict__ pairs, uint64_t K, const uint32_t* __restrict__ bits, int rows,
+    uint64_t* __restrict__ mask, uint32_t* __restrict__ before, uint32_t* __restrict__ cnt) {
+  __shared__ uint32_t w[kPairRounds * kPairWaves];
+  const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+  const uint64_t base = (uint64_t)blockIdx.x * kPairTile;
+  uint32_t id[kPairRounds];
+#pragma unroll
+  for (uint32_t r = 0; r < kPairRounds; ++r) {
+    const uint64_t i = base + r * kPairThreads + tid;
+    const uint64_t k = i < K ? pairs[i] : 0u;
+    id[r] = rows ? (uint32_t)k : (uint32_t)(k >> 32);
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < kPairRounds; ++r) {
+    const bool stay = base + r * kPairThreads + tid < K &&
+                      !((bits[id[r] >> 5] >> (id[r] & 31u)) & 1u);
+    const uint64_t b = ballot(stay);
+    const uint32_t q = r * kPairWaves + wave;
+    if (lane == 0) {
+      mask[base / 64 + q] = b;
+      w[q] = (uint32_t)__popcll(b);
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    constexpr uint32_t Q = kPairRounds * kPairWaves;
+    const uint32_t v = lane < Q ? w[lane] : 0u;
+    const uint32_t inc = wave_scan_dpp(v);
+    if (lane < Q) before[base / 64 + lane] = inc - v;
+    if (lane == Q - 1) cnt[blockIdx.x] = inc;
+  }
 }
 
-// number of elements of sorted v[0..len) below x
-__device__ __forceinline__ uint64_t count_below(const uint64_t* __restrict__ v, uint64_t len,
-                                                uint64_t x) {
-  uint64_t lo = 0, hi = len;
+// elements of sorted v[lo, hi) below x, plus lo
+__device__ __forceinline__ uint64_t count_below(const uint64_t* __restrict__ v, uint64_t lo,
+                                                uint64_t hi, uint64_t x) {
   while (lo < hi) {
     const uint64_t mid = (lo + hi) >> 1;
     if (v[mid] < x) lo = mid + 1;
@@ -143,16 +274,74 @@ __device__ __forceinline__ uint64_t count_below(const uint64_t* __restrict__ v, 
   return lo;
 }
 
-// merge of two sorted, disjoint lists A (a elements) and B (b elements)
-__global__ void dyn_merge_kernel(const uint64_t* __restrict__ A, uint64_t a,
-                                 const uint64_t* __restrict__ B, uint64_t b,
-                                 uint64_t* __restrict__ out) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < a) {
-    out[i + count_below(B, b, A[i])] = A[i];
-  } else if (i < a + b) {
-    const uint64_t jb = i - a;
-    out[jb + count_below(A, a, B[jb])] = B[jb];
+// the same from 0, by one wavefront (64 probes at a time)
+__device__ __forceinline__ uint64_t wave_count_below(const uint64_t* __restrict__ v, uint64_t len,
+                                                     uint64_t x) {
+  uint64_t at = 0;
+  while (len) {
+    const uint64_t step = (len + kWave - 1) / kWave;
+    const uint64_t o = lane_id() * step + step - 1;
+    const bool less = o < len && v[at + o] < x;
+    const uint64_t full = (uint64_t)__popcll(ballot(less)) * step;
+    at += full;
+    len = min(step - 1, len - full);
+  }
+  return at;
+}
+
+// The new result: workgroups 0 .. tiles-1 take a tile of the old pairs each (the
+// new ones that fall into it are found by two searches and held in LDS), the
+// others 256 new pairs each.  The compaction and the merge were three passes
+// over the result before (39 us for 10^6 pairs, 16 with this).
+constexpr uint32_t kPairCache = 1024;
+__global__ __launch_bounds__(kPairThreads) void dyn_merge_kernel(
+    const uint64_t* __restrict__ pairs, uint64_t K, const uint64_t* __restrict__ mask,
+    const uint32_t* __restrict__ before, const uint64_t* __restrict__ tile_off, uint32_t tiles,
+    const uint64_t* __restrict__ fresh, uint64_t F, uint64_t* __restrict__ out) {
+  const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+  if (blockIdx.x >= tiles) {
+    const uint64_t q = (uint64_t)(blockIdx.x - tiles) * kPairThreads + tid;
+    if (q >= F) return;
+    const uint64_t x = fresh[q];
+    const uint64_t j = count_below(pairs, 0, K, x);
+    uint64_t kept;
+    if (j == K)
+      kept = tile_off ? tile_off[tiles] : 0;
+    else
+      kept = tile_off[j / kPairTile] + before[j / 64] +
+             (uint64_t)__popcll(mask[j / 64] & ((1ull << (j & 63u)) - 1ull));
+    out[q + kept] = x;
+    return;
+  }
+  __shared__ uint64_t cache[kPairCache];
+  __shared__ uint64_t bound[2];
+  const uint64_t base = (uint64_t)blockIdx.x * kPairTile;
+  const uint64_t off = tile_off[blockIdx.x];
+  uint64_t key[kPairRounds];
+#pragma unroll
+  for (uint32_t r = 0; r < kPairRounds; ++r) {
+    const uint64_t i = base + r * kPairThreads + tid;
+    key[r] = i < K ? pairs[i] : ~0ull;
+  }
+  if (wave < 2) {
+    const uint64_t at = base + wave * (uint64_t)kPairTile;
+    const uint64_t v = at < K ? wave_count_below(fresh, F, pairs[at]) : F;
+    if (lane == 0) bound[wave] = v;
+  }
+  __syncthreads();
+  const uint64_t i0 = bound[0], i1 = bound[1];
+  const bool cached = i1 - i0 <= kPairCache;
+  if (cached)
+    for (uint64_t q = i0 + tid; q < i1; q += kPairThreads) cache[q - i0] = fresh[q];
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < kPairRounds; ++r) {
+    const uint64_t w = base / 64 + r * kPairWaves + wave;
+    const uint64_t m = mask[w];
+    if (!((m >> lane) & 1u)) continue;
+    const uint64_t at = cached ? i0 + count_below(cache, 0, i1 - i0, key[r])
+                               : count_below(fresh, i0, i1, key[r]);
+    out[off + before[w] + mask_rank(m) + at] = key[r];
   }
 }
 
@@ -185,61 +374,51 @@ static uint32_t passes_for(uint32_t max_value) {
   return p;
 }
 
-// the pairs of the sorted moved extents (glo/ghi, `count` of them, ids
-// sid) against the other set's tree, as (update << 32) | subscription keys
-// sorted ascending; rows: the moved extents are subscriptions
-static ddm_status recompute(ddm_dynamic* dy, bool rows, const uint32_t* sid, const float* glo,
-                            const float* ghi, uint32_t count, uint64_t** out, uint64_t* outK,
-                            char** block, hipStream_t s) {
-  const ddm_tree* other = rows ? dy->tu : dy->ts;
-  uint64_t K = 0;
-  ddm_pending* pend = nullptr;
-  ddm_status r = ddm_match_begin(other, glo, ghi, count, &K, s, nullptr, &pend);
-  if (r != DDM_OK) return r;
-  *outK = K;
-  *out = nullptr;
-  *block = nullptr;
-  if (K == 0) return ddm_match_finish(pend, nullptr, 0);
-  if (K >= (1ull << 32)) {
-    ddm_match_abort(pend);
-    set_detail("dynamic move: more than 2^32 - 1 recomputed pairs");
-    return DDM_E_INVALID_ARG;
-  }
-  const size_t bytes = sizeof(uint64_t) * K + (rows ? 4 * sizeof(uint32_t) * K + 1024 : 0);
-  char* mem = dev_alloc(bytes, s);
-  if (!mem) {
-    ddm_match_abort(pend);
-    set_detail("dynamic move: device allocation failed");
-    return DDM_E_NOMEM;
-  }
-  uint64_t* keys = (uint64_t*)mem;
-  r = ddm_match_finish(pend, keys, K);
-  if (r != DDM_OK) {
-    dev_free(mem, s);
-    return r;
-  }
+// the K pairs of the moved extents (ids sid) out of a match against the other
+// set's tree, as (update << 32) | subscription keys sorted ascending, in keys;
+// rows: the moved extents are subscriptions, and keys has room for 16 more
+// bytes per pair if K > kRowsSmall
+static ddm_status recomputed_keys(const ddm_dynamic* dy, bool rows, const uint32_t* sid,
+                                  uint64_t* keys, uint64_t K, hipStream_t s) {
   if (!rows) {
     dyn_remap_cols_kernel<<<blocks(K), 256, 0, s>>>(keys, K, sid);
     DDM_LAUNCHED("dyn_remap_cols_kernel");
-  } else {
-    // (subscription, update) order -> (update, subscription) order: a stable
-    // sort by update id keeps each update's subscriptions ascending
-    uint32_t* base = (uint32_t*)(mem + sizeof(uint64_t) * K);
-    uint32_t* const ku[2] = {base, base + K};
-    uint32_t* const vs[2] = {base + 2 * K, base + 3 * K};
-    dyn_split_rows_kernel<<<blocks(K), 256, 0, s>>>(keys, K, sid, ku[0], vs[0]);
-    DDM_LAUNCHED("dyn_split_rows_kernel");
-    const uint32_t passes = passes_for(dy->m - 1);
-    r = sort_pairs(ku, vs, (uint32_t)K, passes, s);
-    if (r != DDM_OK) {
-      dev_free(mem, s);
-      return r;
-    }
-    dyn_join_kernel<<<blocks(K), 256, 0, s>>>(ku[passes & 1], vs[passes & 1], K, keys);
-    DDM_LAUNCHED("dyn_join_kernel");
+    return DDM_OK;
   }
-  *out = keys;
-  *block = mem;
+  // (subscription, update) order -> (update, subscription) order: a stable
+  // sort by update id keeps each update's subscriptions ascending
+  const uint32_t passes = passes_for(dy->m - 1);
+  if (K <= kRowsSmall) {
+#define DDM_ROWS(R) \
+  dyn_rows_kernel<R><<<1, kBlockSortThreads, 0, s>>>(keys, (uint32_t)K, sid, passes)
+    const uint32_t need = (uint32_t)((K + kBlockSortThreads - 1) / kBlockSortThreads);
+    if (need <= 1)
+      DDM_ROWS(1);
+    else if (need <= 2)
+      DDM_ROWS(2);
+    else if (need <= 4)
+      DDM_ROWS(4);
+    else if (need <= 8)
+      DDM_ROWS(8);
+    else if (need <= 10)
+      DDM_ROWS(10);
+    else if (need <= 12)
+      DDM_ROWS(12);
+    else
+      DDM_ROWS(16);
+#undef DDM_ROWS
+    DDM_LAUNCHED("dyn_rows_kernel");
+    return DDM_OK;
+  }
+  uint32_t* base = (uint32_t*)(keys + K);
+  uint32_t* const ku[2] = {base, base + K};
+  uint32_t* const vs[2] = {base + 2 * K, base + 3 * K};
+  dyn_split_rows_kernel<<<blocks(K), 256, 0, s>>>(keys, K, sid, ku[0], vs[0]);
+  DDM_LAUNCHED("dyn_split_rows_kernel");
+  const ddm_status r = sort_pairs(ku, vs, (uint32_t)K, passes, s);
+  if (r != DDM_OK) return r;
+  dyn_join_kernel<<<blocks(K), 256, 0, s>>>(ku[passes & 1], vs[passes & 1], K, keys);
+  DDM_LAUNCHED("dyn_join_kernel");
   return DDM_OK;
 }
 
@@ -340,114 +519,137 @@ extern "C" ddm_status ddm_dynamic_move(ddm_dynamic* dy, uint32_t set, const uint
   hipStream_t s = (hipStream_t)stream;
   dy->home = s;
   const uint32_t d = dy->d;
-  const uint64_t words = ((uint64_t)limit + 31) / 32;
-  // scratch: sorted ids and positions (two buffers each), bitmap, flag, the
-  // moved extents in sorted order
-  Scratch sc(s);
-  for (int i = 0; i < 4; ++i) sc.reserve(sizeof(uint32_t) * count);
-  sc.reserve(sizeof(uint32_t) * words);
-  sc.reserve(sizeof(int32_t));
-  sc.reserve(sizeof(float) * d * (size_t)count);
-  sc.reserve(sizeof(float) * d * (size_t)count);
-  if (!sc.commit()) return DDM_E_NOMEM;
-  uint32_t* const kid[2] = {sc.take<uint32_t>(count), sc.take<uint32_t>(count)};
-  uint32_t* const kpos[2] = {sc.take<uint32_t>(count), sc.take<uint32_t>(count)};
-  uint32_t* bits = sc.take<uint32_t>(words);
-  int32_t* flag = sc.take<int32_t>(1);
-  float* glo = sc.take<float>((size_t)d * count);
-  float* ghi = sc.take<float>((size_t)d * count);
-  if (!sc.fits()) return scratch_overrun("ddm_dynamic_move");
-  // 1. mark the ids (range, repeats), sort them with their positions
-  dyn_zero_kernel<<<blocks(words + 1), 256, 0, s>>>(bits, words);
-  DDM_LAUNCHED("dyn_zero_kernel");
-  dyn_zero_kernel<<<1, 64, 0, s>>>((uint32_t*)flag, 1);
-  DDM_LAUNCHED("dyn_zero_kernel");
-  dyn_mark_kernel<<<blocks(count), 256, 0, s>>>(ids, count, limit, bits, flag);
-  DDM_LAUNCHED("dyn_mark_kernel");
-  int32_t hflag = 0;
-  DDM_HIP(hipMemcpyAsync(&hflag, flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  DDM_HIP(hipStreamSynchronize(s));
-  if (hflag) {
-    set_detail(hflag & 1 ? "ddm_dynamic_move: id out of range"
-                         : "ddm_dynamic_move: an id appears more than once");
-    return DDM_E_INVALID_INPUT;
-  }
-  DDM_HIP(hipMemcpyAsync(kid[0], ids, sizeof(uint32_t) * count, hipMemcpyDeviceToDevice, s));
-  dyn_iota_kernel<<<blocks(count), 256, 0, s>>>(kpos[0], count);
-  DDM_LAUNCHED("dyn_iota_kernel");
-  const uint32_t passes = passes_for(limit - 1);
-  ddm_status r = sort_pairs(kid, kpos, count, passes, s);
-  if (r != DDM_OK) return r;
-  const uint32_t* sid = kid[passes & 1];
-  const uint32_t* spos = kpos[passes & 1];
-  // 2. refit (validates the new extents; nothing changes on error), then
-  // write the new extents into the resident copy, in sorted order
-  r = ddm_tree_update(rows ? dy->ts : dy->tu, ids, new_lo, new_hi, count, stream, nullptr);
-  if (r != DDM_OK) return r;
-  dyn_gather_scatter_kernel<<<blocks(count), 256, 0, s>>>(
-      sid, spos, count, d, new_lo, new_hi, glo, ghi, rows ? dy->s_lo : dy->u_lo,
-      rows ? dy->s_hi : dy->u_hi, limit);
-  DDM_LAUNCHED("dyn_gather_scatter_kernel");
-  // 3. the moved extents' pairs against the other set's tree
-  uint64_t* fresh = nullptr;
-  uint64_t F = 0;
-  char* fresh_mem = nullptr;
-  r = recompute(dy, rows, sid, glo, ghi, count, &fresh, &F, &fresh_mem, s);
-  if (r != DDM_OK) return r;
-  // 4. drop the moved ids' old pairs, merge the new ones in
   const uint64_t K = dy->K;
   if (K >= (1ull << 32)) {
-    if (fresh_mem) dev_free(fresh_mem, s);
     set_detail("ddm_dynamic_move: more than 2^32 - 1 resident pairs");
     return DDM_E_INVALID_ARG;
   }
-  Scratch sk(s);
-  sk.reserve(sizeof(uint32_t) * std::max<uint64_t>(K, 1));
-  sk.reserve(sizeof(uint64_t) * (K + 1));
-  sk.reserve(sizeof(uint64_t) * scan_tmp_words((uint32_t)K));
-  sk.reserve(sizeof(uint64_t) * std::max<uint64_t>(K, 1));
-  if (!sk.commit()) {
-    if (fresh_mem) dev_free(fresh_mem, s);
-    return DDM_E_NOMEM;
-  }
-  uint32_t* keep = sk.take<uint32_t>(std::max<uint64_t>(K, 1));
-  uint64_t* pos = sk.take<uint64_t>(K + 1);
-  uint64_t* stmp = sk.take<uint64_t>(scan_tmp_words((uint32_t)K));
-  uint64_t* kept = sk.take<uint64_t>(std::max<uint64_t>(K, 1));
-  if (!sk.fits()) {
-    if (fresh_mem) dev_free(fresh_mem, s);
-    return scratch_overrun("ddm_dynamic_move");
-  }
-  uint64_t A = 0;
-  if (K) {
-    dyn_keep_kernel<<<blocks(K), 256, 0, s>>>(dy->pairs, K, bits, rows ? 1 : 0, keep);
+  ddm_tree* const own = rows ? dy->ts : dy->tu;
+  const ddm_tree* const other = rows ? dy->tu : dy->ts;
+  const bool merge = tree_move_ok(own, count);
+  const uint32_t words = (limit + 31) / 32;
+  const uint32_t tiles = (uint32_t)((K + kPairTile - 1) / kPairTile);
+  const size_t blk64 = (size_t)tiles * (kPairTile / 64);
+  Scratch sc(s);
+  sc.reserve(sizeof(uint32_t) * words);               // bitmap
+  sc.reserve(sizeof(uint32_t) * words);               // marked before each word
+  sc.reserve(sizeof(int32_t));                        // flag
+  sc.reserve(sizeof(uint32_t) * count);               // moved ids, ascending
+  sc.reserve(sizeof(float) * d * (size_t)count);      // their extents
+  sc.reserve(sizeof(float) * d * (size_t)count);
+  sc.reserve(merge ? sizeof(uint32_t) * tree_move_words(own, count) : 1);
+  sc.reserve(sizeof(uint64_t) * (blk64 + 1));         // resident pairs: masks,
+  sc.reserve(sizeof(uint32_t) * (blk64 + 1));         // counts before them,
+  sc.reserve(sizeof(uint32_t) * (tiles + 1));         // counts of the tiles
+  sc.reserve(sizeof(uint64_t) * ((size_t)tiles + 1)); // and their sums
+  sc.reserve(sizeof(uint64_t) * scan_tmp_words(tiles));
+  if (!sc.commit()) return DDM_E_NOMEM;
+  uint32_t* bits = sc.take<uint32_t>(words);
+  uint32_t* before = sc.take<uint32_t>(words);
+  int32_t* flag = sc.take<int32_t>(1);
+  uint32_t* sid = sc.take<uint32_t>(count);
+  float* glo = sc.take<float>((size_t)d * count);
+  float* ghi = sc.take<float>((size_t)d * count);
+  TreeMove M{sid, glo, ghi, bits, count, nullptr};
+  if (merge)
+    M.words = sc.take<uint32_t>(tree_move_words(own, count));
+  else
+    (void)sc.take<char>(1);
+  uint64_t* mask = sc.take<uint64_t>(blk64 + 1);
+  uint32_t* mask_before = sc.take<uint32_t>(blk64 + 1);
+  uint32_t* tile_cnt = sc.take<uint32_t>((size_t)tiles + 1);
+  uint64_t* tile_off = sc.take<uint64_t>((size_t)tiles + 1);
+  uint64_t* stmp = sc.take<uint64_t>(scan_tmp_words(tiles));
+  if (!sc.fits()) return scratch_overrun("ddm_dynamic_move");
+  uint64_t* hw = nullptr;
+  ddm_status r = host_words(&hw);
+  if (r != DDM_OK) return r;
+  hw += kHostWordsMove;
+  // 1., 2. nothing of the object is written until the host has read the flag
+  dyn_zero_kernel<<<blocks(words), 256, 0, s>>>(bits, words, flag);
+  DDM_LAUNCHED("dyn_zero_kernel");
+  dyn_mark_kernel<<<blocks(count), 256, 0, s>>>(ids, new_lo, new_hi, count, d, limit, bits, flag);
+  DDM_LAUNCHED("dyn_mark_kernel");
+  if (tiles) {
+    dyn_keep_kernel<<<tiles, kPairThreads, 0, s>>>(dy->pairs, K, bits, rows ? 1 : 0, mask,
+                                                   mask_before, tile_cnt);
     DDM_LAUNCHED("dyn_keep_kernel");
-    r = scan_u32_u64(keep, pos, (uint32_t)K, stmp, s);
-    if (r != DDM_OK) {
-      if (fresh_mem) dev_free(fresh_mem, s);
-      return r;
-    }
-    dyn_compact_kernel<<<blocks(K), 256, 0, s>>>(dy->pairs, K, keep, pos, kept);
-    DDM_LAUNCHED("dyn_compact_kernel");
-    DDM_HIP(hipMemcpyAsync(&A, pos + K, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-    DDM_HIP(hipStreamSynchronize(s));
+    r = scan_u32_u64(tile_cnt, tile_off, tiles, stmp, s);
+    if (r != DDM_OK) return r;
   }
-  const uint64_t total = A + F;
-  if (total > dy->cap) {
-    uint64_t* grown = (uint64_t*)dev_alloc(sizeof(uint64_t) * total, s);
-    if (!grown) {
-      if (fresh_mem) dev_free(fresh_mem, s);
-      set_detail("ddm_dynamic_move: device allocation failed");
-      return DDM_E_NOMEM;
-    }
-    dev_free((char*)dy->pairs, s);
-    dy->pairs = grown;
-    dy->cap = total;
+  dyn_rank_kernel<<<1, kRankThreads, 0, s>>>(bits, words, before, flag,
+                                             tiles ? tile_off + tiles : nullptr, hw);
+  DDM_LAUNCHED("dyn_rank_kernel");
+  dyn_gather_kernel<<<blocks(count), 256, 0, s>>>(ids, count, d, limit, new_lo, new_hi, bits,
+                                                  before, sid, glo, ghi);
+  DDM_LAUNCHED("dyn_gather_kernel");
+  if (merge) {
+    r = tree_move_sort(own, M, s);
+    if (r != DDM_OK) return r;
   }
-  if (total) {
-    dyn_merge_kernel<<<blocks(total), 256, 0, s>>>(kept, A, fresh, F, dy->pairs);
+  // 3. the moved extents' pairs against the other set's tree
+  uint64_t F = 0;
+  ddm_pending* pend = nullptr;
+  r = ddm_match_begin(other, glo, ghi, count, &F, stream, nullptr, &pend);
+  const hipError_t sync = hipStreamSynchronize(s);  // (a match without a tree has not waited)
+  if (sync != hipSuccess) {
+    ddm_match_abort(pend);
+    return hip_fail(sync, "hipStreamSynchronize", __FILE__, __LINE__);
+  }
+  if (hw[0]) {
+    ddm_match_abort(pend);
+    set_detail(hw[0] & 1   ? "ddm_dynamic_move: id out of range"
+               : hw[0] & 2 ? "ddm_dynamic_move: an id appears more than once"
+                           : "ddm_dynamic_move: NaN/inf or lo > hi in the new extents");
+    return DDM_E_INVALID_INPUT;
+  }
+  if (r != DDM_OK) return r;
+  if (F >= (1ull << 32)) {
+    ddm_match_abort(pend);
+    set_detail("dynamic move: more than 2^32 - 1 recomputed pairs");
+    return DDM_E_INVALID_ARG;
+  }
+  const uint64_t A = hw[1], total = A + F;
+  // 4. the recomputed pairs, and the memory of the new result
+  uint64_t* fresh = nullptr;
+  char* fresh_mem = nullptr;
+  if (F) {
+    fresh_mem = dev_alloc(sizeof(uint64_t) * F + (rows && F > kRowsSmall ? 16 * F + 1024 : 0), s);
+    fresh = (uint64_t*)fresh_mem;
+  }
+  const uint64_t cap = std::max(dy->cap, total);
+  uint64_t* result = (uint64_t*)dev_alloc(sizeof(uint64_t) * cap, s);
+  auto fail = [&](ddm_status st) {
+    if (fresh_mem) dev_free(fresh_mem, s);
+    if (result) dev_free((char*)result, s);
+    return st;
+  };
+  if ((F && !fresh) || !result) {
+    ddm_match_abort(pend);
+    set_detail("dynamic move: device allocation failed");
+    return fail(DDM_E_NOMEM);
+  }
+  r = ddm_match_finish(pend, fresh, F);
+  if (r == DDM_OK && F) r = recomputed_keys(dy, rows, sid, fresh, F, s);
+  if (r != DDM_OK) return fail(r);
+  // 5. the tree and the resident copy
+  r = merge ? tree_move_apply(own, M, s)
+            : ddm_tree_update(own, ids, new_lo, new_hi, count, stream, nullptr);
+  if (r != DDM_OK) return fail(r);
+  dyn_scatter_kernel<<<blocks(count), 256, 0, s>>>(sid, count, d, glo, ghi,
+                                                   rows ? dy->s_lo : dy->u_lo,
+                                                   rows ? dy->s_hi : dy->u_hi, limit);
+  DDM_LAUNCHED("dyn_scatter_kernel");
+  // 6. the new result
+  const uint64_t groups = tiles + (F + kPairThreads - 1) / kPairThreads;
+  if (groups) {
+    dyn_merge_kernel<<<(unsigned)groups, kPairThreads, 0, s>>>(
+        dy->pairs, K, mask, mask_before, tiles ? tile_off : nullptr, tiles, fresh, F, result);
     DDM_LAUNCHED("dyn_merge_kernel");
   }
+  dev_free((char*)dy->pairs, s);
+  dy->pairs = result;
+  dy->cap = cap;
   dy->K = total;
   if (fresh_mem) dev_free(fresh_mem, s);
   if (out_count) *out_count = total;

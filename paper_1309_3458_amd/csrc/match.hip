@@ -1671,9 +1671,10 @@ struct HostWords {
 };
 static thread_local HostWords g_host;
 
-static ddm_status host_words(uint64_t** out) {
+ddm_status host_words(uint64_t** out) {
   if (!g_host.p) {
-    hipError_t e = hipHostMalloc((void**)&g_host.p, 64, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&g_host.p, sizeof(uint64_t) * kHostWords,
+                                 hipHostMallocDefault);
     if (e != hipSuccess) {
       g_host.p = nullptr;
       (void)hipGetLastError();

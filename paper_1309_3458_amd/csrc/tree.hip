@@ -11,6 +11,7 @@
 // bottom-up; minlower is the lower bound at the leftmost position of the
 // subtree and needs no storage.  Positions beyond n are padding, recognised
 // by index only.
+#include "block_sort.h"
 #include "ddm_internal.h"
 #include "tree_dev.h"
 
@@ -160,30 +161,22 @@ __global__ __launch_bounds__(kKeyThreads) void build_keys_kernel(
   }
 }
 
-// ---------------------------------------------------------------------------
-// Small sets: keys and sort in one kernel, one workgroup per sorted array, all
-// passes in LDS.  The general path's eight launches are bound by latency there:
-// a pass over 5000 keys takes 8 us for what is 60 KB.  Wavefront w ranks keys
-// w * 64 R .. in order (a ballot match per round, counters of its own), so that
-// the sort is stable, as the general one is.
-// ---------------------------------------------------------------------------
-constexpr uint32_t kSmallThreads = 1024, kSmallMax = 8192;
+// Small sets: keys and sort in one kernel, one workgroup per sorted array, in
+// place of the eight launches of the general path (5000 segments: 41 us of
+// kernels and their gaps against 17).
+constexpr uint32_t kSmallThreads = kBlockSortThreads, kSmallMax = 8192;
 
 template <int R>
 __global__ __launch_bounds__(kSmallThreads) void build_small_kernel(
     const float* __restrict__ lo, const float* __restrict__ hi, uint32_t n, uint32_t d,
     uint32_t* __restrict__ klo, uint32_t* __restrict__ khi, uint32_t* __restrict__ id_base,
     int32_t* __restrict__ flag, uint32_t* __restrict__ maxlen_bits, float* __restrict__ recin) {
-  constexpr uint32_t W = kSmallThreads / kWave, N = kSmallThreads * R;
-  __shared__ uint32_t lkey[N];
-  __shared__ uint16_t lval[N];
-  __shared__ uint32_t wcnt[W][256];
-  __shared__ uint32_t wsum[4];
+  __shared__ BlockSortLds<R, uint16_t> L;
   __shared__ uint32_t sbad;
-  const uint32_t tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
-  const uint32_t k = blockIdx.x < d ? blockIdx.x : 0u;  // dimension; array d (d = 1): its upper bounds
+  const uint32_t tid = threadIdx.x;
+  // dimension blockIdx.x, or (d = 1, second workgroup) the upper bounds
+  const uint32_t k = blockIdx.x < d ? blockIdx.x : 0u;
   const bool upper = blockIdx.x >= d;
-  const uint32_t base = wave * (R * kWave) + lane;
   if (tid == 0) sbad = 0;
   uint32_t key[R], val[R];
   bool bad = false;
@@ -191,13 +184,13 @@ __global__ __launch_bounds__(kSmallThreads) void build_small_kernel(
     float a[R], b[R];
 #pragma unroll
     for (uint32_t r = 0; r < R; ++r) {
-      const uint32_t i = base + r * kWave;
+      const uint32_t i = block_sort_index<R>(r);
       a[r] = i < n ? lo[(size_t)k * n + i] : 0.f;
       b[r] = i < n ? hi[(size_t)k * n + i] : 0.f;
     }
 #pragma unroll
     for (uint32_t r = 0; r < R; ++r) {
-      const uint32_t i = base + r * kWave;
+      const uint32_t i = block_sort_index<R>(r);
       key[r] = f2key(upper ? b[r] : a[r]);
       val[r] = i;
       bad = bad || !valid_extent(a[r], b[r]);
@@ -211,7 +204,7 @@ __global__ __launch_bounds__(kSmallThreads) void build_small_kernel(
       float a[R], b[R];
 #pragma unroll
       for (uint32_t r = 0; r < R; ++r) {
-        const uint32_t i = base + r * kWave;
+        const uint32_t i = block_sort_index<R>(r);
         a[r] = i < n ? lo[(size_t)kk * n + i] : 0.f;
         b[r] = i < n ? hi[(size_t)kk * n + i] : 0.f;
       }
@@ -220,64 +213,10 @@ __global__ __launch_bounds__(kSmallThreads) void build_small_kernel(
     }
   __syncthreads();
   if (bad) sbad = 1;
-  for (uint32_t pass = 0; pass < 4; ++pass) {
-    const uint32_t shift = 8u * pass;
-    for (uint32_t i = lane; i < 256; i += kWave) wcnt[wave][i] = 0;
-    uint32_t loc[R];
-    // (a wavefront's own counters: LDS operations of one wavefront are in order)
-#pragma unroll
-    for (uint32_t r = 0; r < R; ++r) {
-      const bool valid = base + r * kWave < n;
-      const uint32_t dig = (key[r] >> shift) & 255u;
-      const uint64_t peers = match_digit8(dig, ballot(valid));
-      const uint32_t rk = mask_rank(peers);
-      const uint32_t c = valid ? wcnt[wave][dig] : 0u;
-      loc[r] = c + rk;
-      if (valid && rk == 0) wcnt[wave][dig] = c + (uint32_t)__popcll(peers);
-    }
-    __syncthreads();
-    // digit tid: the wavefronts' counts become offsets within the digit, then
-    // the digits are placed
-    uint32_t tot = 0, inc = 0;
-    if (tid < 256) {
-#pragma unroll
-      for (uint32_t w = 0; w < W; ++w) tot += wcnt[w][tid];
-      inc = wave_scan_dpp(tot);
-      if (lane == kWave - 1) wsum[wave] = inc;
-    }
-    __syncthreads();
-    if (tid < 256) {
-      uint32_t run = inc - tot;
-      for (uint32_t w = 0; w < wave; ++w) run += wsum[w];
-#pragma unroll
-      for (uint32_t w = 0; w < W; ++w) {
-        const uint32_t c = wcnt[w][tid];
-        wcnt[w][tid] = run;
-        run += c;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t r = 0; r < R; ++r) {
-      if (base + r * kWave < n) {
-        const uint32_t at = wcnt[wave][(key[r] >> shift) & 255u] + loc[r];
-        lkey[at] = key[r];
-        lval[at] = (uint16_t)val[r];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t r = 0; r < R; ++r) {
-      const uint32_t i = base + r * kWave;
-      if (i < n) {
-        key[r] = lkey[i];
-        val[r] = lval[i];
-      }
-    }
-  }
+  block_sort<R>(L, key, val, n, 4);
 #pragma unroll
   for (uint32_t r = 0; r < R; ++r) {
-    const uint32_t i = base + r * kWave;
+    const uint32_t i = block_sort_index<R>(r);
     if (i < n) {
       if (upper) {
         khi[i] = key[r];
@@ -559,9 +498,17 @@ __global__ void upd_keys_kernel(TreePtrs A, const uint32_t* __restrict__ ids,
 __global__ void upd_order_kernel(TreePtrs A, int32_t* __restrict__ flag) {
   const uint32_t k = blockIdx.y;
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i + 1 >= A.n) return;
-  const uint32_t a = A.key[k][i], b = A.key[k][i + 1];
-  if (a > b || (a == b && A.id[k][i + 1] > A.id[k][i + 2])) atomicOr(flag, 8);
+  bool bad = false;
+  if (i + 1 < A.n) {
+    const uint32_t a = A.key[k][i], b = A.key[k][i + 1];
+    bad = a > b || (a == b && A.id[k][i + 1] > A.id[k][i + 2]);
+  }
+  // at most one atomic per workgroup, and none once the bit is seen: they queue
+  // on the word (20,000 of 5*10^5 moved: 21 us, 48 without the look; 88 us with
+  // one per entry and 5000 moved)
+  if (__syncthreads_or(bad) && threadIdx.x == 0 &&
+      !(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 8))
+    atomicOr(flag, 8);
 }
 
 // the moved extents into their record of every tree
@@ -713,6 +660,260 @@ static ddm_status tree_update(ddm_tree* t, const uint32_t* ids, const float* nlo
   upd_scatter_kernel<<<(count + 255) / 256, 256, 0, s>>>(ids, nlo, nhi, count, n, d, lo, hi);
   DDM_LAUNCHED("upd_scatter_kernel");
   return enqueue_tree_build(t, lo, hi, s);
+}
+
+// ---------------------------------------------------------------------------
+// Few moves of a resident tree (d > 1): the sorted arrays stay sorted but for
+// the moved entries, so every tree is merged instead of sorted again.  The
+// moved entries are sorted by their old and by their new (key, id), one
+// workgroup each; then every tile of old positions knows from three searches
+// how many moved entries left and came before it, and every entry its new
+// position.  The moved ids come in ascending order, distinct and checked.
+// 5000 of 5*10^5 squares: 38 us in place of 84 us of keys and sort passes
+// and 145 us for the order check and the set read back.
+// ---------------------------------------------------------------------------
+struct MoveArgs {
+  const uint32_t* sid;  // c moved ids, ascending
+  const float* lo;      // their new extents [d][c]
+  const float* hi;
+  const uint32_t* bits;        // the moved ids as a bitmap
+  uint32_t* mkey[2 * DDM_MAX_D];  // array 2k: sorted old keys of dimension k, 2k + 1: new keys
+  uint32_t* midx[2 * DDM_MAX_D];  // their places in sid
+  uint32_t* key[DDM_MAX_D];    // the merged keys (0..n-1)
+  uint32_t* id[DDM_MAX_D];     // and ids (positions 1..n)
+  const uint32_t* okey[DDM_MAX_D];  // the tree's own
+  const uint32_t* oid[DDM_MAX_D];
+  float* rid;
+  uint32_t* maxlen_bits;
+  uint32_t c, n, d;
+};
+
+template <int R>
+__global__ __launch_bounds__(kBlockSortThreads) void move_sort_kernel(MoveArgs A) {
+  __shared__ BlockSortLds<R, uint16_t> L;
+  const uint32_t k = blockIdx.x >> 1;
+  const bool fresh = blockIdx.x & 1u;
+  uint32_t id[R], key[R], val[R];
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = block_sort_index<R>(r);
+    id[r] = i < A.c ? A.sid[i] : A.n;
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = block_sort_index<R>(r);
+    const bool ok = i < A.c && id[r] < A.n;  // (ids are only checked when the host has read the flag)
+    const float v = !ok ? 0.f
+                    : fresh ? A.lo[(size_t)k * A.c + i]
+                            : A.rid[((size_t)id[r] * A.d + k) * 2];
+    key[r] = f2key(v);
+    val[r] = i;
+  }
+  block_sort<R>(L, key, val, A.c, 4);
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = block_sort_index<R>(r);
+    if (i < A.c) {
+      A.mkey[blockIdx.x][i] = key[r];
+      A.midx[blockIdx.x][i] = val[r];
+    }
+  }
+}
+
+// moved entries (array a, sorted) below (x, id), by one wavefront
+__device__ __forceinline__ uint32_t move_count_below(const MoveArgs& A, uint32_t a, uint32_t x,
+                                                     uint32_t id) {
+  uint32_t at = 0, len = A.c;
+  while (len) {
+    const uint32_t step = (len + kWave - 1) / kWave;
+    const uint32_t o = lane_id() * step + step - 1;
+    bool less = false;
+    if (o < len) {
+      const uint32_t y = A.mkey[a][at + o];
+      less = y < x || (y == x && A.sid[A.midx[a][at + o]] < id);
+    }
+    const uint32_t full = (uint32_t)__popcll(ballot(less)) * step;
+    at += full;
+    len = min(step - 1, len - full);
+  }
+  return at;
+}
+
+constexpr uint32_t kMoveTile = 2048, kMoveThreads = 256, kMoveCache = 1024;
+
+__global__ __launch_bounds__(kMoveThreads) void move_merge_kernel(MoveArgs A) {
+  constexpr uint32_t R = kMoveTile / kMoveThreads, W = kMoveThreads / kWave;
+  __shared__ uint32_t lk[kMoveTile], li[kMoveTile];
+  __shared__ uint16_t gone[kMoveTile];  // moved entries before each, within the tile
+  __shared__ uint32_t ck[kMoveCache], ci[kMoveCache];  // the entries that come into the tile
+  __shared__ uint32_t wgone[R * W + 1];
+  __shared__ uint32_t bound[3];
+  const uint32_t k = blockIdx.y, tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+  const uint32_t p0 = blockIdx.x * kMoveTile, tn = min(kMoveTile, A.n - p0);
+  const uint32_t* __restrict__ okey = A.okey[k];
+  const uint32_t* __restrict__ oid = A.oid[k] + 1;
+  uint32_t key[R], id[R];
+  bool mv[R];
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = r * kMoveThreads + tid;
+    key[r] = i < tn ? okey[p0 + i] : 0u;
+    id[r] = i < tn ? oid[p0 + i] : 0u;
+  }
+  // wavefront 0: moved entries whose old place is before the tile; 1: new
+  // places before it; 2: new places before the next tile
+  if (wave < 3) {
+    const uint32_t at = wave < 2 ? p0 : p0 + kMoveTile;
+    uint32_t v;
+    if (at >= A.n)
+      v = A.c;
+    else if (at == 0)
+      v = 0;
+    else
+      v = move_count_below(A, 2 * k + (wave ? 1u : 0u), okey[at], oid[at]);
+    if (lane == 0) bound[wave] = v;
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = r * kMoveThreads + tid;
+    mv[r] = i < tn && ((A.bits[id[r] >> 5] >> (id[r] & 31u)) & 1u);
+    lk[i] = key[r];
+    li[i] = id[r];
+    const uint64_t b = ballot(mv[r]);
+    if (lane == 0) wgone[r * W + wave] = (uint32_t)__popcll(b);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const uint32_t v = lane < R * W ? wgone[lane] : 0u;
+    const uint32_t inc = wave_scan_dpp(v);
+    if (lane < R * W) wgone[lane] = inc - v;
+    if (lane == R * W - 1) wgone[R * W] = inc;
+  }
+  const uint32_t o0 = bound[0], i0 = bound[1], i1 = bound[2];
+  const uint32_t* __restrict__ nk = A.mkey[2 * k + 1];
+  const uint32_t* __restrict__ ni = A.midx[2 * k + 1];
+  const bool cached = i1 - i0 <= kMoveCache;
+  if (cached)
+    for (uint32_t q = i0 + tid; q < i1; q += kMoveThreads) {
+      ck[q - i0] = nk[q];
+      ci[q - i0] = A.sid[ni[q]];
+    }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    const uint32_t i = r * kMoveThreads + tid;
+    const uint32_t g = wgone[r * W + wave] + mask_rank(ballot(mv[r]));
+    gone[i] = (uint16_t)g;
+    if (i < tn && !mv[r]) {
+      uint32_t at = i0, len = i1 - i0;
+      while (len) {
+        const uint32_t half = len >> 1, q = at + half;
+        const uint32_t y = cached ? ck[q - i0] : nk[q];
+        const bool less = y < key[r] ||
+                          (y == key[r] && (cached ? ci[q - i0] : A.sid[ni[q]]) < id[r]);
+        at = less ? q + 1 : at;
+        len = less ? len - half - 1 : half;
+      }
+      const uint32_t dst = p0 + i - (o0 + g) + at;
+      if (dst < A.n) {
+        A.key[k][dst] = key[r];
+        A.id[k][dst + 1] = id[r];
+      }
+    }
+  }
+  __syncthreads();
+  for (uint32_t q = i0 + tid; q < i1; q += kMoveThreads) {
+    const uint32_t x = nk[q], slot = ni[q], who = A.sid[slot];
+    uint32_t at = 0, len = tn;
+    while (len) {
+      const uint32_t half = len >> 1, j = at + half;
+      const bool less = lk[j] < x || (lk[j] == x && li[j] < who);
+      at = less ? j + 1 : at;
+      len = less ? len - half - 1 : half;
+    }
+    const uint32_t g = o0 + (at < tn ? (uint32_t)gone[at] : wgone[R * W]);
+    const uint32_t dst = q + p0 + at - g;
+    if (dst < A.n) {
+      A.key[k][dst] = x;
+      A.id[k][dst + 1] = who;
+    }
+    *reinterpret_cast<float2*>(A.rid + ((size_t)who * A.d + k) * 2) =
+        make_float2(A.lo[(size_t)k * A.c + slot], A.hi[(size_t)k * A.c + slot]);
+  }
+  if (blockIdx.x == 0 && tid == 0) A.maxlen_bits[k] = 0;
+}
+
+bool tree_move_ok(const ddm_tree* t, uint32_t count) {
+  return t->d > 1 && count <= kTreeMoveMax && count <= t->n;
+}
+
+size_t tree_move_words(const ddm_tree* t, uint32_t count) {
+  return 4 * (size_t)t->d * count + t->d * (2 * (size_t)t->n + 1);
+}
+
+static MoveArgs move_args(const ddm_tree* t, const TreeMove& M) {
+  MoveArgs A{};
+  A.sid = M.sid;
+  A.lo = M.lo;
+  A.hi = M.hi;
+  A.bits = M.bits;
+  A.c = M.count;
+  A.n = t->n;
+  A.d = t->d;
+  A.rid = t->rid;
+  A.maxlen_bits = (uint32_t*)t->maxlen;
+  uint32_t* p = M.words;
+  for (uint32_t a = 0; a < 2 * t->d; ++a) {
+    A.mkey[a] = p;
+    A.midx[a] = p + M.count;
+    p += 2 * (size_t)M.count;
+  }
+  for (uint32_t k = 0; k < t->d; ++k) {
+    A.key[k] = p;
+    A.id[k] = p + t->n;
+    p += 2 * (size_t)t->n + 1;
+    A.okey[k] = t->skey_lo[k];
+    A.oid[k] = t->id[k];
+  }
+  return A;
+}
+
+ddm_status tree_move_sort(const ddm_tree* t, const TreeMove& M, hipStream_t s) {
+  static_assert(kTreeMoveMax <= 8 * kBlockSortThreads, "the largest sort");
+  const MoveArgs A = move_args(t, M);
+#define DDM_MOVE(R) move_sort_kernel<R><<<2 * t->d, kBlockSortThreads, 0, s>>>(A)
+  switch ((M.count + kBlockSortThreads - 1) / kBlockSortThreads) {
+    case 1: DDM_MOVE(1); break;
+    case 2: DDM_MOVE(2); break;
+    case 3: DDM_MOVE(3); break;
+    case 4: DDM_MOVE(4); break;
+    case 5: DDM_MOVE(5); break;
+    case 6: DDM_MOVE(6); break;
+    default: DDM_MOVE(8); break;
+  }
+#undef DDM_MOVE
+  DDM_LAUNCHED("move_sort_kernel");
+  return DDM_OK;
+}
+
+ddm_status tree_move_apply(ddm_tree* t, const TreeMove& M, hipStream_t s) {
+  const MoveArgs A = move_args(t, M);
+  {
+    // learned-sizing statistics describe the old set
+    std::lock_guard<std::mutex> lk(t->fmu);
+    t->fstats_ready = false;
+  }
+  move_merge_kernel<<<dim3((t->n + kMoveTile - 1) / kMoveTile, t->d), kMoveThreads, 0, s>>>(A);
+  DDM_LAUNCHED("move_merge_kernel");
+  TreeJobs J = make_jobs(t, nullptr, nullptr);
+  for (uint32_t k = 0; k < t->d; ++k) {
+    J.j[k].recin = t->rid;
+    J.j[k].id = A.id[k];
+    J.j[k].skey_lo = A.key[k];
+    J.j[k].id_out = t->id[k];
+    J.j[k].key_out = t->skey_lo[k];
+  }
+  return enqueue_tree_passes(t, J, true, s);
 }
 
 // Enqueue the feature statistics on stream s the first time a learned match

@@ -25,6 +25,8 @@ struct TreeJob {
   float* sbox;             // bounding box of every block of 64 of them
   uint32_t n, d, k, P, C, H, ns;
   const float* recin;      // optional: the set as n records (lo_0, hi_0, lo_1, ...)
+  uint32_t* id_out;        // optional: id and skey_lo are scratch and are also kept here
+  uint32_t* key_out;
 };
 
 constexpr int kChunk = 2048;        // positions per workgroup in a maxhi pass
@@ -226,6 +228,10 @@ __device__ __forceinline__ void tree_low_chunk(const TreeJob& J, uint32_t c) {
             l0 = val[it][2 * kk];
             h = val[it][2 * kk + 1];
           }
+        }
+        if (J.id_out) {
+          J.id_out[p] = idx[it];
+          J.key_out[p - 1] = f2key(l0);
         }
         if (valid_extent(l0, h)) lenb = max(lenb, __float_as_uint(nextafterf(h - l0, INFINITY)));
       }
