@@ -173,6 +173,12 @@ __device__ __forceinline__ uint32_t mask_rank(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// the same counted on from `base`
+__device__ __forceinline__ uint32_t mask_rank_from(uint64_t mask, uint32_t base) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, base));
+}
+
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
 // lanes of the wave whose 8-bit digit equals this lane's (restricted to `active`)
@@ -479,8 +485,8 @@ struct ScanWords {
   uint32_t nslices = 0, sfirst = 0, sslice = 0;
   const uint32_t* gcount = nullptr;
   uint32_t d = 0, qpt = 1;
-  const uint64_t* tsum = nullptr;   // [64]
-  const uint32_t* tmax = nullptr;   // [64]
+  const uint64_t* tsum = nullptr;   // [64][tpad]: a sum, then a maximum
+  uint32_t tpad = 1;
 };
 // scan_u32_u64 and the words (out and tmp as there)
 ddm_status scan_counts(const uint32_t* in, uint64_t* out, uint32_t m, uint64_t* tmp,

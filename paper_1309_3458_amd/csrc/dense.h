@@ -12,9 +12,9 @@
 // masks it computes (one bit per test); once the counts are summed and
 // scanned, a second kernel expands the masks into keys at their final places,
 // the only time the pairs move.
-// Measured on that workload, build + match: 20.7 -> 8.3 ms plain and 14.4 -> 7.7
+// Measured on that workload, build + match: 18.9 -> 7.5 ms plain and 13.7 -> 6.8
 // ms learned; 76,543 updates against 123,457 squares (247 pairs each): 0.45 ->
-// 0.28 ms; 250,000 + 250,000 segments (d = 1, 200 pairs each): 0.45 -> 0.41 ms.
+// 0.23 ms; 250,000 + 250,000 segments (d = 1, 200 pairs each): 0.46 -> 0.36 ms.
 #pragma once
 
 #include "traverse.h"
@@ -23,6 +23,11 @@ namespace ddm {
 
 constexpr uint32_t kUnit = 1024;               // candidates of a unit
 constexpr uint32_t kUnitBatches = kUnit / kWave;
+// Units that one workgroup expands, and its wavefronts: long runs of writes where
+// the lists are long; where most tiles have one unit, more and smaller workgroups
+// (250,000 + 250,000 segments, lists of 300: 87 us with 4 units, 63 with one)
+constexpr uint32_t kGroupLong = 4, kGroupShort = 1;
+__host__ __device__ constexpr int expand_waves(uint32_t group) { return group > 1 ? 8 : 4; }
 constexpr int kUnitWaves = 4;
 
 struct DenseUnits {
@@ -30,8 +35,9 @@ struct DenseUnits {
   const uint32_t* list = nullptr;   // candidate ids, ascending within a tile
   uint32_t* ubase = nullptr;        // first unit of each tile
   uint2* umap = nullptr;            // unit -> tile, index within the tile
-  uint32_t* ucount = nullptr;       // units (zeroed beforehand)
-  uint2* bits = nullptr;            // [unit][batch][lane]: hits of the lane's update
+  uint2* gmap = nullptr;            // group of units -> tile, its first unit
+  uint32_t* ucount = nullptr;       // units, groups (zeroed beforehand)
+  uint64_t* bits = nullptr;         // [tile][update][unit][batch]: hits
   uint32_t* ucnt = nullptr;         // [unit][lane]: hits, then those of the units before
 };
 
@@ -106,14 +112,27 @@ __global__ __launch_bounds__(256) void tile_clip_kernel(const uint32_t* __restri
   if (bad && lane_id() == 0) atomicAdd((unsigned long long*)over, (unsigned long long)__popcll(bad));
 }
 
-// units of every tile (one thread per tile), in no particular order
-__global__ __launch_bounds__(256) void dense_units_kernel(DenseUnits U, uint32_t tiles) {
+// units and groups of every tile (one thread per tile), in no particular order; a
+// wavefront takes its places with one atomic for each of the two (8 us at 7800
+// tiles with one a tile, 5 now)
+__global__ __launch_bounds__(256) void dense_units_kernel(DenseUnits U, uint32_t tiles,
+                                                          uint32_t group) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= tiles) return;
-  const uint32_t n = (uint32_t)((U.toff[t + 1] - U.toff[t] + kUnit - 1) / kUnit);
-  const uint32_t b = n ? atomicAdd(U.ucount, n) : 0u;
+  const bool in = t < tiles;
+  const uint32_t n = in ? (uint32_t)((U.toff[t + 1] - U.toff[t] + kUnit - 1) / kUnit) : 0u;
+  const uint32_t g = (n + group - 1) / group;
+  const uint32_t ni = wave_scan_dpp(n), gi = wave_scan_dpp(g);
+  uint32_t b = 0, gb = 0;
+  if (lane_id() == kWave - 1) {
+    b = atomicAdd(U.ucount, ni);
+    gb = atomicAdd(U.ucount + 1, gi);
+  }
+  b = readlane_u32(b, kWave - 1) + ni - n;
+  gb = readlane_u32(gb, kWave - 1) + gi - g;
+  if (!in) return;
   U.ubase[t] = b;
   for (uint32_t i = 0; i < n; ++i) U.umap[b + i] = make_uint2(t, i);
+  for (uint32_t i = 0; i < g; ++i) U.gmap[gb + i] = make_uint2(t, i * group);
 }
 
 // a unit's candidates list[b0 .. b0 + len) and its tile's updates (lane: perm
@@ -121,6 +140,7 @@ __global__ __launch_bounds__(256) void dense_units_kernel(DenseUnits U, uint32_t
 struct UnitSpan {
   uint64_t b0;
   uint32_t len, nq, j;
+  uint32_t y, units;  // the unit's index in its tile, and the tile's units
 };
 template <int D>
 __device__ __forceinline__ UnitSpan unit_span(const DenseUnits& U, const UpdSet& US, uint32_t u,
@@ -128,7 +148,9 @@ __device__ __forceinline__ UnitSpan unit_span(const DenseUnits& U, const UpdSet&
   UnitSpan s;
   const uint2 w = U.umap[u];
   const uint32_t t = uniform_u32(w.x);
-  const uint64_t a = U.toff[t] + (uint64_t)uniform_u32(w.y) * kUnit, e = U.toff[t + 1];
+  s.y = uniform_u32(w.y);
+  const uint64_t o = U.toff[t], a = o + (uint64_t)s.y * kUnit, e = U.toff[t + 1];
+  s.units = uniform_u32((uint32_t)((e - o + kUnit - 1) / kUnit));
   s.b0 = a;
   s.len = uniform_u32((uint32_t)min<uint64_t>(e - a, kUnit));
   uint32_t k, qbeg;
@@ -139,13 +161,17 @@ __device__ __forceinline__ UnitSpan unit_span(const DenseUnits& U, const UpdSet&
 
 // Bound by the tests: 2D + 3 vector instructions for a candidate and 64
 // updates.  The ids of the next batch but one and the records of the next are
-// loaded while a batch is tested.
+// loaded while a batch is tested.  The masks are collected in LDS and written
+// update by update, 8 batches (64 bytes) each; 16 at a time left LDS for four
+// wavefronts a SIMD only (1.86 ms on the 16-hotspot workload, 1.68 with 8).
 template <int D>
 __global__ __launch_bounds__(kUnitWaves * kWave) void dense_test_kernel(
     DenseUnits U, UpdSet US, const float* __restrict__ rid, const float* __restrict__ ulo,
     const float* __restrict__ uhi, uint32_t m) {
   constexpr int R = 2 * D;
   __shared__ __align__(16) float s_cand[kUnitWaves][R * kWave];
+  constexpr uint32_t kHold = 8;
+  __shared__ uint64_t s_bits[kUnitWaves][kWave][kHold + 1];
   const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
   const uint32_t u = uniform_u32(blockIdx.x * kUnitWaves + wave);
   if (u >= uniform_u32(*U.ucount)) return;
@@ -173,16 +199,25 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void dense_test_kernel(
   float v[R], w[R];
   record(0, id_of(0), v);
   uint32_t idn = id_of(1), cnt = 0;
-  uint2* __restrict__ bits = U.bits + (size_t)u * kUnit;
+  uint64_t* __restrict__ bits = U.bits + (size_t)(u - S.y) * kUnit + S.y * kUnitBatches;
   for (uint32_t b = 0; b < nb; ++b) {
     record(b + 1, idn, w);
     idn = id_of(b + 2);
     uint32_t mlo, mhi;
     test_masks<D>(ql, qh, S.nq, v, s_cand[wave], lane, min(S.len - b * kWave, (uint32_t)kWave),
                   true, &mlo, &mhi);
-    bits[b * kWave + lane] = make_uint2(mlo, mhi);  // (0 from lane nq on)
+    s_bits[wave][lane][b % kHold] = (uint64_t)mhi << 32 | mlo;  // (0 from lane nq on)
     cnt += (uint32_t)__popc(mlo) + (uint32_t)__popc(mhi);
     wave_sync();  // the records are read before the next ones are put
+    if (b % kHold == kHold - 1 || b + 1 == nb) {
+      // 4 lanes to an update, two batches each
+      const uint32_t h = b & ~(kHold - 1), c = 2 * (lane & 3u);
+      for (uint32_t q = lane >> 2; q < S.nq; q += kWave / 4)
+        if (h + c < nb)
+          *reinterpret_cast<ulonglong2*>(bits + (size_t)q * S.units * kUnitBatches + h + c) =
+              make_ulonglong2(s_bits[wave][q][c], s_bits[wave][q][c + 1]);
+      wave_sync();
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = w[r];
   }
@@ -216,62 +251,122 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void dense_sum_kernel(DenseUnit
   if (lane < nq) cnt[US.perm[qbeg + lane]] = run;
 }
 
-// Keys from the masks.  The unit's ids and masks are loaded into registers; then
-// one update after the other packs the ids it meets into LDS, batch by batch,
-// and writes them as keys to consecutive places of its segment, 64 at a time and
-// in whole 128-byte lines but for the ends.  Stores straight from the masks (18
-// of 64 lanes active on the 16-hotspot workload) took 38 cycles each whatever
-// they wrote, 6.5 ms for its 1.8*10^9 pairs; with the updates inside the batches
-// each wavefront also had 64 partly written lines open, 8.6 ms; this form
-// 4.6 ms.  Bound by the writes, 8 bytes a pair.
-template <int D>
-__global__ __launch_bounds__(kUnitWaves * kWave) void dense_expand_kernel(
+// Keys from the masks.  A workgroup takes up to GROUP units of a tile, their ids
+// in LDS, and its wavefronts the tile's updates in turn: an update's masks come
+// with one load (a batch to a lane), its ids are packed into LDS, batch by batch,
+// and written as keys to consecutive places of its segment, 64 at a time and in
+// whole 128-byte lines but for the ends of the group.  Bound by the writes, 8
+// bytes a pair.  On the 16-hotspot workload (1.8*10^9 pairs, 18 of 64 candidates
+// are hits): 6.5 ms with stores straight from the masks (38 cycles each whatever
+// they write); 8.6 with the updates inside the batches (64 open lines a
+// wavefront); 4.6 with a unit to a wavefront, ids and masks in registers (runs of
+// 290 pairs, lines written in two parts); 3.9 now, of which the packing alone
+// takes 2.1.
+template <int D, uint32_t GROUP>
+__global__ __launch_bounds__(expand_waves(GROUP) * kWave) void dense_expand_kernel(
     DenseUnits U, UpdSet US, const uint64_t* __restrict__ off, uint64_t* __restrict__ out) {
-  __shared__ uint32_t s_ids[kUnitWaves][kUnit];
-  uint32_t* __restrict__ pack = s_ids[threadIdx.x / kWave];
-  const uint32_t lane = lane_id();
-  const uint32_t u = uniform_u32(blockIdx.x * kUnitWaves + threadIdx.x / kWave);
-  if (u >= uniform_u32(*U.ucount)) return;
-  const UnitSpan S = unit_span<D>(U, US, u, lane);
-  const uint64_t base = lane < S.nq ? off[S.j] + U.ucnt[(size_t)u * kWave + lane] : 0ull;
-  const uint32_t* __restrict__ ids = U.list + S.b0;
-  const uint2* __restrict__ bits = U.bits + (size_t)u * kUnit;
-  const uint32_t nb = (S.len + kWave - 1) / kWave;
-  uint32_t id[kUnitBatches];
-  uint2 mk[kUnitBatches];
-  uint32_t any = 0;
+  constexpr uint32_t kLine = 16;  // keys of a line
+  constexpr uint32_t kPack = kUnit + 2 * kLine;
+  constexpr int kExpandWaves = expand_waves(GROUP);
+  constexpr uint32_t kThreads = kExpandWaves * kWave, kIds = GROUP * kUnit;
+  __shared__ uint32_t s_ids[kIds];
+  __shared__ uint32_t s_pack[kExpandWaves][kPack + 1];  // and one for the lanes without a hit
+  const uint32_t gi = blockIdx.x;
+  if (gi >= uniform_u32(U.ucount[1])) return;
+  const uint32_t lane = lane_id(), wave = uniform_u32(threadIdx.x / kWave);
+  uint32_t* __restrict__ pack = s_pack[wave];
+  const uint2 gw = U.gmap[gi];
+  const uint32_t t = uniform_u32(gw.x), y0 = uniform_u32(gw.y);
+  const uint64_t tb = U.toff[t], te = U.toff[t + 1];
+  const uint32_t u0 = uniform_u32(U.ubase[t]);
+  const uint32_t row = uniform_u32((uint32_t)((te - tb + kUnit - 1) / kUnit)) * kUnitBatches;
+  const uint64_t b0 = tb + (uint64_t)y0 * kUnit;
+  const uint32_t len = uniform_u32((uint32_t)min<uint64_t>(te - b0, kIds));
+  uint32_t v[kIds / kThreads];
 #pragma unroll
-  for (uint32_t b = 0; b < kUnitBatches; ++b) {
-    id[b] = 0;
-    mk[b] = make_uint2(0u, 0u);
-    if (b < nb) {  // (the last batch: no mask has a bit past the unit's end)
-      id[b] = ids[min(b * kWave + lane, S.len - 1u)];
-      mk[b] = bits[b * kWave + lane];
-    }
+  for (uint32_t r = 0; r < kIds / kThreads; ++r) {
+    const uint32_t i = r * kThreads + threadIdx.x;
+    v[r] = i < len ? U.list[b0 + i] : 0u;
   }
+  uint32_t k, qbeg, nq;
+  tile_span<D>(US, t, &k, &qbeg, &nq);
+  const uint32_t j = lane < nq ? US.perm[qbeg + lane] : 0u;
+  // lane: its update's first place of the group
+  const uint64_t base = lane < nq ? off[j] + U.ucnt[(size_t)(u0 + y0) * kWave + lane] : 0ull;
+  const uint32_t nb = (len + kWave - 1) / kWave;
+  // one load brings the masks of kRows updates, a batch to a lane
+  constexpr uint32_t kRow = GROUP * kUnitBatches, kRows = kWave / kRow;
+  static_assert(kRows * kRow == kWave, "whole rows");
+  const uint64_t* __restrict__ masks =
+      U.bits + (size_t)u0 * kUnit + y0 * kUnitBatches + lane % kRow;
+  auto masks_of = [&](uint32_t first) {
+    const uint32_t q = first + lane / kRow;
+    return q < nq && lane % kRow < nb ? masks[(size_t)q * row] : 0ull;
+  };
+  uint64_t next = masks_of(wave * kRows);
 #pragma unroll
-  for (uint32_t b = 0; b < kUnitBatches; ++b) any |= mk[b].x | mk[b].y;
-  uint64_t some = ballot(any != 0);
-  while (some) {
-    const uint32_t q = (uint32_t)__builtin_ctzll(some);
-    some &= some - 1;
-    const uint64_t at = readlane_u64(base, q);
-    const uint64_t jq = (uint64_t)readlane_u32(S.j, q) << 32;
-    uint32_t n = 0;
-#pragma unroll
-    for (uint32_t b = 0; b < kUnitBatches; ++b) {
-      if (b < nb) {
-        const uint64_t m = (uint64_t)readlane_u32(mk[b].y, q) << 32 | readlane_u32(mk[b].x, q);
-        if (lane_of(m)) pack[n + mask_rank(m)] = id[b];
-        n += (uint32_t)__popcll(m);
-      }
+  for (uint32_t r = 0; r < kIds / kThreads; ++r) s_ids[r * kThreads + threadIdx.x] = v[r];
+  __syncthreads();
+  uint64_t mine = 0, some = 0;
+  for (uint32_t i = 0, q = wave * kRows; q < nq; ++i) {
+    const uint32_t r = i % kRows;
+    if (r == 0) {
+      mine = next;
+      next = masks_of(q + kExpandWaves * kRows);
+      some = ballot(mine != 0);
     }
-    wave_sync();
-    // from the start of the line the run begins in
-    const uint32_t skip = (uint32_t)(((uintptr_t)(out + at) >> 3) & 15u);
+    const uint32_t here = q, r0 = r * kRow;
+    q += r == kRows - 1 ? (kExpandWaves - 1) * kRows + 1 : 1;
+    if (!((some >> r0) & (~0ull >> (kWave - kRow)))) continue;
+    const uint64_t at = readlane_u64(base, here);
+    const uint32_t who = readlane_u32(j, here);
+    // from the start of the line the run begins in: pack[i] goes to dst[i]
+    uint32_t skip = (uint32_t)(((uintptr_t)(out + at) >> 3) & (kLine - 1));
     uint64_t* __restrict__ dst = out + at - skip;
-    for (uint32_t i = lane; i < n + skip; i += kWave)
-      if (i >= skip) dst[i] = jq | pack[i - skip];
+    uint32_t n = skip;
+#pragma unroll
+    for (uint32_t y = 0; y < GROUP; ++y) {
+      const bool last = (y + 1) * kUnitBatches >= nb;
+#pragma unroll
+      for (uint32_t c = 0; c < kUnitBatches; c += 4) {
+        if (y * kUnitBatches + c < nb) {
+#pragma unroll
+          for (uint32_t b = y * kUnitBatches + c; b < y * kUnitBatches + c + 4; ++b) {
+            const uint64_t m = readlane_u64(mine, r0 + b);
+            const uint32_t to = mask_rank_from(m, n);
+            pack[lane_of(m) ? to : kPack] = s_ids[b * kWave + lane];
+            n += (uint32_t)__popcll(m);
+          }
+        }
+      }
+      wave_sync();
+      // to the end of the run, or to the last line that is full
+      const uint32_t end = last ? n : n & ~(kLine - 1);
+      for (uint32_t i0 = 0; i0 < end; i0 += 4 * kWave) {
+        uint32_t p[4];  // (their reads are in flight together)
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) p[r] = pack[min(i0 + r * kWave + lane, kPack)];
+        uint64_t* __restrict__ to = dst + i0;
+        const uint32_t room = end - i0;
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+          const uint32_t i = r * kWave + lane;
+          if (i < room && (r > 0 || i0 + lane >= skip)) to[i] = (uint64_t)who << 32 | p[r];
+        }
+      }
+      if (last) break;
+      if (end) {  // what is left moves to the front
+        if (end + lane < n) {
+          const uint32_t w = pack[end + lane];
+          wave_sync();
+          pack[lane] = w;
+        }
+        n -= end;
+        dst += end;
+        skip = 0;
+      }
+      wave_sync();
+    }
     wave_sync();
   }
 }

@@ -412,8 +412,7 @@ __global__ __launch_bounds__(1024) void order_small_kernel(
     const uint32_t* __restrict__ bucket, uint32_t m, uint32_t* __restrict__ perm,
     uint32_t* __restrict__ gstart, uint32_t* __restrict__ gcount, int32_t* __restrict__ flag,
     uint32_t* __restrict__ lists_count, uint32_t* __restrict__ snext, uint32_t sfirst,
-    uint32_t sslice, uint64_t* __restrict__ tsum,
-    uint32_t* __restrict__ tmaxs) {
+    uint32_t sslice, uint64_t* __restrict__ tsum) {
   constexpr uint32_t R = kSmallOrder / 1024, C = D * kSmallCells, PER = C / 1024;
   static_assert(C % 1024 == 0, "whole rounds");
   __shared__ uint32_t cnt[C];
@@ -432,8 +431,8 @@ __global__ __launch_bounds__(1024) void order_small_kernel(
   for (uint32_t r = 0; r < PER; ++r) cnt[r * 1024 + tid] = 0;
   if (tid < 2) lists_count[tid] = 0;
   if (tid < kListSlices) {
-    tsum[tid] = 0;
-    tmaxs[tid] = 0;
+    tsum[tid * kListPad] = 0;
+    tsum[tid * kListPad + 1] = 0;
   }
   if (snext)
     for (uint32_t i = tid; i < kStashSlices; i += 1024) snext[i] = sfirst + i * sslice;
@@ -1740,14 +1739,13 @@ struct MatchState {
   bool stash_ok = false;
   // candidates of the tiles (counted when the set is dense)
   uint32_t* tcand = nullptr;   // per tile
-  uint64_t* tsum = nullptr;    // [kListSlices] sums
-  uint32_t* tmaxs = nullptr;   // [kListSlices] maxima
+  uint64_t* tsum = nullptr;    // [kListSlices][kListPad]: sum, then maximum
   bool may_dense = false;      // the caller allows the scratch of the dense form
   bool dense = false;          // the units hold the hits
   bool plain_fill = false;     // learned, but neither slots nor units: a fill by the counts
   Scratch dense_sc;
   DenseUnits units;
-  uint32_t units_max = 0;
+  uint32_t groups_max = 0, group = 1;  // groups of units at most, units of each
   // no allocation of any kind (the scratch is external, the read-back goes
   // to pageable host memory): the no-allocation entry point
   bool noalloc = false;
@@ -1769,15 +1767,15 @@ struct MatchState {
 // slices' next free chunks
 __global__ __launch_bounds__(1024) void match_init_kernel(
     int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
-    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum, uint32_t* __restrict__ tmaxs) {
+    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum) {
   static_assert(kCells % 1024 == 0, "whole workgroups");
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   bcnt[(size_t)i * kCntPad] = 0;
   if (i == 0) *flag = 0;
   if (i < 2) lists_count[i] = 0;
   if (i < kListSlices) {
-    tsum[i] = 0;
-    tmaxs[i] = 0;
+    tsum[i * kListPad] = 0;
+    tsum[i * kListPad + 1] = 0;
   }
   if (snext && i < kStashSlices) snext[i] = sfirst + i * sslice;
 }
@@ -1793,8 +1791,7 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
   const bool small = m <= kSmallOrder;
   if (!small) {
     match_init_kernel<<<D * kCells / 1024, 1024, 0, s>>>(st.flag, lists_count, st.bcnt, sn,
-                                                         st.sfirst, st.sslice, st.tsum,
-                                                         st.tmaxs);
+                                                         st.sfirst, st.sslice, st.tsum);
     DDM_LAUNCHED("match_init_kernel");
   }
   if constexpr (D == 1) {
@@ -1826,7 +1823,7 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
   if (small) {
     order_small_kernel<D><<<1, 1024, 0, s>>>(st.bucket, m, st.perm, st.gstart, st.gcount, st.flag,
                                              lists_count, sn, st.sfirst, st.sslice,
-                                             st.tsum, st.tmaxs);
+                                             st.tsum);
     DDM_LAUNCHED("order_small_kernel");
     return DDM_OK;
   }
@@ -1968,8 +1965,7 @@ static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
   sc.reserve(sizeof(uint64_t) * 8);              // device words for readback
   sc.reserve(sizeof(uint32_t) * 2 * (size_t)m);       // candidate position bounds
   sc.reserve(sizeof(uint32_t) * stash_tiles(m));      // candidates per tile
-  sc.reserve(sizeof(uint64_t) * kListSlices);         // their sums
-  sc.reserve(sizeof(uint32_t) * kListSlices);         // and maxima
+  sc.reserve(sizeof(uint64_t) * kListSlices * kListPad);  // their sums and maxima
 }
 
 static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, FrontPieces* fp) {
@@ -1993,8 +1989,7 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
   fp->dwords = sc.take<uint64_t>(8);
   st.pb = sc.take<uint32_t>(2 * (size_t)m);
   st.tcand = sc.take<uint32_t>(stash_tiles(m));
-  st.tsum = sc.take<uint64_t>(kListSlices);
-  st.tmaxs = sc.take<uint32_t>(kListSlices);
+  st.tsum = sc.take<uint64_t>(kListSlices * kListPad);
   if (learned) {
     st.X = sc.take<float>((size_t)m * kFeatures);
     st.cap = sc.take<uint32_t>(m);
@@ -2072,14 +2067,17 @@ static ddm_status dense_units(const ddm_tree* t, const TreeDev& T, const float* 
   *made = false;
   if (total > kDenseMaxCandidates || tiles == 0) return DDM_OK;
   const uint64_t umax = total / kUnit + tiles;
+  st.group = total > 2ull * kUnit * tiles ? kGroupLong : kGroupShort;
+  const uint64_t gmax = std::min<uint64_t>(umax, umax / st.group + tiles);
   Scratch& sc = st.dense_sc;  // until the pairs are written
   sc.drop();
   sc.reserve(sizeof(uint64_t) * ((size_t)tiles + 1));
   sc.reserve(sizeof(uint32_t) * std::max<uint64_t>(total, 1));
   sc.reserve(sizeof(uint32_t) * tiles);
   sc.reserve(sizeof(uint2) * umax);
+  sc.reserve(sizeof(uint2) * gmax);
   sc.reserve(sizeof(uint32_t) * 4);
-  sc.reserve(sizeof(uint2) * kUnit * umax);
+  sc.reserve(sizeof(uint64_t) * kUnit * umax);
   sc.reserve(sizeof(uint32_t) * kWave * umax);
   Scratch tc(s);              // until the lists are sorted
   tc.reserve(sizeof(uint32_t) * std::max<uint64_t>(total, 1));
@@ -2097,8 +2095,9 @@ static ddm_status dense_units(const ddm_tree* t, const TreeDev& T, const float* 
   uint32_t* sorted = sc.take<uint32_t>(std::max<uint64_t>(total, 1));
   U.ubase = sc.take<uint32_t>(tiles);
   U.umap = sc.take<uint2>(umax);
+  U.gmap = sc.take<uint2>(gmax);
   U.ucount = sc.take<uint32_t>(4);  // and the two counters of the sort's lists
-  U.bits = sc.take<uint2>((size_t)kUnit * umax);
+  U.bits = sc.take<uint64_t>((size_t)kUnit * umax);
   U.ucnt = sc.take<uint32_t>((size_t)kWave * umax);
   uint32_t* raw = tc.take<uint32_t>(std::max<uint64_t>(total, 1));
   uint32_t* lists = tc.take<uint32_t>(2 * (size_t)tiles);
@@ -2108,7 +2107,7 @@ static ddm_status dense_units(const ddm_tree* t, const TreeDev& T, const float* 
   if (!sc.fits() || !tc.fits()) return scratch_overrun("dense match");
   U.toff = toff;
   U.list = sorted;
-  st.units_max = (uint32_t)umax;
+  st.groups_max = (uint32_t)gmax;
   zero_u32_kernel<<<1, 64, 0, s>>>(U.ucount, 4);
   DDM_LAUNCHED("zero_u32_kernel");
   SegOut O{};
@@ -2129,7 +2128,6 @@ static ddm_status dense_units(const ddm_tree* t, const TreeDev& T, const float* 
     O.base = roff;
     O.tcand = st.tcand;
     O.tsum = st.tsum;
-    O.tmax = st.tmaxs;
     r = list_any(d, T, ulo, uhi, m, US, O, s);
     if (r != DDM_OK) return r;
     tile_clip_kernel<<<(tiles + 255) / 256, 256, 0, s>>>(st.tcand, room, tiles, len, over);
@@ -2142,11 +2140,11 @@ static ddm_status dense_units(const ddm_tree* t, const TreeDev& T, const float* 
   }
   {
     ProfScope ps("listsort", s);
-    r = sort_segments_window(toff, tiles, sorted, tree_n(t), lists, U.ucount + 1, s, S, longest);
+    r = sort_segments_window(toff, tiles, sorted, tree_n(t), lists, U.ucount + 2, s, S, longest);
     if (r != DDM_OK) return r;
   }
   ProfScope ps("dense_test", s);
-  dense_units_kernel<<<(tiles + 255) / 256, 256, 0, s>>>(U, tiles);
+  dense_units_kernel<<<(tiles + 255) / 256, 256, 0, s>>>(U, tiles, st.group);
   DDM_LAUNCHED("dense_units_kernel");
   const uint32_t g = (uint32_t)((umax + kUnitWaves - 1) / kUnitWaves), th = kUnitWaves * kWave;
   const uint32_t gt = (tiles + kUnitWaves - 1) / kUnitWaves;
@@ -2193,14 +2191,21 @@ static ddm_status predict_room(const ddm_tree* t, const float* ulo, const float*
 // the pairs of the units, at their final places
 static ddm_status dense_expand(uint32_t d, const MatchState& st, uint64_t* out, hipStream_t s) {
   ProfScope ps(st.learned ? "traverse_tile_fill_balanced" : "traverse_tile_fill_units", s);
-  const uint32_t g = (st.units_max + kUnitWaves - 1) / kUnitWaves, th = kUnitWaves * kWave;
   const UpdSet US = st.all();
+#define DDM_EXPAND(DD)                                                                          \
+  if (st.group == kGroupLong)                                                                   \
+    dense_expand_kernel<DD, kGroupLong>                                                         \
+        <<<st.groups_max, expand_waves(kGroupLong) * kWave, 0, s>>>(st.units, US, st.off, out); \
+  else                                                                                          \
+    dense_expand_kernel<DD, kGroupShort>                                                        \
+        <<<st.groups_max, expand_waves(kGroupShort) * kWave, 0, s>>>(st.units, US, st.off, out)
   switch (d) {
-    case 1: dense_expand_kernel<1><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
-    case 2: dense_expand_kernel<2><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
-    case 3: dense_expand_kernel<3><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
-    default: dense_expand_kernel<4><<<g, th, 0, s>>>(st.units, US, st.off, out); break;
+    case 1: DDM_EXPAND(1); break;
+    case 2: DDM_EXPAND(2); break;
+    case 3: DDM_EXPAND(3); break;
+    default: DDM_EXPAND(4); break;
   }
+#undef DDM_EXPAND
   DDM_LAUNCHED("dense_expand_kernel");
   return DDM_OK;
 }
@@ -2368,8 +2373,7 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
       O.sslice = st.sslice;
       O.tcand = st.tcand;
       O.tsum = st.tsum;
-      O.tmax = st.tmaxs;
-    }
+      }
     r = traverse_any<false>(d, P, T, ulo, uhi, m, st.all(), st.kstar, O, s);
     if (r != DDM_OK) return r;
     counts = st.cnt;
@@ -2395,7 +2399,7 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   W.d = d;
   W.qpt = tile_updates(m);
   W.tsum = st.tsum;
-  W.tmax = st.tmaxs;
+  W.tpad = kListPad;
   static_assert(kListSlices == kWave, "one lane per slice");
   auto offsets = [&]() -> ddm_status {
     W.snext = st.stash ? st.snext : nullptr;
@@ -2480,7 +2484,6 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     SegOut O{};
     O.tcand = st.tcand;
     O.tsum = st.tsum;
-    O.tmax = st.tmaxs;
     r = list_any(d, T, ulo, uhi, m, st.all(), O, s);
     if (r == DDM_OK) r = offsets();
     if (r == DDM_OK) r = read_words();

@@ -756,11 +756,12 @@ __device__ __forceinline__ void write_scan_words(const ScanWords& W, uint64_t to
   mx = wave_fold_dpp(mx, [](uint32_t a, uint32_t b) { return max(a, b); });
   uint32_t tiles = 0;
   for (uint32_t g = 0; g < W.d; ++g) tiles += (W.gcount[g] + W.qpt - 1) / W.qpt;
-  uint64_t ts = W.tsum[lane];
+  uint64_t ts = W.tsum[(size_t)lane * W.tpad];
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) ts += __shfl_xor(ts, o, kWave);
   const uint32_t tm =
-      wave_fold_dpp(W.tmax[lane], [](uint32_t a, uint32_t b) { return max(a, b); });
+      wave_fold_dpp((uint32_t)W.tsum[(size_t)lane * W.tpad + 1],
+                    [](uint32_t a, uint32_t b) { return max(a, b); });
   if (lane == 0) {
     W.dst[0] = total;
     W.dst[1] = (uint64_t)(uint32_t)(*W.tflag) | ((uint64_t)(uint32_t)(*W.uflag) << 32);

@@ -158,7 +158,9 @@ constexpr uint32_t kStashStatic = 2;
 constexpr uint32_t kStashSlices = 256;
 // snext[kStashSlices]: 1 overflow, 2 (set before the count) a dense set
 constexpr uint32_t kStashDense = 2;
-constexpr uint32_t kListSlices = 64;
+// (a slice has a line of its own, sum and maximum: with the slices packed, the
+// atomics of 7800 tiles queued on six lines, 46 us for a traversal that takes 17)
+constexpr uint32_t kListSlices = 64, kListPad = 16;
 constexpr uint32_t kStashGrab = 4;  // at least this many counted chunks per request
 // at most 2^28 stashed hits (4 GiB of stash); larger results overflow it and
 // take the fill traversal
@@ -191,7 +193,6 @@ struct SegOut {
   // they fit, to ids[base[t] .. base[t + 1])
   uint32_t* tcand = nullptr;
   uint64_t* tsum = nullptr;
-  uint32_t* tmax = nullptr;
 };
 
 __device__ __forceinline__ bool upd_index(const UpdSet& U, uint32_t t, uint32_t d,
@@ -649,8 +650,9 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
   if (listing) {
     if (O.tcand && lane == 0) {
       O.tcand[tile_id] = tail;
-      atomicAdd((unsigned long long*)(O.tsum + tile_id % kListSlices), (unsigned long long)tail);
-      atomicMax(O.tmax + tile_id % kListSlices, tail);
+      uint64_t* __restrict__ slice = O.tsum + (size_t)(tile_id % kListSlices) * kListPad;
+      atomicAdd((unsigned long long*)slice, (unsigned long long)tail);
+      atomicMax(reinterpret_cast<uint32_t*>(slice + 1), tail);
     }
     if (MODE == kTileList) return;
   }
