@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kProbeThreads) void b_probe_kernel(const BInst* __r
       sub = (uint32_t)(((uint64_t)(bad ? 0u : res[0]) * b.nb) / ((uint64_t)b.n + 1));
     } else {
       // class and cell as in the single-instance matcher: dimension 0 unless
-      // another one's range is less than half as long, cells of quantile
+      // another one's range is less than a third as long, cells of quantile
       // ranges along a serpentine
       uint32_t best = 0, mid[DDM_MAX_D];
 #pragma unroll
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kProbeThreads) void b_probe_kernel(const BInst* __r
             quant_count(sq[k], f2key(nextafterf(a - b.T.maxlen[k], -INFINITY)), false);
         mid[k] = quant_count(sq[k], f2key(0.5f * a + 0.5f * c), true);
         const uint32_t est = qa - min(qa, qb);
-        if (k == 0 || 2u * est + 16u < best) {
+        if (k == 0 || 3u * est + 16u < best) {
           best = est;
           bk = k;
         }

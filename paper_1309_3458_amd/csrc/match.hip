@@ -148,6 +148,7 @@ template <int D>
 struct ProbeEst {
   uint32_t bk, bqa, bqb;
   uint32_t mid[D];
+  uint32_t est[D];  // quantiles of the candidate positions in every dimension
   float hits;  // subscriptions met, were the dimensions independent
   bool bad;
 };
@@ -189,10 +190,18 @@ __device__ __forceinline__ void load_quant_lds(const TreeDev& T, uint32_t (*sq)[
     for (uint32_t r = 0; r < Q; ++r) sq[k][qslot(r * THREADS + threadIdx.x)] = v[k][r];
 }
 
+// The class of an update is its probe dimension; cls names one for the whole set
+// (the dimension whose ranges are the shortest on average, by the sample), or
+// lets every update take its own, for small sets and the lane form.  With own
+// classes the few updates of a set that leave the common one make up tiles that
+// span the space: the 16-hotspot workload, ten seeds, 6.5 .. 9.4 ms, mean 7.5,
+// against 6.5 .. 7.3, mean 6.8; d = 4, 62,266 updates, a count of 284 us against 84.
+constexpr uint32_t kOwnClass = ~0u;
+
 template <int D>
 __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
                                                       const uint32_t (*sq)[kQuantPad],
-                                                      const UpdExt<D>& e) {
+                                                      const UpdExt<D>& e, uint32_t cls) {
   ProbeEst<D> P;
   P.bad = false;
   uint32_t xh[D], xl[D], xm[D], qa[D], qb[D], qm[D];
@@ -220,10 +229,8 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
       if (cm <= kQuant && vm <= xm[k]) qm[k] = cm;
     }
   }
-  // dimension 0, unless another one's range is less than half as long: one
-  // class where the dimensions are alike (a tile's neighbours are then not
-  // spread over several classes), separate ones for updates that are narrow
-  // in different dimensions
+  // an update's own class: dimension 0, unless another one's range is less than
+  // a third as long (at the edge of the space a range is half as long)
   uint32_t best = 0;
   P.hits = (float)T.n;
 #pragma unroll
@@ -231,7 +238,8 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
     const uint32_t est = qa[k] - min(qa[k], qb[k]);
     P.hits *= fmaxf((float)est, 0.5f) * (1.f / (float)kQuant);
     P.mid[k] = qm[k];
-    if (k == 0 || 2u * est + 16u < best) {
+    P.est[k] = est;
+    if (cls == kOwnClass ? k == 0 || 3u * est + 16u < best : (uint32_t)k == cls) {
       best = est;
       P.bk = (uint32_t)k;
       P.bqa = qa[k];
@@ -244,26 +252,34 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
 constexpr uint32_t kShapeSamples = 256;
 
 // Up to kShapeSamples updates spread evenly over the set decide whether the
-// count traversal keeps its hits: when
-// the estimated hits (the candidate fractions of the dimensions multiplied,
-// as if they were independent) exceed kStashDenseHits per update or the
-// stash's counted chunks, the stash is marked full before it is used, and the
-// count only counts.  Such a set overflows it anyway, or pays for every
-// 12-byte entry written and moved: 76,543 updates against 123,457 squares
-// (d = 2, alpha = 100, 247 hits each) counted in 466 us with the attempt and
-// 137 us without it, while at 21 hits each and 17,389 updates keeping them
-// (204 us a step) still beats traversing again (208 us).  A set whose
-// dimensions are correlated may still overflow the stash.
-constexpr float kStashDenseHits = 32.f;
+// count traversal keeps its hits: the stash is marked full before it is used,
+// and the set matched as a dense one, when the estimated hits (the candidate
+// fractions of the dimensions multiplied, as if they were independent) exceed
+// four fifths of the stash's counted chunks (tiles leave some of theirs), or per
+// update the larger of kDenseHits and
+// kDenseScale * d / sqrt(m).  The dense form takes two more synchronizations and
+// nine more launches, a fixed 70 us, and saves on every pair, the more the more
+// updates lie near each other.  Match of m updates against m subscriptions, us,
+// keeping hits / dense form (10, 20, 40, 80 hits each):
+//   d = 2  m =  20,000   86/157   91/158  138/157  232/152
+//          m =  80,000  128/164  164/159  306/164  345/173
+//          m = 250,000  240/229  388/236  530/245  603/273
+//   d = 3  m =  20,000   92/160  101/169  146/170  184/178
+//          m =  80,000  145/189  181/199  370/211  492/251
+//   d = 4  m =  80,000  208/283  211/305  505/369  731/424
+// A set whose dimensions are correlated may still overflow the stash.
+constexpr float kDenseHits = 10.f, kDenseScale = 3000.f;
 
-// (run by one workgroup of at least kShapeSamples threads)
+// (run by one workgroup of at least kShapeSamples threads; full, cls: may be null)
 template <int D, uint32_t THREADS>
-__device__ __forceinline__ void sample_density(const TreeDev& T, const float* __restrict__ ulo,
-                                               const float* __restrict__ uhi, uint32_t m,
-                                               uint32_t (*sq)[kQuantPad],
-                                               uint32_t* __restrict__ full, uint32_t room) {
+__device__ __forceinline__ void sample_set(const TreeDev& T, const float* __restrict__ ulo,
+                                           const float* __restrict__ uhi, uint32_t m,
+                                           uint32_t (*sq)[kQuantPad], uint32_t* __restrict__ full,
+                                           uint32_t room, uint32_t* __restrict__ cls) {
   static_assert(THREADS >= kShapeSamples, "one sample per thread");
-  __shared__ float whits[kShapeSamples / kWave];
+  constexpr uint32_t W = kShapeSamples / kWave;
+  __shared__ float whits[W];
+  __shared__ uint32_t west[D][W];
   const uint32_t S = min(m, kShapeSamples);
   UpdExt<D> e{};
   if (threadIdx.x < S) e = load_ext<D>(ulo, uhi, m, (uint32_t)(((uint64_t)threadIdx.x * m) / S));
@@ -271,20 +287,42 @@ __device__ __forceinline__ void sample_density(const TreeDev& T, const float* __
   __syncthreads();
   if (threadIdx.x < kShapeSamples) {
     float hits = 0.f;
+    uint32_t est[D] = {};
     if (threadIdx.x < S) {
-      const ProbeEst<D> P = probe_estimate<D>(T, sq, e);
-      if (!P.bad) hits = P.hits;
+      const ProbeEst<D> P = probe_estimate<D>(T, sq, e, kOwnClass);
+      if (!P.bad) {
+        hits = P.hits;
+#pragma unroll
+        for (int k = 0; k < D; ++k) est[k] = P.est[k];
+      }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, kWave);
     if (lane_id() == 0) whits[threadIdx.x / kWave] = hits;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const uint32_t sum = wave_scan_dpp(est[k]);
+      if (lane_id() == kWave - 1) west[k][threadIdx.x / kWave] = sum;
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     float t = 0.f;
-    for (uint32_t w = 0; w < kShapeSamples / kWave; ++w) t += whits[w];
+    for (uint32_t w = 0; w < W; ++w) t += whits[w];
     t /= (float)S;
-    *full = t > kStashDenseHits || t * (float)m > (float)room ? kStashDense : 0u;
+    const float dense = fmaxf(kDenseHits, kDenseScale * (float)D * rsqrtf((float)m));
+    if (full) *full = t > dense || t * (float)m > 0.8f * (float)room ? kStashDense : 0u;
+    uint32_t c = 0, best = 0;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      uint32_t sum = 0;
+      for (uint32_t w = 0; w < W; ++w) sum += west[k][w];
+      if (k == 0 || 2u * sum + 16u * S < best) {
+        best = sum;
+        c = (uint32_t)k;
+      }
+    }
+    if (cls) *cls = c;
   }
 }
 
@@ -299,12 +337,14 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
                                                      uint32_t* __restrict__ bhist,
                                                      int32_t* __restrict__ flag,
                                                      uint2* __restrict__ pb,
-                                                     uint32_t* __restrict__ full, uint32_t room) {
+                                                     uint32_t* __restrict__ full, uint32_t room,
+                                                     const uint32_t* __restrict__ cls) {
   __shared__ uint32_t sq[D][kQuantPad];
   if (SMALL && full && blockIdx.x == gridDim.x - 1) {
-    sample_density<D, kProbeThreads>(T, ulo, uhi, m, sq, full, room);
+    sample_set<D, kProbeThreads>(T, ulo, uhi, m, sq, full, room, nullptr);
     return;
   }
+  const uint32_t set_class = !SMALL && cls ? uniform_u32(*cls) : kOwnClass;
   const uint32_t j = blockIdx.x * kProbeThreads + threadIdx.x;
   const bool act = j < m;
   UpdExt<D> e{};
@@ -313,7 +353,7 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
   __syncthreads();
   bool bad = false;
   if (act) {
-    const ProbeEst<D> P = probe_estimate<D>(T, sq, e);
+    const ProbeEst<D> P = probe_estimate<D>(T, sq, e, set_class);
     bad = P.bad;
     const uint32_t bk = bad ? 0u : P.bk;
     kstar[j] = (uint8_t)bk;
@@ -348,23 +388,12 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
   if (!SMALL && ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
 }
 
-// exclusive scan of each workgroup's kCellBlock cell counts, and its total;
-// one more workgroup takes the sample (beside the scan, so that it costs no time)
-template <int D>
-__global__ __launch_bounds__(256) void cell_scan_kernel(
-    const uint32_t* __restrict__ bcnt, uint32_t* __restrict__ boff, uint32_t* __restrict__ bsum,
-    TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
-    uint32_t* __restrict__ full, uint32_t room) {
+// exclusive scan of each workgroup's kCellBlock cell counts, and its total
+__global__ __launch_bounds__(256) void cell_scan_kernel(const uint32_t* __restrict__ bcnt,
+                                                        uint32_t* __restrict__ boff,
+                                                        uint32_t* __restrict__ bsum) {
   constexpr uint32_t PER = kCellBlock / 256;
-  __shared__ uint32_t sq[D][kQuantPad];  // the sample's, or the scan's
-  static_assert(kCellBlock + 256 <= kQuantPad * 1, "the scan's words fit");
-  if constexpr (D > 1) {
-    if (blockIdx.x == D * kCellBlocks) {
-      sample_density<D, 256>(T, ulo, uhi, m, sq, full, room);
-      return;
-    }
-  }
-  uint32_t* sb = sq[0];
+  __shared__ uint32_t sb[kCellBlock + 256];
   __shared__ uint32_t wsum[256 / kWave];
   const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const uint32_t base = blockIdx.x * kCellBlock;
@@ -1698,6 +1727,7 @@ struct MatchState {
   uint32_t* perm = nullptr;
   uint32_t* gstart = nullptr;
   uint32_t* gcount = nullptr;
+  uint32_t* cls = nullptr;    // the set's class, by the sample
   uint32_t* pb = nullptr;     // per update: candidate position bounds (d > 1)
   bool pb_ok = false;
   bool balanced = false;  // the learned single pass runs the work-cut tile list
@@ -1764,11 +1794,21 @@ struct MatchState {
 };
 
 // zeroes the match's counters; with a stash (snext non-null) also sets the
-// slices' next free chunks
+// slices' next free chunks; d > 1: one more workgroup takes the sample
+template <int D>
 __global__ __launch_bounds__(1024) void match_init_kernel(
     int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
-    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum) {
+    uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum,
+    TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
+    uint32_t room, uint32_t* __restrict__ cls) {
   static_assert(kCells % 1024 == 0, "whole workgroups");
+  if constexpr (D > 1) {
+    if (blockIdx.x == D * kCells / 1024) {
+      __shared__ uint32_t sq[D][kQuantPad];
+      sample_set<D, 1024>(T, ulo, uhi, m, sq, snext ? snext + kStashSlices : nullptr, room, cls);
+      return;
+    }
+  }
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   bcnt[(size_t)i * kCntPad] = 0;
   if (i == 0) *flag = 0;
@@ -1784,14 +1824,16 @@ __global__ __launch_bounds__(1024) void match_init_kernel(
 // a stash, a sample of them decides whether it is used
 template <int D>
 static ddm_status order_updates(const TreeDev& T, const float* ulo, const float* uhi, uint32_t m,
-                                MatchState& st, uint32_t* lists_count, hipStream_t s) {
+                                MatchState& st, uint32_t* lists_count, bool own_class,
+                                hipStream_t s) {
   uint32_t* sn = st.stash ? st.snext : nullptr;  // (a stash exists only for d > 1)
   uint32_t* full = sn ? sn + kStashSlices : nullptr;
   const uint32_t room = st.sslice * (kStashSlices * kStashChunk);
   const bool small = m <= kSmallOrder;
   if (!small) {
-    match_init_kernel<<<D * kCells / 1024, 1024, 0, s>>>(st.flag, lists_count, st.bcnt, sn,
-                                                         st.sfirst, st.sslice, st.tsum);
+    match_init_kernel<D><<<D * kCells / 1024 + (D > 1 ? 1 : 0), 1024, 0, s>>>(
+        st.flag, lists_count, st.bcnt, sn, st.sfirst, st.sslice, st.tsum, T, ulo, uhi, m, room,
+        st.cls);
     DDM_LAUNCHED("match_init_kernel");
   }
   if constexpr (D == 1) {
@@ -1812,11 +1854,11 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
     uint2* pb = reinterpret_cast<uint2*>(st.pb);
     if (small)
       probe_kernel<D, true><<<g + (full ? 1u : 0u), kProbeThreads, 0, s>>>(
-          T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, room);
+          T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, room, nullptr);
     else
       probe_kernel<D, false><<<g, kProbeThreads, 0, s>>>(T, ulo, uhi, m, shape, st.kstar,
                                                          st.bucket, st.rank, st.bcnt, st.flag, pb,
-                                                         nullptr, 0);
+                                                         nullptr, 0, own_class ? nullptr : st.cls);
     DDM_LAUNCHED("probe_kernel");
   }
   ProfScope ps("order", s);
@@ -1828,8 +1870,7 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
     return DDM_OK;
   }
   constexpr uint32_t nb = D * kCellBlocks;
-  cell_scan_kernel<D><<<nb + (full ? 1u : 0u), 256, 0, s>>>(st.bcnt, st.boff, st.bsum, T, ulo, uhi,
-                                                            m, full, room);
+  cell_scan_kernel<<<nb, 256, 0, s>>>(st.bcnt, st.boff, st.bsum);
   DDM_LAUNCHED("cell_scan_kernel");
   cell_scatter_kernel<<<(m + 255) / 256, 256, 0, s>>>(st.bucket, st.rank, m, st.boff, st.bsum, nb,
                                                      st.perm, st.gstart, st.gcount);
@@ -1957,6 +1998,7 @@ static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
   sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // gstart
   sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // gcount
   sc.reserve(sizeof(int32_t));               // flag
+  sc.reserve(sizeof(uint32_t));              // class
   sc.reserve(sizeof(uint32_t) * m);          // cnt
   sc.reserve(sizeof(uint64_t) * (m + 1));    // off
   sc.reserve(sizeof(uint64_t) * scan_tmp_words(m));
@@ -1981,6 +2023,7 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
   st.gcount = sc.take<uint32_t>(DDM_MAX_D);
   st.m = m;
   st.flag = sc.take<int32_t>(1);
+  st.cls = sc.take<uint32_t>(1);
   st.cnt = sc.take<uint32_t>(m);
   st.off = sc.take<uint64_t>(m + 1);
   fp->stmp = sc.take<uint64_t>(scan_tmp_words(m));
@@ -2039,9 +2082,11 @@ static ddm_status list_any(uint32_t d, const TreeDev& T, const float* ulo, const
   return DDM_OK;
 }
 
-// d = 1: hits per update from which the dense form is taken (the counts are
-// exact before any traversal)
-constexpr uint64_t kDenseHits1 = 16;
+// d = 1: pairs from which the dense form is taken (the counts are exact before
+// any traversal).  Match, us, fill and sort / dense form: 250,000 + 250,000
+// segments 141/219 at 5*10^6 pairs, 265/219 at 10^7, 486/295 at 4*10^7; 80,000 +
+// 80,000 150/154 at 6*10^6, 186/160 at 1.3*10^7.
+constexpr uint64_t kDensePairs1 = 1u << 23;
 // learned: predicted hits per update from which it is taken
 constexpr double kLearnedDenseHits = 32.0;
 // most candidates whose lists and masks (16 bytes each) the match allocates
@@ -2253,12 +2298,13 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
       if (!st.stash_sc.fits()) return scratch_overrun("stash");
     }
   }
+  const bool own = P.traversal != DDM_TRAVERSE_TILE;  // lanes work alone
   ddm_status r;
   switch (d) {
-    case 1: r = order_updates<1>(T, ulo, uhi, m, st, *lists_count, s); break;
-    case 2: r = order_updates<2>(T, ulo, uhi, m, st, *lists_count, s); break;
-    case 3: r = order_updates<3>(T, ulo, uhi, m, st, *lists_count, s); break;
-    default: r = order_updates<4>(T, ulo, uhi, m, st, *lists_count, s); break;
+    case 1: r = order_updates<1>(T, ulo, uhi, m, st, *lists_count, own, s); break;
+    case 2: r = order_updates<2>(T, ulo, uhi, m, st, *lists_count, own, s); break;
+    case 3: r = order_updates<3>(T, ulo, uhi, m, st, *lists_count, own, s); break;
+    default: r = order_updates<4>(T, ulo, uhi, m, st, *lists_count, own, s); break;
   }
   if (r != DDM_OK) return r;
   // per-update counts
@@ -2480,7 +2526,7 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   const bool fits = st.may_dense && tree_n(t) <= kMaxBitWords * 32;
   bool dense = marked;
   if (!marked && fits && P.traversal == DDM_TRAVERSE_TILE && !counts_out && !st.learned &&
-      (d == 1 ? st.K > kDenseHits1 * m : st.stash && !st.stash_ok)) {
+      (d == 1 ? st.K > kDensePairs1 : st.stash && !st.stash_ok)) {
     SegOut O{};
     O.tcand = st.tcand;
     O.tsum = st.tsum;

@@ -39,19 +39,23 @@ def _match(inst, learned=None, info=None):
 @pytest.mark.parametrize("d", [1, 2, 3, 4])
 @pytest.mark.parametrize("n", [63, 64, 65, 1023, 1024, 1025, 2049, 5000])
 def test_list_lengths(d, n):
-    """Extents half as long as the space: every list holds about every id."""
-    inst = W.uniform_instance(1000 + n, n, 131, d, 0.5e6)
-    want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo, inst.u_hi)
+    """Long extents: every list holds about every id, and there are updates
+    enough for the dense form."""
+    side = 0.9e6 if n < 1000 else 0.5e6
+    hits = n * (0.98 if n < 1000 else 0.74) ** d
+    m = 131 + int(9.5e6 / hits if d == 1 else 1.4 * (3000.0 * d / hits) ** 2)
+    inst = W.uniform_instance(1000 + n, n, m, d, side)
+    want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo, inst.u_hi, threads=8)
     got, rec = _match(inst)
-    if len(want) > 40 * inst.m:
-        assert "traverse_tile_fill_units" in rec
+    assert "traverse_tile_fill_units" in rec
     assert np.array_equal(got, want)
 
 
 @pytest.mark.parametrize("m", [1, 4, 5, 255, 32768, 32769, 65537])
 def test_update_counts(m):
     """Tiles of 4, 8 and 16 updates, full and partial."""
-    inst = W.uniform_instance(2000 + m, 3000, m, 2, 130000.0)
+    inst = W.uniform_instance(2000 + m, 3000 if m > 255 else 20000, m, 2,
+                              130000.0 if m > 255 else 0.5e6)
     want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo, inst.u_hi, threads=8)
     got, rec = _match(inst)
     assert "traverse_tile_fill_units" in rec
