@@ -307,9 +307,9 @@ ddm_status ddm_match_scratch_bytes(uint32_t m, uint32_t d, uint32_t form, uint64
  * its scratch from one static device array of DDM_NOALLOC_SCRATCH_MB MiB,
  * which each device that runs it keeps until the process ends.  It calls no
  * allocator of any kind (the count is read back into pageable host memory).
- *  Limit: the match takes about 45 bytes per update plus 4.4 MiB
+ *  Limit: the match takes about 45 bytes per update plus 2.3 MiB
  *  (ddm_match_scratch_bytes with DDM_SCRATCH_PLAIN gives the exact figure),
- *  i.e. up to about 1.38e6 updates; beyond that, and for a result that needs
+ *  i.e. up to about 1.43e6 updates; beyond that, and for a result that needs
  *  the segment sort's id copy (more than 2^20 subscriptions and a segment
  *  over 2048 pairs: 4 bytes per pair) beyond what is left, it returns
  *  DDM_E_INVALID_ARG with a detail message, before writing anything.
@@ -658,6 +658,10 @@ uint32_t ddm_server_wait_any(ddm_server* s, uint32_t timeout_ms, uint64_t* ticke
 /* State and result of a request (host struct).  For a failed request
  * ddm_last_error_detail() holds its detail after this call.                 */
 ddm_status ddm_server_result(ddm_server* s, uint64_t ticket, ddm_result* res);
+
+/* Copies host memory (a result out of the server's pool, say) with up to four
+ * threads; the ranges must not overlap.                                     */
+ddm_status ddm_host_copy(void* dst, const void* src, uint64_t bytes);
 
 /* Returns a finished request's result memory to the server.                 */
 ddm_status ddm_server_release(ddm_server* s, uint64_t ticket);

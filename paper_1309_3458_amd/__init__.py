@@ -592,6 +592,16 @@ class Batch:
             pass
 
 
+def _host_copy(address, count: int, dtype):
+    """A new array of `count` elements from host memory at `address`."""
+    import numpy as np
+    a = np.empty(count, dtype=dtype)
+    check(lib().ddm_host_copy(a.ctypes.data_as(ctypes.c_void_p),
+                              ctypes.c_void_p(int(address)) if count else None, a.nbytes),
+          "ddm_host_copy")
+    return a
+
+
 class Server:
     """Concurrent matching of requests that arrive at any time (ddm_server_*).
 
@@ -670,10 +680,8 @@ class Server:
                 # compact form (copied as the library delivers it): subscription
                 # ids of every pair, and each update's first pair
                 K, m = int(r.count), int(r.m)
-                ids = np.frombuffer((ctypes.c_uint32 * K).from_address(int(r.sub_ids)),
-                                    dtype=np.uint32).copy() if K else np.zeros(0, np.uint32)
-                off = np.frombuffer((ctypes.c_uint64 * (m + 1)).from_address(int(r.upd_offsets)),
-                                    dtype=np.uint64).copy()
+                ids = _host_copy(r.sub_ids, K, np.uint32)
+                off = _host_copy(r.upd_offsets, m + 1, np.uint64)
                 d["sub_ids"], d["upd_offsets"] = ids, off
             elif r.count == 0:
                 d["pairs"] = np.zeros(0, dtype=np.uint64)
@@ -686,8 +694,7 @@ class Server:
 
                 d["pairs"] = torch.as_tensor(_Dev(), device="cuda").cpu().numpy().view(np.uint64)
             else:
-                buf = (ctypes.c_uint64 * int(r.count)).from_address(int(r.pairs))
-                d["pairs"] = np.frombuffer(buf, dtype=np.uint64).copy()
+                d["pairs"] = _host_copy(r.pairs, int(r.count), np.uint64)
         return d
 
     def release(self, ticket: int):

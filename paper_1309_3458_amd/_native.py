@@ -168,6 +168,7 @@ def lib():
     _sig(L, "ddm_server_submit", i32, vp, P(Request), ctypes.c_int64, vp, P(u64))
     _sig(L, "ddm_server_wait_any", u32, vp, u32, vp, u32)
     _sig(L, "ddm_server_result", i32, vp, u64, P(Result))
+    _sig(L, "ddm_host_copy", i32, vp, vp, u64)
     _sig(L, "ddm_server_release", i32, vp, u64)
     _sig(L, "ddm_server_stats", i32, vp, P(ServerCounters))
     _sig(L, "ddm_server_destroy", None, vp)
