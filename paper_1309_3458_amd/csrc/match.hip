@@ -7,9 +7,9 @@
 //      two binary searches on sorted lower and upper bounds (the BITS
 //      identity recalled in Sec. II), already the final count.  d > 1
 //      (probe_kernel): the probe dimension k* (of the few candidate
-//      positions), estimated from quantiles of the sorted lower bounds held
-//      in LDS, bounds of those positions, and the update's cell (k* and its
-//      place in every dimension) with its rank inside the cell.
+//      positions; one for the set, by a sample), bounds of those positions
+//      from quantiles of the sorted lower bounds held in LDS, and the update's
+//      cell (k* and its place in every dimension) with its rank inside it.
 //   2. updates placed in cell order (a counting sort); a tile is up to 64
 //      consecutive ones.
 //   3. count traversal (d > 1): one wavefront per tile reads the blocks of
@@ -61,8 +61,9 @@ int tree_device(const ddm_tree* t);
 // positions that can hold a candidate, i.e. positions p with
 // t <= lo_p <= q.hi where t <= q.lo - maxlen (rounded down): a segment that
 // meets q has hi >= q.lo and lo >= hi - maxlen >= t.  The count is estimated
-// from kQuant quantiles of the sorted lower bounds held in LDS; any choice of
-// k* gives the same pairs, only the work differs.
+// from kQuant quantiles of the sorted lower bounds held in LDS, for the set by a
+// sample or for every update (kOwnClass); any choice of k* gives the same pairs,
+// only the work differs.
 //
 // Both kernels put the update into a cell and take its rank inside the cell
 // from the histogram atomic, so the order is a counting sort without a second
@@ -70,7 +71,7 @@ int tree_device(const ddm_tree* t);
 // class per probe dimension, each with a grid of cells over the quantiles of
 // every dimension, numbered along a serpentine (each line runs back where the
 // last one ended), so that any 64 consecutive updates are neighbours in every
-// dimension.  A tile is 64 (or 32 or 16) consecutive updates of a class, full
+// dimension.  A tile is 4 to 64 consecutive updates of a class, full
 // wherever it starts: its enclosing box, which decides how many blocks it
 // reads and how many candidates it tests, is that of about 64 neighbours.
 // Cells that tiles could not cross left them a third full where updates were
@@ -1747,7 +1748,7 @@ struct MatchState {
   uint64_t slots_total = 0;
   uint32_t* perm_ovf = nullptr;
   uint32_t* govf = nullptr;
-  // tiles cut by predicted work (learned): list, bucket of each, count
+  // tiles cut by predicted work (learned): list, class of each, count
   uint32_t* wtile = nullptr;   // work in perm order, then cut flags
   uint64_t* cwork = nullptr;   // exclusive scan of the work, then of the flags
   uint32_t* tstart = nullptr;
@@ -2903,7 +2904,7 @@ static void balance_reserve(uint32_t m, Scratch& bsc) {
   bsc.reserve(sizeof(uint32_t) * m);                  // work, then cut flags
   bsc.reserve(sizeof(uint64_t) * ((size_t)m + 1));    // their scans
   bsc.reserve(sizeof(uint32_t) * ((size_t)m + 1));    // tile starts
-  bsc.reserve(sizeof(uint32_t) * m);                  // tile buckets
+  bsc.reserve(sizeof(uint32_t) * m);                  // tile classes
   bsc.reserve(sizeof(uint64_t) * scan_tmp_words(m));  // scan scratch
 }
 

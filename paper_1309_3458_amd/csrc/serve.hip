@@ -155,7 +155,7 @@ namespace {
 uint64_t admission_bytes(const ddm_request& r, bool build) {
   // inputs (already in device memory, held until the request completes),
   // the tree unless it is resident, and the match scratch (per update: probe
-  // words, order, counts, offsets, lists; plus the bucket tables; and the
+  // words, order, counts, offsets, lists; plus the cell tables; and the
   // count traversal's stash of hits)
   uint64_t b = 8ull * r.d * ((uint64_t)r.n + r.m);
   if (build) b += tree_bytes_estimate(r.n, r.d);

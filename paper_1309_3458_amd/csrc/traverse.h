@@ -222,8 +222,8 @@ __device__ __forceinline__ void seg_bounds(const SegOut& O, uint32_t j, uint64_t
 }
 
 // --------------------------------------------------------------------------
-// 3/5b. one wavefront per tile of 64 updates (same probe dimension k, ordered
-// by bucket).
+// 3/5b. one wavefront per tile of up to 64 updates (same probe dimension k,
+// consecutive in the cell order).
 //
 // The tile's candidates in tree k are confined to positions
 // [Pbeg, Pend] = [min plo, max phi] of its updates.  The wave walks that
