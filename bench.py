@@ -207,7 +207,7 @@ def roofline_record(inst, K, cand, dom, dom_avg_ms, wname, path):
     alu = ops / sec / 1e9
     r["alu"] = {"achieved": round(alu, 1), "peak": ALU_PEAK_GOPS, "unit": "Gop/s",
                 "frac": round(alu / ALU_PEAK_GOPS, 4), "candidates_per_launch": int(cand),
-                "what": "2d float compares per probe-dimension candidate"}
+                "what": "2d float compares per probe-dimension candidate, tested or filtered by boxes"}
     return r
 
 

