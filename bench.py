@@ -138,8 +138,8 @@ TRAFFIC_SOURCES = ("paper_1309_3458_amd/csrc/match.hip", "paper_1309_3458_amd/cs
                    "paper_1309_3458_amd/csrc/tree_dev.h", "paper_1309_3458_amd/csrc/sort_scan.hip")
 TRAFFIC = {
     ("d2_N1e6_alpha1_uniform", "plain", "traverse_tile_count_stash"): {
-        "sha": "fe60348aa3cf40ba", "kernel_fetch_kib": 113149.1, "kernel_write_kib": 28321.1,
-        "step_fetch_kib": 231872.0, "step_write_kib": 200652.0, "step_kernel_us": 287.3,
+        "sha": "cd7794ad6293a3c0", "kernel_fetch_kib": 113122.3, "kernel_write_kib": 28293.2,
+        "step_fetch_kib": 231706.7, "step_write_kib": 200564.3, "step_kernel_us": 286.8,
         "profile": "profiles/traffic_d2_N1e6_alpha1_pmc.md"},
 }
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0

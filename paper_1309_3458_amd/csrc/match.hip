@@ -71,7 +71,7 @@ int tree_device(const ddm_tree* t);
 // class per probe dimension, each with a grid of cells over the quantiles of
 // every dimension, numbered along a serpentine (each line runs back where the
 // last one ended), so that any 64 consecutive updates are neighbours in every
-// dimension.  A tile is 4 to 64 consecutive updates of a class, full
+// dimension.  A tile is 1 to 64 consecutive updates of a class, full
 // wherever it starts: its enclosing box, which decides how many blocks it
 // reads and how many candidates it tests, is that of about 64 neighbours.
 // Cells that tiles could not cross left them a third full where updates were
@@ -99,12 +99,15 @@ struct CellShape {
   uint32_t b[DDM_MAX_D];  // cells along each dimension, as cell_shape gives them
 };
 
-// updates per tile: 64, or fewer (down to 4) while that leaves at most
-// kFewTiles tiles, so that the chip has wavefronts to run (17,389 updates of
-// 21 hits each, count: 73 us with 16 to a tile, 21 with 4)
+// updates per tile: 64, or fewer (down to one) while that leaves at most
+// kFewTiles tiles, so that the chip has wavefronts to run and few updates in a
+// large set do not share boxes wider than their own (17,389 updates of 21 hits
+// each, count: 73 us with 16 to a tile, 21 with 4; 1100 updates against 490,000
+// subscriptions: d = 4 563 us with 4, 22 with one, d = 3 165 and 10, d = 1 51
+// and 9)
 constexpr uint32_t kFewTiles = 8192;
 static uint32_t tile_updates(uint32_t m) {
-  uint32_t q = 4;
+  uint32_t q = 1;
   while (q < 64u && m > q * kFewTiles) q *= 2;
   return q;
 }
@@ -1948,7 +1951,7 @@ __global__ void stash_scatter_kernel(const uint64_t* __restrict__ skey,
 // (a bound of the tiles that grows with m)
 static uint64_t stash_tiles(uint32_t m) {
   return std::max<uint64_t>(((uint64_t)m + 63) / 64,
-                            std::min<uint64_t>(((uint64_t)m + 3) / 4, kFewTiles)) +
+                            std::min<uint64_t>(m, kFewTiles)) +
          DDM_MAX_D;
 }
 // counted chunks per slice: room for the hint (or 4 hits per update) plus

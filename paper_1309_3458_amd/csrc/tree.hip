@@ -242,25 +242,25 @@ __global__ void flag_zero_kernel(int32_t* __restrict__ flag) {
 }
 
 // job blockIdx.y, chunk blockIdx.x
-// job blockIdx.y, chunk blockIdx.x - 1; the first workgroup takes the samples
-// and quantiles instead (they need the sorted keys only, so their loads run
-// beside the other workgroups': 5 us less than a kernel of their own at 5*10^5)
-__device__ __forceinline__ bool tree_index_group(const TreeJob& J) {
-  if (blockIdx.x != 0) return false;
-  const uint32_t items = max(J.ns, (uint32_t)kQuant);
-  for (uint32_t c = threadIdx.x; c < items; c += kTreeThreads) tree_index_item(J, c);
+// job blockIdx.y, chunk blockIdx.x - ig; the first ig workgroups take the samples
+// and quantiles instead, one item to a thread (they need the sorted keys only, so
+// their loads run beside the other workgroups': 5 us less than a kernel of their
+// own at 5*10^5; all items in one workgroup took 24 us where the pass takes 12)
+__device__ __forceinline__ bool tree_index_group(const TreeJob& J, uint32_t ig) {
+  if (blockIdx.x >= ig) return false;
+  tree_index_item(J, blockIdx.x * kTreeThreads + threadIdx.x);
   return true;
 }
 
-__global__ __launch_bounds__(kTreeThreads) void tree_low_kernel(TreeJobs J) {
-  if (tree_index_group(J.j[blockIdx.y])) return;
-  tree_low_chunk(J.j[blockIdx.y], blockIdx.x - 1);
+__global__ __launch_bounds__(kTreeThreads) void tree_low_kernel(TreeJobs J, uint32_t ig) {
+  if (tree_index_group(J.j[blockIdx.y], ig)) return;
+  tree_low_chunk(J.j[blockIdx.y], blockIdx.x - ig);
 }
 
 // the same pass over records already in place (extents moved)
-__global__ __launch_bounds__(kTreeThreads) void tree_refit_kernel(TreeJobs J) {
-  if (tree_index_group(J.j[blockIdx.y])) return;
-  tree_low_chunk<false>(J.j[blockIdx.y], blockIdx.x - 1);
+__global__ __launch_bounds__(kTreeThreads) void tree_refit_kernel(TreeJobs J, uint32_t ig) {
+  if (tree_index_group(J.j[blockIdx.y], ig)) return;
+  tree_low_chunk<false>(J.j[blockIdx.y], blockIdx.x - ig);
 }
 
 __global__ __launch_bounds__(kTreeThreads) void tree_high_kernel(TreeJobs J, uint32_t S) {
@@ -344,16 +344,17 @@ static ddm_status enqueue_tree_passes(const ddm_tree* t, const TreeJobs& J, bool
                                       hipStream_t s) {
   const uint32_t d = t->d;
   ProfScope ps("tree_build", s);
-  dim3 g((t->P + 1 + kChunk - 1) / kChunk + 1, d);
+  const uint32_t ig = (std::max(t->ns, kQuant) + kTreeThreads - 1) / kTreeThreads;
+  dim3 g((t->P + 1 + kChunk - 1) / kChunk + ig, d);
   const size_t lds = d > 1 ? strip_lds_bytes(d) : 0;
   if (lds) {
     const ddm_status st = ensure_tree_attr();
     if (st != DDM_OK) return st;
   }
   if (gather)
-    tree_low_kernel<<<g, kTreeThreads, lds, s>>>(J);
+    tree_low_kernel<<<g, kTreeThreads, lds, s>>>(J, ig);
   else
-    tree_refit_kernel<<<g, kTreeThreads, lds, s>>>(J);
+    tree_refit_kernel<<<g, kTreeThreads, lds, s>>>(J, ig);
   DDM_LAUNCHED("tree_low_kernel");
   for (uint32_t S = kChunkLog; S < t->H; S += kChunkLog) {
     const uint32_t q_end = (t->P >> S) + 1;
