@@ -274,12 +274,15 @@ constexpr uint32_t kShapeSamples = 256;
 // A set whose dimensions are correlated may still overflow the stash.
 constexpr float kDenseHits = 10.f, kDenseScale = 3000.f;
 
-// (run by one workgroup of at least kShapeSamples threads; full, cls: may be null)
+// (run by one workgroup of at least kShapeSamples threads; full, cls: may be null;
+// mark: kStashDense where the dense form may follow, else 1, a stash that is full,
+// so that the count traversal counts at once)
 template <int D, uint32_t THREADS>
 __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __restrict__ ulo,
                                            const float* __restrict__ uhi, uint32_t m,
                                            uint32_t (*sq)[kQuantPad], uint32_t* __restrict__ full,
-                                           uint32_t room, uint32_t* __restrict__ cls) {
+                                           uint32_t mark, uint32_t room,
+                                           uint32_t* __restrict__ cls) {
   static_assert(THREADS >= kShapeSamples, "one sample per thread");
   constexpr uint32_t W = kShapeSamples / kWave;
   __shared__ float whits[W];
@@ -315,7 +318,7 @@ __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __rest
     for (uint32_t w = 0; w < W; ++w) t += whits[w];
     t /= (float)S;
     const float dense = fmaxf(kDenseHits, kDenseScale * (float)D * rsqrtf((float)m));
-    if (full) *full = t > dense || t * (float)m > 0.8f * (float)room ? kStashDense : 0u;
+    if (full) *full = t > dense || t * (float)m > 0.8f * (float)room ? mark : 0u;
     uint32_t c = 0, best = 0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -341,11 +344,12 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
                                                      uint32_t* __restrict__ bhist,
                                                      int32_t* __restrict__ flag,
                                                      uint2* __restrict__ pb,
-                                                     uint32_t* __restrict__ full, uint32_t room,
+                                                     uint32_t* __restrict__ full, uint32_t mark,
+                                                     uint32_t room,
                                                      const uint32_t* __restrict__ cls) {
   __shared__ uint32_t sq[D][kQuantPad];
   if (SMALL && full && blockIdx.x == gridDim.x - 1) {
-    sample_set<D, kProbeThreads>(T, ulo, uhi, m, sq, full, room, nullptr);
+    sample_set<D, kProbeThreads>(T, ulo, uhi, m, sq, full, mark, room, nullptr);
     return;
   }
   const uint32_t set_class = !SMALL && cls ? uniform_u32(*cls) : kOwnClass;
@@ -1774,7 +1778,7 @@ struct MatchState {
   // candidates of the tiles (counted when the set is dense)
   uint32_t* tcand = nullptr;   // per tile
   uint64_t* tsum = nullptr;    // [kListSlices][kListPad]: sum, then maximum
-  bool may_dense = false;      // the caller allows the scratch of the dense form
+  bool may_dense = false;      // the dense form may be taken (scratch, and ids in one window)
   bool dense = false;          // the units hold the hits
   bool plain_fill = false;     // learned, but neither slots nor units: a fill by the counts
   Scratch dense_sc;
@@ -1804,12 +1808,13 @@ __global__ __launch_bounds__(1024) void match_init_kernel(
     int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
     uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum,
     TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
-    uint32_t room, uint32_t* __restrict__ cls) {
+    uint32_t mark, uint32_t room, uint32_t* __restrict__ cls) {
   static_assert(kCells % 1024 == 0, "whole workgroups");
   if constexpr (D > 1) {
     if (blockIdx.x == D * kCells / 1024) {
       __shared__ uint32_t sq[D][kQuantPad];
-      sample_set<D, 1024>(T, ulo, uhi, m, sq, snext ? snext + kStashSlices : nullptr, room, cls);
+      sample_set<D, 1024>(T, ulo, uhi, m, sq, snext ? snext + kStashSlices : nullptr, mark, room,
+                          cls);
       return;
     }
   }
@@ -1833,11 +1838,12 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
   uint32_t* sn = st.stash ? st.snext : nullptr;  // (a stash exists only for d > 1)
   uint32_t* full = sn ? sn + kStashSlices : nullptr;
   const uint32_t room = st.sslice * (kStashSlices * kStashChunk);
+  const uint32_t mark = st.may_dense ? kStashDense : 1u;
   const bool small = m <= kSmallOrder;
   if (!small) {
     match_init_kernel<D><<<D * kCells / 1024 + (D > 1 ? 1 : 0), 1024, 0, s>>>(
-        st.flag, lists_count, st.bcnt, sn, st.sfirst, st.sslice, st.tsum, T, ulo, uhi, m, room,
-        st.cls);
+        st.flag, lists_count, st.bcnt, sn, st.sfirst, st.sslice, st.tsum, T, ulo, uhi, m, mark,
+        room, st.cls);
     DDM_LAUNCHED("match_init_kernel");
   }
   if constexpr (D == 1) {
@@ -1858,11 +1864,12 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
     uint2* pb = reinterpret_cast<uint2*>(st.pb);
     if (small)
       probe_kernel<D, true><<<g + (full ? 1u : 0u), kProbeThreads, 0, s>>>(
-          T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, room, nullptr);
+          T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, mark,
+          room, nullptr);
     else
       probe_kernel<D, false><<<g, kProbeThreads, 0, s>>>(T, ulo, uhi, m, shape, st.kstar,
                                                          st.bucket, st.rank, st.bcnt, st.flag, pb,
-                                                         nullptr, 0, own_class ? nullptr : st.cls);
+                                                         nullptr, 0, 0, own_class ? nullptr : st.cls);
     DDM_LAUNCHED("probe_kernel");
   }
   ProfScope ps("order", s);
@@ -2270,6 +2277,8 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   Scratch& sc = st.sc;
   // the single pass replaces the count traversal, which only exists for d > 1
   st.learned = pred != nullptr && d > 1;
+  // (the lists are sorted within one bitmap window of ids)
+  may_dense = may_dense && tree_n(t) <= kMaxBitWords * 32;
   st.may_dense = may_dense;
   front_reserve(sc, m, st.learned);
   if (!sc.commit()) return DDM_E_NOMEM;
@@ -2336,7 +2345,7 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     DDM_HIP(hipStreamSynchronize(s));
     const uint64_t predicted = hw0[4];
     if (may_dense && budget == 0 && !grant && P.traversal == DDM_TRAVERSE_TILE &&
-        tree_n(t) <= kMaxBitWords * 32 && (double)predicted > kLearnedDenseHits * (double)m) {
+        (double)predicted > kLearnedDenseHits * (double)m) {
       // dense by prediction, and no limit on the memory: the tiles' candidate
       // lists are sized by the predictor and filled in one pass, and the pairs
       // come from them (the predicted slots are then only reported)
@@ -2527,9 +2536,8 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   // so far; one that overflowed the stash, or (d = 1) has its exact counts,
   // takes the dense form too, once its candidates are counted.
   const bool marked = st.stash && (hw[3] & kStashDense);
-  const bool fits = st.may_dense && tree_n(t) <= kMaxBitWords * 32;
   bool dense = marked;
-  if (!marked && fits && P.traversal == DDM_TRAVERSE_TILE && !counts_out && !st.learned &&
+  if (!marked && may_dense && P.traversal == DDM_TRAVERSE_TILE && !counts_out && !st.learned &&
       (d == 1 ? st.K > kDensePairs1 : st.stash && !st.stash_ok)) {
     SegOut O{};
     O.tcand = st.tcand;
@@ -2545,10 +2553,8 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
     st.stash = false;  // its memory goes back
     st.stash_sc.drop();
     bool made = false;
-    if (fits) {
-      r = dense_units(t, T, ulo, uhi, m, st, hw[5], hw[6], nullptr, nullptr, st.cnt, s, &made);
-      if (r != DDM_OK) return r;
-    }
+    r = dense_units(t, T, ulo, uhi, m, st, hw[5], hw[6], nullptr, nullptr, st.cnt, s, &made);
+    if (r != DDM_OK) return r;
     st.dense = made;
     if (marked) {
       if (!made) {  // no memory for the units: count by a traversal after all
