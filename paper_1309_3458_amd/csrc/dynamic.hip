@@ -135,17 +135,28 @@ __global__ __launch_bounds__(kRankThreads) void dyn_rank_kernel(
   }
 }
 
-// the moved ids ascending, and their new extents in that order
+// The moved ids ascending, and their new extents in that order.  A move that the
+// flag refuses leaves gaps there (a repeated id), and the host reads the flag only
+// after the match: every column then becomes an extent that is not valid, so that
+// the match meets nothing and stops at its own check, whatever the scratch held.
 __global__ void dyn_gather_kernel(const uint32_t* __restrict__ ids, uint32_t count, uint32_t d,
                                   uint32_t limit, const float* __restrict__ new_lo,
                                   const float* __restrict__ new_hi,
                                   const uint32_t* __restrict__ bits,
-                                  const uint32_t* __restrict__ before, uint32_t* __restrict__ sid,
+                                  const uint32_t* __restrict__ before,
+                                  const int32_t* __restrict__ flag, uint32_t* __restrict__ sid,
                                   float* __restrict__ glo, float* __restrict__ ghi) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= count) return;
+  if (*flag != 0) {
+    sid[c] = limit;
+    for (uint32_t k = 0; k < d; ++k) {
+      glo[(size_t)k * count + c] = INFINITY;
+      ghi[(size_t)k * count + c] = -INFINITY;
+    }
+    return;
+  }
   const uint32_t id = ids[c];
-  if (id >= limit) return;  // (refused by the host later)
   const uint32_t at =
       before[id >> 5] + (uint32_t)__popc(bits[id >> 5] & ((1u << (id & 31u)) - 1u));
   sid[at] = id;
@@ -581,7 +592,7 @@ extern "C" ddm_status ddm_dynamic_move(ddm_dynamic* dy, uint32_t set, const uint
                                              tiles ? tile_off + tiles : nullptr, hw);
   DDM_LAUNCHED("dyn_rank_kernel");
   dyn_gather_kernel<<<blocks(count), 256, 0, s>>>(ids, count, d, limit, new_lo, new_hi, bits,
-                                                  before, sid, glo, ghi);
+                                                  before, flag, sid, glo, ghi);
   DDM_LAUNCHED("dyn_gather_kernel");
   if (merge) {
     r = tree_move_sort(own, M, s);

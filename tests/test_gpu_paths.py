@@ -45,3 +45,29 @@ def test_one_count_where_the_dense_form_is_not_allowed(m):
     K, rec = match(W.uniform_instance(32, (1 << 20) + 77, m, 2, 9000.0))
     assert K > 100 * m
     assert rec["traverse_tile_count_stash"] == 1 and "traverse_tile_count" not in rec
+
+
+@pytest.mark.parametrize("which", [0, 1])
+def test_refused_move_matches_nothing(which):
+    """A move with a repeated id leaves gaps in the gathered extents; what the
+    scratch held there (the wide extents of the move before) must not be matched."""
+    import paper_1309_3458_amd as P
+    n, c = 60000, 64
+    inst = W.uniform_instance(33, n, n, 2, 300.0)
+    dyn = P.Dynamic(dev(inst.s_lo), dev(inst.s_hi), dev(inst.u_lo), dev(inst.u_hi))
+    lo = dev(np.zeros((2, c), np.float32))
+    hi = dev(np.full((2, c), 2e6, np.float32))
+    ids = dev(np.arange(c, dtype=np.int32))
+    for _ in range(3):  # the last one finds its scratch where the one before had it
+        K = dyn.move(which, ids, lo, hi)
+    assert K >= c * (n - c)
+    before = dyn.pairs()
+
+    def refused():
+        with pytest.raises(P.DDMError):
+            dyn.move(which, dev(np.full(c, 5, np.int32)), lo, hi)
+
+    _, rec = recorded(refused)
+    assert "listsort" not in rec and "traverse_tile_fill_units" not in rec
+    assert bool((dyn.pairs() == before).all())
+    dyn.free()
