@@ -1665,9 +1665,9 @@ static ddm_status launch_traverse(const MatchPlan& P, const TreeDev& T, const fl
     lane_kernel<D, FILL><<<(US.total + bs - 1) / bs, bs, 0, s>>>(T, ulo, uhi, m, US, kstar, O);
     DDM_LAUNCHED("lane_kernel");
   } else {
-    ProfScope ps(FILL ? (US.qpt == 1 ? "traverse_tile1_fill"
-                                     : US.tstart ? "traverse_tile_fill_balanced"
-                                                 : "traverse_tile_fill")
+    ProfScope ps(FILL ? (US.refill ? "traverse_tile1_fill"
+                                   : US.tstart ? "traverse_tile_fill_balanced"
+                                               : "traverse_tile_fill")
                       : (O.skey ? "traverse_tile_count_stash" : "traverse_tile_count"),
                  s);
     // at most one partial tile per class; a tile list cut by work as well has
@@ -2244,9 +2244,11 @@ static ddm_status predict_room(const ddm_tree* t, const float* ulo, const float*
   return DDM_OK;
 }
 
-// the pairs of the units, at their final places
+// the pairs of the units, at their final places (recorded as the step of its path
+// that writes the pairs, which is a fill traversal otherwise, and by its own name)
 static ddm_status dense_expand(uint32_t d, const MatchState& st, uint64_t* out, hipStream_t s) {
-  ProfScope ps(st.learned ? "traverse_tile_fill_balanced" : "traverse_tile_fill_units", s);
+  ProfScope step(st.learned ? "traverse_tile_fill_balanced" : "traverse_tile_fill_units", s);
+  ProfScope ps("dense_expand", s);
   const UpdSet US = st.all();
 #define DDM_EXPAND(DD)                                                                          \
   if (st.group == kGroupLong)                                                                   \
@@ -2970,6 +2972,7 @@ extern "C" ddm_status ddm_match_finish(ddm_pending* pd, uint64_t* out_pairs, uin
         // overflowed updates are few and scattered, and each has many
         // hits: one wavefront per update scans its candidate range
         UpdSet OV{st.perm_ovf, st.gstart, st.govf, st.novf, 1};
+        OV.refill = true;
         OV.pb = st.all().pb;
         MatchPlan TP = pd->plan;
         TP.traversal = DDM_TRAVERSE_TILE;

@@ -135,6 +135,7 @@ struct UpdSet {
   const uint32_t* tstart = nullptr;
   const uint32_t* tclass = nullptr;
   const uint64_t* ntiles = nullptr;
+  bool refill = false;  // the updates that overflowed their slots (names the kernel's record)
 };
 
 // Where a traversal writes.  COUNT (fill == false): cnt[j] = hits of j.

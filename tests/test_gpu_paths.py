@@ -71,3 +71,65 @@ def test_refused_move_matches_nothing(which):
     assert "listsort" not in rec and "traverse_tile_fill_units" not in rec
     assert bool((dyn.pairs() == before).all())
     dyn.free()
+
+
+def diagonal(seed, n, m, d, side):
+    """Extents along the diagonal: the sample takes the dimensions as
+    independent and expects few hits."""
+    rng = np.random.default_rng(seed)
+
+    def draw(count):
+        c = rng.uniform(0, 1e6, count)
+        lo = np.stack([(c + rng.uniform(0, 100, count)) for _ in range(d)]).astype(np.float32)
+        return lo, (lo + np.float32(side)).astype(np.float32)
+
+    u = draw(m)
+    s = draw(n)
+    return W.Instance(s[0], s[1], u[0], u[1])
+
+
+FILLS = ("traverse_tile_fill", "traverse_tile_fill_balanced")
+
+
+@pytest.mark.parametrize("d", [2, 3])
+def test_overflowing_stash_takes_the_dense_form(d):
+    K, rec = match(diagonal(34, 150000, 20000, d, 1500.0))
+    assert K > 100 * 20000
+    assert rec["traverse_tile_count_stash"] == 1 and rec["dense_expand"] == 1
+    assert not any(k in rec for k in FILLS)
+
+
+@pytest.mark.parametrize("m", [8000, 20000])
+def test_overflowing_stash_fills_where_the_dense_form_is_not_allowed(m):
+    """More than 2^20 subscriptions."""
+    K, rec = match(diagonal(35, (1 << 20) + 5, m, 2, 100.0))
+    assert K > 100 * m
+    assert rec["traverse_tile_count_stash"] == 1 and "stash_scatter" not in rec
+    assert any(k in rec for k in FILLS) and "dense_expand" not in rec
+    assert "traverse_tile1_fill" not in rec
+
+
+@pytest.mark.parametrize("m", [300, 8192, 20000])
+def test_name_of_a_plain_fill(m):
+    """One update to a tile is not the refill of overflowed slots."""
+    K, rec = match(W.uniform_instance(36, 50000, m, 1, 60.0))
+    assert K > 0 and any(k in rec for k in FILLS) and "traverse_tile1_fill" not in rec
+
+
+def test_name_of_a_refill():
+    """A predictor that gives every update two slots: the others are refilled."""
+    import paper_1309_3458_amd as P
+    from oracle import mlp_ref
+    p = P.Predictor(0)
+    w = np.zeros(mlp_ref.N_PARAMS, np.float32)
+    w[-1] = np.log1p(2.0)
+    p.set_params(w, 0.0)
+    inst = W.uniform_instance(37, 20000, 9001, 2, 9000.0)
+    want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo, inst.u_hi, threads=8)
+    t = P.build(dev(inst.s_lo), dev(inst.s_hi))
+    keys, rec = recorded(lambda: P.match_learned(t, dev(inst.u_lo), dev(inst.u_hi), p))
+    assert np.array_equal(keys.cpu().numpy().view(np.uint64), want)
+    assert rec["traverse_tile1_fill"] == 1 and rec["traverse_tile_fill_balanced"] == 1
+    assert "dense_expand" not in rec
+    t.free()
+    p.free()
