@@ -99,10 +99,10 @@ def test_overflowing_stash_takes_the_dense_form(d):
     assert not any(k in rec for k in FILLS)
 
 
-@pytest.mark.parametrize("m", [8000, 20000])
-def test_overflowing_stash_fills_where_the_dense_form_is_not_allowed(m):
-    """More than 2^20 subscriptions."""
-    K, rec = match(diagonal(35, (1 << 20) + 5, m, 2, 100.0))
+@pytest.mark.parametrize("m, side", [(8000, 600.0), (20000, 150.0)])
+def test_overflowing_stash_fills_where_the_dense_form_is_not_allowed(m, side):
+    """More than 2^20 subscriptions, more hits than the stash has room for."""
+    K, rec = match(diagonal(35, (1 << 20) + 5, m, 2, side))
     assert K > 100 * m
     assert rec["traverse_tile_count_stash"] == 1 and "stash_scatter" not in rec
     assert any(k in rec for k in FILLS) and "dense_expand" not in rec
