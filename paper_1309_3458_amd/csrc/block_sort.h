@@ -35,7 +35,9 @@ __device__ __forceinline__ void block_sort(BlockSortLds<R, V>& L, uint32_t (&key
     const uint32_t shift = 8u * pass;
     for (uint32_t i = lane; i < 256; i += kWave) L.wcnt[wave][i] = 0;
     uint32_t loc[R];
-    // (a wavefront's own counters: LDS operations of one wavefront are in order)
+    // (the counters are the wavefront's own, but a lane reads what others wrote:
+    // cleared above, counted in the round before)
+    wave_sync();
 #pragma unroll
     for (uint32_t r = 0; r < R; ++r) {
       const bool valid = block_sort_index<R>(r) < n;
@@ -44,7 +46,9 @@ __device__ __forceinline__ void block_sort(BlockSortLds<R, V>& L, uint32_t (&key
       const uint32_t rk = mask_rank(peers);
       const uint32_t c = valid ? L.wcnt[wave][dig] : 0u;
       loc[r] = c + rk;
+      wave_sync();
       if (valid && rk == 0) L.wcnt[wave][dig] = c + (uint32_t)__popcll(peers);
+      wave_sync();
     }
     __syncthreads();
     // digit tid: the wavefronts' counts become offsets within the digit, then

@@ -196,6 +196,14 @@ __device__ __forceinline__ uint64_t match_digit8(uint32_t dig, uint64_t active) 
   return ((uint64_t)phi << 32) | plo;
 }
 
+// LDS written by other lanes of the wavefront may be read after this: orders the
+// accesses in the compiler (the hardware keeps a wavefront's in order)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);

@@ -75,12 +75,6 @@ __device__ __forceinline__ bool overlaps(const float (&v)[2 * D], const float (&
   return ok;
 }
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   return wave_fold_dpp(v, [](uint32_t a, uint32_t b) { return min(a, b); });
 }
