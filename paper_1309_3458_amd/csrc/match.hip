@@ -2093,11 +2093,26 @@ static ddm_status list_any(uint32_t d, const TreeDev& T, const float* ulo, const
   return DDM_OK;
 }
 
-// d = 1: pairs from which the dense form is taken (the counts are exact before
-// any traversal).  Match, us, fill and sort / dense form: 250,000 + 250,000
-// segments 141/219 at 5*10^6 pairs, 265/219 at 10^7, 486/295 at 4*10^7; 80,000 +
-// 80,000 150/154 at 6*10^6, 186/160 at 1.3*10^7.
-constexpr uint64_t kDensePairs1 = 1u << 23;
+// d = 1: whether K pairs of m updates and n subscriptions take the dense form (the
+// counts are exact before any traversal).  It lists and tests every tile, so it
+// pays where a tile has many updates and an update many hits.  Match, us, fill and
+// sort / dense form (n = 10^6; in brackets n = 20,000):
+//   m =     9,000  10^7 pairs  252/315 [236/260]   4*10^7  477/594 [432/470]
+//   m =    20,000        10^7  214/240 [185/193]   2.5*10^7  366/347
+//   m =    60,000     1.5*10^7  218/256 [178/194]  4*10^7  495/344 [464/299]
+//   m =   150,000        10^7  241/242 [212/188]   2.5*10^7  339/269
+//   m =   500,000        10^7  256/376             1.5*10^7  397/378, 2.5*10^7  542/411
+//   m = 3,000,000     4*10^7  1007/1555            10^8  2235/1619
+// Up to 8192 updates a tile has one, its list is the update's hits, and the form
+// loses; such sets still take it where more than half of all pairs meet (2700
+// updates, 5000 subscriptions, 9.6*10^6 pairs: 283/357), which is where long lists
+// of one-update tiles are tested.
+constexpr uint64_t kDensePairs1 = 1u << 23, kDenseHits1 = 28;
+static bool dense_pays_1d(uint64_t K, uint32_t n, uint32_t m) {
+  if (K > kDensePairs1 && K > (uint64_t)n * m / 2) return true;
+  const uint32_t q = tile_updates(m);
+  return q >= 4 && K > (q >= 32 ? 1 : 2) * kDensePairs1 && K > kDenseHits1 * m;
+}
 // learned: predicted hits per update from which it is taken
 constexpr double kLearnedDenseHits = 32.0;
 // most candidates whose lists and masks (16 bytes each) the match allocates
@@ -2540,7 +2555,7 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   const bool marked = st.stash && (hw[3] & kStashDense);
   bool dense = marked;
   if (!marked && may_dense && P.traversal == DDM_TRAVERSE_TILE && !counts_out && !st.learned &&
-      (d == 1 ? st.K > kDensePairs1 : st.stash && !st.stash_ok)) {
+      (d == 1 ? dense_pays_1d(st.K, tree_n(t), m) : st.stash && !st.stash_ok)) {
     SegOut O{};
     O.tcand = st.tcand;
     O.tsum = st.tsum;

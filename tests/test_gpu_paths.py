@@ -133,3 +133,19 @@ def test_name_of_a_refill():
     assert "dense_expand" not in rec
     t.free()
     p.free()
+
+
+@pytest.mark.parametrize("n, m, hits, dense", [
+    (20000, 8000, 1200, False),       # one update to a tile
+    (100000, 700000, 14, False),      # many updates, few hits each
+    (100000, 60000, 167, False),      # tiles of 8: from 2^24 pairs
+    (100000, 60000, 400, True),
+    (20000, 154000, 62, True),        # tiles of 32: from 2^23 pairs
+    (3000, 4000, 2200, True),         # more than half of all pairs
+])
+def test_one_dimension_takes_the_dense_form_where_it_pays(n, m, hits, dense):
+    f = hits / n
+    side = 1e6 * (1.0 - (1.0 - f) ** 0.5)
+    K, rec = match(W.uniform_instance(38, n, m, 1, side))
+    assert K > (1 << 23)
+    assert ("dense_expand" in rec) == dense and any(k in rec for k in FILLS) != dense
