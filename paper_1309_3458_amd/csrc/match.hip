@@ -2288,7 +2288,8 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
                              uint32_t** lists, uint32_t** lists_count, hipStream_t s,
                              const ddm_predictor* pred = nullptr, uint64_t budget = 0,
                              bool want_stash = false, uint64_t stash_hint = 0,
-                             const ArenaGrant* grant = nullptr, bool may_dense = false) {
+                             const ArenaGrant* grant = nullptr, bool may_dense = false,
+                             uint64_t max_pairs = ~0ull) {
   const uint32_t d = tree_d(t);
   const TreeDev T = tree_dev(t);
   Scratch& sc = st.sc;
@@ -2551,11 +2552,13 @@ static ddm_status front_half(const ddm_tree* t, const float* ulo, const float* u
   }
   // Dense sets: a set marked before the count has only its candidates counted
   // so far; one that overflowed the stash, or (d = 1) has its exact counts,
-  // takes the dense form too, once its candidates are counted.
+  // takes the dense form too, once its candidates are counted (not for more pairs
+  // than the caller has room for: those are refused by their number).
   const bool marked = st.stash && (hw[3] & kStashDense);
   bool dense = marked;
   if (!marked && may_dense && P.traversal == DDM_TRAVERSE_TILE && !counts_out && !st.learned &&
-      (d == 1 ? dense_pays_1d(st.K, tree_n(t), m) : st.stash && !st.stash_ok)) {
+      (d == 1 ? dense_pays_1d(st.K, tree_n(t), m) : st.stash && !st.stash_ok) &&
+      st.K <= max_pairs) {
     SegOut O{};
     O.tcand = st.tcand;
     O.tsum = st.tsum;
@@ -2771,7 +2774,8 @@ struct ddm_pending {
 static ddm_status match_begin(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
                               uint32_t m, uint64_t* out_count, void* stream,
                               const ddm_match_opts* opts, ddm_pending** out_pending,
-                              bool want_stash, uint64_t stash_hint, bool may_dense);
+                              bool want_stash, uint64_t stash_hint, bool may_dense,
+                              uint64_t max_pairs = ~0ull);
 
 extern "C" ddm_status ddm_match_begin(const ddm_tree* t, const float* upd_lo,
                                       const float* upd_hi, uint32_t m, uint64_t* out_count,
@@ -2791,7 +2795,8 @@ ddm_status match_begin_bounded(const ddm_tree* t, const float* upd_lo, const flo
 static ddm_status match_begin(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
                               uint32_t m, uint64_t* out_count, void* stream,
                               const ddm_match_opts* opts, ddm_pending** out_pending,
-                              bool want_stash, uint64_t stash_hint, bool may_dense) {
+                              bool want_stash, uint64_t stash_hint, bool may_dense,
+                              uint64_t max_pairs) {
   set_detail("");
   if (!out_count || !out_pending) {
     set_detail("out_count / out_pending is NULL");
@@ -2817,7 +2822,7 @@ static ddm_status match_begin(const ddm_tree* t, const float* upd_lo, const floa
   pd->uhi = upd_hi;
   pd->m = m;
   r = front_half(t, upd_lo, upd_hi, m, P, pd->st, nullptr, &pd->lists, &pd->lists_count, s,
-                 nullptr, 0, want_stash, stash_hint, nullptr, may_dense);
+                 nullptr, 0, want_stash, stash_hint, nullptr, may_dense, max_pairs);
   if (r != DDM_OK) {
     delete pd;
     return r;
@@ -3058,7 +3063,8 @@ extern "C" ddm_status ddm_match_ex(const ddm_tree* t, const float* upd_lo, const
   // the capacity sizes the count traversal's stash (none for a size query),
   // up to kStashMaxPerUpdate hits per update
   ddm_status r = match_begin(t, upd_lo, upd_hi, m, out_count, stream, opts, &pd, capacity > 0,
-                             std::min<uint64_t>(capacity, kStashMaxPerUpdate * m), capacity > 0);
+                             std::min<uint64_t>(capacity, kStashMaxPerUpdate * m), capacity > 0,
+                             capacity);
   if (r != DDM_OK) return r;
   if (*out_count > capacity) {
     ddm_match_abort(pd);

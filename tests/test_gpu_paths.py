@@ -149,3 +149,27 @@ def test_one_dimension_takes_the_dense_form_where_it_pays(n, m, hits, dense):
     K, rec = match(W.uniform_instance(38, n, m, 1, side))
     assert K > (1 << 23)
     assert ("dense_expand" in rec) == dense and any(k in rec for k in FILLS) != dense
+
+
+@pytest.mark.parametrize("d", [1, 2])
+def test_a_result_beyond_the_capacity_is_only_counted(d):
+    """The number of pairs is known before the dense form is begun."""
+    import paper_1309_3458_amd as P
+    import torch
+    inst = diagonal(39, 150000, 154000, d, 400.0)
+    want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo, inst.u_hi, threads=8)
+    t = P.build(dev(inst.s_lo), dev(inst.s_hi))
+    out = torch.full((1000,), -1, dtype=torch.int64, device="cuda")
+
+    def refused():
+        with pytest.raises(P.DDMError) as e:
+            P.match_into(t, dev(inst.u_lo), dev(inst.u_hi), out)
+        assert str(len(want)) in str(e.value)
+
+    _, rec = recorded(refused)
+    assert "listsort" not in rec and bool((out == -1).all())
+    big = torch.empty(len(want), dtype=torch.int64, device="cuda")
+    K, rec = recorded(lambda: P.match_into(t, dev(inst.u_lo), dev(inst.u_hi), big))
+    assert rec["dense_expand"] == 1
+    assert np.array_equal(big[:K].cpu().numpy().view(np.uint64), want)
+    t.free()
