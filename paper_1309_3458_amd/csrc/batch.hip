@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "ddm_internal.h"
+#include "order.h"
 #include "traverse.h"
 #include "tree_dev.h"
 
@@ -44,6 +45,21 @@ struct BInst {
   uint32_t* khi;   // n upper keys (d == 1), else null
   uint32_t* idb;   // d * (n + 1) payload / ids
 };
+
+// Cells of m updates in d dimensions (d > 1): along each dimension, the class's
+// own first and the others ascending.  All but the last are cut into as many
+// ranges as there are tiles of 64 along a dimension, the last into as many as
+// the rest of the `cells` allow, so that a tile takes a few cells of one line.
+static void batch_cell_shape(uint32_t m, uint32_t d, uint32_t cells, uint32_t (&b)[DDM_MAX_D]) {
+  uint32_t rest = cells;
+  for (uint32_t s = 0; s < DDM_MAX_D; ++s) b[s] = 1;
+  const double g = std::pow((double)m / 64.0, 1.0 / (double)d);
+  for (uint32_t s = 0; s + 1 < d; ++s) {
+    b[s] = std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(g + 0.5), rest / 2));
+    rest /= b[s];
+  }
+  b[d - 1] = std::max<uint32_t>(1u, rest);
+}
 
 constexpr uint32_t kProbeThreads = 1024;
 // trees are a grid dimension of the index kernel (at most 65535)
@@ -775,7 +791,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
     bi.qbase = (uint32_t)qbase;
     bi.bbase = (uint32_t)bbase;
     bi.nb = std::max<uint32_t>(1, (q.m + 7) / 8);
-    cell_shape(q.m, q.d, bi.nb, bi.cb);
+    batch_cell_shape(q.m, q.d, bi.nb, bi.cb);
     bi.qpt = q.qpt ? q.qpt : o.qpt;
     bi.ebase = ebase;
     qbase += q.m;

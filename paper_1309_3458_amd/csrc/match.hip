@@ -31,6 +31,7 @@
 // slots sized by a predictor while counting exactly.
 #include "ddm_internal.h"
 #include "dense.h"
+#include "order.h"
 #include "traverse.h"
 
 #include <algorithm>
@@ -95,10 +96,6 @@ constexpr uint32_t kCellBlocks = kCells / kCellBlock;  // per class
 constexpr uint32_t kSmallOrder = 8192, kSmallCells = 2048;
 constexpr uint32_t kBadCell = 0xffffffffu;  // an update with an invalid extent
 
-struct CellShape {
-  uint32_t b[DDM_MAX_D];  // cells along each dimension, as cell_shape gives them
-};
-
 // updates per tile: 64, or fewer (down to one) while that leaves at most
 // kFewTiles tiles, so that the chip has wavefronts to run and few updates in a
 // large set do not share boxes wider than their own (17,389 updates of 21 hits
@@ -145,219 +142,38 @@ __global__ __launch_bounds__(256) void bits1_kernel(TreeDev T, const float* __re
   if (!SMALL && ballot(bad) != 0 && lane_id() == 0) atomicOr(flag, 2);
 }
 
-// the probe estimate of an update: the probe dimension bk, #quantiles <=
-// q.hi and < q.lo - maxlen there (bqa, bqb), #quantiles <= the box centre in
-// every dimension, and whether the extent is invalid
-template <int D>
-struct ProbeEst {
-  uint32_t bk, bqa, bqb;
-  uint32_t mid[D];
-  uint32_t est[D];  // quantiles of the candidate positions in every dimension
-  float hits;  // subscriptions met, were the dimensions independent
-  bool bad;
-};
-
-// the update's extents (ua, ub: dimension k of update j), loaded before the
-// quantiles are (their loads overlap)
-template <int D>
-struct UpdExt {
-  float a[D], b[D];
-};
-template <int D>
-__device__ __forceinline__ UpdExt<D> load_ext(const float* __restrict__ ulo,
-                                              const float* __restrict__ uhi, uint32_t m,
-                                              uint32_t j) {
-  UpdExt<D> e;
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    e.a[k] = ulo[(size_t)k * m + j];
-    e.b[k] = uhi[(size_t)k * m + j];
-  }
-  return e;
-}
-
-// the kQuant quantiles of every dimension into LDS (sq[k][qslot(i)]), by
-// THREADS threads: every load is issued before the first LDS store, so that
-// they are in flight together
-template <int D, uint32_t THREADS>
-__device__ __forceinline__ void load_quant_lds(const TreeDev& T, uint32_t (*sq)[kQuantPad]) {
-  static_assert(kQuant % THREADS == 0, "whole rounds");
-  constexpr uint32_t Q = kQuant / THREADS;
-  uint32_t v[D][Q];
-#pragma unroll
-  for (int k = 0; k < D; ++k)
-#pragma unroll
-    for (uint32_t r = 0; r < Q; ++r) v[k][r] = T.quant[k][r * THREADS + threadIdx.x];
-#pragma unroll
-  for (int k = 0; k < D; ++k)
-#pragma unroll
-    for (uint32_t r = 0; r < Q; ++r) sq[k][qslot(r * THREADS + threadIdx.x)] = v[k][r];
-}
-
-// The class of an update is its probe dimension; cls names one for the whole set
-// (the dimension whose ranges are the shortest on average, by the sample), or
-// lets every update take its own, for small sets and the lane form.  With own
-// classes the few updates of a set that leave the common one make up tiles that
-// span the space: the 16-hotspot workload, ten seeds, 6.5 .. 9.4 ms, mean 7.5,
-// against 6.5 .. 7.3, mean 6.8; d = 4, 62,266 updates, a count of 284 us against 84.
-constexpr uint32_t kOwnClass = ~0u;
-
-template <int D>
-__device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
-                                                      const uint32_t (*sq)[kQuantPad],
-                                                      const UpdExt<D>& e, uint32_t cls) {
-  ProbeEst<D> P;
-  P.bad = false;
-  uint32_t xh[D], xl[D], xm[D], qa[D], qb[D], qm[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const float a = e.a[k], b = e.b[k];
-    P.bad = P.bad || !valid_extent(a, b);
-    xh[k] = f2key(b);
-    xl[k] = f2key(nextafterf(a - T.maxlen[k], -INFINITY));
-    xm[k] = f2key(0.5f * a + 0.5f * b);
-    qa[k] = qb[k] = qm[k] = 0;
-  }
-  // the 3D quantile searches (#quantiles <= xh, < xl, <= xm per dimension)
-  // advance in lockstep, so their LDS reads overlap
-#pragma unroll
-  for (uint32_t step = kQuant; step > 0; step >>= 1) {
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      const uint32_t ca = qa[k] + step, cb = qb[k] + step, cm = qm[k] + step;
-      const uint32_t va = ca <= kQuant ? sq[k][qslot(ca - 1)] : 0xffffffffu;
-      const uint32_t vb = cb <= kQuant ? sq[k][qslot(cb - 1)] : 0xffffffffu;
-      const uint32_t vm = cm <= kQuant ? sq[k][qslot(cm - 1)] : 0xffffffffu;
-      if (ca <= kQuant && va <= xh[k]) qa[k] = ca;
-      if (cb <= kQuant && vb < xl[k]) qb[k] = cb;
-      if (cm <= kQuant && vm <= xm[k]) qm[k] = cm;
-    }
-  }
-  // an update's own class: dimension 0, unless another one's range is less than
-  // a third as long (at the edge of the space a range is half as long)
-  uint32_t best = 0;
-  P.hits = (float)T.n;
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const uint32_t est = qa[k] - min(qa[k], qb[k]);
-    P.hits *= fmaxf((float)est, 0.5f) * (1.f / (float)kQuant);
-    P.mid[k] = qm[k];
-    P.est[k] = est;
-    if (cls == kOwnClass ? k == 0 || 3u * est + 16u < best : (uint32_t)k == cls) {
-      best = est;
-      P.bk = (uint32_t)k;
-      P.bqa = qa[k];
-      P.bqb = qb[k];
-    }
-  }
-  return P;
-}
-
-constexpr uint32_t kShapeSamples = 256;
-
-// Up to kShapeSamples updates spread evenly over the set decide whether the
-// count traversal keeps its hits: the stash is marked full before it is used,
-// and the set matched as a dense one, when the estimated hits (the candidate
-// fractions of the dimensions multiplied, as if they were independent) exceed
-// four fifths of the stash's counted chunks (tiles leave some of theirs), or per
-// update the larger of kDenseHits and
-// kDenseScale * d / sqrt(m).  The dense form takes two more synchronizations and
-// nine more launches, a fixed 70 us, and saves on every pair, the more the more
-// updates lie near each other.  Match of m updates against m subscriptions, us,
-// keeping hits / dense form (10, 20, 40, 80 hits each):
-//   d = 2  m =  20,000   86/157   91/158  138/157  232/152
-//          m =  80,000  128/164  164/159  306/164  345/173
-//          m = 250,000  240/229  388/236  530/245  603/273
-//   d = 3  m =  20,000   92/160  101/169  146/170  184/178
-//          m =  80,000  145/189  181/199  370/211  492/251
-//   d = 4  m =  80,000  208/283  211/305  505/369  731/424
-// A set whose dimensions are correlated may still overflow the stash.
-constexpr float kDenseHits = 10.f, kDenseScale = 3000.f;
-
-// (run by one workgroup of at least kShapeSamples threads; full, cls: may be null;
-// mark: kStashDense where the dense form may follow, else 1, a stash that is full,
-// so that the count traversal counts at once)
-template <int D, uint32_t THREADS>
-__device__ __forceinline__ void sample_set(const TreeDev& T, const float* __restrict__ ulo,
-                                           const float* __restrict__ uhi, uint32_t m,
-                                           uint32_t (*sq)[kQuantPad], uint32_t* __restrict__ full,
-                                           uint32_t mark, uint32_t room,
-                                           uint32_t* __restrict__ cls) {
-  static_assert(THREADS >= kShapeSamples, "one sample per thread");
-  constexpr uint32_t W = kShapeSamples / kWave;
-  __shared__ float whits[W];
-  __shared__ uint32_t west[D][W];
-  const uint32_t S = min(m, kShapeSamples);
-  UpdExt<D> e{};
-  if (threadIdx.x < S) e = load_ext<D>(ulo, uhi, m, (uint32_t)(((uint64_t)threadIdx.x * m) / S));
-  load_quant_lds<D, THREADS>(T, sq);
-  __syncthreads();
-  if (threadIdx.x < kShapeSamples) {
-    float hits = 0.f;
-    uint32_t est[D] = {};
-    if (threadIdx.x < S) {
-      const ProbeEst<D> P = probe_estimate<D>(T, sq, e, kOwnClass);
-      if (!P.bad) {
-        hits = P.hits;
-#pragma unroll
-        for (int k = 0; k < D; ++k) est[k] = P.est[k];
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, kWave);
-    if (lane_id() == 0) whits[threadIdx.x / kWave] = hits;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      const uint32_t sum = wave_scan_dpp(est[k]);
-      if (lane_id() == kWave - 1) west[k][threadIdx.x / kWave] = sum;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (uint32_t w = 0; w < W; ++w) t += whits[w];
-    t /= (float)S;
-    const float dense = fmaxf(kDenseHits, kDenseScale * (float)D * rsqrtf((float)m));
-    if (full) *full = t > dense || t * (float)m > 0.8f * (float)room ? mark : 0u;
-    uint32_t c = 0, best = 0;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      uint32_t sum = 0;
-      for (uint32_t w = 0; w < W; ++w) sum += west[k][w];
-      if (k == 0 || 2u * sum + 16u * S < best) {
-        best = sum;
-        c = (uint32_t)k;
-      }
-    }
-    if (cls) *cls = c;
-  }
-}
-
-constexpr uint32_t kProbeThreads = 1024;
+// SMALL: own classes, and the last workgroup takes the sample for `full`
 template <int D, bool SMALL>
-__global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const float* __restrict__ ulo,
-                                                     const float* __restrict__ uhi, uint32_t m,
-                                                     CellShape shape,
-                                                     uint8_t* __restrict__ kstar,
-                                                     uint32_t* __restrict__ bucket,
-                                                     uint32_t* __restrict__ rank,
-                                                     uint32_t* __restrict__ bhist,
-                                                     int32_t* __restrict__ flag,
-                                                     uint2* __restrict__ pb,
-                                                     uint32_t* __restrict__ full, uint32_t mark,
-                                                     uint32_t room,
-                                                     const uint32_t* __restrict__ cls) {
+__global__ __launch_bounds__(kPlanThreads) void probe_kernel(
+    TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
+    const OrderPlan* __restrict__ plan, uint8_t* __restrict__ kstar,
+    uint32_t* __restrict__ bucket, uint32_t* __restrict__ rank, uint32_t* __restrict__ bhist,
+    int32_t* __restrict__ flag, uint2* __restrict__ pb, uint32_t* __restrict__ full, uint32_t mark,
+    uint32_t room) {
   __shared__ uint32_t sq[D][kQuantPad];
-  if (SMALL && full && blockIdx.x == gridDim.x - 1) {
-    sample_set<D, kProbeThreads>(T, ulo, uhi, m, sq, full, mark, room, nullptr);
-    return;
+  __shared__ uint32_t shape[D][DDM_MAX_D];
+  if constexpr (SMALL) {
+    if (full && blockIdx.x == gridDim.x - 1) {
+      __shared__ SampleLds<D> L;
+      sample_set<D>(T, ulo, uhi, m, sq, L, full, mark, room, nullptr, 0, true);
+      return;
+    }
   }
-  const uint32_t set_class = !SMALL && cls ? uniform_u32(*cls) : kOwnClass;
-  const uint32_t j = blockIdx.x * kProbeThreads + threadIdx.x;
+  const uint32_t set_class = SMALL ? kOwnClass : uniform_u32(plan->cls);
+  const uint32_t j = blockIdx.x * kPlanThreads + threadIdx.x;
   const bool act = j < m;
   UpdExt<D> e{};
   if (act) e = load_ext<D>(ulo, uhi, m, j);
-  load_quant_lds<D, kProbeThreads>(T, sq);
+  load_quant_lds<D, kPlanThreads>(T, sq);
+  if (threadIdx.x < D * DDM_MAX_D) {
+    const uint32_t c = threadIdx.x / DDM_MAX_D, i = threadIdx.x % DDM_MAX_D;
+    if (SMALL) {
+      const float r[D] = {};
+      if (i == 0) cell_shape<D>((float)m, c, kSmallCells, r, shape[c]);
+    } else {
+      shape[c][i] = plan->b[c][i];
+    }
+  }
   __syncthreads();
   bool bad = false;
   if (act) {
@@ -376,20 +192,10 @@ __global__ __launch_bounds__(kProbeThreads) void probe_kernel(TreeDev T, const f
       const uint32_t hi = qa < kQuant ? (uint32_t)(((uint64_t)qa * T.n) / kQuant) : T.n;
       pb[j] = bad ? make_uint2(1u, 0u) : make_uint2(lo + 1u, hi);
     }
-    uint32_t sub = 0;
-#pragma unroll
-    for (int s = 0; s < D; ++s) {
-      const uint32_t kk = s == 0 ? bk : (uint32_t)(s - 1) + (((uint32_t)(s - 1) >= bk) ? 1u : 0u);
-      uint32_t qp = 0;
-#pragma unroll
-      for (int k = 0; k < D; ++k)
-        if ((uint32_t)k == kk) qp = P.mid[k];
-      const uint32_t n = shape.b[s];
-      uint32_t i = min(qp * n / (kQuant + 1u), n - 1u);
-      if (sub & 1u) i = n - 1u - i;  // the serpentine's way back
-      sub = sub * n + i;
-    }
-    const uint32_t bu = bk * (SMALL ? kSmallCells : kCells) + (bad ? 0u : sub);
+    // (classes that the sample did not meet have cells too)
+    const uint32_t sub = bad ? 0u : grid_cell<D>(shape[bk], bk, P.mid);
+    const uint32_t bu =
+        (set_class != kOwnClass ? 0u : bk * (SMALL ? kSmallCells : kCells)) + sub;
     bucket[j] = SMALL && bad ? kBadCell : bu;
     if (!SMALL) rank[j] = atomicAdd(&bhist[bu * kCntPad], 1u);
   }
@@ -513,7 +319,8 @@ __global__ __launch_bounds__(1024) void order_small_kernel(
 __global__ __launch_bounds__(256) void cell_scatter_kernel(
     const uint32_t* __restrict__ bucket, const uint32_t* __restrict__ rank, uint32_t m,
     const uint32_t* __restrict__ boff, const uint32_t* __restrict__ bsum, uint32_t nb,
-    uint32_t* __restrict__ perm, uint32_t* __restrict__ gstart, uint32_t* __restrict__ gcount) {
+    uint32_t* __restrict__ perm, uint32_t* __restrict__ gstart, uint32_t* __restrict__ gcount,
+    const OrderPlan* __restrict__ plan) {
   static_assert(kCellBlocks * DDM_MAX_D <= kWave, "one lane per cell block");
   __shared__ uint32_t first[kWave + 1];
   const uint32_t j = blockIdx.x * 256 + threadIdx.x;
@@ -527,7 +334,12 @@ __global__ __launch_bounds__(256) void cell_scatter_kernel(
   __syncthreads();
   if (j < m) perm[first[bu / kCellBlock] + boff[bu] + r] = j;
   if (blockIdx.x == 0 && threadIdx.x < DDM_MAX_D) {
-    const uint32_t a = first[threadIdx.x * kCellBlocks], e = first[(threadIdx.x + 1) * kCellBlocks];
+    const uint32_t cls = plan ? plan->cls : kOwnClass;
+    uint32_t a = first[threadIdx.x * kCellBlocks], e = first[(threadIdx.x + 1) * kCellBlocks];
+    if (cls != kOwnClass) {  // one class, in the cells of all
+      a = threadIdx.x > cls ? m : 0u;
+      e = threadIdx.x >= cls ? m : 0u;
+    }
     gstart[threadIdx.x] = a;
     gcount[threadIdx.x] = e - a;
   }
@@ -1735,7 +1547,7 @@ struct MatchState {
   uint32_t* perm = nullptr;
   uint32_t* gstart = nullptr;
   uint32_t* gcount = nullptr;
-  uint32_t* cls = nullptr;    // the set's class, by the sample
+  OrderPlan* plan = nullptr;  // classes and cells, by the sample
   uint32_t* pb = nullptr;     // per update: candidate position bounds (d > 1)
   bool pb_ok = false;
   bool balanced = false;  // the learned single pass runs the work-cut tile list
@@ -1804,17 +1616,18 @@ struct MatchState {
 // zeroes the match's counters; with a stash (snext non-null) also sets the
 // slices' next free chunks; d > 1: one more workgroup takes the sample
 template <int D>
-__global__ __launch_bounds__(1024) void match_init_kernel(
+__global__ __launch_bounds__(kPlanThreads) void match_init_kernel(
     int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
     uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum,
     TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
-    uint32_t mark, uint32_t room, uint32_t* __restrict__ cls) {
-  static_assert(kCells % 1024 == 0, "whole workgroups");
+    uint32_t mark, uint32_t room, OrderPlan* __restrict__ plan, bool own_class) {
+  static_assert(kCells % kPlanThreads == 0, "whole workgroups");
   if constexpr (D > 1) {
-    if (blockIdx.x == D * kCells / 1024) {
+    if (blockIdx.x == D * kCells / kPlanThreads) {
       __shared__ uint32_t sq[D][kQuantPad];
-      sample_set<D, 1024>(T, ulo, uhi, m, sq, snext ? snext + kStashSlices : nullptr, mark, room,
-                          cls);
+      __shared__ SampleLds<D> L;
+      sample_set<D>(T, ulo, uhi, m, sq, L, snext ? snext + kStashSlices : nullptr, mark, room,
+                    plan, kCells, own_class);
       return;
     }
   }
@@ -1841,9 +1654,9 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
   const uint32_t mark = st.may_dense ? kStashDense : 1u;
   const bool small = m <= kSmallOrder;
   if (!small) {
-    match_init_kernel<D><<<D * kCells / 1024 + (D > 1 ? 1 : 0), 1024, 0, s>>>(
+    match_init_kernel<D><<<D * kCells / kPlanThreads + (D > 1 ? 1 : 0), kPlanThreads, 0, s>>>(
         st.flag, lists_count, st.bcnt, sn, st.sfirst, st.sslice, st.tsum, T, ulo, uhi, m, mark,
-        room, st.cls);
+        room, st.plan, own_class);
     DDM_LAUNCHED("match_init_kernel");
   }
   if constexpr (D == 1) {
@@ -1858,18 +1671,16 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
     DDM_LAUNCHED("bits1_kernel");
   } else {
     ProfScope ps("probe", s);
-    CellShape shape;
-    cell_shape(m, D, small ? kSmallCells : kCells, shape.b);
-    const unsigned g = (m + kProbeThreads - 1) / kProbeThreads;
+    const unsigned g = (m + kPlanThreads - 1) / kPlanThreads;
     uint2* pb = reinterpret_cast<uint2*>(st.pb);
     if (small)
-      probe_kernel<D, true><<<g + (full ? 1u : 0u), kProbeThreads, 0, s>>>(
-          T, ulo, uhi, m, shape, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, mark,
-          room, nullptr);
+      probe_kernel<D, true><<<g + (full ? 1u : 0u), kPlanThreads, 0, s>>>(
+          T, ulo, uhi, m, nullptr, st.kstar, st.bucket, st.rank, st.bcnt, st.flag, pb, full, mark,
+          room);
     else
-      probe_kernel<D, false><<<g, kProbeThreads, 0, s>>>(T, ulo, uhi, m, shape, st.kstar,
-                                                         st.bucket, st.rank, st.bcnt, st.flag, pb,
-                                                         nullptr, 0, 0, own_class ? nullptr : st.cls);
+      probe_kernel<D, false><<<g, kPlanThreads, 0, s>>>(T, ulo, uhi, m, st.plan, st.kstar,
+                                                        st.bucket, st.rank, st.bcnt, st.flag, pb,
+                                                        nullptr, 0, 0);
     DDM_LAUNCHED("probe_kernel");
   }
   ProfScope ps("order", s);
@@ -1884,7 +1695,8 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
   cell_scan_kernel<<<nb, 256, 0, s>>>(st.bcnt, st.boff, st.bsum);
   DDM_LAUNCHED("cell_scan_kernel");
   cell_scatter_kernel<<<(m + 255) / 256, 256, 0, s>>>(st.bucket, st.rank, m, st.boff, st.bsum, nb,
-                                                     st.perm, st.gstart, st.gcount);
+                                                     st.perm, st.gstart, st.gcount,
+                                                     D > 1 ? st.plan : nullptr);
   DDM_LAUNCHED("cell_scatter_kernel");
   return DDM_OK;
 }
@@ -2009,7 +1821,7 @@ static void front_reserve(Scratch& sc, uint32_t m, bool learned) {
   sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // gstart
   sc.reserve(sizeof(uint32_t) * DDM_MAX_D);  // gcount
   sc.reserve(sizeof(int32_t));               // flag
-  sc.reserve(sizeof(uint32_t));              // class
+  sc.reserve(sizeof(OrderPlan));             // classes and cells
   sc.reserve(sizeof(uint32_t) * m);          // cnt
   sc.reserve(sizeof(uint64_t) * (m + 1));    // off
   sc.reserve(sizeof(uint64_t) * scan_tmp_words(m));
@@ -2034,7 +1846,7 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
   st.gcount = sc.take<uint32_t>(DDM_MAX_D);
   st.m = m;
   st.flag = sc.take<int32_t>(1);
-  st.cls = sc.take<uint32_t>(1);
+  st.plan = sc.take<OrderPlan>(1);
   st.cnt = sc.take<uint32_t>(m);
   st.off = sc.take<uint64_t>(m + 1);
   fp->stmp = sc.take<uint64_t>(scan_tmp_words(m));

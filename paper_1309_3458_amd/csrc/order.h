@@ -1,0 +1,353 @@
+// The order that updates are matched in (d > 1): what a sample of them decides
+// about the whole set (probe dimensions, cells, whether the set is dense), and the
+// cell of every update.  Shared by the single-instance and the batched matcher.
+#pragma once
+
+#include "traverse.h"
+
+namespace ddm {
+
+// Quantiles held in LDS are padded by one word after every 64: the lanes of
+// a binary search read indices a power of two apart, which without padding
+// fall into one LDS bank at the middle levels of the search.
+constexpr uint32_t kQuantPad = kQuant + kQuant / 64;
+__device__ __forceinline__ uint32_t qslot(uint32_t i) { return i + (i >> 6); }
+
+// number of quantiles <= x (upper) or < x, LDS binary lifting over the
+// padded copy
+__device__ __forceinline__ uint32_t quant_count(const uint32_t* __restrict__ q, uint32_t x,
+                                                bool upper) {
+  uint32_t pos = 0;
+#pragma unroll
+  for (uint32_t step = kQuant; step > 0; step >>= 1) {
+    const uint32_t c = pos + step;
+    if (c <= kQuant) {
+      const uint32_t v = q[qslot(c - 1)];
+      if (upper ? (v <= x) : (v < x)) pos = c;
+    }
+  }
+  return pos;
+}
+
+// the probe estimate of an update: the probe dimension bk, #quantiles <=
+// q.hi and < q.lo - maxlen there (bqa, bqb), #quantiles <= the box centre in
+// every dimension, and whether the extent is invalid
+template <int D>
+struct ProbeEst {
+  uint32_t bk, bqa, bqb;
+  uint32_t mid[D];
+  uint32_t est[D];  // quantiles of the candidate positions in every dimension
+  float hits;  // subscriptions met, were the dimensions independent
+  bool bad;
+};
+
+// the update's extents (ua, ub: dimension k of update j), loaded before the
+// quantiles are (their loads overlap)
+template <int D>
+struct UpdExt {
+  float a[D], b[D];
+};
+template <int D>
+__device__ __forceinline__ UpdExt<D> load_ext(const float* __restrict__ ulo,
+                                              const float* __restrict__ uhi, uint32_t m,
+                                              uint32_t j) {
+  UpdExt<D> e;
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    e.a[k] = ulo[(size_t)k * m + j];
+    e.b[k] = uhi[(size_t)k * m + j];
+  }
+  return e;
+}
+
+// the kQuant quantiles of every dimension into LDS (sq[k][qslot(i)]), by
+// THREADS threads: every load is issued before the first LDS store, so that
+// they are in flight together
+template <int D, uint32_t THREADS>
+__device__ __forceinline__ void load_quant_lds(const TreeDev& T, uint32_t (*sq)[kQuantPad]) {
+  static_assert(kQuant % THREADS == 0, "whole rounds");
+  constexpr uint32_t Q = kQuant / THREADS;
+  uint32_t v[D][Q];
+#pragma unroll
+  for (int k = 0; k < D; ++k)
+#pragma unroll
+    for (uint32_t r = 0; r < Q; ++r) v[k][r] = T.quant[k][r * THREADS + threadIdx.x];
+#pragma unroll
+  for (int k = 0; k < D; ++k)
+#pragma unroll
+    for (uint32_t r = 0; r < Q; ++r) sq[k][qslot(r * THREADS + threadIdx.x)] = v[k][r];
+}
+
+// The class of an update is its probe dimension: one for the whole set (the
+// dimension whose ranges are the shortest on average), or every update's own
+// (kOwnClass), for small sets, the lane form, and where a second dimension holds a
+// real share.  With own classes the few updates of a set that leave the common
+// one make up tiles that span the space: the 16-hotspot workload, ten seeds, 6.5 ..
+// 9.4 ms, mean 7.5, against 6.5 .. 7.3, mean 6.8; d = 4, 62,266 updates, a count of
+// 284 us against 84.  With one class where half of the updates are long in the one
+// dimension and half in the other, every tile is long in both (100,000 updates, 0.2
+// of the space by 20 units, against 250,000 squares: match 694 us, own classes 126).
+// So the set has one class unless that makes its ranges kClassCost times as long as
+// the updates' own would be (hotspots: up to 1.15, equal boxes 1, that set 2 to 400).
+constexpr uint32_t kOwnClass = ~0u;
+constexpr float kClassCost = 1.5f;
+
+template <int D>
+__device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
+                                                      const uint32_t (*sq)[kQuantPad],
+                                                      const UpdExt<D>& e, uint32_t cls) {
+  ProbeEst<D> P;
+  P.bad = false;
+  uint32_t xh[D], xl[D], xm[D], qa[D], qb[D], qm[D];
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    const float a = e.a[k], b = e.b[k];
+    P.bad = P.bad || !valid_extent(a, b);
+    xh[k] = f2key(b);
+    xl[k] = f2key(nextafterf(a - T.maxlen[k], -INFINITY));
+    xm[k] = f2key(0.5f * a + 0.5f * b);
+    qa[k] = qb[k] = qm[k] = 0;
+  }
+  // the 3D quantile searches (#quantiles <= xh, < xl, <= xm per dimension)
+  // advance in lockstep, so their LDS reads overlap
+#pragma unroll
+  for (uint32_t step = kQuant; step > 0; step >>= 1) {
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const uint32_t ca = qa[k] + step, cb = qb[k] + step, cm = qm[k] + step;
+      const uint32_t va = ca <= kQuant ? sq[k][qslot(ca - 1)] : 0xffffffffu;
+      const uint32_t vb = cb <= kQuant ? sq[k][qslot(cb - 1)] : 0xffffffffu;
+      const uint32_t vm = cm <= kQuant ? sq[k][qslot(cm - 1)] : 0xffffffffu;
+      if (ca <= kQuant && va <= xh[k]) qa[k] = ca;
+      if (cb <= kQuant && vb < xl[k]) qb[k] = cb;
+      if (cm <= kQuant && vm <= xm[k]) qm[k] = cm;
+    }
+  }
+  // an update's own class: dimension 0, unless another one's range is less than
+  // a third as long (at the edge of the space a range is half as long)
+  uint32_t best = 0;
+  P.hits = (float)T.n;
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    const uint32_t est = qa[k] - min(qa[k], qb[k]);
+    P.hits *= fmaxf((float)est, 0.5f) * (1.f / (float)kQuant);
+    P.mid[k] = qm[k];
+    P.est[k] = est;
+    if (cls == kOwnClass ? k == 0 || 3u * est + 16u < best : (uint32_t)k == cls) {
+      best = est;
+      P.bk = (uint32_t)k;
+      P.bqa = qa[k];
+      P.bqb = qb[k];
+    }
+  }
+  return P;
+}
+
+// What the sample decides.  The rows of b are the classes; one class for the set
+// has the cells of all.
+struct OrderPlan {
+  uint32_t cls;                     // the set's class, or kOwnClass
+  uint32_t b[DDM_MAX_D][DDM_MAX_D]; // cells along the class's own dimension, then the others
+};
+
+constexpr uint32_t kPlanThreads = 1024, kPlanSamples = 256;
+
+// Cells of a class of m updates whose ranges are r quantile steps long on average:
+// along each dimension, the class's own first and the others ascending.  A tile of
+// width w reads what meets w + r, and its widths multiply to the same volume
+// whatever the shape, so that the sum is least where widths go with ranges: all
+// dimensions but the last are cut into as many ranges as there are tiles of 64
+// along one, more where ranges are shorter than their mean, the last into as many
+// as the rest of the `cells` allow, so that a tile takes a few cells of one line.
+// (250,000 + 250,000 boxes, half 60,000 long in the one and half in the other of
+// two dimensions, 3000 in the third: match 383 us with the same cut in all, 315 now.)
+template <int D>
+__device__ __forceinline__ void cell_shape(float m, uint32_t cls, uint32_t cells,
+                                           const float (&r)[D], uint32_t (&b)[DDM_MAX_D]) {
+  float lg[D], mean = 0.f;
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    lg[k] = log2f(fmaxf(r[k], 1.f));
+    mean += lg[k] / (float)D;
+  }
+  const float along = log2f(m / 64.f) / (float)D;
+  uint32_t rest = cells;
+#pragma unroll
+  for (int s = 0; s < DDM_MAX_D; ++s) {
+    if (s >= D) {
+      b[s] = 1;
+      continue;
+    }
+    const uint32_t kk = s == 0 ? cls : (uint32_t)(s - 1) + (((uint32_t)(s - 1) >= cls) ? 1u : 0u);
+    float l = 0.f;
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+      if ((uint32_t)k == kk) l = lg[k];
+    const float want = fminf(exp2f(along + mean - l) + 0.5f, (float)kQuant);
+    b[s] = max(1u, s + 1 < D ? min((uint32_t)want, rest / 2u) : rest);
+    rest /= b[s];
+  }
+}
+
+// the cell of an update of class c on the grid b (its row), from the quantiles
+// below its centre; the numbering is a serpentine (each line runs back where the
+// last one ended)
+template <int D>
+__device__ __forceinline__ uint32_t grid_cell(const uint32_t* __restrict__ b, uint32_t c,
+                                              const uint32_t (&mid)[D]) {
+  uint32_t sub = 0;
+#pragma unroll
+  for (int s = 0; s < D; ++s) {
+    const uint32_t kk = s == 0 ? c : (uint32_t)(s - 1) + (((uint32_t)(s - 1) >= c) ? 1u : 0u);
+    uint32_t qp = 0;
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+      if ((uint32_t)k == kk) qp = mid[k];
+    const uint32_t n = b[s];
+    uint32_t i = min(qp * n / (kQuant + 1u), n - 1u);
+    if (sub & 1u) i = n - 1u - i;  // the serpentine's way back
+    sub = sub * n + i;
+  }
+  return sub;
+}
+
+// Up to kPlanSamples updates spread evenly over the set decide whether the
+// count traversal keeps its hits: the stash is marked full before it is used,
+// and the set matched as a dense one, when the estimated hits (the candidate
+// fractions of the dimensions multiplied, as if they were independent) exceed
+// four fifths of the stash's counted chunks (tiles leave some of theirs), or per
+// update the larger of kDenseHits and
+// kDenseScale * d / sqrt(m).  The dense form takes two more synchronizations and
+// nine more launches, a fixed 70 us, and saves on every pair, the more the more
+// updates lie near each other.  Match of m updates against m subscriptions, us,
+// keeping hits / dense form (10, 20, 40, 80 hits each):
+//   d = 2  m =  20,000   86/157   91/158  138/157  232/152
+//          m =  80,000  128/164  164/159  306/164  345/173
+//          m = 250,000  240/229  388/236  530/245  603/273
+//   d = 3  m =  20,000   92/160  101/169  146/170  184/178
+//          m =  80,000  145/189  181/199  370/211  492/251
+//   d = 4  m =  80,000  208/283  211/305  505/369  731/424
+// A set whose dimensions are correlated may still overflow the stash.
+constexpr float kDenseHits = 10.f, kDenseScale = 3000.f;
+
+// LDS of the sample, beside the quantiles
+template <int D>
+struct SampleLds {
+  static constexpr int kWaves = kPlanSamples / kWave;
+  uint32_t part[D * (D + 1)][kWaves];  // sums of the wavefronts
+  float hits[kWaves];
+  uint32_t sum[D * (D + 1)];
+  float total;
+};
+
+// adds up `count` values of part and the hits
+template <int D>
+__device__ __forceinline__ void sample_sums(SampleLds<D>& L, uint32_t count) {
+  constexpr uint32_t W = SampleLds<D>::kWaves;
+  __syncthreads();
+  if (threadIdx.x < count) {
+    uint32_t s = 0;
+    for (uint32_t w = 0; w < W; ++w) s += L.part[threadIdx.x][w];
+    L.sum[threadIdx.x] = s;
+  }
+  if (threadIdx.x == kWave) {
+    float t = 0.f;
+    for (uint32_t w = 0; w < W; ++w) t += L.hits[w];
+    L.total = t;
+  }
+  __syncthreads();
+}
+
+// Run by one workgroup of kPlanThreads; the first kPlanSamples of them take a
+// sample each (1024 samples took 5 us longer at d = 2, 10 at d = 4: one compute
+// unit does the searches).  full (may be null):
+// where the stash is marked, with mark (kStashDense where the dense form may
+// follow, else 1, a stash that is full, so that the count traversal counts at
+// once).  plan (may be null): cells to a class; own: classes of their own
+// whatever the ranges.
+template <int D>
+__device__ __forceinline__ void sample_set(const TreeDev& T, const float* __restrict__ ulo,
+                                           const float* __restrict__ uhi, uint32_t m,
+                                           uint32_t (*sq)[kQuantPad], SampleLds<D>& L,
+                                           uint32_t* __restrict__ full, uint32_t mark,
+                                           uint32_t room, OrderPlan* __restrict__ plan,
+                                           uint32_t cells, bool own) {
+  const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const uint32_t S = min(m, kPlanSamples);
+  UpdExt<D> e{};
+  if (tid < S) e = load_ext<D>(ulo, uhi, m, (uint32_t)(((uint64_t)tid * m) / S));
+  load_quant_lds<D, kPlanThreads>(T, sq);
+  __syncthreads();
+  ProbeEst<D> P{};
+  bool in = tid < S;
+  if (tid < kPlanSamples) {
+    if (in) {
+      P = probe_estimate<D>(T, sq, e, kOwnClass);
+      in = !P.bad;
+    }
+    float hits = in ? P.hits : 0.f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, kWave);
+    uint32_t mine = 0;  // the range in the sample's own class
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const uint32_t v = wave_scan_dpp(in ? P.est[k] : 0u);
+      if (lane == kWave - 1) L.part[k][wave] = v;
+      if ((uint32_t)k == P.bk) mine = P.est[k];
+    }
+    const uint32_t v = wave_scan_dpp(in ? mine : 0u);
+    if (lane == kWave - 1) L.part[D][wave] = v;
+    if (lane == 0) L.hits[wave] = hits;
+  }
+  sample_sums(L, D + 1);
+  if (tid == 0 && full) {
+    const float t = L.total / (float)S;
+    const float dense = fmaxf(kDenseHits, kDenseScale * (float)D * rsqrtf((float)m));
+    *full = t > dense || t * (float)m > 0.8f * (float)room ? mark : 0u;
+  }
+  if (!plan) return;
+  uint32_t c = 0, best = L.sum[0];
+#pragma unroll
+  for (int k = 1; k < D; ++k)
+    if (2u * L.sum[k] + 16u * S < best) {
+      best = L.sum[k];
+      c = (uint32_t)k;
+    }
+  if ((float)best > kClassCost * (float)L.sum[D] + 16.f * (float)S) own = true;
+  float r[D], mc = (float)m;  // of class tid
+  uint32_t cc = c;
+#pragma unroll
+  for (int k = 0; k < D; ++k) r[k] = (float)L.sum[k] / (float)S;
+  if (own) {  // every class by its own samples
+    if (tid < kPlanSamples) {
+#pragma unroll
+      for (int g = 0; g < D; ++g)
+#pragma unroll
+        for (int k = 0; k <= D; ++k) {
+          const bool here = in && P.bk == (uint32_t)g;
+          const uint32_t w = wave_scan_dpp(!here ? 0u : k < D ? P.est[k < D ? k : 0] : 1u);
+          if (lane == kWave - 1) L.part[g * (D + 1) + k][wave] = w;
+        }
+    }
+    sample_sums(L, D * (D + 1));
+    if (tid < D) {
+      const uint32_t* __restrict__ s = L.sum + tid * (D + 1);
+      const float n = (float)max(s[D], 1u);
+#pragma unroll
+      for (int k = 0; k < D; ++k) r[k] = (float)s[k] / n;
+      mc *= n / (float)S;
+      cc = tid;
+    }
+  }
+  // (a class of its own for the whole set has the others' cells too)
+  const uint32_t all = own ? cells : D * cells;
+  if (tid < (own ? (uint32_t)D : 1u)) {
+    uint32_t b[DDM_MAX_D];
+    cell_shape<D>(mc, cc, all, r, b);
+#pragma unroll
+    for (int s = 0; s < DDM_MAX_D; ++s) plan->b[cc][s] = b[s];
+    if (tid == 0) plan->cls = own ? kOwnClass : c;
+  }
+}
+
+}  // namespace ddm

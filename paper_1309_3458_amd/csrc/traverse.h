@@ -657,41 +657,4 @@ __device__ __forceinline__ void tile_body(const TreeDev& T, const float* __restr
   }
 }
 
-// Cells of m updates in d dimensions (d > 1): along each dimension, the class's
-// own first and the others ascending.  All but the last are cut into as many
-// ranges as there are tiles of 64 along a dimension, the last into as many as
-// the rest of the `cells` allow, so that a tile takes a few cells of one line.
-inline void cell_shape(uint32_t m, uint32_t d, uint32_t cells, uint32_t (&b)[DDM_MAX_D]) {
-  uint32_t rest = cells;
-  for (uint32_t s = 0; s < DDM_MAX_D; ++s) b[s] = 1;
-  const double g = std::pow((double)m / 64.0, 1.0 / (double)d);
-  for (uint32_t s = 0; s + 1 < d; ++s) {
-    b[s] = std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(g + 0.5), rest / 2));
-    rest /= b[s];
-  }
-  b[d - 1] = std::max<uint32_t>(1u, rest);
-}
-
-// Quantiles held in LDS are padded by one word after every 64: the lanes of
-// a binary search read indices a power of two apart, which without padding
-// fall into one LDS bank at the middle levels of the search.
-constexpr uint32_t kQuantPad = kQuant + kQuant / 64;
-__device__ __forceinline__ uint32_t qslot(uint32_t i) { return i + (i >> 6); }
-
-// number of quantiles <= x (upper) or < x, LDS binary lifting over the
-// padded copy
-__device__ __forceinline__ uint32_t quant_count(const uint32_t* __restrict__ q, uint32_t x,
-                                                bool upper) {
-  uint32_t pos = 0;
-#pragma unroll
-  for (uint32_t step = kQuant; step > 0; step >>= 1) {
-    const uint32_t c = pos + step;
-    if (c <= kQuant) {
-      const uint32_t v = q[qslot(c - 1)];
-      if (upper ? (v <= x) : (v < x)) pos = c;
-    }
-  }
-  return pos;
-}
-
 }  // namespace ddm
