@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kPlanThreads) void probe_kernel(
   if constexpr (SMALL) {
     if (full && blockIdx.x == gridDim.x - 1) {
       __shared__ SampleLds<D> L;
-      sample_set<D>(T, ulo, uhi, m, sq, L, full, mark, room, nullptr, 0, true);
+      sample_set<D>(T, ulo, uhi, m, sq, L, full, mark, room, nullptr, 0, 0, true);
       return;
     }
   }
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kPlanThreads) void probe_kernel(
     const uint32_t c = threadIdx.x / DDM_MAX_D, i = threadIdx.x % DDM_MAX_D;
     if (SMALL) {
       const float r[D] = {};
-      if (i == 0) cell_shape<D>((float)m, c, kSmallCells, r, shape[c]);
+      if (i == 0) cell_shape<D>((float)m, c, kSmallCells, r, 0, shape[c]);
     } else {
       shape[c][i] = plan->b[c][i];
     }
@@ -1620,14 +1620,14 @@ __global__ __launch_bounds__(kPlanThreads) void match_init_kernel(
     int32_t* __restrict__ flag, uint32_t* __restrict__ lists_count, uint32_t* __restrict__ bcnt,
     uint32_t* __restrict__ snext, uint32_t sfirst, uint32_t sslice, uint64_t* __restrict__ tsum,
     TreeDev T, const float* __restrict__ ulo, const float* __restrict__ uhi, uint32_t m,
-    uint32_t mark, uint32_t room, OrderPlan* __restrict__ plan, bool own_class) {
+    uint32_t mark, uint32_t room, OrderPlan* __restrict__ plan, uint32_t q, bool own_class) {
   static_assert(kCells % kPlanThreads == 0, "whole workgroups");
   if constexpr (D > 1) {
     if (blockIdx.x == D * kCells / kPlanThreads) {
       __shared__ uint32_t sq[D][kQuantPad];
       __shared__ SampleLds<D> L;
       sample_set<D>(T, ulo, uhi, m, sq, L, snext ? snext + kStashSlices : nullptr, mark, room,
-                    plan, kCells, own_class);
+                    plan, kCells, q, own_class);
       return;
     }
   }
@@ -1656,7 +1656,7 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
   if (!small) {
     match_init_kernel<D><<<D * kCells / kPlanThreads + (D > 1 ? 1 : 0), kPlanThreads, 0, s>>>(
         st.flag, lists_count, st.bcnt, sn, st.sfirst, st.sslice, st.tsum, T, ulo, uhi, m, mark,
-        room, st.plan, own_class);
+        room, st.plan, tile_updates(m), own_class);
     DDM_LAUNCHED("match_init_kernel");
   }
   if constexpr (D == 1) {

@@ -151,6 +151,30 @@ struct OrderPlan {
 };
 
 constexpr uint32_t kPlanThreads = 1024, kPlanSamples = 256;
+constexpr uint32_t kQuantLog = 12;
+static_assert(1u << kQuantLog == kQuant, "quantiles are counted in so many bits");
+
+// Sets whose dimensions depend on each other (extents along a line or a plane, or in
+// clusters) fill few cells of a grid, and the updates of a cell come in no order, so
+// that every tile is as wide as its cell.  How crowded the cells are shows in the
+// pairs of samples that share one: their share of all pairs is that of a cell's
+// candidates among the subscriptions.  Where it is more than twice a tile's and
+// not by chance (kCrowdedPairs), grids that are finer in the class's own dimension
+// are tried, and the finest taken that reads as little as any (within kFinerSlack:
+// the largest tile is the smaller, the finer it is).  Candidates of a tile on
+// average, 500,000 + 500,000 boxes, first grid / own dimension 4, 16 and 64 times
+// finer / every quantile:
+//   along a line, d = 3         12,234 / 5749 / 1562 / 443 / 189
+//   16 clusters,  d = 2            199 /  217 /  291 /   - / 511
+//                 d = 3           1310 / 1176 /  767 / 760 / 1043
+//                 d = 4           2995 / 2772 / 1355 / 675 / 1130
+//   uniform,      d = 4 (200,000)   71 /   92 /  194 / 554 / 4496
+// Match, us, before there were such grids / first grid / now: a line of 500,000,
+// d = 2 303/886/298, d = 3 236/4507/226, d = 4 260/8845/245; a plane, d = 4, 200,000
+// 205/3120/210; 100 clusters, d = 3 269/530/228.
+constexpr uint32_t kCrowdedPairs = 20, kFinest = 4;
+constexpr float kFinerSlack = 1.3f;
+constexpr uint32_t kSeen = 16384;  // counters of samples in a cell (16 bits each)
 
 // Cells of a class of m updates whose ranges are r quantile steps long on average:
 // along each dimension, the class's own first and the others ascending.  A tile of
@@ -161,17 +185,24 @@ constexpr uint32_t kPlanThreads = 1024, kPlanSamples = 256;
 // as the rest of the `cells` allow, so that a tile takes a few cells of one line.
 // (250,000 + 250,000 boxes, half 60,000 long in the one and half in the other of
 // two dimensions, 3000 in the third: match 383 us with the same cut in all, 315 now.)
+// finer > 0: 4^finer as many ranges along the class's own dimension (the last
+// step: every quantile), and what is left over the others.
+// Returns the share of the space that a tile reads, in volumes of a cell.
 template <int D>
-__device__ __forceinline__ void cell_shape(float m, uint32_t cls, uint32_t cells,
-                                           const float (&r)[D], uint32_t (&b)[DDM_MAX_D]) {
-  float lg[D], mean = 0.f;
+__device__ __forceinline__ float cell_shape(float m, uint32_t cls, uint32_t cells,
+                                            const float (&r)[D], uint32_t finer,
+                                            uint32_t (&b)[DDM_MAX_D]) {
+  float lg[D], mean = 0.f, own = 0.f;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     lg[k] = log2f(fmaxf(r[k], 1.f));
     mean += lg[k] / (float)D;
+    if ((uint32_t)k == cls) own = lg[k];
   }
   const float along = log2f(m / 64.f) / (float)D;
+  const float others = (mean * (float)D - own) / (float)(D - 1);  // their mean
   uint32_t rest = cells;
+  float reads = 1.f, left = 0.f;
 #pragma unroll
   for (int s = 0; s < DDM_MAX_D; ++s) {
     if (s >= D) {
@@ -183,10 +214,19 @@ __device__ __forceinline__ void cell_shape(float m, uint32_t cls, uint32_t cells
 #pragma unroll
     for (int k = 0; k < D; ++k)
       if ((uint32_t)k == kk) l = lg[k];
-    const float want = fminf(exp2f(along + mean - l) + 0.5f, (float)kQuant);
-    b[s] = max(1u, s + 1 < D ? min((uint32_t)want, rest / 2u) : rest);
+    float want = along + mean - l;
+    if (finer) {
+      if (s == 0) want = finer < kFinest ? want + 2.f * (float)finer : (float)kQuantLog;
+      else want = left + others - l;
+    }
+    const uint32_t most = s == 0 ? min(rest, kQuant) : max(rest / 2u, 1u);
+    b[s] = max(1u, s + 1 < D ? min((uint32_t)(exp2f(want) + 0.5f), finer ? most : rest / 2u)
+                             : rest);
     rest /= b[s];
+    if (s == 0) left = log2f((float)rest) / (float)(D - 1);
+    reads *= 1.f + exp2f(l - (float)kQuantLog) * (float)min(b[s], kQuant);
   }
+  return reads;
 }
 
 // the cell of an update of class c on the grid b (its row), from the quantiles
@@ -238,6 +278,9 @@ struct SampleLds {
   float hits[kWaves];
   uint32_t sum[D * (D + 1)];
   float total;
+  uint32_t b[D][DDM_MAX_D];
+  float reads[D];
+  uint32_t pairs;
 };
 
 // adds up `count` values of part and the hits
@@ -263,15 +306,15 @@ __device__ __forceinline__ void sample_sums(SampleLds<D>& L, uint32_t count) {
 // unit does the searches).  full (may be null):
 // where the stash is marked, with mark (kStashDense where the dense form may
 // follow, else 1, a stash that is full, so that the count traversal counts at
-// once).  plan (may be null): cells to a class; own: classes of their own
-// whatever the ranges.
+// once).  plan (may be null): cells to a class, q updates to a tile; own: classes
+// of their own whatever the ranges.  (sq is overwritten.)
 template <int D>
 __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __restrict__ ulo,
                                            const float* __restrict__ uhi, uint32_t m,
                                            uint32_t (*sq)[kQuantPad], SampleLds<D>& L,
                                            uint32_t* __restrict__ full, uint32_t mark,
                                            uint32_t room, OrderPlan* __restrict__ plan,
-                                           uint32_t cells, bool own) {
+                                           uint32_t cells, uint32_t q, bool own) {
   const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const uint32_t S = min(m, kPlanSamples);
   UpdExt<D> e{};
@@ -341,12 +384,43 @@ __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __rest
   }
   // (a class of its own for the whole set has the others' cells too)
   const uint32_t all = own ? cells : D * cells;
-  if (tid < (own ? (uint32_t)D : 1u)) {
-    uint32_t b[DDM_MAX_D];
-    cell_shape<D>(mc, cc, all, r, b);
+  const uint32_t rows = own ? (uint32_t)D : 1u;  // rows of L.b: the classes, or the set's
+  uint32_t* __restrict__ seen = sq[0];           // (the quantiles are read)
+  static_assert(kSeen / 2 <= D * kQuantPad, "the counters take the quantiles' place");
+  float least = 0.f;
+  for (uint32_t finer = 0; finer <= kFinest; ++finer) {
+    if (tid < rows) L.reads[tid] = cell_shape<D>(mc, cc, all, r, finer, L.b[tid]);
+    if (tid == 0) L.pairs = 0;
+    for (uint32_t i = tid; i < kSeen / 2; i += kPlanThreads) seen[i] = 0;
+    __syncthreads();
+    if (tid < kPlanSamples) {
+      uint32_t met = 0;  // samples in the cell already
+      if (in) {
+        const uint32_t g = own ? P.bk : c;
+        const uint32_t i =
+            (grid_cell<D>(L.b[own ? g : 0u], g, P.mid) + g * (kSeen / DDM_MAX_D + 1u)) & (kSeen - 1u);
+        met = atomicAdd(&seen[i >> 1], i & 1u ? 0x10000u : 1u);
+        met = i & 1u ? met >> 16 : met & 0xffffu;
+      }
+      const uint32_t sum = wave_scan_dpp(met);
+      if (lane == kWave - 1) atomicAdd(&L.pairs, sum);
+    }
+    __syncthreads();
+    const uint32_t pairs = L.pairs;
+    float reads = 0.f;
+    for (uint32_t g = 0; g < rows; ++g) reads += L.reads[g] / (float)rows;
+    // a tile's share of the updates, or its cell's
+    const float tile = (float)q / (float)m;
+    const float cell = 2.f * (float)pairs / ((float)S * (float)S);
+    const float cost = fmaxf(tile, cell) * reads;
+    if ((finer == 0 || cost <= (finer < kFinest ? kFinerSlack : 1.f) * least) && tid < rows) {
+      plan->cls = own ? kOwnClass : c;
 #pragma unroll
-    for (int s = 0; s < DDM_MAX_D; ++s) plan->b[cc][s] = b[s];
-    if (tid == 0) plan->cls = own ? kOwnClass : c;
+      for (int s = 0; s < DDM_MAX_D; ++s) plan->b[cc][s] = L.b[tid][s];
+    }
+    least = finer == 0 ? cost : fminf(least, cost);
+    if (finer == 0 && (pairs <= kCrowdedPairs || cell <= 2.f * tile)) return;
+    __syncthreads();
   }
 }
 

@@ -113,6 +113,10 @@ def count_us(inst):
 @pytest.mark.parametrize("kind, d, like, factor", [
     ("long either way", 2, "long updates", 3.0),
     ("all long either way", 3, "uniform", 3.0),
+    ("line", 3, "uniform", 3.0),
+    ("line", 4, "uniform", 3.0),
+    ("plane", 4, "uniform", 3.0),
+    ("100 clusters", 3, "uniform", 5.0),
 ])
 def test_order_fits(kind, d, like, factor):
     n, m = 250000, 200000
