@@ -269,6 +269,11 @@ __device__ __forceinline__ void tree_low_chunk(const TreeJob& J, uint32_t c) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) lenb = max(lenb, (uint32_t)__shfl_xor((int)lenb, o, kWave));
   if (lane_id() == 0) wlen[threadIdx.x / kWave] = lenb;
+  // Unrolled: as a loop, the compiler placed the wait for the LDS writes of one
+  // height before the loop and not on its back edge, so a wavefront could pass the
+  // barrier with its write still under way, and a block's maximum was now and then
+  // that of a subtree not yet folded (one in some 700 replays of 256 instances).
+#pragma unroll
   for (int h = 1; h < kChunkLog; ++h) {
     __syncthreads();
     if (h == 1 && threadIdx.x == 0) {
@@ -327,6 +332,7 @@ __device__ __forceinline__ void tree_high_chunk(const TreeJob& J, uint32_t c, ui
     }
     mx[r] = h;
   }
+#pragma unroll
   for (int h = 1; h < kChunkLog; ++h) {
     __syncthreads();
     for (uint32_t r = threadIdx.x; r < kChunk; r += kTreeThreads) {
