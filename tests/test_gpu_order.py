@@ -116,6 +116,8 @@ def count_us(inst):
     ("line", 3, "uniform", 3.0),
     ("line", 4, "uniform", 3.0),
     ("plane", 4, "uniform", 3.0),
+    ("16 clusters", 2, "uniform", 3.0),
+    ("16 clusters", 3, "uniform", 5.0),
     ("100 clusters", 3, "uniform", 5.0),
 ])
 def test_order_fits(kind, d, like, factor):
