@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "ddm_internal.h"
@@ -37,7 +38,7 @@ struct BInst {
   uint32_t qbase;  // first global update index
   uint32_t bbase;  // first bucket
   uint32_t nb;     // cells per class (probe dimension)
-  uint32_t cb[DDM_MAX_D];  // d > 1: cells along each dimension, the class's own first
+  OrderPlan* plan; // d > 1: classes and cells, by the sample
   uint32_t qpt;    // updates per traversal work item
   uint64_t ebase;  // first element of the key kernel (d * n elements)
   int32_t* flag;   // nonzero: invalid coordinates
@@ -46,22 +47,7 @@ struct BInst {
   uint32_t* idb;   // d * (n + 1) payload / ids
 };
 
-// Cells of m updates in d dimensions (d > 1): along each dimension, the class's
-// own first and the others ascending.  All but the last are cut into as many
-// ranges as there are tiles of 64 along a dimension, the last into as many as
-// the rest of the `cells` allow, so that a tile takes a few cells of one line.
-static void batch_cell_shape(uint32_t m, uint32_t d, uint32_t cells, uint32_t (&b)[DDM_MAX_D]) {
-  uint32_t rest = cells;
-  for (uint32_t s = 0; s < DDM_MAX_D; ++s) b[s] = 1;
-  const double g = std::pow((double)m / 64.0, 1.0 / (double)d);
-  for (uint32_t s = 0; s + 1 < d; ++s) {
-    b[s] = std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(g + 0.5), rest / 2));
-    rest /= b[s];
-  }
-  b[d - 1] = std::max<uint32_t>(1u, rest);
-}
-
-constexpr uint32_t kProbeThreads = 1024;
+constexpr uint32_t kProbeThreads = kPlanThreads;
 // trees are a grid dimension of the index kernel (at most 65535)
 constexpr uint32_t kBatchMaxInstances = DDM_BATCH_MAX_INSTANCES;
 static_assert(kBatchMaxInstances * DDM_MAX_D <= 65535, "index grid");
@@ -115,10 +101,46 @@ __global__ __launch_bounds__(kTreeThreads) void b_tree_high_kernel(const TreeJob
   tree_high_chunk(jobs[w.x], w.y, S);
 }
 
+// Classes and cells of every instance (d > 1), by its sample as in the
+// single-instance matcher; one workgroup to an instance.  The cells are those for
+// its tiles: with the batch's own, of 64, a cell of 50 updates on a plane counted as
+// fine enough (d = 4, count of four sets of 40,000, 345 us).
+__global__ __launch_bounds__(kPlanThreads) void b_plan_kernel(const BInst* __restrict__ I) {
+  __shared__ uint32_t sq[DDM_MAX_D][kQuantPad];
+  __shared__ SampleLds<DDM_MAX_D> lds;
+  const BInst& b = I[blockIdx.x];
+  auto sample = [&](auto dim) {
+    constexpr int D = decltype(dim)::value;
+    static_assert(sizeof(SampleLds<D>) <= sizeof(lds), "one block for every dimension");
+    sample_set<D>(b.T, b.u_lo, b.u_hi, b.m, sq, reinterpret_cast<SampleLds<D>&>(lds), nullptr, 0,
+                  0, b.plan, b.nb, min(b.qpt, tile_updates(b.m)), false);
+  };
+  switch (uniform_u32(b.d)) {
+    case 1: break;
+    case 2: sample(std::integral_constant<int, 2>{}); break;
+    case 3: sample(std::integral_constant<int, 3>{}); break;
+    default: sample(std::integral_constant<int, 4>{}); break;
+  }
+}
+
+// class and cell of update j (d > 1); whether its extents are invalid
+template <int D>
+__device__ __forceinline__ bool probe_update(const BInst& b, uint32_t (*sq)[kQuantPad], uint32_t j,
+                                             uint32_t* bk, uint32_t* sub) {
+  const UpdExt<D> e = load_ext<D>(b.u_lo, b.u_hi, b.m, min(j, b.m - 1u));
+  load_quant_lds<D, kProbeThreads>(b.T, sq);
+  __syncthreads();
+  const uint32_t cls = uniform_u32(b.plan->cls);
+  const ProbeEst<D> P = probe_estimate<D>(b.T, sq, e, cls);
+  *bk = P.bad ? 0u : P.bk;
+  const uint32_t c = P.bad ? 0u : grid_cell<D>(b.plan->b[*bk], *bk, P.mid);
+  *sub = cls == kOwnClass ? *bk * b.nb + min(c, b.nb - 1u) : min(c, D * b.nb - 1u);
+  return P.bad;
+}
+
 // Probe dimension, bucket and rank of every update; one workgroup belongs to
 // one instance (map entry: instance, block within it).  d = 1: exact BITS
-// count (also the final count); d > 1: quantile estimate of the candidate
-// range as in the single-instance matcher.
+// count (also the final count).
 __global__ __launch_bounds__(kProbeThreads) void b_probe_kernel(const BInst* __restrict__ I,
                                                                 const uint2* __restrict__ map,
                                                                 uint8_t* __restrict__ kstar,
@@ -129,75 +151,35 @@ __global__ __launch_bounds__(kProbeThreads) void b_probe_kernel(const BInst* __r
   __shared__ uint32_t sq[DDM_MAX_D][kQuantPad];
   const uint2 w = map[blockIdx.x];
   const BInst& b = I[w.x];
-  const uint32_t d = b.d;
-  if (d > 1)
-    for (uint32_t k = 0; k < d; ++k) {
-      // a dimension's loads are issued before its LDS stores (in flight together)
-      constexpr uint32_t Q = kQuant / kProbeThreads;
-      uint32_t v[Q];
-#pragma unroll
-      for (uint32_t r = 0; r < Q; ++r) v[r] = b.T.quant[k][r * kProbeThreads + threadIdx.x];
-#pragma unroll
-      for (uint32_t r = 0; r < Q; ++r) sq[k][qslot(r * kProbeThreads + threadIdx.x)] = v[r];
-    }
-  __syncthreads();
   const uint32_t j = w.y * kProbeThreads + threadIdx.x;
   const bool act = j < b.m;
+  const uint32_t gj = b.qbase + j;
+  uint32_t bk = 0, sub = 0;
   bool bad = false;
+  switch (uniform_u32(b.d)) {
+    case 1:
+      if (act) {
+        const float a = b.u_lo[j], c = b.u_hi[j];
+        bad = !valid_extent(a, c);
+        const uint32_t* keys[2] = {b.T.skey_lo[0], b.T.skey_hi[0]};
+        const uint32_t* idx[2] = {b.T.sidx_lo[0], b.T.sidx_hi[0]};
+        const uint32_t x[2] = {f2key(c), f2key(a)};
+        const bool up[2] = {true, false};
+        uint32_t res[2];
+        count_2l<2>(keys, idx, x, up, b.n, b.T.ns, res);
+        cnt[gj] = bad ? 0u : res[0] - res[1];
+        sub = (uint32_t)(((uint64_t)(bad ? 0u : res[0]) * b.nb) / ((uint64_t)b.n + 1));
+        sub = min(sub, b.nb - 1u);
+      }
+      break;
+    case 2: bad = probe_update<2>(b, sq, j, &bk, &sub); break;
+    case 3: bad = probe_update<3>(b, sq, j, &bk, &sub); break;
+    default: bad = probe_update<4>(b, sq, j, &bk, &sub); break;
+  }
+  bad = bad && act;
   if (act) {
-    const uint32_t gj = b.qbase + j;
-    uint32_t bk = 0, sub = 0;
-    if (d == 1) {
-      const float a = b.u_lo[j], c = b.u_hi[j];
-      bad = !valid_extent(a, c);
-      const uint32_t* keys[2] = {b.T.skey_lo[0], b.T.skey_hi[0]};
-      const uint32_t* idx[2] = {b.T.sidx_lo[0], b.T.sidx_hi[0]};
-      const uint32_t x[2] = {f2key(c), f2key(a)};
-      const bool up[2] = {true, false};
-      uint32_t res[2];
-      count_2l<2>(keys, idx, x, up, b.n, b.T.ns, res);
-      cnt[gj] = bad ? 0u : res[0] - res[1];
-      sub = (uint32_t)(((uint64_t)(bad ? 0u : res[0]) * b.nb) / ((uint64_t)b.n + 1));
-    } else {
-      // class and cell as in the single-instance matcher: dimension 0 unless
-      // another one's range is less than a third as long, cells of quantile
-      // ranges along a serpentine
-      uint32_t best = 0, mid[DDM_MAX_D];
-#pragma unroll
-      for (uint32_t k = 0; k < DDM_MAX_D; ++k) {
-        mid[k] = 0;
-        if (k >= d) continue;
-        const float a = b.u_lo[(size_t)k * b.m + j], c = b.u_hi[(size_t)k * b.m + j];
-        bad = bad || !valid_extent(a, c);
-        const uint32_t qa = quant_count(sq[k], f2key(c), true);
-        const uint32_t qb =
-            quant_count(sq[k], f2key(nextafterf(a - b.T.maxlen[k], -INFINITY)), false);
-        mid[k] = quant_count(sq[k], f2key(0.5f * a + 0.5f * c), true);
-        const uint32_t est = qa - min(qa, qb);
-        if (k == 0 || 3u * est + 16u < best) {
-          best = est;
-          bk = k;
-        }
-      }
-      if (bad) bk = 0;
-#pragma unroll
-      for (uint32_t s = 0; s < DDM_MAX_D; ++s) {
-        if (s >= d) continue;
-        const uint32_t kk = s == 0 ? bk : s - 1 + (s - 1 >= bk ? 1u : 0u);
-        uint32_t qp = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < DDM_MAX_D; ++k)
-          if (k == kk) qp = mid[k];
-        const uint32_t n = b.cb[s];
-        uint32_t i = min(qp * n / (kQuant + 1u), n - 1u);
-        if (sub & 1u) i = n - 1u - i;
-        sub = sub * n + i;
-      }
-      if (bad) sub = 0;
-    }
-    sub = min(sub, b.nb - 1u);
     kstar[gj] = (uint8_t)bk;
-    const uint32_t bu = b.bbase + bk * b.nb + sub;
+    const uint32_t bu = b.bbase + sub;
     bucket[gj] = bu;
     rank[gj] = atomicAdd(&bhist[bu], 1u);
   }
@@ -237,7 +219,11 @@ __global__ __launch_bounds__(1024) void b_groups_kernel(const BInst* __restrict_
       const uint32_t i = g / DDM_MAX_D, k = g % DDM_MAX_D;
       const BInst& b = I[i];
       uint32_t st = 0, sz = 0;
-      if (k < b.d) {
+      const uint32_t cls = b.d > 1 ? b.plan->cls : kOwnClass;
+      if (cls != kOwnClass) {  // one class, in the cells of all
+        st = (uint32_t)boff[b.bbase];
+        sz = k == cls ? b.m : 0u;
+      } else if (k < b.d) {
         const uint32_t b0 = b.bbase + k * b.nb;
         st = (uint32_t)boff[b0];
         sz = (uint32_t)(boff[b0 + b.nb] - boff[b0]);
@@ -501,6 +487,7 @@ struct ddm_batch {
   uint32_t* list_counters = nullptr;  // two words in the cleared block
   bool counted = false;               // ddm_batch_count ran, ddm_batch_fill may follow
   // the count traversal's stash of hits (capacity > 0, some instance d > 1)
+  bool any_multi = false;
   bool stash = false;
   uint64_t* skey = nullptr;
   uint32_t *srank = nullptr, *sused = nullptr, *sowner = nullptr, *snext = nullptr;
@@ -542,6 +529,10 @@ static ddm_status batch_count_half(ddm_batch* b, hipStream_t s) {
     b_tree_high_kernel<<<hm.second, kTreeThreads, 0, s>>>(b->jobs, hm.first, S);
     DDM_LAUNCHED("b_tree_high_kernel");
     S += kChunkLog;
+  }
+  if (b->any_multi) {
+    b_plan_kernel<<<b->count, kPlanThreads, 0, s>>>(b->inst);
+    DDM_LAUNCHED("b_plan_kernel");
   }
   b_probe_kernel<<<b->nprobe, kProbeThreads, 0, s>>>(b->inst, b->probemap, b->kstar, b->bucket,
                                                      b->rank, b->bhist, b->cnt);
@@ -791,7 +782,6 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
     bi.qbase = (uint32_t)qbase;
     bi.bbase = (uint32_t)bbase;
     bi.nb = std::max<uint32_t>(1, (q.m + 7) / 8);
-    batch_cell_shape(q.m, q.d, bi.nb, bi.cb);
     bi.qpt = q.qpt ? q.qpt : o.qpt;
     bi.ebase = ebase;
     qbase += q.m;
@@ -802,6 +792,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
   // instance), bucket histogram, tickets, segment-list counters
   const size_t zero_words = (size_t)count * (2 + DDM_MAX_D) + Btot + 2 + 2;
   const size_t o_zero = take(sizeof(uint32_t) * zero_words);
+  const size_t o_plan = take(sizeof(OrderPlan) * count);
   const size_t o_jobs = take(sizeof(TreeJob) * ntrees);
   const size_t o_low = take(sizeof(uint2) * nlow);
   // high passes
@@ -839,9 +830,8 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
   const size_t o_words = take(sizeof(uint64_t) * (count + 3));
   // the stash: static chunks of every possible count tile, then slices for
   // the capacity (or 4 hits per update) plus a partly used chunk per tile
-  bool any_multi = false;
-  for (uint32_t i = 0; i < count; ++i) any_multi = any_multi || inst[i].d > 1;
-  b->stash = any_multi && capacity > 0 && capacity <= kStashMaxEntries &&
+  for (uint32_t i = 0; i < count; ++i) b->any_multi = b->any_multi || inst[i].d > 1;
+  b->stash = b->any_multi && capacity > 0 && capacity <= kStashMaxEntries &&
              capacity <= kStashMaxPerUpdate * M;
   size_t o_skey = 0, o_srank = 0, o_sused = 0, o_sowner = 0, o_snext = 0;
   if (b->stash) {
@@ -892,6 +882,7 @@ extern "C" ddm_status ddm_batch_create(const ddm_batch_instance* inst, uint32_t 
     InstOff& f = io[i];
     BInst& bi = hin[i];
     bi.flag = (int32_t*)(zflags + 2 * i);
+    bi.plan = (OrderPlan*)(base + o_plan) + i;
     bi.klo = P32(f.klo);
     bi.khi = q.d == 1 ? P32(f.khi) : nullptr;
     bi.idb = P32(f.id);

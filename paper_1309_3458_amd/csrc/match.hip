@@ -96,19 +96,6 @@ constexpr uint32_t kCellBlocks = kCells / kCellBlock;  // per class
 constexpr uint32_t kSmallOrder = 8192, kSmallCells = 2048;
 constexpr uint32_t kBadCell = 0xffffffffu;  // an update with an invalid extent
 
-// updates per tile: 64, or fewer (down to one) while that leaves at most
-// kFewTiles tiles, so that the chip has wavefronts to run and few updates in a
-// large set do not share boxes wider than their own (17,389 updates of 21 hits
-// each, count: 73 us with 16 to a tile, 21 with 4; 1100 updates against 490,000
-// subscriptions: d = 4 563 us with 4, 22 with one, d = 3 165 and 10, d = 1 51
-// and 9)
-constexpr uint32_t kFewTiles = 8192;
-static uint32_t tile_updates(uint32_t m) {
-  uint32_t q = 1;
-  while (q < 64u && m > q * kFewTiles) q *= 2;
-  return q;
-}
-
 template <bool SMALL>
 __global__ __launch_bounds__(256) void bits1_kernel(TreeDev T, const float* __restrict__ ulo,
                                                     const float* __restrict__ uhi, uint32_t m,

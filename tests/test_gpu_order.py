@@ -126,3 +126,49 @@ def test_order_fits(kind, d, like, factor):
     ref = count_us(instance(like, 300 + d, n, m, d))
     print(f"{kind} d={d}: {got:.0f} us, {like} {ref:.0f} us")
     assert got < factor * ref
+
+
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_batch_pairs(use_graph):
+    """Sets of every kind in one batch, of sizes around a class's few cells."""
+    import paper_1309_3458_amd as P
+    insts = [instance(kind, 400 + 10 * d + i, 700 + 900 * i, m, d) for d in (2, 3, 4)
+             for i, kind in enumerate(KINDS + ["uniform"]) for m in (1, 63, 256, 5000 + 1000 * i)]
+    want = [oracle.itm(i.s_lo, i.s_hi, i.u_lo, i.u_hi, threads=8) for i in insts]
+    tens = [(dev(i.s_lo), dev(i.s_hi), dev(i.u_lo), dev(i.u_hi)) for i in insts]
+    b = P.Batch(tens, sum(len(w) for w in want), use_graph=use_graph)
+    for _ in range(3):
+        b.out.fill_(-1)
+        b.run()
+        b.result()
+        for i, w in enumerate(want):
+            assert np.array_equal(b.pairs(i).cpu().numpy().view(np.uint64), w), i
+    b.free()
+
+
+def batch_count_us(insts):
+    import paper_1309_3458_amd as P
+    tens = [(dev(i.s_lo), dev(i.s_hi), dev(i.u_lo), dev(i.u_hi)) for i in insts]
+    b = P.Batch(tens, 1 << 25, use_graph=False)
+    best = np.inf
+    b.run()
+    P.prof_enable(True, only="batch_traverse_count")
+    for _ in range(7):
+        P.prof_read()
+        b.run()
+        best = min(best, 1e3 * P.prof_read()["batch_traverse_count"][0])
+    P.prof_enable(False)
+    b.result()
+    b.free()
+    return best
+
+
+@pytest.mark.parametrize("kind, d, factor", [
+    ("all long either way", 3, 4.0), ("long either way", 4, 4.0), ("line", 3, 4.0),
+    ("plane", 4, 4.0), ("16 clusters", 2, 4.0), ("100 clusters", 3, 5.0)])
+def test_batch_order_fits(kind, d, factor):
+    n, m = 50000, 40000
+    got = batch_count_us([instance(kind, 500 + i, n, m, d) for i in range(4)])
+    ref = batch_count_us([instance("uniform", 600 + i, n, m, d) for i in range(4)])
+    print(f"{kind} d={d}: {got:.0f} us, uniform {ref:.0f} us")
+    assert got < factor * ref
