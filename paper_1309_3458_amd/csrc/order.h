@@ -251,8 +251,8 @@ __device__ __forceinline__ uint32_t grid_cell(const uint32_t* __restrict__ b, ui
 // Up to kPlanSamples updates spread evenly over the set decide whether the
 // count traversal keeps its hits: the stash is marked full before it is used,
 // and the set matched as a dense one, when the estimated hits (the candidate
-// fractions of the dimensions multiplied, as if they were independent) exceed
-// four fifths of the stash's counted chunks (tiles leave some of theirs), or per
+// fractions of the dimensions multiplied, as if they were independent, with the
+// lengths of a sample of subscriptions) exceed four fifths of the stash's counted chunks (tiles leave some of theirs), or per
 // update the larger of kDenseHits and
 // kDenseScale * d / sqrt(m).  The dense form takes two more synchronizations and
 // nine more launches, a fixed 70 us, and saves on every pair, the more the more
@@ -316,6 +316,10 @@ __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __rest
   const uint32_t S = min(m, kPlanSamples);
   UpdExt<D> e{};
   if (tid < S) e = load_ext<D>(ulo, uhi, m, (uint32_t)(((uint64_t)tid * m) / S));
+  // a subscription for each sample, at even positions of a tree
+  float rec[2 * D] = {};
+  if (full && tid < S)
+    load_rec<D>(T.rec[0] + (size_t)(1u + (uint32_t)(((uint64_t)tid * T.n) / S)) * 2 * D, rec);
   load_quant_lds<D, kPlanThreads>(T, sq);
   __syncthreads();
   ProbeEst<D> P{};
@@ -326,6 +330,18 @@ __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __rest
       in = !P.bad;
     }
     float hits = in ? P.hits : 0.f;
+    if (full) {
+      // the ranges are those of the longest subscriptions; the sample's own meets
+      // the update with this share of the probability (250,000 + 250,000 boxes, half
+      // 60,000 long in the one and half in the other of two dimensions, 3.3 hits
+      // each, taken for 10.6: match 318 us, 176 now)
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        const float u = e.b[k] - e.a[k], l = nextafterf(rec[2 * k + 1] - rec[2 * k], INFINITY);
+        const float f = (u + l) / (u + T.maxlen[k]);
+        hits *= f < 1.f ? f : 1.f;
+      }
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, kWave);
     uint32_t mine = 0;  // the range in the sample's own class

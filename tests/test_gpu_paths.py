@@ -173,3 +173,31 @@ def test_a_result_beyond_the_capacity_is_only_counted(d):
     assert rec["dense_expand"] == 1
     assert np.array_equal(big[:K].cpu().numpy().view(np.uint64), want)
     t.free()
+
+
+@pytest.mark.parametrize("d, long, short, n, m, hits", [
+    (2, 2e4, 200.0, 18000, 250000, 3.8), (2, 2e4, 200.0, 100000, 8000, 21.0),
+    (3, 6e4, 3e3, 250000, 250000, 3.5), (4, 3e5, 2e4, 40000, 250000, 3.0)])
+def test_hits_of_mixed_lengths_are_kept(d, long, short, n, m, hits):
+    """Half of the boxes long in one dimension, half in another: three to four times
+    as many hits were all subscriptions as long as the longest."""
+    rng = np.random.default_rng(37)
+
+    def boxes(count):
+        side = np.full((d, count), short)
+        side[rng.integers(0, 2, count), np.arange(count)] = long
+        lo = rng.uniform(0, 1e6, (d, count)).astype(np.float32)
+        return lo, (lo + side).astype(np.float32)
+
+    import paper_1309_3458_amd as P
+    inst = W.Instance(*boxes(n), *boxes(m))
+    t = P.build(dev(inst.s_lo), dev(inst.s_hi))
+    keys, rec = recorded(lambda: P.match(t, dev(inst.u_lo), dev(inst.u_hi)))
+    t.free()
+    keys = keys.cpu().numpy().view(np.uint64)
+    # (the oracle takes a minute for all of them)
+    some = 1000
+    want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo[:, :some], inst.u_hi[:, :some], threads=8)
+    assert np.array_equal(keys[:len(want)], want) and keys[len(want)] >> np.uint64(32) >= some
+    assert 0.8 * hits < len(keys) / m < 1.2 * hits
+    assert rec["stash_scatter"] == 1 and "dense_expand" not in rec
