@@ -89,13 +89,16 @@ __device__ __forceinline__ void load_quant_lds(const TreeDev& T, uint32_t (*sq)[
 constexpr uint32_t kOwnClass = ~0u;
 constexpr float kClassCost = 1.5f;
 
+// len (may be null): the lengths of a subscription, which the hits are then for, as
+// the ranges are for the longest ones
 template <int D>
 __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
                                                       const uint32_t (*sq)[kQuantPad],
-                                                      const UpdExt<D>& e, uint32_t cls) {
+                                                      const UpdExt<D>& e, uint32_t cls,
+                                                      const float* len = nullptr) {
   ProbeEst<D> P;
   P.bad = false;
-  uint32_t xh[D], xl[D], xm[D], qa[D], qb[D], qm[D];
+  uint32_t xh[D], xl[D], xm[D], xs[D], qa[D], qb[D], qm[D], qs[D];
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const float a = e.a[k], b = e.b[k];
@@ -103,10 +106,11 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
     xh[k] = f2key(b);
     xl[k] = f2key(nextafterf(a - T.maxlen[k], -INFINITY));
     xm[k] = f2key(0.5f * a + 0.5f * b);
-    qa[k] = qb[k] = qm[k] = 0;
+    xs[k] = len ? f2key(nextafterf(a - len[k], -INFINITY)) : 0u;
+    qa[k] = qb[k] = qm[k] = qs[k] = 0;
   }
-  // the 3D quantile searches (#quantiles <= xh, < xl, <= xm per dimension)
-  // advance in lockstep, so their LDS reads overlap
+  // the 3D quantile searches (#quantiles <= xh, < xl, <= xm per dimension; 4D with
+  // len) advance in lockstep, so their LDS reads overlap
 #pragma unroll
   for (uint32_t step = kQuant; step > 0; step >>= 1) {
 #pragma unroll
@@ -118,6 +122,11 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
       if (ca <= kQuant && va <= xh[k]) qa[k] = ca;
       if (cb <= kQuant && vb < xl[k]) qb[k] = cb;
       if (cm <= kQuant && vm <= xm[k]) qm[k] = cm;
+      if (len) {
+        const uint32_t cs = qs[k] + step;
+        const uint32_t vs = cs <= kQuant ? sq[k][qslot(cs - 1)] : 0xffffffffu;
+        if (cs <= kQuant && vs < xs[k]) qs[k] = cs;
+      }
     }
   }
   // an update's own class: dimension 0, unless another one's range is less than
@@ -127,7 +136,8 @@ __device__ __forceinline__ ProbeEst<D> probe_estimate(const TreeDev& T,
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const uint32_t est = qa[k] - min(qa[k], qb[k]);
-    P.hits *= fmaxf((float)est, 0.5f) * (1.f / (float)kQuant);
+    const uint32_t meets = len ? qa[k] - min(qa[k], qs[k]) : est;
+    P.hits *= fmaxf((float)meets, 0.5f) * (1.f / (float)kQuant);
     P.mid[k] = qm[k];
     P.est[k] = est;
     if (cls == kOwnClass ? k == 0 || 3u * est + 16u < best : (uint32_t)k == cls) {
@@ -316,9 +326,11 @@ __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __rest
   const uint32_t S = min(m, kPlanSamples);
   UpdExt<D> e{};
   if (tid < S) e = load_ext<D>(ulo, uhi, m, (uint32_t)(((uint64_t)tid * m) / S));
-  // a subscription for each sample, at even positions of a tree
+  // a subscription for each sample, at even positions of a tree: were all as long as
+  // the longest, 250,000 + 250,000 boxes, half 60,000 long in the one and half in the
+  // other of two dimensions, 3.3 hits each, would count as dense (match 318 us, 178 now)
   float rec[2 * D] = {};
-  if (full && tid < S)
+  if (tid < S)
     load_rec<D>(T.rec[0] + (size_t)(1u + (uint32_t)(((uint64_t)tid * T.n) / S)) * 2 * D, rec);
   load_quant_lds<D, kPlanThreads>(T, sq);
   __syncthreads();
@@ -326,22 +338,13 @@ __device__ __forceinline__ void sample_set(const TreeDev& T, const float* __rest
   bool in = tid < S;
   if (tid < kPlanSamples) {
     if (in) {
-      P = probe_estimate<D>(T, sq, e, kOwnClass);
+      float len[D];
+#pragma unroll
+      for (int k = 0; k < D; ++k) len[k] = nextafterf(rec[2 * k + 1] - rec[2 * k], INFINITY);
+      P = probe_estimate<D>(T, sq, e, kOwnClass, len);
       in = !P.bad;
     }
     float hits = in ? P.hits : 0.f;
-    if (full) {
-      // the ranges are those of the longest subscriptions; the sample's own meets
-      // the update with this share of the probability (250,000 + 250,000 boxes, half
-      // 60,000 long in the one and half in the other of two dimensions, 3.3 hits
-      // each, taken for 10.6: match 318 us, 176 now)
-#pragma unroll
-      for (int k = 0; k < D; ++k) {
-        const float u = e.b[k] - e.a[k], l = nextafterf(rec[2 * k + 1] - rec[2 * k], INFINITY);
-        const float f = (u + l) / (u + T.maxlen[k]);
-        hits *= f < 1.f ? f : 1.f;
-      }
-    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) hits += __shfl_xor(hits, o, kWave);
     uint32_t mine = 0;  // the range in the sample's own class
