@@ -1571,6 +1571,7 @@ struct MatchState {
   uint32_t smax = 0;
   uint32_t sfirst = 0;
   uint32_t sslice = 0;
+  uint32_t sroom = 0;      // counted chunks per slice, as the sample takes them
   uint32_t stiles = 0;     // tiles that ran
   uint32_t sused_max = 0;  // most counted chunks used in one slice
   bool stash_ok = false;
@@ -1637,7 +1638,7 @@ static ddm_status order_updates(const TreeDev& T, const float* ulo, const float*
                                 hipStream_t s) {
   uint32_t* sn = st.stash ? st.snext : nullptr;  // (a stash exists only for d > 1)
   uint32_t* full = sn ? sn + kStashSlices : nullptr;
-  const uint32_t room = st.sslice * (kStashSlices * kStashChunk);
+  const uint32_t room = st.sroom * (kStashSlices * kStashChunk);
   const uint32_t mark = st.may_dense ? kStashDense : 1u;
   const bool small = m <= kSmallOrder;
   if (!small) {
@@ -1761,11 +1762,21 @@ static uint64_t stash_tiles(uint32_t m) {
          DDM_MAX_D;
 }
 // counted chunks per slice: room for the hint (or 4 hits per update) plus
-// one partly used chunk per tile and 1024 more, over the slices
-static uint32_t stash_slice(uint32_t m, uint64_t hint) {
+// `tiles` partly used requests and 1024 chunks more, over the slices
+static uint32_t stash_chunks(uint32_t m, uint64_t hint, uint64_t tiles) {
   const uint64_t dyn = std::min<uint64_t>(std::max<uint64_t>(hint, 4ull * m), kStashMaxEntries);
-  const uint64_t c = (dyn + kStashChunk - 1) / kStashChunk + stash_tiles(m) * kStashGrab + 1024;
+  const uint64_t c = (dyn + kStashChunk - 1) / kStashChunk + tiles * kStashGrab + 1024;
   return (uint32_t)((c + kStashSlices - 1) / kStashSlices);
+}
+// The sample decides by the room for the tiles there are.  Sets whose dimensions
+// depend on each other have more hits than it expects; those that fill the stash are
+// counted in vain, so there is room for some 40 hits per update up to 260,000 of
+// them (200,000 boxes on a plane, d = 3, 24 hits each: match 608 us where the stash
+// held 14, 456 now; at 80 each the dense form is the faster,
+// also after a count in vain).
+static uint32_t stash_slice(uint32_t m, uint64_t hint) {
+  const uint64_t spare = (uint64_t)m / 64 + std::min<uint64_t>(m / 8, 32768);
+  return stash_chunks(m, hint, std::max(stash_tiles(m), spare));
 }
 
 size_t match_stash_bytes(uint32_t m) {
@@ -1860,6 +1871,7 @@ static void front_take(Scratch& sc, MatchState& st, uint32_t m, bool learned, Fr
 static void stash_reserve(Scratch& sc, MatchState& st, uint32_t m, uint64_t hint) {
   st.sfirst = (uint32_t)(stash_tiles(m) * kStashStatic);
   st.sslice = stash_slice(m, hint);
+  st.sroom = stash_chunks(m, hint, stash_tiles(m));
   st.smax = st.sfirst + st.sslice * kStashSlices;
   const uint64_t e = (uint64_t)st.smax * kStashChunk;
   sc.reserve(sizeof(uint64_t) * e);

@@ -201,3 +201,27 @@ def test_hits_of_mixed_lengths_are_kept(d, long, short, n, m, hits):
     assert np.array_equal(keys[:len(want)], want) and keys[len(want)] >> np.uint64(32) >= some
     assert 0.8 * hits < len(keys) / m < 1.2 * hits
     assert rec["stash_scatter"] == 1 and "dense_expand" not in rec
+
+
+def test_hits_of_dependent_dimensions_are_kept():
+    """Boxes on a plane in three dimensions: the sample expects a hundredth of their
+    24 hits each, and the stash has room for them."""
+    rng = np.random.default_rng(38)
+
+    def boxes(count):
+        p, q = rng.uniform(0, 1e6, (2, count))
+        lo = np.stack([p, p + rng.uniform(0, 100, count), q]).astype(np.float32)
+        return lo, (lo + np.float32([[1000], [1000], [11000]])).astype(np.float32)
+
+    import paper_1309_3458_amd as P
+    m = 200000
+    inst = W.Instance(*boxes(600000), *boxes(m))
+    t = P.build(dev(inst.s_lo), dev(inst.s_hi))
+    keys, rec = recorded(lambda: P.match(t, dev(inst.u_lo), dev(inst.u_hi)))
+    t.free()
+    keys = keys.cpu().numpy().view(np.uint64)
+    some = 1000
+    want = oracle.itm(inst.s_lo, inst.s_hi, inst.u_lo[:, :some], inst.u_hi[:, :some], threads=8)
+    assert np.array_equal(keys[:len(want)], want) and keys[len(want)] >> np.uint64(32) >= some
+    assert 22 < len(keys) / m < 28
+    assert rec["stash_scatter"] == 1 and "dense_expand" not in rec
