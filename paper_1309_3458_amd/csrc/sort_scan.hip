@@ -145,7 +145,9 @@ __global__ __launch_bounds__(kSortThreads) void rs_scatter_kernel(const SortArr*
     const uint32_t rk = mask_rank(peers);
     const uint32_t c = valid ? wc[wave][dig] : 0u;
     loc[r] = c + rk;
+    wave_sync();  // (the counts of one round are read by other lanes in the next)
     if (valid && rk == 0) wc[wave][dig] = c + (uint32_t)__popcll(peers);
+    wave_sync();
   }
   __syncthreads();
   // thread tid owns digit tid: the tile's offset of the digit (from the
@@ -368,7 +370,9 @@ __global__ __launch_bounds__(kOsThreads) void os_pass_kernel(OsDesc D,
     const uint32_t rk = mask_rank(peers);
     const uint32_t b = valid ? wcnt[wave][dig] : 0u;
     loc[r] = b + rk;
+    wave_sync();  // (the counts of one round are read by other lanes in the next)
     if (valid && rk == 0) wcnt[wave][dig] = b + (uint32_t)__popcll(peers);
+    wave_sync();
   }
   __syncthreads();
   // digit owners: the tile's count of digit d, the digit's base in the array
