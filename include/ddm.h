@@ -71,8 +71,10 @@ typedef struct ddm_tree ddm_tree;
  * bound (a device radix sort; equal lower bounds keep id order) form the
  * in-order sequence of a complete binary tree, and each position stores the
  * maximum upper bound of its subtree (the paper's maxupper; minlower is the
- * leftmost lower bound of the subtree and needs no storage).  The tree owns
- * its device memory.  The inputs may be freed or overwritten once the stream
+ * leftmost lower bound of the subtree and needs no storage).  For d > 1 the
+ * subscriptions also lie in compact blocks of 64, and once by id.  The tree
+ * owns its device memory: for 5*10^5 subscriptions 16 MB at d = 1, 61 at
+ * d = 2, 115 at d = 3 and 186 at d = 4.  The inputs may be freed or overwritten once the stream
  * has passed this call.  Validation of the coordinates runs on the device;
  * its outcome is reported by the first ddm_match on the tree (or by
  * ddm_tree_check), not by ddm_build.
@@ -94,10 +96,18 @@ ddm_status ddm_build(const float* sub_lo, const float* sub_hi, uint32_t n, uint3
  *  out_count      host pointer; ALWAYS receives the exact pair count K when
  *                 the call returns DDM_OK or DDM_E_CAPACITY.
  *
- * Synchronizes the stream once (to read K).  If K > capacity the call returns
+ * Synchronizes the stream once (to read K), twice for a dense set (below).
+ * If K > capacity the call returns
  * DDM_E_CAPACITY and writes no pair; call again with capacity >= K.  On
  * DDM_OK the first K slots receive the sorted keys when the stream reaches
  * the end of the enqueued work.
+ *
+ * A dense set (many hits per update, as a sample of 256 updates expects them or
+ * the count finds them; at most 2^20 subscriptions; capacity > 0) is matched from
+ * the tiles' candidate lists: 16 bytes of scratch per candidate and up to 9 KiB
+ * per tile of 1 to 64 updates, for at most 2^30 candidates, until the pairs are
+ * written.  Where that memory is not to be had the set is counted and filled
+ * as any other.  Results never depend on it.
  */
 ddm_status ddm_match(const ddm_tree* t, const float* upd_lo, const float* upd_hi, uint32_t m,
                      uint64_t* out_pairs, uint64_t capacity, uint64_t* out_count,
@@ -106,10 +116,11 @@ ddm_status ddm_match(const ddm_tree* t, const float* upd_lo, const float* upd_hi
 /* Traversal kernels selectable through ddm_match_ex (results never differ):
  *  DDM_TRAVERSE_LANE  one GPU lane per update, stackless form of Algorithm 4
  *                     on the implicit tree.
- *  DDM_TRAVERSE_TILE  one wavefront per 64 updates sorted by lower bound:
- *                     Algorithm 4 runs once on the tile's enclosing interval,
+ *  DDM_TRAVERSE_TILE  one wavefront per tile of up to 64 updates that lie near
+ *                     each other (fewer, down to one, up to 2^18 updates):
+ *                     Algorithm 4 runs once on the tile's enclosing box,
  *                     candidates are compacted into LDS with wavefront
- *                     ballots and tested against all 64 updates.
+ *                     ballots and tested against all its updates.
  *  DDM_TRAVERSE_AUTO  library default (currently TILE).                     */
 #define DDM_TRAVERSE_AUTO 0u
 #define DDM_TRAVERSE_LANE 1u
@@ -130,18 +141,18 @@ ddm_status ddm_match_ex(const ddm_tree* t, const float* upd_lo, const float* upd
 /* Two-step form of ddm_match_ex for callers that size the output from K.
  *
  * ddm_match_begin runs everything up to the pair count (validation, probe
- * dimension, counts per update, offsets), synchronizes the stream once, and
- * returns K through out_count (host pointer) plus a pending handle (host
+ * dimension, counts per update, offsets), synchronizes the stream once (twice
+ * for a dense set, whose candidate lists it then holds), and returns K through out_count (host pointer) plus a pending handle (host
  * pointer receives it; NULL when m == 0 or n == 0, and ddm_match_finish
  * accepts NULL).  A non-NULL handle must be passed to ddm_match_finish or
  * ddm_match_abort exactly once.  It keeps the device state of the count; the
  * update coordinates must stay valid until ddm_match_finish.  For d > 1 the
  * count also keeps the hits it finds, 12 bytes each, in scratch with room
- * for 4 hits per update plus six 64-hit chunks per possible work tile
- * (m/64 + min(m, 32768) tiles): if all of them fit, ddm_match_finish places
- * them instead of running the traversal again.  ddm_match_ex sizes this
- * scratch for its capacity instead, and keeps no hits when the capacity
- * exceeds 8 hits per update or 2^28 hits.  Results never depend on it.
+ * for 4 hits per update, two 64-hit chunks per tile and four more per tile
+ * or eight updates (ddm_match_scratch_bytes, DDM_SCRATCH_STASH): if all of
+ * them fit, ddm_match_finish places them instead of running the traversal
+ * again.  ddm_match_ex makes room for its capacity, up to 8 hits per update
+ * and 2^28 in all, if that is more.  Results never depend on it.
  *
  * ddm_match_finish writes the K sorted pairs into out_pairs (device, capacity
  * slots) on the stream given to ddm_match_begin, and releases the handle in
@@ -255,7 +266,10 @@ ddm_status ddm_predictor_train(ddm_predictor* p, const float* X, const float* Y,
  * without any traversal, so it is the plain path).  slot_budget > 0 fixes
  * the slot arena (updates whose slots fall beyond it are treated as
  * overflowed); 0 sizes the arena to the predicted total, at the cost of one
- * more stream synchronization.  Finish with ddm_match_finish.               */
+ * more stream synchronization.  With 0, a set predicted to be dense is matched
+ * from candidate lists sized by the predictor (scratch as for ddm_match, one
+ * synchronization more, two where a list had more candidates than predicted);
+ * no slots are taken then.  Finish with ddm_match_finish.                   */
 ddm_status ddm_match_learned_begin(const ddm_tree* t, const float* upd_lo, const float* upd_hi,
                                    uint32_t m, const ddm_predictor* pred, uint64_t slot_budget,
                                    uint64_t* out_count, void* stream, const ddm_match_opts* opts,
@@ -288,6 +302,9 @@ ddm_status ddm_count(const ddm_tree* t, const float* upd_lo, const float* upd_hi
  *                                  the default of 4 hits per update),
  *             DDM_SCRATCH_LEARNED  the single pass (d > 1) without its slot
  *                                  arena (4 bytes per predicted slot).
+ *             The candidate lists of a dense set (ddm_match) come on top of
+ *             DDM_SCRATCH_STASH and DDM_SCRATCH_LEARNED, and of PLAIN at d = 1;
+ *             ddm_match_noalloc takes none.
  *  bytes      host pointer, receives the size (0 for m = 0).
  * Computed on the host by the same layout code the match runs, with no GPU
  * and no memory behind it; it also checks that every piece the match takes
@@ -364,18 +381,20 @@ ddm_status ddm_match_sbm(const float* sub_lo, const float* sub_hi, uint32_t n,
  *  sub_lo/sub_hi  device, d*n float32, dimension-major; upd_lo/upd_hi
  *                 device, d*m float32.
  *  swap_policy    DDM_SWAP_AUTO (swap when n > m and d >= 3), DDM_SWAP_NEVER
- *                 or DDM_SWAP_ALWAYS.  AUTO follows measurements on the
- *                 GPU: for d <= 2 the tree on the larger set is as fast or
- *                 faster (per-update work and the transposition outweigh
- *                 the smaller tree), for d >= 3 the tree on the smaller set
- *                 is 1.5x to 11x faster.  A swap transposes on the device
+ *                 or DDM_SWAP_ALWAYS.  For d <= 2 the tree on the larger set
+ *                 is as fast or faster (per-update work and the transposition
+ *                 outweigh the smaller tree).  For d >= 3 the tree on the
+ *                 smaller set is the faster by 1.2x to 2.3x where n is 10 to
+ *                 200 times m; where n is up to 3 times m it is the slower by
+ *                 0.7x to 0.9x, and NEVER is the better choice.
+ *                 A swap transposes on the device
  *                 and needs capacity < 2^32: AUTO does not swap beyond it,
  *                 ALWAYS returns DDM_E_INVALID_ARG.
  *  out_pairs      device, capacity uint64 (may be NULL when capacity is 0).
  *  out_count      host, receives K on DDM_OK / DDM_E_CAPACITY.
  *  out_swapped    host, may be NULL: 1 if the tree was built on the updates.
- * The tree is freed before return.  Synchronizes the stream once (to read
- * K).  DDM_E_CAPACITY writes nothing; invalid coordinates of either set give
+ * The tree is freed before return.  Synchronizes the stream as ddm_match
+ * does.  DDM_E_CAPACITY writes nothing; invalid coordinates of either set give
  * DDM_E_INVALID_INPUT.  A swap needs 16 bytes of scratch per pair.          */
 #define DDM_SWAP_AUTO 0
 #define DDM_SWAP_NEVER 1

@@ -92,7 +92,6 @@ __global__ __launch_bounds__(kUnitWaves * kWave) void tile_boxes_kernel(
 }
 
 // a tile's list gets half as much again as the predictor says, and 64 more
-// (tiles past the last one, of a class that ended early: none)
 __global__ __launch_bounds__(256) void tile_room_kernel(uint32_t* __restrict__ cap, uint32_t tiles,
                                                         uint32_t n) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;

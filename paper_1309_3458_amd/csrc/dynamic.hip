@@ -402,6 +402,8 @@ static ddm_status recomputed_keys(const ddm_dynamic* dy, bool rows, const uint32
   if (K <= kRowsSmall) {
 #define DDM_ROWS(R) \
   dyn_rows_kernel<R><<<1, kBlockSortThreads, 0, s>>>(keys, (uint32_t)K, sid, passes)
+    // (a key's round costs the same whether it is there or not; sizes in between take
+    // the next one, at most a quarter more rounds from 8 on)
     const uint32_t need = (uint32_t)((K + kBlockSortThreads - 1) / kBlockSortThreads);
     if (need <= 1)
       DDM_ROWS(1);

@@ -61,9 +61,13 @@ extern "C" ddm_status ddm_match_sets(const float* sub_lo, const float* sub_hi, u
     }
     swap = true;
   } else if (swap_policy == DDM_SWAP_AUTO) {
-    // measured: with d <= 2 the per-update work and the transposition cost
-    // more than the larger tree saves; with d >= 3 the larger tree's long
-    // candidate ranges dominate
+    // With d <= 2 the per-update work and the transposition cost more than the
+    // smaller tree saves.  d >= 3, us, tree on the larger / smaller set:
+    //   n = 2,000,000  m = 100,000  d = 3 904/769  d = 4 1102/704
+    //       2,000,000       10,000        947/615        1636/714
+    //         300,000      200,000        355/518         526/708
+    //          30,000       10,000        193/240         238/264
+    // (the line lies where it lay before tiles read compact blocks)
     swap = n > m && d >= 3 && small_cap;
   }
   hipStream_t s = (hipStream_t)stream;

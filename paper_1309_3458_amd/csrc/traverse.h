@@ -160,9 +160,9 @@ constexpr uint32_t kStashGrab = 4;  // at least this many counted chunks per req
 // at most 2^28 stashed hits (4 GiB of stash); larger results overflow it and
 // take the fill traversal
 constexpr uint64_t kStashMaxEntries = 1ull << 28;
-// a caller's capacity above this many hits per update means dense results,
-// for which writing and moving every hit costs more than traversing again
-// (measured: 2 hits per update gain, 18 lose); no stash then
+// the stash has room for a caller's capacity up to this many hits per update: what
+// has more is matched from candidate lists, or filled by a second traversal (with a
+// batch, which has no lists, no stash beyond it: 2 hits per update gain, 18 lose)
 constexpr uint64_t kStashMaxPerUpdate = 8;
 
 struct SegOut {
@@ -271,6 +271,7 @@ constexpr int kRing = 128;
 // per candidate over the updates sorted in a second dimension took fewer only
 // where cells were wide (10^6 boxes, d = 3, count with strips and cells alike:
 // 217 us with it, 177 us this way).
+
 // Tests 64 candidates (lane l holds record v of candidate l; past c they are
 // empty) against the updates of the lanes (bounds ql, qh; lanes from nq on hold
 // none): *mlo and *mhi receive the mask of the candidates that the lane's update

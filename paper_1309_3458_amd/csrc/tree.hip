@@ -241,7 +241,6 @@ __global__ void flag_zero_kernel(int32_t* __restrict__ flag) {
   if (threadIdx.x == 0) *flag = 0;
 }
 
-// job blockIdx.y, chunk blockIdx.x
 // job blockIdx.y, chunk blockIdx.x - ig; the first ig workgroups take the samples
 // and quantiles instead, one item to a thread (they need the sorted keys only, so
 // their loads run beside the other workgroups': 5 us less than a kernel of their
