@@ -133,13 +133,13 @@ def candidates(inst):
 # sources only when every kernel the step launches compiles to the same
 # code object, which the profile records).  `kernel` is the dominant
 # kernel's own launch; `step` sums every kernel of one build + match step.
-TRAFFIC_SOURCES = ("paper_1309_3458_amd/csrc/match.hip", "paper_1309_3458_amd/csrc/traverse.h",
-                   "paper_1309_3458_amd/csrc/ddm_internal.h", "paper_1309_3458_amd/csrc/tree.hip",
-                   "paper_1309_3458_amd/csrc/tree_dev.h", "paper_1309_3458_amd/csrc/sort_scan.hip")
+TRAFFIC_SOURCES = tuple("paper_1309_3458_amd/csrc/" + f for f in (
+    "match.hip", "order.h", "traverse.h", "dense.h", "ddm_internal.h", "tree.hip", "tree_dev.h",
+    "block_sort.h", "sort_scan.hip"))
 TRAFFIC = {
     ("d2_N1e6_alpha1_uniform", "plain", "traverse_tile_count_stash"): {
-        "sha": "cd7794ad6293a3c0", "kernel_fetch_kib": 113122.3, "kernel_write_kib": 28293.2,
-        "step_fetch_kib": 231706.7, "step_write_kib": 200564.3, "step_kernel_us": 286.8,
+        "sha": "72102b71f5e1080e", "kernel_fetch_kib": 113191.0, "kernel_write_kib": 28203.5,
+        "step_fetch_kib": 232050.5, "step_write_kib": 201282.2, "step_kernel_us": 289.5,
         "profile": "profiles/traffic_d2_N1e6_alpha1_pmc.md"},
 }
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
